@@ -288,7 +288,17 @@ __device__ __forceinline__ void load16_to_lds(LdsSource src, uint32_t byte_offse
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)l, 16, (int)byte_offset, 0, 0, 0);
 }
-
+// the same with a descriptor that covers `bytes` bytes (lanes past them read zeros) and a
+// wave-uniform offset beside the lane's own
+__device__ __forceinline__ LdsSource lds_source_sized(const void *base, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void load16_to_lds_at(LdsSource src, uint32_t lane_offset, uint32_t offset, void *l)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)l, 16, (int)lane_offset,
+                                             (int)offset, 0, 0);
+}
 
 // Tiles of K/V rows sit in LDS unpadded (a wave-wide load fills whole rows back to back), so the bank
 // spread comes from permuting the 16-byte chunks inside each row: chunk c of row r is kept at

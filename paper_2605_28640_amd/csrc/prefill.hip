@@ -9,14 +9,24 @@
 // rows' own blocks are dense causal tiles of the same kernel, launched afterwards: their
 // epilogue folds in the row's partials and writes the output.  Executed flops stay at the algorithmic count (plus tile padding).
 //
-// Tile kernel, per wave: 32 query rows against 64-key steps with v_mfma_f32_32x32x16_bf16.
+// Tile kernel, per wave: 32 query rows against 32-key steps with v_mfma_f32_32x32x16_bf16.
 // Scores are formed transposed, S^T = K Q^T, so that a lane holds the keys of ONE query and
-// the softmax row reductions are in-lane plus one cross-half shuffle; O^T = V^T P^T then
+// the softmax row reductions are in-lane plus one cross-half swap; O^T = V^T P^T then
 // takes P^T straight from the accumulator registers, and V^T through LDS transpose reads of
-// the row-major V tile.  K/V tiles are double-buffered in LDS and filled by direct
-// global -> LDS loads (no staging registers): the next tile's loads are issued one at a time
-// between the current tile's matrix instructions, one barrier per step.  Tiles are unpadded;
-// an XOR permutation of the 16-byte chunks of each row keeps both operand reads conflict-free.
+// the row-major V tile.  K/V tiles pass through a ring of three LDS slots filled by direct
+// global -> LDS loads (no staging registers): the loads of the tile two steps ahead are issued one
+// at a time between the current tile's matrix instructions, one barrier per step that waits for
+// the next tile only.  Tiles are unpadded; an XOR permutation of the 16-byte chunks of each row
+// keeps both operand reads conflict-free.
+// What bounds it: the causal form holds the matrix units 65 % busy and is then limited by power (the
+// clock falls from 1.67 to 1.54 GHz against the 59 % of two waves per SIMD); the routed forms wait
+// for memory and for the fixed parts of a tile.  Hence 168 registers (steps of 32 keys, 48 KB of
+// LDS) and three workgroups per CU instead of 64-key steps with two, every kind of tile as its own
+// instantiation with nothing spilled in its loop, and causal tiles launched heaviest first over all
+// heads of an XCD (head by head, the last head's long tiles started late and the chip drained for a
+// quarter of the launch).  Before / after: causal, 32 over 8 heads, 16001 tokens 1.86 / 1.77 ms;
+// bit sets, 2 x 32 heads x 4001, blocks of 64, top-8 0.285 / 0.24 ms; regrouped, 32 heads x 32768,
+// blocks of 512, top-3 1.19 / 1.09 ms (listed tiles 0.78 / 0.69).
 // The softmax runs in the base-2 domain (one FMA + one v_exp_f32 per score), moves its
 // reference point (and rescales the accumulators) only when a row maximum has grown by more
 // than 2^8, and masks only on steps a boundary crosses.  Partials are kept as bfloat16 o
@@ -35,7 +45,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMT = 128;        // query rows per workgroup tile (4 waves x 32)
-constexpr int kKT = 64;         // keys per step (two 32-key MFMA sub-tiles)
+constexpr int kKT = 32;         // keys per step (one 32-key MFMA sub-tile)
 constexpr uint32_t kSlotShift = 27;
 constexpr float kLazy = 8.f;    // slack (base-2 exponent) before the softmax reference point moves
 
@@ -158,7 +168,6 @@ struct PrefillParams {
     bf16 *out;
     float *lse_out;
     int Hq, Hkv, Nb, K, block, n_diag;
-    int phase;                 // 0: tiles of listed rows (partials); 1: own-block tiles, fold the partials, write y
     long T, Tcap, list_stride;
     float scale;
 };
@@ -175,13 +184,29 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const uint16_t *p)
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
 }
 
-// MASKED: the routed form for dense routings (small blocks, many picks per row): contiguous
-// causal tiles as in the dense case, each lane carrying the bit set of its row's listed blocks
-// (nothing is attended that is not listed, the row's own block included);
-// a 64-key step lies inside one block (block % 64 == 0), a lane whose row did not list it adds
-// nothing there, and a wave none of whose rows listed it skips the step's arithmetic.
-template <int D, bool MASKED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_attn_kernel(const PrefillParams a)
+// The four forms of the tile kernel.
+//   kDense    causal tiles over all keys
+//   kBitSets  the routed form for dense routings (small blocks, many picks per row): the dense
+//             causal tiles, each lane carrying the bit set of its row's listed blocks (nothing is
+//             attended that is not listed, the row's own block included); a step lies inside one
+//             block (block % 64 == 0), a lane whose row did not list it adds nothing there, and a
+//             wave none of whose rows listed it skips the step's arithmetic
+//   kListed   tiles of listed rows against one block, leaving partials
+//   kOwn      rows against their own blocks; folds the partials in and writes y
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// the bitwise or over the wave's lanes, as a scalar
+__device__ __forceinline__ uint32_t wave_or(uint32_t x)
+{
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) x |= (uint32_t)__shfl_xor((int)x, m);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+enum PrefillForm { kDense, kBitSets, kListed, kOwn };
+
+template <int D, PrefillForm FORM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void prefill_attn_kernel(const PrefillParams a)
 {
     constexpr int NC = D / 16;     // 16-wide d chunks of the QK^T contraction
     constexpr int NDT = D / 32;    // 32-wide d tiles of O^T
@@ -189,162 +214,176 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int RW = 64 / CR;    // rows one wave-wide load covers
     constexpr int RPI = 4 * RW;    // rows one pass of the four waves covers
     constexpr int CPT = kKT / RPI; // passes per tile (loads per thread per tile, for K and for V)
-    // two K and two V buffers as separate objects, addressed with a compile-time buffer index:
-    // the compiler then knows that a step's operand reads and its direct loads into the other
-    // buffer cannot overlap, and puts no wait between them
+    // a ring of three K and three V tiles as separate objects, addressed with a compile-time index:
+    // the compiler then knows that a step's operand reads and the direct loads into another slot
+    // cannot overlap, and puts no wait between them
     __shared__ __attribute__((aligned(1024))) uint16_t sK0[kKT * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sK1[kKT * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sK2[kKT * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sV0[kKT * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sV1[kKT * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sV2[kKT * D];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lq = lane & 31, h = lane >> 5;
     // Workgroups are handed to the eight XCDs round-robin in launch order, and each XCD has an L2
-    // of its own.  Launch slot L therefore runs on XCD L % 8; give that XCD whole (batch, head)
-    // units (unit % 8 == XCD) and consecutive tiles of one unit, so that the workgroups resident
-    // on an XCD stream the same K and V rows at about the same time and share them in its L2.
-    int unit = blockIdx.y, xtile = blockIdx.x;
+    // of its own.  Launch slot L therefore runs on XCD L % 8; give that XCD a run of whole (batch,
+    // head) units (query heads that share a KV head stay together).  Causal tiles go out heaviest
+    // first over all units of the XCD: the last ones to start are the lightest, and the tiles of a
+    // KV head that run together stream the same K and V rows through that L2.  Tiles of listed rows
+    // and own-block tiles are about equally heavy and go out unit by unit.
+    int unit, xtile;
     {
         const unsigned nu = gridDim.y, nt = gridDim.x;
+        unsigned L = blockIdx.y * nt + blockIdx.x, base = 0, U = nu;
         if (nu % 8 == 0) {
-            const unsigned L = blockIdx.y * nt + blockIdx.x;
-            const unsigned xcd = L & 7, s = L >> 3;
-            unit = (int)(xcd + 8 * (s / nt));
-            xtile = (int)(s % nt);
+            U = nu / 8;
+            base = (L & 7) * U;
+            L >>= 3;
+        }
+        if (FORM == kDense || FORM == kBitSets) {
+            unit = (int)(base + L % U);
+            xtile = (int)(L / U);
+        } else {
+            unit = (int)(base + L / nt);
+            xtile = (int)(L % nt);
         }
     }
     const int b = unit / a.Hq, hq = unit % a.Hq, kvh = hq / (a.Hq / a.Hkv);
-    const bf16 *kb = a.k_cache + (long)(b * a.Hkv + kvh) * a.Tcap * D;
-    const bf16 *vb = a.v_cache + (long)(b * a.Hkv + kvh) * a.Tcap * D;
 
     // ---- which tile is this ----
-    bool gathered = false;
-    long r0 = 0;            // first row of a contiguous tile
-    long kv_begin, kv_end;  // keys visited
+    long r0 = 0;       // first row of a contiguous tile
+    long kv_begin;     // first key visited
+    int n_keys;        // keys visited
     uint32_t lbase = 0, lcount = 0;
-    {
-        const int x = xtile;
-        if (MASKED || a.idx == nullptr) {  // dense causal (or routed by bit sets): heavy tiles first
-            const int tile = a.n_diag - 1 - x;
-            r0 = (long)tile * kMT;
-            kv_begin = 0;
-            kv_end = (r0 + kMT < a.T) ? r0 + kMT : a.T;
-        } else if (a.phase == 1) {  // rows against their own blocks (causal inside)
-            r0 = (long)x * kMT;
-            kv_begin = (r0 / a.block) * a.block;
-            kv_end = (r0 + kMT < a.T) ? r0 + kMT : a.T;
-        } else {
-            if ((uint32_t)x >= a.tile_off[(long)unit * (a.Nb + 1) + a.Nb]) return;
-            const uint4 dd = *reinterpret_cast<const uint4 *>(a.desc + (long)unit * a.desc_stride + x);
-            const int j = (int)dd.x;
-            gathered = true;
-            lbase = dd.y;
-            lcount = dd.z;
-            kv_begin = (long)j * a.block;
-            kv_end = (kv_begin + a.block < a.T) ? kv_begin + a.block : a.T;
-        }
+    if constexpr (FORM == kListed) {
+        if ((uint32_t)xtile >= a.tile_off[(long)unit * (a.Nb + 1) + a.Nb]) return;
+        const uint4 dd = *reinterpret_cast<const uint4 *>(a.desc + (long)unit * a.desc_stride + xtile);
+        lbase = dd.y;
+        lcount = dd.z;
+        kv_begin = (long)dd.x * a.block;
+        n_keys = (int)((kv_begin + a.block < a.T) ? a.block : a.T - kv_begin);
+    } else {
+        const int tile = (FORM == kOwn) ? xtile : a.n_diag - 1 - xtile;  // causal tiles: heavy ones first
+        r0 = (long)tile * kMT;
+        kv_begin = (FORM == kOwn) ? (r0 / a.block) * a.block : 0;
+        n_keys = (int)(((r0 + kMT < a.T) ? r0 + kMT : a.T) - kv_begin);
     }
+    const int n_steps = (n_keys + kKT - 1) / kKT;
 
     // ---- staging: global -> LDS, 2 CPT wave-wide loads per tile and wave ----
-    // Pass i of a tile: this lane fetches 16 bytes of row RPI i + srow; the wave's four (eight)
-    // rows land contiguously.  Rows past kv_end are replaced by the tile's last valid row
-    // (finite data; their scores are masked).
+    // Pass i of a tile: this lane fetches 16 bytes of row RPI i + srow; the wave's rows land
+    // contiguously.  The source is a buffer descriptor re-based to the tile's first row and sized
+    // to its valid rows: rows past the last visited key read as zeros (finite; their scores are masked).
     const int srow = wave * RW + lane / CR;
-    const int gchunk = (lane % CR) ^ chunk_swizzle<D>(srow);
-    auto stage = [&](const bf16 *base, uint16_t *tile, int i, long k0) {
-        const int rem = (int)((kv_end - k0 < kKT) ? kv_end - k0 : kKT);  // valid rows, >= 1
-        const int r = (i * RPI + srow < rem) ? i * RPI + srow : rem - 1;
-        load16_to_lds(lds_source(base + k0 * D), (uint32_t)(r * D + gchunk * 8) * 2u, tile + (i * RPI + wave * RW) * D);
+    const uint32_t gk = (uint32_t)(srow * D + ((lane % CR) ^ chunk_swizzle<D>(srow)) * 8) * 2u;
+    const uint32_t gv = (uint32_t)(srow * D + ((lane % CR) ^ chunk_swizzle<D>(srow & 7)) * 8) * 2u;
+    const bf16 *kb = a.k_cache + ((long)(b * a.Hkv + kvh) * a.Tcap + kv_begin) * D;
+    const bf16 *vb = a.v_cache + ((long)(b * a.Hkv + kvh) * a.Tcap + kv_begin) * D;
+    auto stage = [&](const bf16 *base, uint32_t gsrc, uint16_t *tile, int i, int t) __attribute__((always_inline)) {
+        const int rem = n_keys - t * kKT;  // valid rows from here on, >= 1
+        const LdsSource src = lds_source_sized(base + (long)t * kKT * D, (rem < kKT ? rem : kKT) * D * 2);
+        load16_to_lds_at(src, gsrc, (uint32_t)(i * RPI * D * 2), tile + (i * RPI + wave * RW) * D);
     };
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {  // the first tile only needs the block: issue it before the row list is chased
-        stage(kb, sK0, i, kv_begin);
-        stage(vb, sV0, i, kv_begin);
+    for (int i = 0; i < CPT; ++i) {  // the first tiles only need the block: issue them before the row list is chased
+        stage(kb, gk, sK0, i, 0);
+        stage(vb, gv, sV0, i, 0);
+    }
+    if (n_steps > 1) {
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            stage(kb, gk, sK1, i, 1);
+            stage(vb, gv, sV1, i, 1);
+        }
     }
 
     // ---- this lane's query (a column of S^T) ----
     const int rq = wave * 32 + lq;
-    long tq = -1;
-    int slot = 0;
-    if (gathered) {
-        if ((uint32_t)rq < lcount) {
-            const uint32_t e = a.list[(long)unit * a.list_stride + lbase + rq];
-            tq = (long)(e & ((1u << kSlotShift) - 1u));
+    // whether the lane's row exists, the row, and (listed rows) its slot
+    auto row_of_lane = [&](long &t, int &slot) __attribute__((always_inline)) {
+        slot = 0;
+        if constexpr (FORM == kListed) {
+            const uint32_t e = ((uint32_t)rq < lcount) ? a.list[(long)unit * a.list_stride + lbase + rq] : 0xffffffffu;
+            t = (e == 0xffffffffu) ? -1 : (long)(e & ((1u << kSlotShift) - 1u));
             slot = (int)(e >> kSlotShift);
+        } else {
+            t = (r0 + rq < a.T) ? r0 + rq : -1;
         }
-    } else if (r0 + rq < a.T) {
-        tq = r0 + rq;
-    }
-    const bool causal = !gathered;
-    const long own_begin = (!MASKED && a.idx != nullptr && !gathered && tq >= 0) ? (tq / a.block) * a.block : 0;
-    // last key any lane of this wave may see (contiguous tiles): later steps are skipped by the wave
+    };
+    // last key (from kv_begin) any lane of this wave may see: later steps are skipped by the wave
     // (a wave none of whose 32 rows exists skips every step; it still stages its share of the tiles)
-    const bool wave_live = gathered ? ((uint32_t)(wave * 32) < lcount) : (r0 + wave * 32 < a.T);
-    const long wave_last = !wave_live ? -1 : causal ? ((r0 + wave * 32 + 31 < a.T) ? r0 + wave * 32 + 31 : a.T - 1) : kv_end - 1;
+    const bool wave_live = (FORM == kListed) ? ((uint32_t)(wave * 32) < lcount) : (r0 + wave * 32 < a.T);
+    int wave_last = n_keys - 1;
+    if constexpr (FORM != kListed) {
+        const int e = (int)(r0 - kv_begin) + wave * 32 + 31;
+        wave_last = (e < wave_last) ? e : wave_last;
+    }
+    if (!wave_live) wave_last = -1;
 
-    // keys visible to this lane's query, as 32-bit offsets from kv_begin (everything for a padding
-    // lane: it never triggers the masking path, its results are dropped)
-    int vis_lo = 0, vis_hi = (int)(kv_end - kv_begin) - 1;
-    if (causal) {
-        vis_lo = (int)(own_begin - kv_begin);
-        vis_hi = (tq - kv_begin < vis_hi) ? (int)(tq - kv_begin) : vis_hi;
-    }
-    if (tq < 0) {
-        vis_lo = INT32_MIN / 2;
-        vis_hi = INT32_MAX / 2;
-    }
+    // keys visible to this lane's query, as 32-bit offsets from kv_begin: vis_lo .. vis_hi (a row that
+    // does not exist is treated as one; its results are dropped)
+    int vis_lo = 0;  // kOwn: past every key where the row's own block is not listed
+    auto vis_hi = [&]() __attribute__((always_inline)) -> int {
+        if constexpr (FORM == kListed) return n_keys - 1;
+        const int e = (int)(r0 - kv_begin) + wave * 32 + (lane & 31);
+        return (e < n_keys - 1) ? e : n_keys - 1;
+    };
+    uint64_t selmask = ~0ull;  // kBitSets: the blocks this lane's row listed (its own block only if listed)
+    uint32_t others = 0u;      // kOwn: the slots of the row's other blocks
     bf16x8 qf[NC];
     {
+        long tq;
+        int slot;
+        row_of_lane(tq, slot);
         const bf16 *qrow = a.q + ((long)unit * a.T + (tq >= 0 ? tq : 0)) * D;
 #pragma unroll
         for (int c = 0; c < NC; ++c) qf[c] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * c + 8 * h);
-    }
-
-    // ---- routed by bit sets: the blocks this lane's row listed (its own block only if listed) ----
-    uint64_t selmask = ~0ull;
-    if constexpr (MASKED) {
-        selmask = 0ull;
-        if (tq >= 0) {
-            const int32_t *row = a.idx + ((long)unit * a.T + tq) * a.K;
-            for (int kk = 0; kk < a.K; ++kk) {
-                const int j = row[kk];
-                if (j >= 0 && j < 64) selmask |= 1ull << j;
-            }
-        }
-    }
-    // the blocks any row of this wave listed, as a scalar: steps outside it are skipped by the wave
-    uint64_t wave_mask = ~0ull;
-    if constexpr (MASKED) {
-        uint32_t lo = (uint32_t)selmask, hi = (uint32_t)(selmask >> 32);
+        // the row's list, eight entries at a time so that their loads are on their way together
+        if constexpr (FORM == kBitSets || FORM == kOwn) {
+            selmask = 0ull;
+            const int own = (FORM == kOwn && tq >= 0) ? (int)(tq / a.block) : -1;
+            bool own_listed = false;
+            const int32_t *row = a.idx + ((long)unit * a.T + (tq >= 0 ? tq : 0)) * a.K;
+            for (int kk = 0; kk < a.K; kk += 8) {
+                int j[8];
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            lo |= (uint32_t)__shfl_xor((int)lo, m);
-            hi |= (uint32_t)__shfl_xor((int)hi, m);
+                for (int u = 0; u < 8; ++u) j[u] = row[(kk + u < a.K) ? kk + u : a.K - 1];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const bool in = tq >= 0 && kk + u < a.K && j[u] >= 0;
+                    if constexpr (FORM == kBitSets) {
+                        if (in && j[u] < 64) selmask |= 1ull << j[u];
+                    } else {
+                        own_listed = own_listed || j[u] == own;
+                        if (in && j[u] != own) others |= 1u << (kk + u);
+                    }
+                }
+            }
+            if constexpr (FORM == kOwn) vis_lo = own_listed ? (int)((long)own * a.block - kv_begin) : INT32_MAX / 2;
         }
-        wave_mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)hi) << 32) |
-                    (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
     }
+    // kBitSets: the blocks any row of this wave listed, as a scalar: steps outside it are skipped by the wave
+    uint64_t wave_mask = ~0ull;
+    if constexpr (FORM == kBitSets) wave_mask = (uint64_t)wave_or((uint32_t)(selmask >> 32)) << 32 | wave_or((uint32_t)selmask);
 
     // ---- operand addresses inside a tile (elements), fixed per lane ----
-    // K operand: row 32 sub + lq, chunk 2 c + h.  V operand through the transpose read: lane =
-    // 32 h + 16 dg + L supplies 8 bytes of row 32 sub + 16 c + 4 h + (L >> 2) (+ 8 for the
-    // second read) at d = 32 dt + 16 dg + 4 (L & 3).  The swizzle only depends on the row
-    // modulo 16, so sub and c enter as plain row offsets.
+    // K operand: row lq, chunk 2 c + h.  V operand through the transpose read: lane =
+    // 32 h + 16 dg + L supplies 8 bytes of row 16 c + 4 h + (L >> 2) (+ 8 for the
+    // second read) at d = 32 dt + 16 dg + 4 (L & 3).  The swizzle of K depends on the row modulo
+    // 16 and that of V on the row modulo 8 (a transpose read touches eight consecutive rows), so c
+    // and the second read enter as plain row offsets.
     const int L = lane & 15, dg = (lane >> 4) & 1;
-    uint32_t koff[NC], voff[NDT][2];
+    uint32_t koff[NC], voff[NDT];
     {
         const int sw = chunk_swizzle<D>(lq);
 #pragma unroll
         for (int c = 0; c < NC; ++c) koff[c] = (uint32_t)(lq * D + (((2 * c + h) ^ sw) * 8));
-        const int rowa = 4 * h + (L >> 2);
+        const int rowa = 4 * h + (L >> 2), sv = chunk_swizzle<D>(rowa);
 #pragma unroll
-        for (int ab = 0; ab < 2; ++ab) {
-            const int sv = chunk_swizzle<D>(rowa + 8 * ab);
-#pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) {
-                const int cg = 4 * dt + 2 * dg + ((L & 3) >> 1);
-                voff[dt][ab] = (uint32_t)((rowa + 8 * ab) * D + ((cg ^ sv) * 8) + 4 * (L & 1));
-            }
+        for (int dt = 0; dt < NDT; ++dt) {
+            const int cg = 4 * dt + 2 * dg + ((L & 3) >> 1);
+            voff[dt] = (uint32_t)(rowa * D + ((cg ^ sv) * 8) + 4 * (L & 1));
         }
     }
 
@@ -353,99 +392,89 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
-    // running max and sum in the base-2 domain: p = 2^(s * scale * log2(e) - m)
+    // running max (the reference point, -inf: none yet), minus it (0 while there is none) and this
+    // lane's half of the running sum, in the base-2 domain: p = 2^(s * scale * log2(e) - m)
     const float cs = a.scale * 1.4426950408889634f;
-    float m = -INFINITY, l = 0.f;
+    float m = -INFINITY, nb = 0.f, l = 0.f;
 
-    const int n_steps = (int)((kv_end - kv_begin + kKT - 1) / kKT);
     const int steps_per_block = a.block / kKT;
-    int cur_blk = 0, cur_rem = steps_per_block;  // MASKED: kv_begin = 0
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's part of tile 0 is in LDS
-    __syncthreads();
+    int cur_blk = 0, cur_rem = steps_per_block;  // kBitSets: kv_begin = 0
+    // this wave's parts of the first tiles are in LDS
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    asm volatile("s_barrier" ::: "memory");
 
-    // One step: keys k0 .. k0 + 63 from buffer buf; with NEXT, the tile after it is staged
-    // into the other buffer, one load at a time between the matrix instructions (a wave that
-    // issues its loads in one burst stalls until the CU's vector memory path has taken them).
-    auto step = [&](auto next_tag, auto buf_tag, int it) {
-        constexpr bool NEXT = decltype(next_tag)::value;
+    // One step: keys 32 it .. 32 it + 31 from ring slot BUF; with NEXT, the tile two steps ahead is
+    // staged into the slot the previous step has left, one load at a time between the matrix
+    // instructions (a wave that issues its loads in one burst stalls until the CU's vector memory
+    // path has taken them).
+    auto step = [&](auto main_tag, auto skip_tag, auto mask_tag, auto buf_tag, int it) __attribute__((always_inline)) {
+        // MAIN: a further tile two steps ahead is known to exist; otherwise that is looked up here
+        constexpr bool MAIN = decltype(main_tag)::value, SKIP = decltype(skip_tag)::value, MASK = decltype(mask_tag)::value;
+        constexpr bool NEXT = MAIN && !SKIP;  // stage between the matrix instructions
         constexpr int BUF = decltype(buf_tag)::value;
-        const long k0 = kv_begin + (long)it * kKT;
-        const uint16_t *cK = BUF ? sK1 : sK0, *cV = BUF ? sV1 : sV0;
-        uint16_t *nK = BUF ? sK0 : sK1, *nV = BUF ? sV0 : sV1;
-        const long kn = k0 + kKT;
+        const uint16_t *cK = BUF == 0 ? sK0 : BUF == 1 ? sK1 : sK2, *cV = BUF == 0 ? sV0 : BUF == 1 ? sV1 : sV2;
+        uint16_t *nK = BUF == 0 ? sK2 : BUF == 1 ? sK0 : sK1, *nV = BUF == 0 ? sV2 : BUF == 1 ? sV0 : sV1;
+        const int kr = it * kKT;
 
         bool sel = true;
-        if constexpr (MASKED) sel = (selmask >> cur_blk) & 1ull;
-        if (k0 > wave_last || (MASKED && !((wave_mask >> cur_blk) & 1ull))) {
-            if constexpr (NEXT) {
+        if constexpr (FORM == kBitSets) sel = (selmask >> cur_blk) & 1ull;
+        const bool more = MAIN || it + 2 < n_steps;
+        if (!NEXT && more) {
 #pragma unroll
-                for (int i = 0; i < CPT; ++i) {
-                    stage(kb, nK, i, kn);
-                    stage(vb, nV, i, kn);
-                }
+            for (int i = 0; i < CPT; ++i) {
+                stage(kb, gk, nK, i, it + 2);
+                stage(vb, gv, nV, i, it + 2);
             }
-        } else {
-            // S^T[key][query] = sum_d K[key][d] Q[query][d], two 32-key sub-tiles; consecutive
-            // matrix instructions go to different accumulators (a dependent one issued back to
-            // back waits for the previous result)
-            // matrix phases run at raised priority: of the two waves that share a SIMD, the one
-            // feeding the matrix pipe is issued first and the other's softmax fills the gaps
+        }
+        if (!SKIP || (kr <= wave_last && (FORM != kBitSets || ((wave_mask >> cur_blk) & 1ull)))) {
+            // S^T[key][query] = sum_d K[key][d] Q[query][d].  Matrix phases run at raised priority:
+            // of the waves that share a SIMD, the one feeding the matrix pipe is issued first and the
+            // others' softmax fills the gaps
             __builtin_amdgcn_s_setprio(1);
-            f32x16 sacc[2];
+            f32x16 sacc;
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) sacc[sub][v] = 0.f;
+            for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 if constexpr (NEXT) {
-                    if (c % (NC / CPT) == 0) stage(kb, nK, c / (NC / CPT), kn);
+                    if (c % (NC / CPT) == 0) stage(kb, gk, nK, c / (NC / CPT), it + 2);
                 }
-#pragma unroll
-                for (int sub = 0; sub < 2; ++sub) {
-                    const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(&cK[32 * sub * D + koff[c]]);
-                    sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], sacc[sub], 0, 0, 0);
-                }
+                const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(&cK[koff[c]]);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], sacc, 0, 0, 0);
             }
-            // issue order for the block above: operand reads run two matrix-instruction pairs
-            // ahead of their use, the direct loads go out one at a time in between
-            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+            // issue order: operand reads run three matrix instructions ahead of their use, the direct
+            // loads go out one at a time in between
+            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
 #pragma unroll
-            for (int g = 0; g < NC - 2; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            for (int g = 0; g < NC - 3; ++g) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 if (NEXT && g < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-            // masks only where a boundary crosses this step (uniform over the wave)
-            // (all in 32-bit offsets from kv_begin: the lane sees keys vis_lo .. vis_hi)
+            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
             __builtin_amdgcn_s_setprio(0);
-            const int kr = it * kKT;
-            if (__any(kr < vis_lo || kr + kKT - 1 > vis_hi)) {
-                const int hi = ((vis_hi - kr > kKT) ? kKT : ((vis_hi - kr < -1) ? -1 : vis_hi - kr)) - 4 * h;
-                const int lo = ((vis_lo - kr > kKT) ? kKT : ((vis_lo - kr < -1) ? -1 : vis_lo - kr)) - 4 * h;
+            // masks only where a boundary crosses this step (uniform over the wave)
+            if (MASK && __any(kr < vis_lo || kr + kKT - 1 > vis_hi())) {
+                // (in offsets from this lane's first key of the step; far values stay far)
+                const int hi = vis_hi() - kr - 4 * h, lo = vis_lo - kr - 4 * h;
 #pragma unroll
-                for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int e = 32 * sub + 8 * (v / 4) + (v % 4);  // + 4 h: folded into lo, hi
-                        if (e > hi || e < lo) sacc[sub][v] = -INFINITY;
-                    }
+                for (int v = 0; v < 16; ++v) {
+                    const int e = 8 * (v / 4) + (v % 4);  // + 4 h: folded into lo, hi
+                    if (e > hi || e < lo) sacc[v] = -INFINITY;
+                }
             }
-            float mx = -INFINITY;
+            float mx = sacc[0];
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[sub][v]);
+            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
             mx = half_pair_max(mx) * cs;  // cs > 0: scaling commutes with max
-            if (MASKED && !sel) mx = -INFINITY;
+            if (FORM == kBitSets && !sel) mx = -INFINITY;
             // the reference point of the exponentials follows the running maximum lazily: it moves
             // only when the maximum has grown by more than kLazy (p then stays below 2^kLazy,
             // harmless in float32 and bfloat16), so the accumulators are rarely rescaled
-            const float m_cand = fmaxf(m, mx);
-            const float m_new = (m_cand - m > kLazy) ? m_cand : m;  // -inf -> finite counts as a move
-            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-            if (__any(m_new != m)) {
+            // (-inf -> finite counts as a move; -inf -> -inf compares false)
+            if (__any(mx - m > kLazy)) {
+                const float m_new = (mx - m > kLazy) ? mx : m;
+                const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
                 const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_safe);
                 l *= alpha;
 #pragma unroll
@@ -453,90 +482,117 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                     for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
                 m = m_new;
+                nb = -m_safe;
             }
-            float psum = 0.f;
             // a row that did not list this step's block: every exponent is -inf, p = 0
-            const float ebias = (MASKED && !sel) ? -INFINITY : -m_safe;
+            const float ebias = (FORM == kBitSets && !sel) ? -INFINITY : nb;
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
+            for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(fmaf(sacc[v], cs, ebias));
+            {
+                float s4[4];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    sacc[sub][v] = __builtin_amdgcn_exp2f(fmaf(sacc[sub][v], cs, ebias));
-                    psum += sacc[sub][v];
-                }
-            l += half_pair_sum(psum);
-            __builtin_amdgcn_s_setprio(1);
+                for (int v = 0; v < 4; ++v) s4[v] = (sacc[v] + sacc[v + 4]) + (sacc[v + 8] + sacc[v + 12]);
+                l += (s4[0] + s4[1]) + (s4[2] + s4[3]);
+            }
             // P^T as the B operand: accumulator values 8c .. 8c+7 are this lane's keys
             // 16c + 4h + {0..3} and 16c + 8 + 4h + {0..3}; V^T is read in the same key order
+            bf16x8 pf[2];
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                bf16x8 pf[2];
+            for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int s8 = 0; s8 < 8; ++s8) pf[c][s8] = (__bf16)sacc[8 * c + s8];
+            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                    for (int s8 = 0; s8 < 8; ++s8) pf[c][s8] = (__bf16)sacc[sub][8 * c + s8];
+            for (int c = 0; c < 2; ++c) {
+                if constexpr (NEXT) {
+                    if (c < CPT) stage(vb, gv, nV, c, it + 2);
+                }
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    if constexpr (NEXT) {
-                        if (2 * sub + c < CPT) stage(vb, nV, 2 * sub + c, kn);
-                    }
-#pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) {
-                        const uint16_t *vq = &cV[(32 * sub + 16 * c) * D];
-                        union {
-                            s16x4 s[2];
-                            bf16x8 f;
-                        } vf;
-                        vf.s[0] = lds_read_tr16(vq + voff[dt][0]);
-                        vf.s[1] = lds_read_tr16(vq + voff[dt][1]);
-                        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f, pf[c], oacc[dt], 0, 0, 0);
-                    }
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const uint16_t *vq = &cV[(16 * c) * D];
+                    union {
+                        s16x4 s[2];
+                        bf16x8 f;
+                    } vf;
+                    vf.s[0] = lds_read_tr16(vq + voff[dt]);
+                    vf.s[1] = lds_read_tr16(vq + voff[dt] + 8 * D);
+                    oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f, pf[c], oacc[dt], 0, 0, 0);
                 }
             }
-            // issue order for the P V block: the transposed operand reads (two per matrix
-            // instruction) run ahead of their use, the direct loads go out in between
-            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
-            for (int g = 0; g < 2 * NDT - 2; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+            for (int g = 0; g < 2 * NDT - 3; ++g) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                 if (NEXT && g < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
             __builtin_amdgcn_s_setprio(0);
         }
-        if constexpr (MASKED) {  // block of the next step (wave-uniform counters, no division)
+        if constexpr (FORM == kBitSets) {  // block of the next step (wave-uniform counters, no division)
             if (--cur_rem == 0) {
                 cur_rem = steps_per_block;
                 ++cur_blk;
             }
         }
-        if constexpr (NEXT) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads have landed
-        __syncthreads();
+        // the next step's tile has landed (the one after it, staged above, may still be on its way),
+        // and this wave has read what it needs of the current one
+        if (more) __builtin_amdgcn_s_waitcnt(0x0070 | (2 * CPT));
+        else __builtin_amdgcn_s_waitcnt(0x0070);
+        asm volatile("s_barrier" ::: "memory");
     };
     {
         using B0 = std::integral_constant<int, 0>;
         using B1 = std::integral_constant<int, 1>;
+        using B2 = std::integral_constant<int, 2>;
+        using Main = std::integral_constant<bool, FORM == kBitSets || FORM == kOwn>;  // which loops may skip
+        // keys past a row only occur in the last four steps of a tile (128 keys from the tile's own rows on;
+        // kListed: past the block's end), keys before its own block only in kOwn
+        using MainMask = std::integral_constant<bool, FORM == kOwn>;
+        constexpr std::true_type yes{};
+        constexpr std::false_type no{};
         int it = 0;
-        for (; it + 2 < n_steps; it += 2) {
-            step(std::true_type{}, B0{}, it);
-            step(std::true_type{}, B1{}, it + 1);
+        if (FORM == kListed && !wave_live) {  // this wave only stages
+            for (; it < n_steps; ++it) {
+                const int slot2 = (it + 2) % 3;
+                if (it + 2 < n_steps) {
+                    uint16_t *nK = slot2 == 0 ? sK0 : slot2 == 1 ? sK1 : sK2, *nV = slot2 == 0 ? sV0 : slot2 == 1 ? sV1 : sV2;
+#pragma unroll
+                    for (int i = 0; i < CPT; ++i) {
+                        stage(kb, gk, nK, i, it + 2);
+                        stage(vb, gv, nV, i, it + 2);
+                    }
+                    __builtin_amdgcn_s_waitcnt(0x0070 | (2 * CPT));
+                } else {
+                    __builtin_amdgcn_s_waitcnt(0x0070);
+                }
+                asm volatile("s_barrier" ::: "memory");
+            }
+            return;
         }
-        if (it + 2 == n_steps) {
-            step(std::true_type{}, B0{}, it);
-            step(std::false_type{}, B1{}, it + 1);
-        } else {
-            step(std::false_type{}, B0{}, it);
+        for (; it + 6 < n_steps; it += 3) {
+            step(yes, Main{}, MainMask{}, B0{}, it);
+            step(yes, Main{}, MainMask{}, B1{}, it + 1);
+            step(yes, Main{}, MainMask{}, B2{}, it + 2);
+        }
+        for (;;) {  // at most six steps are left, the first of them in slot 0
+            step(no, yes, yes, B0{}, it);
+            if (++it == n_steps) break;
+            step(no, yes, yes, B1{}, it);
+            if (++it == n_steps) break;
+            step(no, yes, yes, B2{}, it);
+            if (++it == n_steps) break;
         }
     }
+    l = half_pair_sum(l);
 
     // ---- epilogue ----
     // Rows leave (and partial records enter) through LDS, so that global memory sees whole rows:
     // a lane that wrote its own row's channels straight from the accumulator layout would touch
-    // 64 cache lines per store instruction.  After the last step's barrier the four tile buffers
-    // are free; wave w takes buffer w as 64 private rows of D bf16 (two slots of 32 rows), chunks
-    // permuted as in the K/V tiles.  Rows are in channel order: the lane of query row lq, half h
-    // holds channels 32 dt + 8 g + 4 h + {0..3} in oacc[dt][4 g ..].
+    // 64 cache lines per store instruction.  After the last step's barrier the tile buffers are
+    // free; wave w takes one of them as 32 private rows of D bf16, chunks permuted as in the K/V
+    // tiles.  Rows are in channel order: the lane of query row lq, half h holds channels
+    // 32 dt + 8 g + 4 h + {0..3} in oacc[dt][4 g ..].
     if (!wave_live) return;  // no barrier below
     uint16_t *stg = (wave == 0) ? sK0 : (wave == 1) ? sK1 : (wave == 2) ? sV0 : sV1;
     const int sw_lq = chunk_swizzle<D>(lq);
@@ -553,17 +609,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
     };
     auto flush_rows = [&](auto dest_of_row) __attribute__((always_inline)) {
+        int ln = lane;  // (opaque: the addresses below are worked out here and not held in registers until then)
+        asm volatile("" : "+v"(ln));
 #pragma unroll
         for (int i = 0; i < 32 / RW; ++i) {
-            const int row = i * RW + frow;
+            const int row = i * RW + ln / CR, c = ln % CR;
             bf16 *dst = dest_of_row(i, row);
-            const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * D + ((fchunk ^ chunk_swizzle<D>(row)) * 8));
-            if (dst) *reinterpret_cast<uint4 *>(dst + fchunk * 8) = v;
+            const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * D + ((c ^ chunk_swizzle<D>(row)) * 8));
+            if (dst) *reinterpret_cast<uint4 *>(dst + c * 8) = v;
         }
     };
+    long tq;
+    int slot;
+    row_of_lane(tq, slot);
     const float inv = (l > 0.f) ? 1.f / l : 0.f;
     const float lse = (l > 0.f) ? (m + __log2f(l)) * 0.6931471805599453f : -INFINITY;
-    if (!MASKED && a.idx != nullptr && gathered) {
+    if constexpr (FORM == kListed) {
         // a partial record: the row's normalised output over one listed block as bf16 (channel
         // order), its log-sum-exp as float32 in an array of its own
         uint32_t ent[32 / RW];  // list entries of the rows this lane helps to flush
@@ -585,81 +646,71 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const long wrow0 = r0 + wave * 32;  // contiguous tiles: the wave's first row
     float out_scale = inv;
     float out_lse = lse;
-    if (!MASKED && a.idx != nullptr) {
+    if constexpr (FORM == kOwn) {
         // own-block tile: fold in the partials the listed-row tiles left for this row's other
         // blocks (they ran in the previous launch).  Two slots at a time: their records of the
-        // wave's 32 rows come in by row-contiguous direct loads, the lanes then pick their channels.
-        const long tqc = (tq >= 0) ? tq : wrow0;  // padding lanes read a valid row and drop the result
-        const int own = (int)(tqc / a.block);
-        const long rbase = ((long)unit * a.T + tqc) * a.K;
-        const int32_t *row = a.idx + rbase;
-        bool own_listed = false;
-        for (int k = 0; k < a.K; ++k) own_listed = own_listed || (row[k] == own);
-        float M = own_listed ? lse : -INFINITY;  // an own block that is not listed does not count
+        // wave's 32 rows come in by row-contiguous loads, pass through LDS one slot after the
+        // other, and the lanes pick their channels there.
+        const long rbase = ((long)unit * a.T + (tq >= 0 ? tq : wrow0)) * a.K;
+        float M = lse;  // (-inf, and nothing accumulated, where the own block is not listed)
         float wsum = (M == -INFINITY) ? 0.f : 1.f;
-        {
-            const float w_own = wsum * inv;  // o_own = oacc * inv
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
+        for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) oacc[dt][v] *= w_own;
-        }
+            for (int v = 0; v < 16; ++v) oacc[dt][v] *= inv;
         const int rows_here = (int)((a.T - wrow0 < 32) ? a.T - wrow0 : 32);  // >= 1
-        for (int kc = 0; kc < a.K; kc += 2) {
+        for (uint32_t todo = wave_or(others); todo != 0u;) {
+            int slots[2];
+            slots[0] = __builtin_ctz(todo);
+            todo &= todo - 1u;
+            const bool two = todo != 0u;
+            slots[1] = two ? __builtin_ctz(todo) : slots[0];
+            todo &= todo - 1u;  // (0 stays 0)
+            u32x4 rec[2][32 / RW];
             float ls[2];
-            bool any_valid = false;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const int k = kc + i;
-                const int jk = (k < a.K) ? row[k] : -1;
-                const bool valid = jk >= 0 && jk != own && tq >= 0;
-                ls[i] = valid ? a.part_lse[rbase + k] : -INFINITY;
-                any_valid = any_valid || valid;
-            }
-            if (!__any(any_valid)) continue;  // wave-uniform
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int k = (kc + i < a.K) ? kc + i : a.K - 1;
-                const LdsSource src = lds_source(reinterpret_cast<const bf16 *>(a.part_o) + (((long)unit * a.T + wrow0) * a.K + k) * D);
+                const bool valid = ((others >> slots[i]) & 1u) && (i == 0 || two);
+                const float x = a.part_lse[rbase + slots[i]];
+                ls[i] = valid ? x : -INFINITY;
+                const uint16_t *src = a.part_o + (((long)unit * a.T + wrow0) * a.K + slots[i]) * D;
 #pragma unroll
                 for (int j = 0; j < 32 / RW; ++j) {
                     const int rr = j * RW + frow;
                     const int rc = (rr < rows_here) ? rr : rows_here - 1;
-                    load16_to_lds(src, (uint32_t)(rc * a.K * D + ((fchunk ^ chunk_swizzle<D>(rr)) * 8)) * 2u,
-                                  stg + (i * 32 + j * RW) * D);
+                    rec[i][j] = *reinterpret_cast<const u32x4 *>(src + (uint32_t)(rc * a.K * D + fchunk * 8));
                 }
             }
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the records are in LDS
-            uint2 rc2[2][4 * NDT];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int u = 0; u < 4 * NDT; ++u)
-                    rc2[i][u] = *reinterpret_cast<const uint2 *>(stg + (i * 32 + lq) * D + ((u ^ sw_lq) * 8) + 4 * h);
             float Mn = M;
 #pragma unroll
             for (int i = 0; i < 2; ++i) Mn = fmaxf(Mn, ls[i]);
+            const float al = (M == -INFINITY || Mn == -INFINITY) ? 0.f : __expf(M - Mn);
             if (Mn != -INFINITY) {
-                const float al = (M == -INFINITY) ? 0.f : __expf(M - Mn);
                 M = Mn;
                 wsum *= al;
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) oacc[dt][v] *= al;
+            }
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const float w = (ls[i] == -INFINITY) ? 0.f : __expf(ls[i] - M);
-                    wsum += w;
-                    if (ls[i] != -INFINITY) {  // a record that was never written may hold anything
+            for (int i = 0; i < 2; ++i) {
 #pragma unroll
-                        for (int u = 0; u < 4 * NDT; ++u) {
-                            const int dt = u >> 2, g = u & 3;
-                            oacc[dt][4 * g] = fmaf(w, __uint_as_float(rc2[i][u].x << 16), oacc[dt][4 * g]);
-                            oacc[dt][4 * g + 1] = fmaf(w, __uint_as_float(rc2[i][u].x & 0xffff0000u), oacc[dt][4 * g + 1]);
-                            oacc[dt][4 * g + 2] = fmaf(w, __uint_as_float(rc2[i][u].y << 16), oacc[dt][4 * g + 2]);
-                            oacc[dt][4 * g + 3] = fmaf(w, __uint_as_float(rc2[i][u].y & 0xffff0000u), oacc[dt][4 * g + 3]);
-                        }
+                for (int j = 0; j < 32 / RW; ++j) {
+                    const int rr = j * RW + frow;
+                    *reinterpret_cast<u32x4 *>(stg + rr * D + ((fchunk ^ chunk_swizzle<D>(rr)) * 8)) = rec[i][j];
+                }
+                const float w = (ls[i] == -INFINITY) ? 0.f : __expf(ls[i] - M);
+                wsum += w;
+                if (ls[i] != -INFINITY) {  // a record that was never written may hold anything
+#pragma unroll
+                    for (int u = 0; u < 4 * NDT; ++u) {
+                        const uint2 rc2 = *reinterpret_cast<const uint2 *>(stg + lq * D + ((u ^ sw_lq) * 8) + 4 * h);
+                        const int dt = u >> 2, g = u & 3;
+                        oacc[dt][4 * g] = fmaf(w, __uint_as_float(rc2.x << 16), oacc[dt][4 * g]);
+                        oacc[dt][4 * g + 1] = fmaf(w, __uint_as_float(rc2.x & 0xffff0000u), oacc[dt][4 * g + 1]);
+                        oacc[dt][4 * g + 2] = fmaf(w, __uint_as_float(rc2.y << 16), oacc[dt][4 * g + 2]);
+                        oacc[dt][4 * g + 3] = fmaf(w, __uint_as_float(rc2.y & 0xffff0000u), oacc[dt][4 * g + 3]);
                     }
                 }
             }
@@ -746,7 +797,6 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     p.part_o = nullptr;
     p.part_lse = nullptr;
     p.list_stride = 0;
-    p.phase = 2;
     if (idx && Nb > 256) return RS_UNSUPPORTED;
     // Routings that are dense for their length (small blocks, many picks: the paper's 64- and
     // 128-token blocks with top-8 / top-16 at 4K) run as causal tiles with a bit set per row
@@ -756,13 +806,13 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     // skipped.  Measured at 8 x 32 heads x 4096 tokens (regrouped / bit sets / plain causal, ms):
     // blocks of 64: top-16 3.14 / 1.20 / 1.30, top-8 1.75 / 1.16, top-4 0.98 / 1.08;
     // blocks of 128: top-8 1.72 / 1.19, top-4 0.98 / 1.15; 8192 tokens, 128, top-8: 0.92 / 1.03.
-    const bool can_mask = idx && Nb <= 64 && block % kKT == 0;
+    const bool can_mask = idx && Nb <= 64 && block % 64 == 0;
     const double by_sets = 0.85 * (p.n_diag + 4.0), regrouped = (K - 1) * (4.3 + block / 64.0) + 9.0;
     const int masked = can_mask ? knob_or(knobs().prefill_masked, by_sets < regrouped ? 1 : 0) : 0;
     if (masked) {
         const dim3 grid((unsigned)p.n_diag, (unsigned)units);
-        if (s->D == 128) prefill_attn_kernel<128, true><<<grid, 256, 0, stream>>>(p);
-        else prefill_attn_kernel<64, true><<<grid, 256, 0, stream>>>(p);
+        if (s->D == 128) prefill_attn_kernel<128, kBitSets><<<grid, 256, 0, stream>>>(p);
+        else prefill_attn_kernel<64, kBitSets><<<grid, 256, 0, stream>>>(p);
         return hipGetLastError() == hipSuccess ? RS_OK : RS_LAUNCH_FAILED;
     }
     if (idx) {
@@ -790,17 +840,20 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     if (idx) {
         // launch 1: tiles of listed rows leave partials; launch 2: own-block tiles fold them in
         const long gathered_tiles = p.desc_stride;  // upper bound per (batch, head)
-        p.phase = 0;
         const dim3 g0((unsigned)gathered_tiles, (unsigned)units);
         if (K > 1) {
-            if (s->D == 128) prefill_attn_kernel<128, false><<<g0, 256, 0, stream>>>(p);
-            else prefill_attn_kernel<64, false><<<g0, 256, 0, stream>>>(p);
+            if (s->D == 128) prefill_attn_kernel<128, kListed><<<g0, 256, 0, stream>>>(p);
+            else prefill_attn_kernel<64, kListed><<<g0, 256, 0, stream>>>(p);
         }
-        p.phase = 1;
     }
     const dim3 grid((unsigned)p.n_diag, (unsigned)units);
-    if (s->D == 128) prefill_attn_kernel<128, false><<<grid, 256, 0, stream>>>(p);
-    else prefill_attn_kernel<64, false><<<grid, 256, 0, stream>>>(p);
+    if (idx) {
+        if (s->D == 128) prefill_attn_kernel<128, kOwn><<<grid, 256, 0, stream>>>(p);
+        else prefill_attn_kernel<64, kOwn><<<grid, 256, 0, stream>>>(p);
+    } else {
+        if (s->D == 128) prefill_attn_kernel<128, kDense><<<grid, 256, 0, stream>>>(p);
+        else prefill_attn_kernel<64, kDense><<<grid, 256, 0, stream>>>(p);
+    }
     return hipGetLastError() == hipSuccess ? RS_OK : RS_LAUNCH_FAILED;
 }
 

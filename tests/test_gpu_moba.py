@@ -211,3 +211,35 @@ def test_lists_are_taken_as_given(rs, knobs, form):
     assert ok, worst
     np.testing.assert_allclose(glse[~empty], olse[~empty], rtol=2e-3, atol=2e-3)
     ws.async_status()
+
+
+@pytest.mark.parametrize("D,Hq,Hkv", [(64, 3, 1), (128, 8, 2)])  # units in launch order; eight units, one per XCD
+def test_prefill_tile_edges(rs, knobs, D, Hq, Hkv):
+    """Lengths around the edges of the 32-key tiles, of the ring of three of them and of the 128-row
+    tiles, in every form of the kernel; cache rows past T hold NaN and must not be looked at."""
+    block, K, rng = 64, 3, np.random.default_rng(31)
+    for T in (1, 31, 32, 33, 64, 96, 97, 128, 129, 190, 225, 257, 330):
+        say("prefill tile edges", D, T)
+        w, q, kc, vc = _setup(synth.C4.scaled(B=1, Hq=Hq, Hkv=Hkv, D=D, n_needles=1), T, T + 16)
+        dk, dv = kc.copy(), vc.copy()
+        dk[:, :, T:], dv[:, :, T:] = np.nan, np.nan
+        idx = np.full((1, Hq, T, K), -1, dtype=np.int32)
+        for h in range(Hq):
+            for t in range(T):
+                n = min(K, t // block + 1)
+                idx[0, h, t, :n] = np.sort(rng.choice(t // block + 1, size=n, replace=False))
+        s = rs.make_shape(1, Hq, Hkv, D, T + 16, 16, torch.bfloat16)
+        ws = rs.Workspace(rs.sparse_attn_prefill_workspace_bytes(s, T, block, K))
+        scale = 1.0 / np.sqrt(D)
+        for form in ("dense", "0", "1"):
+            knobs.setenv("RATSPARSE_PREFILL_MASKED", "0" if form == "dense" else form)
+            lists = None if form == "dense" else idx
+            out = torch.full((1, Hq, T, D), 7.0, dtype=torch.bfloat16, device="cuda")
+            lse = torch.full((1, Hq, T), 7.0, device="cuda")
+            rs.sparse_attn_prefill(s, to_dev(q, "bf16"), to_dev(dk, "bf16"), to_dev(dv, "bf16"), T, block, scale,
+                                   None if lists is None else torch.from_numpy(lists).cuda(), K, out, lse, ws)
+            oout, olse = oracle.sparse_attn_prefill(q, kc, vc, T, block, scale, lists)
+            ok, worst = attn_close(to_np(out), oout)  # one bf16 step of the output is 4e-3 of it; 2e-2 allows five
+            assert ok, (T, form, worst)
+            np.testing.assert_allclose(to_np(lse), olse, rtol=2e-3, atol=2e-3)
+        ws.async_status()
