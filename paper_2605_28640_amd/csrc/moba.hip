@@ -9,7 +9,8 @@ namespace rs {
 // ------------------------------------------------------------------------------------
 // block means: one workgroup per (block, batch*KV head); float32 accumulation
 // ------------------------------------------------------------------------------------
-template <typename ST, int D>
+// Bound by memory: eight rows per lane are on their way at a time; STREAM: as streaming loads (kStreamBytes).
+template <typename ST, int D, bool STREAM>
 __global__ __launch_bounds__(256) void moba_block_means_kernel(const ST *__restrict__ k_cache,
                                                                float *__restrict__ means, uint16_t *__restrict__ split,
                                                                long Tcap, long T, int block, int Nb)
@@ -39,9 +40,12 @@ __global__ __launch_bounds__(256) void moba_block_means_kernel(const ST *__restr
     float acc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+#pragma unroll 8
     for (long t = t0 + wave * RPW + rg; t < t1; t += 4 * RPW) {
+        const ST *row = k_cache + (bh * Tcap + t) * D + c0;
+        const typename R::raw_t raw = STREAM ? R::load_raw_nt(row) : R::load_raw(row);
         float x[8];
-        R::load(k_cache + (bh * Tcap + t) * D + c0, x);
+        R::unpack(raw, x);
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[c] += x[c];
     }
@@ -565,15 +569,21 @@ int moba_select_dispatch(const rs_shape *s, const void *q, const void *k_cache, 
     // worth its set-up from about 8192 tiles on (C4 0.148 -> 0.138 ms; 8 x 32 heads x 4096 tokens, blocks of 64,
     // top-8: 0.184 -> 0.150 ms; 32 heads x 4096 tokens: 0.026 against 0.031 ms the other way)
     const bool shared_ops = in_registers && (eso != kKnobUnset ? eso != 0 : units * n_tiles >= 8192);
+    const bool big = (long)s->B * s->Hkv * T * s->D * (s->dtype == RS_BF16 ? 2 : 4) >= kStreamBytes;
+#define RS_MEANS(ST, DD, GRID, SPLIT)                                                                                          \
+    do {                                                                                                                       \
+        if (big) moba_block_means_kernel<ST, DD, true><<<GRID, 256, 0, stream>>>((const ST *)k_cache, means_out, SPLIT, s->Tcap, T, block, Nb); \
+        else moba_block_means_kernel<ST, DD, false><<<GRID, 256, 0, stream>>>((const ST *)k_cache, means_out, SPLIT, s->Tcap, T, block, Nb);    \
+    } while (0)
 #define RS_LAUNCH(ST, DD)                                                                                          \
     do {                                                                                                           \
-        moba_block_means_kernel<ST, DD><<<g1, 256, 0, stream>>>((const ST *)k_cache, means_out, nullptr, s->Tcap, T, block, Nb); \
+        RS_MEANS(ST, DD, g1, nullptr);                                                                                 \
         moba_gate_topk_kernel<ST, DD><<<g2, 64, lds, stream>>>((const ST *)q, means_out, idx_out, s->Hq, s->Hkv, T,  \
                                                                 block, Nb, K, n_first);                            \
     } while (0)
     if (s->dtype == RS_BF16) {
         if (s->D == 128) {
-            moba_block_means_kernel<bf16, 128><<<g1p, 256, 0, stream>>>((const bf16 *)k_cache, means_out, split, s->Tcap, T, block, Nb);
+            RS_MEANS(bf16, 128, g1p, split);
 #define RS_GATE1(DD, KLL, WW, LDS) moba_gate_mfma_kernel<DD, KLL, WW, 1><<<g3, 64, LDS, stream>>>((const bf16 *)q, split, idx_out, s->Hq, s->Hkv, T, block, Nb, K, n_first)
 #define RS_GATE4(DD, KLL) moba_gate_mfma_kernel<DD, KLL, false, 6><<<g4, 384, 0, stream>>>((const bf16 *)q, split, idx_out, s->Hq, s->Hkv, T, block, Nb, K, n_first)
 #define RS_GATE(DD)                                            \
@@ -593,7 +603,7 @@ int moba_select_dispatch(const rs_shape *s, const void *q, const void *k_cache, 
     } while (0)
             RS_GATE(128);
         } else {
-            moba_block_means_kernel<bf16, 64><<<g1p, 256, 0, stream>>>((const bf16 *)k_cache, means_out, split, s->Tcap, T, block, Nb);
+            RS_MEANS(bf16, 64, g1p, split);
             RS_GATE(64);
         }
 #undef RS_GATE
@@ -604,6 +614,7 @@ int moba_select_dispatch(const rs_shape *s, const void *q, const void *k_cache, 
         else RS_LAUNCH(float, 64);
     }
 #undef RS_LAUNCH
+#undef RS_MEANS
     return hipGetLastError() == hipSuccess ? RS_OK : RS_LAUNCH_FAILED;
 }
 
