@@ -12,7 +12,7 @@
 namespace rs {
 // scan.hip
 int scan_chunk_tokens(int dtype, int D);
-bool scan_writes_meta(int dtype, int D, int P, int BH, long T_new, long t0);
+bool scan_writes_meta(int dtype, int D, int P, int BH, long T_new, long t0, bool has_records);
 bool scan_uses_step_kernel(long T_new);
 void scan_dispatch(int dtype, int D, const void *k, const void *v, const float *g, float *state_k,
                    float *state_v, void *k_cache, void *v_cache, void *meta, int P, int BH, long T_new, long t0,
@@ -439,14 +439,15 @@ int32_t rat_scan(const rs_shape *s, const void *k, const void *v, const float *g
     if (BH * n_chunks > 0x7fffffffL) return RS_UNSUPPORTED;
     uint32_t *ctrl = nullptr;
     uint64_t *rec = nullptr;
-    if (!scan_uses_step_kernel(T_new) && n_chunks > 1) {
-        if (!ws || !aligned16(ws) || ws_bytes < rat_scan_workspace_bytes(s, T_new)) return RS_WORKSPACE_TOO_SMALL;
+    const bool fits = ws && aligned16(ws) && ws_bytes >= rat_scan_workspace_bytes(s, T_new);
+    if (!scan_uses_step_kernel(T_new) && n_chunks > 1 && !fits) return RS_WORKSPACE_TOO_SMALL;
+    if (!scan_uses_step_kernel(T_new) && fits) {
         ctrl = (uint32_t *)ws;
         rec = (uint64_t *)((char *)ws + RS_WS_CTRL_BYTES);
     }
     // the page bounds leave with the states where the kernel can do that (one token: always; long
-    // runs: full-row form, a page size that tiles the chunk, chunk-aligned start); else a pass over the touched pages
-    const bool in_scan = meta && scan_writes_meta(s->dtype, s->D, s->P, (int)BH, T_new, t0);
+    // runs: a page size that tiles the chunk); else a pass over the touched pages
+    const bool in_scan = meta && scan_writes_meta(s->dtype, s->D, s->P, (int)BH, T_new, t0, rec != nullptr);
     scan_dispatch(s->dtype, s->D, k, v, g, state_k, state_v, k_cache, v_cache, in_scan ? meta : nullptr, s->P, (int)BH,
                   T_new, t0, s->Tcap, ctrl, rec, next_tag(), g_spin_limit.load(), (hipStream_t)stream);
     if (meta && !in_scan) {  // the pages the new rows touch are recomputed after the scan

@@ -20,7 +20,9 @@
 // The chunks of one unit form a serial chain (one hop is about 0.7 us), which bounds the
 // time when there are few (batch, head) pairs.  The channels of Eq. 1 are independent, so
 // the kernel can also take a unit to be a slab of DS < D channels of a (batch, head): more,
-// shorter chains (a chunk then spans D / DS times as many tokens for the same bytes).
+// shorter chains (a chunk then spans D / DS times as many tokens for the same bytes).  In that form
+// the chunks may be laid out from a chunk boundary before the run, so that a run that starts anywhere
+// leaves its pages' bounds too (8 heads x 3001 tokens from 5003: 19.6 -> 16.1 us, one launch for two).
 #include <cstdlib>
 
 #include "common.h"
@@ -28,8 +30,8 @@
 
 namespace rs {
 
-// PAGE > 0 (a run that starts on a chunk boundary, PAGE a power of two from 16 tokens
-// to the chunk length): a wave's tokens (16 or 32 in bfloat16, 8 or 16 in float32, at 128 or 64
+// PAGE > 0 (a power of two from 16 tokens to the chunk length; the chunks are laid out from the chunk
+// boundary at or below t0, `lead` tokens before the run, where they pass the state on): a wave's tokens (16 or 32 in bfloat16, 8 or 16 in float32, at 128 or 64
 // channels) are whole pages or an aligned part of one, so the page's channelwise min / max of the stored keys (App. A.1,
 // Quest) leave with the states -- in-lane over the lane's four tokens, shuffles over the row
 // groups of a page, and for pages longer than a wave's tokens a fold of the waves' bounds
@@ -39,8 +41,9 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const ST *__restrict__ k, const ST *__restrict__ v, const float *__restrict__ g,
     float *__restrict__ state_k, float *__restrict__ state_v, ST *__restrict__ k_cache,
     ST *__restrict__ v_cache, int BH, long T_new, long t0, long Tcap, int n_chunks,
-    uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit, ST *__restrict__ meta, int deep)
+    uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit, ST *__restrict__ meta, int deep, int lead_arg)
 {
+    const int lead = DS < D ? lead_arg : 0;  // (the full-row form starts on a chunk boundary where it leaves bounds)
     constexpr bool META = PAGE > 0;
     constexpr int TW = (64 / (DS / 8)) * NT;  // tokens of a wave
     static_assert(!META || (PAGE >= 16 && (NW * TW) % (PAGE > 0 ? PAGE : 1) == 0), "pages tile the chunk");
@@ -92,14 +95,14 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         const int unit = ticket % units;
         const int bh = unit / NS;
         const int ch0 = (unit % NS) * DS;
-        const long tbase = (long)j * CHUNK + (long)(wave * RPW + rg) * NT;
+        const long tbase = (long)j * CHUNK + (long)(wave * RPW + rg) * NT - lead;
         const long in_row0 = (long)bh * T_new;
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             const long t = tbase + i;
             typename R::raw_t kq = R::zero_raw(), vq = R::zero_raw();
-            float4 ga = make_float4(1.f, 1.f, 1.f, 1.f), gb = ga;  // past the end: the identity element (g = 1 keeps the state)
-            if (t < T_new) {
+            float4 ga = make_float4(1.f, 1.f, 1.f, 1.f), gb = ga;  // outside the run: the identity element (g = 1 keeps the state)
+            if ((DS == D || t >= 0) && t < T_new) {
                 const long off = (in_row0 + t) * D + ch0 + c0;
                 if constexpr (DS == D) {
                     // whole rows, read once: streaming loads (a slab shares its cache lines with the
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const int unit = ticket % units;  // consecutive tickets walk the units first
     const int bh = unit / NS;
     const int ch0 = (unit % NS) * DS;  // first channel of the slab
-    const long tbase = (long)j * CHUNK + (long)(wave * RPW + rg) * NT;
+    const long tbase = (long)j * CHUNK + (long)(wave * RPW + rg) * NT - lead;
     typename R::raw_t kr[NT], vr[NT];
     float4 g0[NT], g1[NT];
 #pragma unroll
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     // its round trip overlaps the fold; the wait below re-polls only if it was not there yet
     uint64_t early0 = 0, early1 = 0;
     if (tid < DS && j > 0) {
-        const uint64_t *p = rec + (((long)unit * n_chunks + (j - 1)) * 2) * DS + tid;
+        const uint64_t *p = rec + (((long)unit * (n_chunks - 1) + (j - 1)) * 2) * DS + tid;
         early0 = load_u64_agent(p);
         early1 = load_u64_agent(p + DS);
     }
@@ -275,7 +278,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             Sk = state_k[bh * D + ch0 + c];
             Sv = state_v[bh * D + ch0 + c];
         } else {
-            const uint64_t *p = rec + (((long)unit * n_chunks + (j - 1)) * 2) * DS + c;
+            const uint64_t *p = rec + (((long)unit * (n_chunks - 1) + (j - 1)) * 2) * DS + c;
             uint64_t w0 = early0, w1 = early1;
             int spins = 0;
             bool ok = ((uint32_t)(w0 >> 32) == tag) && ((uint32_t)(w1 >> 32) == tag);
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             state_k[bh * D + ch0 + c] = Ok;
             state_v[bh * D + ch0 + c] = Ov;
         } else {
-            uint64_t *p = rec + (((long)unit * n_chunks + j) * 2) * DS + c;
+            uint64_t *p = rec + (((long)unit * (n_chunks - 1) + j) * 2) * DS + c;
             store_u64_agent(p, ((uint64_t)tag << 32) | __float_as_uint(Ok));
             store_u64_agent(p + DS, ((uint64_t)tag << 32) | __float_as_uint(Ov));
         }
@@ -331,10 +334,25 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         plo[c] = INFINITY;
         phi[c] = -INFINITY;
     }
+    if constexpr (META && DS < D) {
+        if (tbase < 0) {  // stored rows of the run's first page: only their bounds are wanted
+            const int page0 = (int)(t0 & (PAGE - 1));
+#pragma unroll 1
+            for (int i = (int)(tbase < -page0 ? -page0 - tbase : 0); i < NT && tbase + i < 0; ++i) {
+                float xs[8];
+                R::load(k_cache + (out_row0 + tbase + i) * D + ch0 + c0, xs);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    plo[c] = fminf(plo[c], xs[c]);
+                    phi[c] = fmaxf(phi[c], xs[c]);
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         const long t = tbase + i;
-        if (t < T_new) {
+        if ((DS == D || t >= 0) && t < T_new) {
             float kx[8], vx[8];
             R::unpack(kr[i], kx);
             R::unpack(vr[i], vx);
@@ -381,8 +399,8 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                     plo[c] = fminf(plo[c], shfl_xor_f(plo[c], msk));
                     phi[c] = fmaxf(phi[c], shfl_xor_f(phi[c], msk));
                 }
-            const long tp = (long)j * CHUNK + (long)wave * TW + (long)(rg / RGP) * PAGE;  // the page's first token
-            if (tp < T_new && rg % RGP < 2) {
+            const long tp = (long)j * CHUNK + (long)wave * TW + (long)(rg / RGP) * PAGE - lead;  // the page's first token
+            if (tp < T_new && (DS == D || tp + PAGE > 0) && rg % RGP < 2) {
                 const long page = (t0 + tp) / PAGE;
                 ST *mrow = meta + (((long)bh * (Tcap / PAGE) + page) * 2) * D + ch0 + c0;
                 if (rg % RGP == 0) R::store(mrow, plo);
@@ -407,8 +425,8 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                 }
             }
             __syncthreads();
-            const long tp = (long)j * CHUNK + (long)wave * PAGE;  // first token of page `wave` of this chunk
-            if (wave < NW / WPP && rg < 2 && tp < T_new) {
+            const long tp = (long)j * CHUNK + (long)wave * PAGE - lead;  // first token of page `wave` of this chunk
+            if (wave < NW / WPP && rg < 2 && tp < T_new && (DS == D || tp + PAGE > 0)) {
                 float x[8];
 #pragma unroll
                 for (int c = 0; c < 8; ++c) x[c] = s_pg[wave * WPP][rg][c0 + c];
@@ -550,7 +568,8 @@ static int launch_scan(const void *k, const void *v, const float *g, float *stat
     constexpr int NW = 8;
     constexpr int CHUNK = NW * (64 / (DS / 8)) * NT;
     constexpr int PAGE = (PAGE_ARG <= CHUNK) ? PAGE_ARG : 0;  // larger pages never get here with the bounds asked for
-    const int n_chunks = (int)((T_new + CHUNK - 1) / CHUNK);
+    const int lead = (PAGE > 0 && DS < D) ? (int)(t0 % CHUNK) : 0;
+    const int n_chunks = (int)((T_new + lead + CHUNK - 1) / CHUNK);
     long grid = (long)BH * (D / DS) * n_chunks;
     if (n_chunks > 1) {
         static int per_cu = 0, cus = 0;  // resident workgroups of this kernel
@@ -568,7 +587,7 @@ static int launch_scan(const void *k, const void *v, const float *g, float *stat
     }
     rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(
         (const ST *)k, (const ST *)v, g, state_k, state_v, (ST *)k_cache, (ST *)v_cache, BH, T_new,
-        t0, Tcap, n_chunks, ctrl, rec, tag, spin_limit, (ST *)meta, (n_chunks > 1 && (long)BH * (D / DS) >= 128) ? 1 : 0);
+        t0, Tcap, n_chunks, ctrl, rec, tag, spin_limit, (ST *)meta, (n_chunks > 1 && (long)BH * (D / DS) >= 128) ? 1 : 0, lead);
     return 0;
 }
 
@@ -581,23 +600,43 @@ int scan_chunk_tokens(int dtype, int D)
 // host entry used by the C ABI (arguments already validated)
 bool scan_uses_step_kernel(long T_new) { return T_new <= 8; }
 
-static bool scan_uses_slabs(int BH, long T_new)
+// 32-channel slabs (shorter chains, more of them, four or two times the workgroups) or whole rows?
+// Measured at 128 channels in bfloat16 from an aligned start with page bounds (rows / slabs, us):
+// 8 heads x 400 12.9 / 9.7, x 2500 27.2 / 14.9, x 16000 110 / 62; 16 x 16000 127 / 114; 32 x 400
+// 13.9 / 10.7, x 2500 41.6 / 39.4, x 6000 78.6 / 86.5; 64 x 400 16.5 / 13.5, x 2500 65 / 74; 128 x 400
+// 31.3 / 24.3, x 1000 55 / 61; 256 x 400 46 / 49, x 40 9.9 / 25.8 (a slab's chunk is 512 tokens: short
+// runs on many heads leave it empty).  The slabs read 64-byte pieces of the rows, which costs
+// bandwidth once the chip is full; in float32 the pieces are whole 128-byte lines and the slabs stay
+// ahead: 128 heads x 700 66 / 64, x 6000 461 / 429; 64 channels 43 / 33 and 256 / 225.
+static bool scan_uses_slabs(int dtype, int D, int BH, long T_new)
 {
-    // few (batch, head) pairs and a long run: 32-channel slabs, so that the chunk chains are
-    // shorter and there are more of them
     const int forced = knobs().scan_slab;
-    return forced != kKnobUnset ? forced != 0 : (BH <= 16 && T_new >= 2048);
+    if (forced != kKnobUnset) return forced != 0;
+    if (BH <= 16) return true;
+    const long chunk = (long)scan_chunk_tokens(dtype, D) * (D / 32), slabs = (long)BH * (D / 32);
+    if (T_new < chunk / 4 || slabs > 512) return false;
+    if (dtype == RS_F32) return true;
+    return (long)BH * T_new * D <= (D == 128 && slabs <= 128 ? 10500000 : 6600000);
 }
 
 // whether the chunk kernel leaves the Quest page bounds of the rows it stores (else the caller
-// recomputes the touched pages afterwards)
-bool scan_writes_meta(int dtype, int D, int P, int BH, long T_new, long t0)
+// recomputes the touched pages afterwards).  The slab form also does it for a run that starts inside
+// a chunk (`lead` tokens of it lie before the run).  That may take one chunk more, which a short run on many heads does not
+// pay back (32 heads x 150 tokens from an odd start: 15.4 us against 12.6 with the second pass; 32 x
+// 2500 42.3 / 48.8, 8 x 2500 15.5 / 19.3); has_records: the workspace through which chunks hand their
+// state on is there (a run of one chunk's length may have come without).
+bool scan_writes_meta(int dtype, int D, int P, int BH, long T_new, long t0, bool has_records)
 {
     if (scan_uses_step_kernel(T_new)) return true;  // the step kernel keeps the touched page current
     if (knobs().scan_meta == 0) return false;
-    // chunk of the form in use: bfloat16 128 tokens at D = 128, 256 at D = 64 (float32: half); 32-channel slabs: D / 32 times that
-    const long chunk = (long)scan_chunk_tokens(dtype, D) * (scan_uses_slabs(BH, T_new) ? D / 32 : 1);
-    return P >= 16 && P <= chunk && (P & (P - 1)) == 0 && t0 % chunk == 0;
+    // tokens of a chunk: bfloat16 128 at D = 128, 256 at D = 64 (float32: half); 32-channel slabs: D / 32 times that
+    const bool slabs = scan_uses_slabs(dtype, D, BH, T_new);
+    const long chunk = (long)scan_chunk_tokens(dtype, D) * (slabs ? D / 32 : 1);
+    if (P < 16 || P > chunk || (P & (P - 1)) != 0) return false;
+    if (t0 % chunk == 0) return true;
+    if (!slabs) return false;
+    if (t0 % chunk + T_new <= chunk) return true;
+    return has_records && ((long)BH * (D / 32) <= 64 || T_new > chunk * 3 / 2);
 }
 
 void scan_dispatch(int dtype, int D, const void *k, const void *v, const float *g, float *state_k,
@@ -616,9 +655,9 @@ void scan_dispatch(int dtype, int D, const void *k, const void *v, const float *
                                                               (float *)k_cache, (float *)v_cache, (float *)meta, P, BH, D, T_new, t0, Tcap, nullptr, 0, 0);
         return;
     }
-    const bool slab = scan_uses_slabs(BH, T_new);
+    const bool slab = scan_uses_slabs(dtype, D, BH, T_new);
 #define RS_SCAN(ST, DD, DSS, MM) launch_scan<ST, DD, DSS, MM>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec, tag, spin_limit, meta, stream)
-    const bool in_scan = meta && scan_writes_meta(dtype, D, P, BH, T_new, t0);
+    const bool in_scan = meta && scan_writes_meta(dtype, D, P, BH, T_new, t0, rec != nullptr);
     // page sizes up to 512 tokens have their own instantiation where they tile the form's chunk
 #define RS_SCAN_P(ST, DD, DSS)                           \
     do {                                                 \

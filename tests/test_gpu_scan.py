@@ -247,3 +247,48 @@ def test_scan_in_place(rs, dtype, T):
         assert scan_close(to_np(tk), ko)[0] and scan_close(to_np(tv), vo)[0]
     else:
         assert bf16_store_ok(to_np(tk), ko) and bf16_store_ok(to_np(tv), vo)
+
+
+@pytest.mark.parametrize("dtype,D,P", [("bf16", 128, 16), ("bf16", 128, 512), ("bf16", 64, 64), ("f32", 128, 32), ("f32", 64, 256)])
+def test_odd_starts_leave_the_page_bounds(rs, dtype, D, P):
+    """Runs that start and end inside pages and chunks, in the channel-slab form: the states are Eq. 1's, the
+    bounds of every touched page are those of its stored keys (rows from before the run among them, infinite and
+    NaN-free extremes included), every other page and row stays as it was.  With and without a workspace."""
+    B, H = 1, 2
+    chunk = {"bf16": 512, "f32": 256}[dtype]
+    for t0, T in ((1, 9), (P - 1, 10), (P, 33), (5, chunk - 5), (chunk - 3, 20), (700, 3 * chunk + 11), (1023, 2 * chunk)):
+        say("odd scan start", dtype, D, P, t0, T)
+        r = np.random.default_rng(t0 * 7919 + T)
+        Tcap = -(-(t0 + T + 3 * P) // P) * P
+        k, v = (r.standard_normal((B, H, T, D)).astype(np.float32) for _ in range(2))
+        stored = r.standard_normal((B, H, Tcap, D)).astype(np.float32)
+        stored[:, :, t0 - 1, 0], stored[:, :, t0 - 1, 1] = np.inf, -1e30
+        if dtype == "bf16":
+            k, v, stored = (synth.to_bf16_grid(x) for x in (k, v, stored))
+        g = _gate(r, (B, H, T, D))
+        s0 = r.standard_normal((B, H, D)).astype(np.float32)
+        s = rs.make_shape(B, H, H, D, Tcap, P, tdtype(dtype))
+        tk, tv, tg = to_dev(k, dtype), to_dev(v, dtype), to_dev(g)
+        ko, vo, osk, osv = oracle.rat_scan(k, v, g, s0, s0)
+        runs = [rs.Workspace(rs.rat_scan_workspace_bytes(s, T))] + ([None] if T <= chunk // (D // 32) else [])
+        for ws in runs:
+            sk, sv, kc, vc = to_dev(s0), to_dev(s0), to_dev(stored, dtype), to_dev(stored, dtype)
+            meta = torch.full((B, H, Tcap // P, 2, D), 99.0, dtype=tdtype(dtype), device="cuda")
+            rs.rat_scan(s, tk, tv, tg, sk, sv, kc, vc, t0, T, ws, meta)
+            torch.cuda.synchronize()
+            if ws is not None:
+                ws.async_status()
+            assert scan_close(to_np(sk), osk)[0] and scan_close(to_np(sv), osv)[0]
+            gk, gv, gm = to_np(kc), to_np(vc), to_np(meta)
+            rows = slice(t0, t0 + T)
+            ok = scan_close if dtype == "f32" else (lambda x, y: (bf16_store_ok(x, y),))
+            assert ok(gk[:, :, rows], ko)[0] and ok(gv[:, :, rows], vo)[0]
+            for got in (gk, gv):
+                assert np.array_equal(got[:, :, :t0], stored[:, :, :t0]) and np.array_equal(got[:, :, t0 + T:], stored[:, :, t0 + T:])
+            first, last = t0 // P, (t0 + T - 1) // P
+            for p in range(Tcap // P):
+                if p < first or p > last:
+                    assert np.all(gm[:, :, p] == 99.0), (t0, T, p)
+                else:
+                    x = gk[:, :, p * P:min((p + 1) * P, t0 + T)]
+                    assert np.array_equal(gm[:, :, p, 0], x.min(2)) and np.array_equal(gm[:, :, p, 1], x.max(2)), (t0, T, p)
