@@ -36,6 +36,11 @@ void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache
                             int Hkv, long Tcap, int P, long T_valid, int K, float scale, int splits,
                             uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit, int idx_per_kv,
                             uint32_t *state, long T_max, hipStream_t stream);
+bool decode_attend_shared_fits(int dtype, int D, int G, int splits);
+void decode_attend_shared_dispatch(int dtype, int D, const void *q, const void *k_cache, const void *v_cache,
+                                   const int32_t *idx, void *out, float *lse_out, uint64_t *partial, int B, int Hq, int Hkv,
+                                   long Tcap, int P, long T_valid, int K, float scale, int splits, uint32_t *unit_ctr,
+                                   uint32_t *err, uint32_t tag, int spin_limit, hipStream_t stream);
 // moba.hip / prefill.hip / snapkv.hip
 size_t moba_select_ws_bytes(const rs_shape *s, long T, int block);
 int moba_select_dispatch(const rs_shape *s, const void *q, const void *k_cache, long T, int block, int K,
@@ -141,6 +146,7 @@ static void knobs_read()
     Knobs &k = g_knobs;
     k.score_wgs = env_or_unset("RATSPARSE_SCORE_WGS");
     k.attend_wgs = env_or_unset("RATSPARSE_ATTEND_WGS");
+    k.attend_shared = env_or_unset("RATSPARSE_ATTEND_SHARED");
     k.fused_grid = env_or_unset("RATSPARSE_FUSED_GRID");
     k.fused_sscore = env_or_unset("RATSPARSE_FUSED_SSCORE");
     k.fused_satt = env_or_unset("RATSPARSE_FUSED_SATT");
@@ -621,6 +627,24 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     }
     int splits = pick_splits(units, tiles, 8, target);
     if (splits > L.splits_att_max) splits = L.splits_att_max;
+    // Heads of a KV head that attend the same rows go through them together where fetching the rows per
+    // head is what takes the time: when the heads' reads come to 300 MB (200 MB for two heads), or when
+    // the splits of a KV head are few enough (8) that merging their partials costs little.  Per head / shared, us,
+    // bfloat16, 128 channels: batch 8, 32 over 8 heads, 1000 rows 24.0 / 13.1, 8000 rows 159 / 67; batch 4
+    // x 32768 183 / 104; batch 1 x 1000 9.4 / 8.3, x 65536 86 / 54, and the other way at 4000 rows 11.2 / 14.3,
+    // at 16416 23.4 / 24.2 and at 200 rows 5.8 / 7.8; batch 1, 16 over 8 heads x 32768 40 / 30, 32 over 4 x 32768 36.5 / 33.8.
+    if (s->Hq > s->Hkv && (group || !use_idx)) {
+        int sp = pick_splits((long)s->B * s->Hkv, tiles, 8, knob_or(knobs().attend_wgs, 256));
+        if (sp > L.splits_att_max) sp = L.splits_att_max;
+        const double read = (double)units * tiles * 16 * s->D * 2 * esize(s->dtype);
+        const bool pays = read >= (s->Hq == 2 * s->Hkv ? 200e6 : 300e6) || (sp <= 8 && tiles >= 32);
+        if (decode_attend_shared_fits(s->dtype, s->D, s->Hq / s->Hkv, sp) && knob_or(knobs().attend_shared, pays ? 1 : 0)) {
+            decode_attend_shared_dispatch(s->dtype, s->D, q, k_cache, v_cache, use_idx, out, lse_out,
+                                          (uint64_t *)(w + L.off_partial), s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_valid, K,
+                                          scale, sp, ctr_att, err, tag, g_spin_limit.load(), (hipStream_t)stream);
+            return launch_status();
+        }
+    }
     decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, use_idx, out, lse_out,
                            (uint64_t *)(w + L.off_partial), s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_valid, K, scale,
                            splits, ctr_att, err, tag, g_spin_limit.load(), group ? 1 : 0, nullptr, 0, (hipStream_t)stream);

@@ -472,6 +472,256 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
 }
 
 // ------------------------------------------------------------------------------------
+// The same for the G query heads of a KV head at once, where they attend the same rows (all of
+// them, or a page list of the KV head): a row is fetched once instead of G times, and its values
+// are unpacked once.  A lane keeps G running (m, l, o).  A wave takes TPI tiles per step and has
+// the next step's on their way while it works on the current ones; the softmax moves its reference
+// point once per step and head.
+// Bound by memory from about a hundred megabytes on (8 x 32 over 8 heads x 8000 rows: 268 MB in 67 us against
+// 159 us with a workgroup per head, which took every row four times through the CUs at 40 bytes per ns
+// each), by the latency of the merge below that.
+// ------------------------------------------------------------------------------------
+constexpr int kSharedThreads = 512;
+constexpr int kSharedMaxSplits = 64;
+
+template <typename ST, int D, int G>
+__global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
+    const ST *__restrict__ q, const ST *__restrict__ k_cache, const ST *__restrict__ v_cache, const int32_t *idx,
+    ST *__restrict__ out, float *__restrict__ lse_out, uint64_t *partial, int Hkv, long Tcap, int P, long T_valid, int K,
+    float scale, int splits, uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit)
+{
+    constexpr int LPR = D / 8;
+    constexpr int RPW = 64 / LPR;  // rows per load instruction
+    constexpr int TR = 16;         // rows per tile
+    constexpr int RPL = TR / RPW;  // rows per lane per tile
+    constexpr int TPI = (sizeof(ST) == 2 && G < 8) ? 2 : 1;  // tiles per step of a wave
+    constexpr int NW = kSharedThreads / 64;
+    using R = Row8<ST>;
+    // partials of a workgroup that meet in LDS: one per row group of a wave (fewer trips than shuffles
+    // between the row groups first), or one per wave where that many would not fit
+    constexpr int PPW = G * RPW <= 16 ? RPW : 1, NP = NW * PPW;
+    __shared__ float s_m[NP][G], s_l[NP][G];
+    __shared__ __attribute__((aligned(16))) float s_o[NP][G][D];
+    __shared__ int s_role;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rg = lane / LPR, c0 = (lane % LPR) * 8;
+    const int unit = blockIdx.y;  // b * Hkv + kvh; its query heads are rows unit * G .. of q, out and the partials
+    const ST *kb = k_cache + (long)unit * Tcap * D + c0;
+    const ST *vb = v_cache + (long)unit * Tcap * D + c0;
+    const int32_t *idx_row = idx ? idx + (long)unit * K : nullptr;
+
+    const int tiles_per_page = P / TR;
+    const long n_tiles = idx ? (long)K * tiles_per_page : (T_valid + TR - 1) / TR;
+    const long per = (n_tiles + splits - 1) / splits;
+    const long tb = (long)blockIdx.x * per;
+    const long te = (tb + per < n_tiles) ? tb + per : n_tiles;
+
+    struct Step {
+        typename R::raw_t k[TPI][RPL], v[TPI][RPL];
+        long row0[TPI];
+    };
+    auto load = [&](long t, Step &x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < TPI; ++u) {
+            const long tt = t + u;
+            x.row0[u] = T_valid;  // nothing to do
+            if (tt < te) {
+                if (idx) {
+                    const int page = idx_row[tt / tiles_per_page];
+                    if (page >= 0) x.row0[u] = (long)page * P + (tt % tiles_per_page) * TR;
+                } else {
+                    x.row0[u] = tt * TR;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < TPI; ++u)
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                const long row = x.row0[u] + i * RPW + rg;
+                if (row < T_valid) {  // each row is read by this workgroup only: streaming loads
+                    x.k[u][i] = R::load_raw_nt(kb + row * D);
+                    x.v[u][i] = R::load_raw_nt(vb + row * D);
+                } else {  // masked rows contribute nothing (and stale memory is never read)
+                    x.k[u][i] = R::zero_raw();
+                    x.v[u][i] = R::zero_raw();
+                }
+            }
+    };
+    Step xa, xb;
+    const long t_first = tb + wave * TPI, stride = NW * TPI;
+    if (t_first < te) load(t_first, xa);
+
+    RowDot<ST> qd[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        float qv[8];
+        R::load(q + ((long)unit * G + g) * D + c0, qv);
+        qd[g].set(qv);
+    }
+    float m[G], l[G], o[G][8];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        m[g] = -INFINITY;
+        l[g] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) o[g][c] = 0.f;
+    }
+    auto attend = [&](const Step &x) __attribute__((always_inline)) {
+        float s[G][TPI][RPL];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            float mt = m[g];
+#pragma unroll
+            for (int u = 0; u < TPI; ++u)
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) {
+                    const float d = group_sum<LPR>(qd[g].dot(x.k[u][i])) * scale;
+                    s[g][u][i] = (x.row0[u] + i * RPW + rg < T_valid) ? d : -INFINITY;
+                    mt = fmaxf(mt, s[g][u][i]);
+                }
+            const float ms = (mt == -INFINITY) ? 0.f : mt;  // nothing to attend yet: every weight below is 0
+            const float corr = __expf(m[g] - ms);
+            m[g] = mt;
+            l[g] *= corr;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) o[g][c] *= corr;
+#pragma unroll
+            for (int u = 0; u < TPI; ++u)
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) {
+                    s[g][u][i] = __expf(s[g][u][i] - ms);
+                    l[g] += s[g][u][i];
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < TPI; ++u)
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                float y[8];
+                R::unpack(x.v[u][i], y);
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) o[g][c] = fmaf(s[g][u][i], y[c], o[g][c]);
+            }
+    };
+    for (long t = t_first; t < te;) {
+        if (t + stride < te) load(t + stride, xb);
+        attend(xa);
+        t += stride;
+        if (t >= te) break;
+        if (t + stride < te) load(t + stride, xa);
+        attend(xb);
+        t += stride;
+    }
+
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if constexpr (PPW == 1) {  // merge the row groups of the wave
+#pragma unroll
+            for (int mask = LPR; mask < 64; mask <<= 1) {
+                const float m2 = shfl_xor_f(m[g], mask);
+                const float l2 = shfl_xor_f(l[g], mask);
+                const float mn = fmaxf(m[g], m2);
+                const float a1 = (m[g] == -INFINITY) ? 0.f : __expf(m[g] - mn);
+                const float a2 = (m2 == -INFINITY) ? 0.f : __expf(m2 - mn);
+                l[g] = l[g] * a1 + l2 * a2;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float o2 = shfl_xor_f(o[g][c], mask);
+                    o[g][c] = o[g][c] * a1 + o2 * a2;
+                }
+                m[g] = mn;
+            }
+        }
+        if (rg < PPW) {
+            const int p = wave * PPW + rg;
+            if (lane % LPR == 0) {
+                s_m[p][g] = m[g];
+                s_l[p][g] = l[g];
+            }
+            float4 *dst = reinterpret_cast<float4 *>(&s_o[p][g][c0]);
+            dst[0] = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
+            dst[1] = make_float4(o[g][4], o[g][5], o[g][6], o[g][7]);
+        }
+    }
+    __syncthreads();
+
+    // merge them; thread (g, c) owns channel c of head g
+    for (int e = tid; e < G * D; e += kSharedThreads) {
+        const int g = e / D, c = e % D;
+        const long head = (long)unit * G + g;
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NP; ++w) M = fmaxf(M, s_m[w][g]);
+        float L = 0.f, O = 0.f;
+#pragma unroll
+        for (int w = 0; w < NP; ++w) {
+            const float a = (s_m[w][g] == -INFINITY) ? 0.f : __expf(s_m[w][g] - M);
+            L += s_l[w][g] * a;
+            O += s_o[w][g][c] * a;
+        }
+        if (splits == 1) {
+            const float inv = (L > 0.f) ? 1.f / L : 0.f;
+            from_f32(out[head * D + c], O * inv);
+            if (c == 0 && lse_out) lse_out[head] = (L > 0.f) ? M + __logf(L) : -INFINITY;
+        } else {
+            uint64_t *part = partial + (head * splits + blockIdx.x) * (D + 2);
+            publish_f32(&part[2 + c], O, tag);
+            if (c == 0) {
+                publish_f32(&part[0], M, tag);
+                publish_f32(&part[1], L, tag);
+            }
+        }
+    }
+    if (splits == 1) return;
+
+    // The last G splits of the unit to arrive share the final merge, a head each (fewer splits: every
+    // splits-th head): one workgroup would take 0.33 us per split for four heads.  The first of them may still wait
+    // for the partials of the others, which are already running or next to be dispatched.
+    const int roles = G < splits ? G : splits;
+    if (tid == 0) {
+        const int prev = (int)atomicAdd(&unit_ctr[unit], 1u);
+        s_role = prev - (splits - roles);
+        if (prev == splits - 1) atomicExch(&unit_ctr[unit], 0u);
+    }
+    __syncthreads();
+    const int role = s_role;
+    if (role < 0) return;
+    constexpr int NG = kSharedThreads / D;  // thread groups, each over every NG-th split
+    const int gi = tid / D, c = tid % D;
+    for (int g = role; g < G; g += roles) {
+        const long head = (long)unit * G + g;
+        float M = -INFINITY, L = 0.f, O = 0.f;
+        merge_partials(partial + head * splits * (D + 2), splits, D + 2, c, tag, spin_limit, err, M, L, O, gi, NG);
+        if (c == 0) {
+            s_m[gi][0] = M;
+            s_l[gi][0] = L;
+        }
+        s_o[gi][0][c] = O;
+        __syncthreads();
+        if (gi == 0) {
+            M = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < NG; ++i) M = fmaxf(M, s_m[i][0]);
+            L = O = 0.f;
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const float a = (s_m[i][0] == -INFINITY) ? 0.f : __expf(s_m[i][0] - M);
+                L += s_l[i][0] * a;
+                O += s_o[i][0][c] * a;
+            }
+            const float inv = (L > 0.f) ? 1.f / L : 0.f;
+            from_f32(out[head * D + c], O * inv);
+            if (c == 0 && lse_out) lse_out[head] = (L > 0.f) ? M + __logf(L) : -INFINITY;
+        }
+        __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------------------------
 // Short contexts (the paper's 4096 tokens): select-then-attend of one (batch, query head)
 // inside one 512-thread workgroup -- page scores into LDS keys, the top-K selection, then
 // attention over the picked pages with the waves splitting the tiles -- so nothing is handed
@@ -696,6 +946,42 @@ void unit_decode_dispatch(int dtype, int D, const void *q, const void *meta, con
     }
 #undef RS_LAUNCH
 #undef RS_LAUNCH1
+}
+
+// the G = Hq / Hkv query heads of a KV head over the same rows: all rows, or a page list per KV head
+bool decode_attend_shared_fits(int dtype, int D, int G, int splits)
+{
+    if (dtype == RS_F32 && D == 128 && G == 8) return false;  // (its registers would not hold them)
+    return (G == 2 || G == 4 || G == 8) && splits <= kSharedMaxSplits;
+}
+
+void decode_attend_shared_dispatch(int dtype, int D, const void *q, const void *k_cache, const void *v_cache,
+                                   const int32_t *idx, void *out, float *lse_out, uint64_t *partial, int B, int Hq, int Hkv,
+                                   long Tcap, int P, long T_valid, int K, float scale, int splits, uint32_t *unit_ctr,
+                                   uint32_t *err, uint32_t tag, int spin_limit, hipStream_t stream)
+{
+    const dim3 grid((unsigned)splits, (unsigned)(B * Hkv));
+    const int G = Hq / Hkv;
+#define RS_LAUNCH(ST, DD, GG)                                                                                \
+    decode_attend_shared_kernel<ST, DD, GG><<<grid, kSharedThreads, 0, stream>>>(                            \
+        (const ST *)q, (const ST *)k_cache, (const ST *)v_cache, idx, (ST *)out, lse_out, partial, Hkv,      \
+        Tcap, P, T_valid, K, scale, splits, unit_ctr, err, tag, spin_limit)
+#define RS_LAUNCH_G(ST, DD)                     \
+    do {                                        \
+        if (G == 2) RS_LAUNCH(ST, DD, 2);       \
+        else if (G == 4) RS_LAUNCH(ST, DD, 4);  \
+        else RS_LAUNCH(ST, DD, 8);              \
+    } while (0)
+    if (dtype == RS_BF16) {
+        if (D == 128) RS_LAUNCH_G(bf16, 128);
+        else RS_LAUNCH_G(bf16, 64);
+    } else {
+        if (D == 64) RS_LAUNCH_G(float, 64);
+        else if (G == 2) RS_LAUNCH(float, 128, 2);
+        else RS_LAUNCH(float, 128, 4);
+    }
+#undef RS_LAUNCH_G
+#undef RS_LAUNCH
 }
 
 void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache, const void *v_cache,

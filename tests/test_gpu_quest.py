@@ -432,3 +432,43 @@ def test_group_shared_selection(rs, case):
         rs.sparse_attn_decode_group(s, tq, tkc, tvc, T, scale, None, 0, None, 0, 0, out2, None, None, ws)
     torch.cuda.synchronize()
     ws.async_status()
+
+
+@pytest.mark.parametrize("dtype,D,G", [("bf16", 128, 4), ("bf16", 128, 8), ("bf16", 64, 2), ("f32", 128, 2), ("f32", 64, 8), ("f32", 128, 8)])
+def test_dense_decode_of_shared_rows(rs, knobs, dtype, D, G):
+    """Dense decode under grouped-query attention with the query heads of a KV head taken together (forced, for any
+    length it may be asked for) and head by head: both against the oracle.  Lengths around a tile, a wave's step, a
+    workgroup's and several splits; rows past T hold NaN; then a page list per KV head with skipped entries."""
+    B, Hkv, P, r = 2, 2, 16, np.random.default_rng(G * D)
+    Tcap, tol = 4128, 2e-2 if dtype == "bf16" else 1e-4  # (the tolerances of the tests above)
+    kc, vc = (r.standard_normal((B, Hkv, Tcap, D)).astype(np.float32) for _ in range(2))
+    q = r.standard_normal((B, Hkv * G, D)).astype(np.float32)
+    if dtype == "bf16":
+        kc, vc, q = (synth.to_bf16_grid(x) for x in (kc, vc, q))
+    s = rs.make_shape(B, Hkv * G, Hkv, D, Tcap, P, tdtype(dtype))
+    ws = rs.Workspace(rs.sparse_attn_decode_workspace_bytes(s, Tcap, Tcap // P))
+    scale, tq = 2.0 / np.sqrt(D), to_dev(q, dtype)
+    for T in (1, 15, 17, 127, 129, 500, 1030, 4100):
+        dk, dv = kc.copy(), vc.copy()
+        dk[:, :, T:], dv[:, :, T:] = np.nan, np.nan
+        tk, tv = to_dev(dk, dtype), to_dev(dv, dtype)
+        all_pages = np.tile(np.arange(-(-T // P), dtype=np.int32), (B, Hkv * G, 1))
+        want, wlse = oracle.sparse_attn_decode(q, kc, vc, P, T, scale, all_pages)
+        lists = np.sort(np.stack([r.choice(-(-T // P), max(1, -(-T // P) // 2), replace=False) for _ in range(B * Hkv)]), 1)
+        lists = lists.reshape(B, Hkv, -1).astype(np.int32)
+        lwant, llse = oracle.sparse_attn_decode(q, kc, vc, P, T, scale, np.repeat(lists, G, axis=1))
+        given = np.concatenate([lists, np.full((B, Hkv, 1), -1, np.int32)], 2) if lists.shape[2] < -(-T // P) else lists
+        for shared in ("1", "0"):
+            knobs.setenv("RATSPARSE_ATTEND_SHARED", shared)
+            for idx, w, wl in ((None, want, wlse), (given, lwant, llse)):
+                out = torch.full((B, Hkv * G, D), 7.0, dtype=tdtype(dtype), device="cuda")
+                lse = torch.full((B, Hkv * G), 7.0, device="cuda")
+                if idx is None:
+                    rs.sparse_attn_decode(s, tq, tk, tv, T, scale, None, 0, None, 0, 0, out, lse, None, ws)
+                else:
+                    rs.sparse_attn_decode_group(s, tq, tk, tv, T, scale, torch.from_numpy(idx).cuda(), idx.shape[2], None, 0, 0,
+                                                out, lse, None, ws)
+                ok, worst = attn_close(to_np(out), w, tol)
+                assert ok, (T, shared, idx is None, worst)
+                np.testing.assert_allclose(to_np(lse), wl, rtol=1e-4, atol=1e-4)
+        ws.async_status()
