@@ -199,8 +199,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 template <int D, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_votes_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, const float *__restrict__ lse,
-    float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg)
+    float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
+    uint32_t *__restrict__ sel_hist, long n_hist)
 {
+    // the selection's bins start at zero
+    for (long z = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; z < n_hist; z += (long)gridDim.x * gridDim.y * 256)
+        sel_hist[z] = 0u;
     constexpr int NC = D / 16;
     using Stage = SnapStage<D, STREAM>;
     __shared__ __attribute__((aligned(1024))) uint16_t sK0[kSnapKT * D];
@@ -347,34 +351,23 @@ __global__ __launch_bounds__(256) void snapkv_lse_kernel(const float *__restrict
     if (lane == 0) lse[i] = M + __logf(Ls);
 }
 
-__global__ void snapkv_pool_kernel(const float *__restrict__ votes, float *__restrict__ pooled, long L, int kernel,
-                                   long total, uint32_t *__restrict__ sel_hist, long n_hist)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    for (long z = i; z < n_hist; z += (long)gridDim.x * blockDim.x) sel_hist[z] = 0u;  // the select's bins start at zero
-    if (i >= total) return;
-    const long row = i / L, p = i % L;
-    const int half = kernel / 2;
-    const long lo = (p - half < 0) ? 0 : p - half;
-    const long hi = (p + half > L - 1) ? L - 1 : p + half;
-    float m = votes[row * L + lo];
-    for (long j = lo + 1; j <= hi; ++j) m = fmaxf(m, votes[row * L + j]);
-    pooled[i] = m;
-}
-
 // ------------------------------------------------------------------------------------
 // top-K_keep of L pooled votes per (batch, KV head): radix select over the order-preserving
 // keys, 8 bits per pass, spread over workgroups of 4096 positions each (one workgroup per
 // head would leave most of the chip idle at 128K positions).  Pass p histograms the keys that
-// match the bits fixed so far into 256 global bins; the next launch starts by locating the
-// bin that holds the K-th largest key (every workgroup repeats that small search instead of
-// passing it on).  After four passes the K-th key is known exactly; a count launch leaves,
-// per workgroup, how many keys are above it and equal to it, and the emit launch writes the
-// kept positions in ascending order (equal keys: lowest positions first).
+// match the bits fixed so far into 256 global bins (the first pass also does the max-pooling); the
+// next launch starts by locating the bin that holds the K-th largest key (every workgroup repeats that
+// small search instead of passing it on).  After four passes the K-th key is known exactly.  The last
+// pass leaves each slice's own bins and its number of keys above the 24 bits fixed before, so that the
+// emit launch knows how many kept positions precede its slice and writes them in ascending order
+// (equal keys: lowest positions first).  Bound by the launches, not by their work: pooling inside
+// the first pass, the slices' bins instead of a launch that counts and 1024 threads a slice took the
+// selection of 8 heads x 128K from 38 to 30 us (a first pass of 256 threads: 41).
 // ------------------------------------------------------------------------------------
-constexpr int kSelThreads = 256;
-constexpr int kSelPerThread = 16;
+constexpr int kSelThreads = 1024;
+constexpr int kSelPerThread = 4;
 constexpr int kSelSlice = kSelThreads * kSelPerThread;
+constexpr int kSelBins = 260;  // words a slice leaves: 256 bins, the count above them, padding to 16 bytes
 
 // K-th largest key so far: the bits fixed by the first npass passes and the rank still wanted
 // inside that prefix.  Called by the 64 lanes of one wave; every lane returns the result.
@@ -414,8 +407,8 @@ __device__ __forceinline__ void sel_resolve(const uint32_t *__restrict__ hist_bk
     }
 }
 
-// this thread's 16 keys of the slice: position slice_base + 1024 wave + 64 j + lane (a wave
-// walks its 1024 positions in order); positions past L are flagged invalid
+// this thread's keys of the slice: position slice_base + 256 wave + 64 j + lane (a wave
+// walks its 256 positions in order); positions past L are flagged invalid
 __device__ __forceinline__ void sel_load_keys(const float *__restrict__ src, long L, long slice_base, uint32_t *key,
                                               uint32_t &valid)
 {
@@ -432,80 +425,93 @@ __device__ __forceinline__ void sel_load_keys(const float *__restrict__ src, lon
     for (int j = 0; j < kSelPerThread; ++j) key[j] = float_to_key(x[j]);
 }
 
-__global__ __launch_bounds__(kSelThreads) void snapkv_sel_hist_kernel(const float *__restrict__ pooled,
+// FIRST: the first pass, which pools the raw votes (a slice and `half` positions on either side in LDS),
+// stores the pooled ones and takes their keys; LAST: the last one, which leaves slice_bins [slice][257]
+template <bool FIRST, bool LAST>
+__global__ __launch_bounds__(kSelThreads) void snapkv_sel_hist_kernel(const float *__restrict__ votes, float *__restrict__ pooled,
                                                                       uint32_t *__restrict__ hist, long L, int K_keep,
-                                                                      int pass)
+                                                                      int pass, int half, uint32_t *__restrict__ slice_bins)
 {
+    constexpr int kHalo = 31;  // pool windows of up to 63
     __shared__ uint32_t lh[256];
     __shared__ uint32_t s_prefix;
+    __shared__ float s_v[FIRST ? kSelSlice + 2 * kHalo : 1];
+    __shared__ uint32_t s_above;
     const int tid = threadIdx.x;
-    const long bk = blockIdx.y;
+    const long bk = blockIdx.y, base = (long)blockIdx.x * kSelSlice;
     uint32_t key[kSelPerThread], valid;
-    sel_load_keys(pooled + bk * L, L, (long)blockIdx.x * kSelSlice, key, valid);
-    lh[tid] = 0u;
-    if (tid < 64) {
-        uint32_t prefix;
-        int remaining;
-        sel_resolve(hist + bk * 1024, pass, K_keep, prefix, remaining);
-        if (tid == 0) s_prefix = prefix;
+    if (tid < 256) lh[tid] = 0u;
+    if (LAST && tid == 0) s_above = 0u;
+    if constexpr (FIRST) {
+        const float *row = votes + bk * L;
+        for (int i = tid; i < kSelSlice + 2 * half; i += kSelThreads) {
+            const long p = base - half + i;
+            if (p >= 0 && p < L) s_v[i] = row[p];
+        }
+        __syncthreads();
+        const int lane = tid & 63, wave = tid >> 6;
+        valid = 0u;
+#pragma unroll
+        for (int j = 0; j < kSelPerThread; ++j) {
+            const int off = wave * (64 * kSelPerThread) + j * 64 + lane;
+            const long p = base + off;
+            float m = 0.f;
+            if (p < L) {
+                valid |= 1u << j;
+                const int lo = (p - half < 0) ? (int)(half - p) : 0;                       // window clipped at the ends,
+                const int hi = (p + half > L - 1) ? (int)(L - 1 - p) + half : 2 * half;  // as places from p - half
+                m = s_v[off + lo];
+                if (lo == 0 && hi == 2 * half) {
+#pragma unroll 4
+                    for (int i = 1; i <= 2 * half; ++i) m = fmaxf(m, s_v[off + i]);
+                } else {
+                    for (int i = lo + 1; i <= hi; ++i) m = fmaxf(m, s_v[off + i]);
+                }
+                pooled[bk * L + p] = m;
+            }
+            key[j] = float_to_key(m);
+        }
+    } else {
+        sel_load_keys(pooled + bk * L, L, base, key, valid);
+        if (tid < 64) {
+            uint32_t prefix;
+            int remaining;
+            sel_resolve(hist + bk * 1024, pass, K_keep, prefix, remaining);
+            if (tid == 0) s_prefix = prefix;
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    const uint32_t prefix = s_prefix;
+    const uint32_t prefix = FIRST ? 0u : s_prefix;
     const int shift = 24 - 8 * pass;
     const uint32_t himask = (pass == 0) ? 0u : (0xffffffffu << (shift + 8));
-#pragma unroll
-    for (int j = 0; j < kSelPerThread; ++j)
-        if (((valid >> j) & 1u) && (key[j] & himask) == prefix) atomicAdd(&lh[(key[j] >> shift) & 255u], 1u);
-    __syncthreads();
-    if (lh[tid]) atomicAdd(&hist[(bk * 4 + pass) * 256 + tid], lh[tid]);
-}
-
-__global__ __launch_bounds__(kSelThreads) void snapkv_sel_count_kernel(const float *__restrict__ pooled,
-                                                                       const uint32_t *__restrict__ hist,
-                                                                       uint32_t *__restrict__ cnt, long L, int K_keep)
-{
-    __shared__ int s_gt[kSelThreads / 64], s_eq[kSelThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long bk = blockIdx.y;
-    uint32_t key[kSelPerThread], valid;
-    sel_load_keys(pooled + bk * L, L, (long)blockIdx.x * kSelSlice, key, valid);
-    uint32_t kth;
-    int take_eq;
-    sel_resolve(hist + bk * 1024, 4, K_keep, kth, take_eq);  // every wave on its own
-    int n_gt = 0, n_eq = 0;
+    int above = 0;
 #pragma unroll
     for (int j = 0; j < kSelPerThread; ++j) {
         const bool ok = (valid >> j) & 1u;
-        n_gt += (ok && key[j] > kth) ? 1 : 0;
-        n_eq += (ok && key[j] == kth) ? 1 : 0;
+        if (ok && (key[j] & himask) == prefix) atomicAdd(&lh[(key[j] >> shift) & 255u], 1u);
+        if (LAST) above += (ok && (key[j] & himask) > prefix) ? 1 : 0;
     }
+    if constexpr (LAST) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        n_gt += __shfl_xor(n_gt, d, 64);
-        n_eq += __shfl_xor(n_eq, d, 64);
-    }
-    if (lane == 0) {
-        s_gt[wave] = n_gt;
-        s_eq[wave] = n_eq;
+        for (int d = 32; d >= 1; d >>= 1) above += __shfl_xor(above, d, 64);
+        if ((tid & 63) == 0) atomicAdd(&s_above, (uint32_t)above);
     }
     __syncthreads();
-    if (tid == 0) {
-        int g = 0, e = 0;
-        for (int w2 = 0; w2 < kSelThreads / 64; ++w2) {
-            g += s_gt[w2];
-            e += s_eq[w2];
-        }
-        cnt[(bk * gridDim.x + blockIdx.x) * 2] = (uint32_t)g;
-        cnt[(bk * gridDim.x + blockIdx.x) * 2 + 1] = (uint32_t)e;
+    if (tid < 256 && lh[tid]) atomicAdd(&hist[(bk * 4 + pass) * 256 + tid], lh[tid]);
+    if (LAST && tid < 256) {
+        uint32_t *mine = slice_bins + (bk * gridDim.x + blockIdx.x) * kSelBins;
+        mine[tid] = lh[tid];
+        if (tid == 0) mine[256] = s_above;
     }
 }
 
 __global__ __launch_bounds__(kSelThreads) void snapkv_sel_emit_kernel(const float *__restrict__ pooled,
                                                                       const uint32_t *__restrict__ hist,
-                                                                      const uint32_t *__restrict__ cnt,
+                                                                      const uint32_t *__restrict__ slice_bins,
                                                                       int32_t *__restrict__ idx_out, long L, int K_keep)
 {
-    __shared__ int s_gt[kSelThreads / 64], s_eq[kSelThreads / 64];
+    constexpr int NW = kSelThreads / 64;
+    __shared__ int s_gt[NW], s_eq[NW], s_gt0[NW], s_eq0[NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long bk = blockIdx.y;
     const long slice_base = (long)blockIdx.x * kSelSlice;
@@ -515,11 +521,19 @@ __global__ __launch_bounds__(kSelThreads) void snapkv_sel_emit_kernel(const floa
     uint32_t kth;
     int take_eq;
     sel_resolve(hist + bk * 1024, 4, K_keep, kth, take_eq);
-    // keys above / equal in the slices before this one
+    // keys above / equal in the slices before this one: the waves take the slices in turn
     int gt_before = 0, eq_before = 0;
-    for (int sl = lane; sl < (int)blockIdx.x; sl += 64) {
-        gt_before += (int)cnt[(bk * gridDim.x + sl) * 2];
-        eq_before += (int)cnt[(bk * gridDim.x + sl) * 2 + 1];
+    for (int sl = wave; sl < (int)blockIdx.x; sl += NW) {
+        const uint32_t *bins = slice_bins + (bk * gridDim.x + sl) * kSelBins;
+        const uint4 b4 = *reinterpret_cast<const uint4 *>(bins + lane * 4);
+        const uint32_t bb[4] = {b4.x, b4.y, b4.z, b4.w};
+        const int b0 = lane * 4, kb = (int)(kth & 255u);
+        gt_before += (lane == 0) ? (int)bins[256] : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            gt_before += (b0 + i > kb) ? (int)bb[i] : 0;
+            eq_before += (b0 + i == kb) ? (int)bb[i] : 0;
+        }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
@@ -537,11 +551,15 @@ __global__ __launch_bounds__(kSelThreads) void snapkv_sel_emit_kernel(const floa
     if (lane == 0) {
         s_gt[wave] = n_gt;
         s_eq[wave] = n_eq;
+        s_gt0[wave] = gt_before;
+        s_eq0[wave] = eq_before;
     }
     __syncthreads();
-    for (int w2 = 0; w2 < wave; ++w2) {
-        gt_before += s_gt[w2];
-        eq_before += s_eq[w2];
+    gt_before = eq_before = 0;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) {
+        gt_before += s_gt0[w2] + (w2 < wave ? s_gt[w2] : 0);
+        eq_before += s_eq0[w2] + (w2 < wave ? s_eq[w2] : 0);
     }
 #pragma unroll
     for (int j = 0; j < kSelPerThread; ++j) {
@@ -618,7 +636,7 @@ static size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct SnapLayout {
     int n_chunks, R, keys_per_wg;
-    size_t off_stats, off_lse, off_votes, off_pooled, off_hist, off_cnt, total;
+    size_t off_stats, off_lse, off_votes, off_pooled, off_hist, total;
     int n_slices;
 };
 
@@ -645,8 +663,6 @@ static SnapLayout snap_layout(const rs_shape *s, long T, int W)
     L.n_slices = (int)((T - W + kSelSlice - 1) / kSelSlice);
     L.off_hist = o;
     o += al256s((size_t)BK * 4 * 256 * 4);
-    L.off_cnt = o;
-    o += al256s((size_t)BK * L.n_slices * 2 * 4);
     L.total = o;
     return L;
 }
@@ -687,8 +703,12 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     }
     // votes exist for prefix keys only: chunks that start past the prefix are not needed
     const dim3 grid2((unsigned)((L + Ly.keys_per_wg - 1) / Ly.keys_per_wg), (unsigned)BK);
+    // knob 0: the spread-out selection at any length that its slices' bins leave room for
+    const bool one_wg = L <= kSnapOneWgKeys && (knobs().snap_one_wg != 0 || (long)Ly.n_slices * kSelBins > L);
+    uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
+    const long n_hist = one_wg ? 0 : BK * 1024;
 #define RS_VOTES(DD, SS) \
-    snapkv_votes_kernel<DD, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg)
+    snapkv_votes_kernel<DD, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
     if (s->D == 128) {
         if (big) RS_VOTES(128, true);
         else RS_VOTES(128, false);
@@ -697,20 +717,20 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
         else RS_VOTES(64, false);
     }
 #undef RS_VOTES
-    const long tot = BK * L;
-    // knob 0: the spread-out selection at any length
-    if (L <= kSnapOneWgKeys && knobs().snap_one_wg != 0) {
+    if (one_wg) {
         snapkv_pool_select_kernel<<<(unsigned)BK, kSnapOneWgThreads, (size_t)L * 4, stream>>>(
             votes, votes_out, idx_out, (int)L, pool_kernel, K_keep);
     } else {
-        uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist), *sel_cnt = (uint32_t *)(ws + Ly.off_cnt);
-        snapkv_pool_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, stream>>>(votes, pooled, L, pool_kernel, tot, sel_hist, BK * 1024);
+        const dim3 gs((unsigned)Ly.n_slices, (unsigned)BK);
+        // the raw votes are not needed past the pooling: the slices' bins take their place (one word for
+        // every 15 votes of a full slice, and there are several slices)
+        uint32_t *slice_bins = (uint32_t *)votes;
+        snapkv_sel_hist_kernel<true, false><<<gs, kSelThreads, 0, stream>>>(votes, pooled, sel_hist, L, K_keep, 0, pool_kernel / 2, nullptr);
         if (K_keep > 0) {
-            const dim3 gs((unsigned)Ly.n_slices, (unsigned)BK);
-            for (int pass = 0; pass < 4; ++pass)
-                snapkv_sel_hist_kernel<<<gs, kSelThreads, 0, stream>>>(pooled, sel_hist, L, K_keep, pass);
-            snapkv_sel_count_kernel<<<gs, kSelThreads, 0, stream>>>(pooled, sel_hist, sel_cnt, L, K_keep);
-            snapkv_sel_emit_kernel<<<gs, kSelThreads, 0, stream>>>(pooled, sel_hist, sel_cnt, idx_out, L, K_keep);
+            for (int pass = 1; pass < 3; ++pass)
+                snapkv_sel_hist_kernel<false, false><<<gs, kSelThreads, 0, stream>>>(nullptr, pooled, sel_hist, L, K_keep, pass, 0, nullptr);
+            snapkv_sel_hist_kernel<false, true><<<gs, kSelThreads, 0, stream>>>(nullptr, pooled, sel_hist, L, K_keep, 3, 0, slice_bins);
+            snapkv_sel_emit_kernel<<<gs, kSelThreads, 0, stream>>>(pooled, sel_hist, slice_bins, idx_out, L, K_keep);
         }
     }
     const int cpr = s->D * 2 / 16;
