@@ -243,3 +243,38 @@ def test_prefill_tile_edges(rs, knobs, D, Hq, Hkv):
             assert ok, (T, form, worst)
             np.testing.assert_allclose(to_np(lse), olse, rtol=2e-3, atol=2e-3)
         ws.async_status()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("order", ["growing", "falling", "mixed"])
+def test_prefill_scores_that_outgrow_the_reference(rs, knobs, D, order):
+    """Row maxima that keep growing by far more than the lazily moved softmax reference allows for, that come first, or
+    that jump about, with weights down to nothing in between: every form of the kernel against the oracle."""
+    T, block, K, Hq, Hkv, r = 900, 64, 3, 2, 1, np.random.default_rng(D)
+    q = r.standard_normal((1, Hq, T, D)).astype(np.float32)
+    d = r.standard_normal(D).astype(np.float32)
+    q += 2.0 * d
+    size = {"growing": np.linspace(0.0, 6.0, T), "falling": np.linspace(6.0, 0.0, T), "mixed": r.uniform(-6.0, 6.0, T)}[order]
+    k = (r.standard_normal((1, Hkv, T, D)) + size[:, None] * d).astype(np.float32)
+    v = r.standard_normal((1, Hkv, T, D)).astype(np.float32)
+    q, k, v = (oracle.round_to_bf16(x) for x in (q, k, v))
+    idx = np.full((1, Hq, T, K), -1, dtype=np.int32)
+    for h in range(Hq):
+        for t in range(T):
+            n = min(K, t // block + 1)
+            idx[0, h, t, :n] = np.sort(r.choice(t // block + 1, size=n, replace=False))
+    s = rs.make_shape(1, Hq, Hkv, D, T, 16, torch.bfloat16)
+    ws = rs.Workspace(rs.sparse_attn_prefill_workspace_bytes(s, T, block, K))
+    scale = 1.0 / np.sqrt(D)
+    for form in ("dense", "0", "1"):
+        knobs.setenv("RATSPARSE_PREFILL_MASKED", "0" if form == "dense" else form)
+        lists = None if form == "dense" else idx
+        out = torch.full((1, Hq, T, D), 7.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((1, Hq, T), 7.0, device="cuda")
+        rs.sparse_attn_prefill(s, to_dev(q, "bf16"), to_dev(k, "bf16"), to_dev(v, "bf16"), T, block, scale,
+                               None if lists is None else torch.from_numpy(lists).cuda(), K, out, lse, ws)
+        oout, olse = oracle.sparse_attn_prefill(q, k, v, T, block, scale, lists)
+        ok, worst = attn_close(to_np(out), oout)  # one bf16 step of the output is 4e-3 of it; 2e-2 allows five
+        assert ok, (order, form, worst)
+        np.testing.assert_allclose(to_np(lse), olse, rtol=2e-3, atol=2e-3)
+    ws.async_status()
