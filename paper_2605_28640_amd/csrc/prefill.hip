@@ -169,6 +169,7 @@ struct PrefillParams {
     bf16 *out;
     float *lse_out;
     int Hq, Hkv, Nb, K, block, n_diag;
+    int group;                 // causal tiles: units of an XCD whose tiles go out together
     long T, Tcap, list_stride;
     float scale;
 };
@@ -230,21 +231,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     // Workgroups are handed to the eight XCDs round-robin in launch order, and each XCD has an L2
     // of its own.  Launch slot L therefore runs on XCD L % 8; give that XCD a run of whole (batch,
     // head) units (query heads that share a KV head stay together).  Causal tiles go out heaviest
-    // first over all units of the XCD: the last ones to start are the lightest, and the tiles of a
-    // KV head that run together stream the same K and V rows through that L2.  Tiles of listed rows
-    // and own-block tiles are about equally heavy and go out unit by unit.
+    // first over a.group units of the XCD at a time (the remainder first): the last ones to start are
+    // the lightest, and the tiles of a unit that run together stream the same K and V rows through that
+    // L2.  Tiles of listed rows and own-block tiles are about equally heavy and go out unit by unit.
     int unit, xtile;
     {
         const unsigned nu = gridDim.y, nt = gridDim.x;
-        unsigned L = blockIdx.y * nt + blockIdx.x, base = 0, U = nu;
+        unsigned L = blockIdx.y * nt + blockIdx.x, base = 0, U = nu, group = (unsigned)a.group * 8;
         if (nu % 8 == 0) {
             U = nu / 8;
             base = (L & 7) * U;
             L >>= 3;
+            group = (unsigned)a.group;
         }
         if (FORM == kDense || FORM == kBitSets) {
-            unit = (int)(base + L % U);
-            xtile = (int)(L / U);
+            if (group > U) group = U;
+            unsigned n = U % group;  // units of the group at hand
+            if (L >= n * nt) {
+                L -= n * nt;
+                base += n + L / (group * nt) * group;
+                L %= group * nt;
+                n = group;
+            }
+            unit = (int)(base + L % n);
+            xtile = (int)(L / n);
         } else {
             unit = (int)(base + L / nt);
             xtile = (int)(L % nt);
@@ -809,6 +819,11 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     p.K = K;
     p.block = block;
     p.n_diag = (int)((T + kMT - 1) / kMT);
+    // the tiles of a group keep the XCD's 96 workgroups busy for about as long as its heaviest tile takes
+    // (group * n_diag^2 / 2 steps over 96, against n_diag); more units than that only widen what its 4 MB of
+    // L2 see at a time: 8 x 32 heads x 4096 tokens by bit sets, 32 units at a time 1530 us, 6 at a time 1213,
+    // one after the other 1270; 9 and 12 at a time measured no better
+    p.group = (192 + p.n_diag - 1) / p.n_diag;
     p.T = T;
     p.Tcap = s->Tcap;
     p.scale = scale;

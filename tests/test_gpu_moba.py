@@ -278,3 +278,32 @@ def test_prefill_scores_that_outgrow_the_reference(rs, knobs, D, order):
         assert ok, (order, form, worst)
         np.testing.assert_allclose(to_np(lse), olse, rtol=2e-3, atol=2e-3)
     ws.async_status()
+
+
+@pytest.mark.parametrize("heads", [56, 50])  # seven units per XCD in groups of six; in launch order in groups of 48
+def test_tile_order_over_many_heads(rs, heads):
+    """Causal tiles go out over groups of heads with a remainder first: every tile once, whatever the
+    grouping, so each head gets the bits it gets in a call with few heads."""
+    T, D, block, K = 4001, 64, 64, 8
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(heads)
+    q, k, v = (torch.randn(1, heads, T, D, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    t = torch.arange(T, device="cuda")[:, None] // block
+    idx = torch.sort(torch.where(torch.arange(K, device="cuda") <= t, t - torch.arange(K, device="cuda"), -1), dim=1).values
+    idx = idx.to(torch.int32).expand(1, heads, T, K).contiguous()
+
+    def run(lo, hi, lists):
+        s = rs.make_shape(1, hi - lo, hi - lo, D, T, 16, torch.bfloat16)
+        ws = rs.Workspace(rs.sparse_attn_prefill_workspace_bytes(s, T, block, K))
+        out = torch.full((1, hi - lo, T, D), 7.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((1, hi - lo, T), 7.0, device="cuda")
+        rs.sparse_attn_prefill(s, *(x[:, lo:hi].contiguous() for x in (q, k, v)), T, block, 0.125,
+                               None if lists is None else lists[:, lo:hi].contiguous(), K, out, lse, ws)
+        return out, lse
+
+    for lists in (None, idx):
+        say("tile order", heads, lists is not None)
+        out, lse = run(0, heads, lists)
+        for lo in range(0, heads, 5):
+            few, few_lse = run(lo, min(lo + 5, heads), lists)
+            assert torch.equal(out[:, lo:lo + 5], few) and torch.equal(lse[:, lo:lo + 5], few_lse), lo
