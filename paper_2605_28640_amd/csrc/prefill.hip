@@ -45,7 +45,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMT = 128;        // query rows per workgroup tile (4 waves x 32)
-constexpr int kKT = 32;         // keys per step (one 32-key MFMA sub-tile)
 constexpr uint32_t kSlotShift = 27;
 constexpr float kLazy = 8.f;    // slack (base-2 exponent) before the softmax reference point moves
 constexpr float kLarge = 4096.f;  // sum of a lane's 16 weights from which it is looked at
@@ -207,9 +206,12 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t x)
 
 enum PrefillForm { kDense, kBitSets, kListed, kOwn };
 
-template <int D, PrefillForm FORM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void prefill_attn_kernel(const PrefillParams a)
+// SUB: 32-key sub-tiles per step.  One, with three workgroups per CU, where a launch fills the chip;
+// two, with twice the independent matrix and vector instructions per wave, where a CU has a workgroup to itself.
+template <int D, PrefillForm FORM, int SUB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 1 ? 3 : D == 64 ? 2 : 1, SUB == 1 ? 3 : 2))) void prefill_attn_kernel(const PrefillParams a)
 {
+    constexpr int kKT = 32 * SUB;  // keys per step
     constexpr int NC = D / 16;     // 16-wide d chunks of the QK^T contraction
     constexpr int NDT = D / 32;    // 32-wide d tiles of O^T
     constexpr int CR = D / 8;      // 16-byte chunks per row
@@ -441,30 +443,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             // S^T[key][query] = sum_d K[key][d] Q[query][d].  Matrix phases run at raised priority:
             // of the waves that share a SIMD, the one feeding the matrix pipe is issued first and the
             // others' softmax fills the gaps
-            f32x16 sacc;
+            f32x16 sacc[SUB];
             auto scores = [&](auto load_tag) __attribute__((always_inline)) {
                 constexpr bool LOAD = decltype(load_tag)::value;
                 __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+                for (int sub = 0; sub < SUB; ++sub)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) sacc[sub][v] = 0.f;
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     if constexpr (LOAD) {
                         if (c % (NC / CPT) == 0) stage(kb, gk, nK, c / (NC / CPT), it + 2);
                     }
-                    const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(&cK[koff[c]]);
-                    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], sacc, 0, 0, 0);
+#pragma unroll
+                    for (int sub = 0; sub < SUB; ++sub) {
+                        const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(&cK[32 * sub * D + koff[c]]);
+                        sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], sacc[sub], 0, 0, 0);
+                    }
                 }
                 // issue order: operand reads run three matrix instructions ahead of their use, the direct
                 // loads go out one at a time in between
-                __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2 + SUB, 0);
 #pragma unroll
-                for (int g = 0; g < NC - 3; ++g) {
+                for (int g = 0; g < SUB * NC - 2 - SUB; ++g) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    if (LOAD && g < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                    if (LOAD && g % SUB == 0 && g / SUB < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
                 }
-                __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 2 + SUB, 0);
                 __builtin_amdgcn_s_setprio(0);
             };
             scores(std::integral_constant<bool, NEXT>{});
@@ -473,28 +480,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                 // (in offsets from this lane's first key of the step; far values stay far)
                 const int hi = vis_hi() - kr - 4 * h, lo = vis_lo - kr - 4 * h;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int e = 8 * (v / 4) + (v % 4);  // + 4 h: folded into lo, hi
-                    if (e > hi || e < lo) sacc[v] = -INFINITY;
-                }
+                for (int sub = 0; sub < SUB; ++sub)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int e = 32 * sub + 8 * (v / 4) + (v % 4);  // + 4 h: folded into lo, hi
+                        if (e > hi || e < lo) sacc[sub][v] = -INFINITY;
+                    }
             }
             // p = 2^(s * cs + bias) in place of the scores, and their sum over this lane's keys
             auto weights = [&](float bias) __attribute__((always_inline)) -> float {
+                float sum = 0.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(fmaf(sacc[v], cs, bias));
-                float s4[4];
+                for (int sub = 0; sub < SUB; ++sub) {
+                    f32x16 &p = sacc[sub];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) s4[v] = (sacc[v] + sacc[v + 4]) + (sacc[v + 8] + sacc[v + 12]);
-                return (s4[0] + s4[1]) + (s4[2] + s4[3]);
+                    for (int v = 0; v < 16; ++v) p[v] = __builtin_amdgcn_exp2f(fmaf(p[v], cs, bias));
+                    float s4[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s4[v] = (p[v] + p[v + 4]) + (p[v + 8] + p[v + 12]);
+                    sum += (s4[0] + s4[1]) + (s4[2] + s4[3]);
+                }
+                return sum;
             };
             // the reference point of the exponentials follows the running maximum lazily: it moves
             // only when the maximum has grown by more than kLazy (p then stays below 2^kLazy,
             // harmless in float32 and bfloat16), so the accumulators are rarely rescaled
             // (-inf -> finite counts as a move; -inf -> -inf compares false)
             auto weights_by_maximum = [&]() __attribute__((always_inline)) -> float {
-                float mx = sacc[0];
+                float mx = sacc[0][0];
 #pragma unroll
-                for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
+                for (int sub = 0; sub < SUB; ++sub)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[sub][v]);
                 mx = half_pair_max(mx) * cs;  // cs > 0: scaling commutes with max
                 if (FORM == kBitSets && !sel) mx = -INFINITY;
                 if (__any(mx - m > kLazy)) {
@@ -527,32 +544,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             }
             // P^T as the B operand: accumulator values 8c .. 8c+7 are this lane's keys
             // 16c + 4h + {0..3} and 16c + 8 + 4h + {0..3}; V^T is read in the same key order
-            bf16x8 pf[2];
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int s8 = 0; s8 < 8; ++s8) pf[c][s8] = (__bf16)sacc[8 * c + s8];
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                if constexpr (NEXT) {
-                    if (c < CPT) stage(vb, gv, nV, c, it + 2);
-                }
+            for (int sub = 0; sub < SUB; ++sub) {
+                bf16x8 pf[2];
 #pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) {
-                    const uint16_t *vq = &cV[(16 * c) * D];
-                    union {
-                        s16x4 s[2];
-                        bf16x8 f;
-                    } vf;
-                    vf.s[0] = lds_read_tr16(vq + voff[dt]);
-                    vf.s[1] = lds_read_tr16(vq + voff[dt] + 8 * D);
-                    oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f, pf[c], oacc[dt], 0, 0, 0);
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int s8 = 0; s8 < 8; ++s8) pf[c][s8] = (__bf16)sacc[sub][8 * c + s8];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    if constexpr (NEXT) {
+                        if (2 * sub + c < CPT) stage(vb, gv, nV, 2 * sub + c, it + 2);
+                    }
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) {
+                        const uint16_t *vq = &cV[(32 * sub + 16 * c) * D];
+                        union {
+                            s16x4 s[2];
+                            bf16x8 f;
+                        } vf;
+                        vf.s[0] = lds_read_tr16(vq + voff[dt]);
+                        vf.s[1] = lds_read_tr16(vq + voff[dt] + 8 * D);
+                        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f, pf[c], oacc[dt], 0, 0, 0);
+                    }
                 }
             }
             __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
-            for (int g = 0; g < 2 * NDT - 3; ++g) {
+            for (int g = 0; g < SUB * 2 * NDT - 3; ++g) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                 if (NEXT && g < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
@@ -576,8 +596,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         using B0 = std::integral_constant<int, 0>;
         using B1 = std::integral_constant<int, 1>;
         using B2 = std::integral_constant<int, 2>;
-        using Main = std::integral_constant<bool, FORM == kBitSets || FORM == kOwn>;  // which loops may skip
-        // keys past a row only occur in the last four steps of a tile (128 keys from the tile's own rows on;
+        using Main = std::integral_constant<bool, (FORM == kBitSets && SUB == 1) || FORM == kOwn>;  // which loops may skip
+        // keys past a row only occur in the last 4 / SUB steps of a tile (128 keys from the tile's own rows on;
         // kListed: past the block's end), keys before its own block only in kOwn
         using MainMask = std::integral_constant<bool, FORM == kOwn>;
         constexpr std::true_type yes{};
@@ -601,7 +621,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             }
             return;
         }
-        for (; it + 6 < n_steps; it += 3) {
+        for (; it + 2 + 4 / SUB < n_steps; it += 3) {
             step(yes, Main{}, MainMask{}, B0{}, it);
             step(yes, Main{}, MainMask{}, B1{}, it + 1);
             step(yes, Main{}, MainMask{}, B2{}, it + 2);
@@ -762,6 +782,19 @@ __global__ void prefill_zero_kernel(uint32_t *p, long n)
     if (i < n) p[i] = 0u;
 }
 
+// causal tiles: steps of 64 keys while the launch leaves the chip idle (kSmallLaunch row tiles at most), else of 32.
+// Steps of 64 / 32 keys (and the two-wave kernel of 64-key steps this one replaced), us: 8 heads x 2000 36 / 47 (41),
+// x 4000 68 / 87 (77), 32 over 8 x 500 15.2 / 17.1 (15.8), x 1000 25.6 / 29.6 (26.0), x 2000 54 / 56 (59), 2 x 8 x 535
+// 14.9 / 16.7 (14.5), by bit sets 8 heads x 4000 84 / 113 (80); 768 tiles: 32 over 8 heads x 300, batch 8, 33 / 20 (25)
+constexpr unsigned kSmallLaunch = 512;
+template <int D, PrefillForm FORM>
+static void prefill_causal_launch(const PrefillParams &p, dim3 grid, hipStream_t stream)
+{
+    const int sub = knob_or(knobs().prefill_sub, grid.x * grid.y <= kSmallLaunch ? 2 : 1);
+    if (sub == 2) prefill_attn_kernel<D, FORM, 2><<<grid, 256, 0, stream>>>(p);
+    else prefill_attn_kernel<D, FORM, 1><<<grid, 256, 0, stream>>>(p);
+}
+
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct PrefillLayout {
@@ -847,8 +880,8 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     const int masked = can_mask ? knob_or(knobs().prefill_masked, by_sets < regrouped ? 1 : 0) : 0;
     if (masked) {
         const dim3 grid((unsigned)p.n_diag, (unsigned)units);
-        if (s->D == 128) prefill_attn_kernel<128, kBitSets><<<grid, 256, 0, stream>>>(p);
-        else prefill_attn_kernel<64, kBitSets><<<grid, 256, 0, stream>>>(p);
+        if (s->D == 128) prefill_causal_launch<128, kBitSets>(p, grid, stream);
+        else prefill_causal_launch<64, kBitSets>(p, grid, stream);
         return hipGetLastError() == hipSuccess ? RS_OK : RS_LAUNCH_FAILED;
     }
     if (idx) {
@@ -878,17 +911,17 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
         const long gathered_tiles = p.desc_stride;  // upper bound per (batch, head)
         const dim3 g0((unsigned)gathered_tiles, (unsigned)units);
         if (K > 1) {
-            if (s->D == 128) prefill_attn_kernel<128, kListed><<<g0, 256, 0, stream>>>(p);
-            else prefill_attn_kernel<64, kListed><<<g0, 256, 0, stream>>>(p);
+            if (s->D == 128) prefill_attn_kernel<128, kListed, 1><<<g0, 256, 0, stream>>>(p);
+            else prefill_attn_kernel<64, kListed, 1><<<g0, 256, 0, stream>>>(p);
         }
     }
     const dim3 grid((unsigned)p.n_diag, (unsigned)units);
     if (idx) {
-        if (s->D == 128) prefill_attn_kernel<128, kOwn><<<grid, 256, 0, stream>>>(p);
-        else prefill_attn_kernel<64, kOwn><<<grid, 256, 0, stream>>>(p);
+        if (s->D == 128) prefill_attn_kernel<128, kOwn, 1><<<grid, 256, 0, stream>>>(p);
+        else prefill_attn_kernel<64, kOwn, 1><<<grid, 256, 0, stream>>>(p);
     } else {
-        if (s->D == 128) prefill_attn_kernel<128, kDense><<<grid, 256, 0, stream>>>(p);
-        else prefill_attn_kernel<64, kDense><<<grid, 256, 0, stream>>>(p);
+        if (s->D == 128) prefill_causal_launch<128, kDense>(p, grid, stream);
+        else prefill_causal_launch<64, kDense>(p, grid, stream);
     }
     return hipGetLastError() == hipSuccess ? RS_OK : RS_LAUNCH_FAILED;
 }

@@ -213,12 +213,14 @@ def test_lists_are_taken_as_given(rs, knobs, form):
     ws.async_status()
 
 
+@pytest.mark.parametrize("sub", ["1", "2"])  # steps of 32 keys, of 64
 @pytest.mark.parametrize("D,Hq,Hkv", [(64, 3, 1), (128, 8, 2)])  # units in launch order; eight units, one per XCD
-def test_prefill_tile_edges(rs, knobs, D, Hq, Hkv):
-    """Lengths around the edges of the 32-key tiles, of the ring of three of them and of the 128-row
+def test_prefill_tile_edges(rs, knobs, D, Hq, Hkv, sub):
+    """Lengths around the edges of the tiles of a step, of the ring of three of them and of the 128-row
     tiles, in every form of the kernel; cache rows past T hold NaN and must not be looked at."""
+    knobs.setenv("RATSPARSE_PREFILL_SUB", sub)
     block, K, rng = 64, 3, np.random.default_rng(31)
-    for T in (1, 31, 32, 33, 64, 96, 97, 128, 129, 190, 225, 257, 330):
+    for T in (1, 31, 32, 33, 64, 96, 97, 128, 129, 190, 225, 257, 330, 500):
         say("prefill tile edges", D, T)
         w, q, kc, vc = _setup(synth.C4.scaled(B=1, Hq=Hq, Hkv=Hkv, D=D, n_needles=1), T, T + 16)
         dk, dv = kc.copy(), vc.copy()
@@ -247,9 +249,11 @@ def test_prefill_tile_edges(rs, knobs, D, Hq, Hkv):
 
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("order", ["growing", "falling", "mixed"])
-def test_prefill_scores_that_outgrow_the_reference(rs, knobs, D, order):
+@pytest.mark.parametrize("sub", ["1", "2"])
+def test_prefill_scores_that_outgrow_the_reference(rs, knobs, D, order, sub):
     """Row maxima that keep growing by far more than the lazily moved softmax reference allows for, that come first, or
     that jump about, with weights down to nothing in between: every form of the kernel against the oracle."""
+    knobs.setenv("RATSPARSE_PREFILL_SUB", sub)
     T, block, K, Hq, Hkv, r = 900, 64, 3, 2, 1, np.random.default_rng(D)
     q = r.standard_normal((1, Hq, T, D)).astype(np.float32)
     d = r.standard_normal(D).astype(np.float32)
@@ -281,9 +285,10 @@ def test_prefill_scores_that_outgrow_the_reference(rs, knobs, D, order):
 
 
 @pytest.mark.parametrize("heads", [56, 50])  # seven units per XCD in groups of six; in launch order in groups of 48
-def test_tile_order_over_many_heads(rs, heads):
+def test_tile_order_over_many_heads(rs, knobs, heads):
     """Causal tiles go out over groups of heads with a remainder first: every tile once, whatever the
-    grouping, so each head gets the bits it gets in a call with few heads."""
+    grouping, so each head gets the bits it gets in a call with few heads (steps of one length in all calls)."""
+    knobs.setenv("RATSPARSE_PREFILL_SUB", "1")
     T, D, block, K = 4001, 64, 64, 8
     gen = torch.Generator(device="cuda")
     gen.manual_seed(heads)
