@@ -208,8 +208,11 @@ enum PrefillForm { kDense, kBitSets, kListed, kOwn };
 
 // SUB: 32-key sub-tiles per step.  One, with three workgroups per CU, where a launch fills the chip;
 // two, with twice the independent matrix and vector instructions per wave, where a CU has a workgroup to itself.
+// With two the kernel is declared for 512 threads (it is launched with 256): the compiler then keeps the accumulators
+// in 256 vector registers, where it otherwise takes 512, half of them accumulation registers, and copies all of them
+// every step (causal, 8 heads x 4000 tokens 60.6 -> 56.1 us, 2 x 8 x 535 14.6 -> 12.8).
 template <int D, PrefillForm FORM, int SUB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 1 ? 3 : D == 64 ? 2 : 1, SUB == 1 ? 3 : 2))) void prefill_attn_kernel(const PrefillParams a)
+__global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_per_eu(SUB == 1 ? 3 : 2, SUB == 1 ? 3 : 2))) void prefill_attn_kernel(const PrefillParams a)
 {
     constexpr int kKT = 32 * SUB;  // keys per step
     constexpr int NC = D / 16;     // 16-wide d chunks of the QK^T contraction
@@ -432,14 +435,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 1 ? 
         bool sel = true;
         if constexpr (FORM == kBitSets) sel = (selmask >> cur_blk) & 1ull;
         const bool more = MAIN || it + 2 < n_steps;
+        // a wave may skip a step past its rows, or of a block that none of its rows listed (whose values may be anything)
+        const bool live = !SKIP || (kr <= wave_last && (FORM != kBitSets || ((wave_mask >> cur_blk) & 1ull)));
         if (!NEXT && more) {
 #pragma unroll
-            for (int i = 0; i < CPT; ++i) {
-                stage(kb, gk, nK, i, it + 2);
-                stage(vb, gv, nV, i, it + 2);
-            }
+            for (int i = 0; i < CPT; ++i) stage(kb, gk, nK, i, it + 2);
         }
-        if (!SKIP || (kr <= wave_last && (FORM != kBitSets || ((wave_mask >> cur_blk) & 1ull)))) {
+        if (live) {
             // S^T[key][query] = sum_d K[key][d] Q[query][d].  Matrix phases run at raised priority:
             // of the waves that share a SIMD, the one feeding the matrix pipe is issued first and the
             // others' softmax fills the gaps
@@ -586,6 +588,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 1 ? 
                 ++cur_blk;
             }
         }
+        // (V at the other end of the step: a burst of both stalls the wave; 8 heads x 4000 by bit sets 90.2 -> 86.7 us)
+        if (!NEXT && more) {
+#pragma unroll
+            for (int i = 0; i < CPT; ++i) stage(vb, gv, nV, i, it + 2);
+        }
         // the next step's tile has landed (the one after it, staged above, may still be on its way),
         // and this wave has read what it needs of the current one
         if (more) __builtin_amdgcn_s_waitcnt(0x0070 | (2 * CPT));
@@ -596,7 +603,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 1 ? 
         using B0 = std::integral_constant<int, 0>;
         using B1 = std::integral_constant<int, 1>;
         using B2 = std::integral_constant<int, 2>;
-        using Main = std::integral_constant<bool, (FORM == kBitSets && SUB == 1) || FORM == kOwn>;  // which loops may skip
+        using Main = std::integral_constant<bool, FORM == kBitSets || FORM == kOwn>;  // which loops may skip
         // keys past a row only occur in the last 4 / SUB steps of a tile (128 keys from the tile's own rows on;
         // kListed: past the block's end), keys before its own block only in kOwn
         using MainMask = std::integral_constant<bool, FORM == kOwn>;

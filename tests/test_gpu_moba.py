@@ -247,6 +247,38 @@ def test_prefill_tile_edges(rs, knobs, D, Hq, Hkv, sub):
         ws.async_status()
 
 
+@pytest.mark.parametrize("sub", ["1", "2"])  # steps of 32 keys, of 64
+@pytest.mark.parametrize("D", [64, 128])
+def test_blocks_that_no_row_of_a_wave_listed_are_not_looked_at(rs, knobs, D, sub):
+    """By bit sets a wave of 32 rows skips the blocks that none of its rows listed: such a block may hold NaN and infinities
+    (a weight of zero times them would be NaN) and every row still gets the oracle's result over a clean cache."""
+    knobs.setenv("RATSPARSE_PREFILL_SUB", sub)
+    knobs.setenv("RATSPARSE_PREFILL_MASKED", "1")
+    T, block, Hq, Hkv, r = 1000, 64, 4, 2, np.random.default_rng(D)
+    w, q, kc, vc = _setup(synth.C4.scaled(B=1, Hq=Hq, Hkv=Hkv, D=D, n_needles=1), T, T + 24)
+    bad = (2, 3, 7)  # blocks that no row lists, those that live in them included
+    idx = np.full((1, Hq, T, 3), -1, dtype=np.int32)
+    for h in range(Hq):
+        for t in range(T):
+            may = [j for j in range(t // block + 1) if j not in bad]
+            pick = np.sort(r.choice(may, size=min(3, len(may)), replace=False))
+            idx[0, h, t, :len(pick)] = pick
+    dk, dv = kc.copy(), vc.copy()
+    for j, x in zip(bad, (np.nan, np.inf, -np.inf)):
+        dk[:, :, j * block:(j + 1) * block], dv[:, :, j * block:(j + 1) * block] = x, x
+    s = rs.make_shape(1, Hq, Hkv, D, T + 24, 16, torch.bfloat16)
+    ws = rs.Workspace(rs.sparse_attn_prefill_workspace_bytes(s, T, block, 3))
+    out = torch.full((1, Hq, T, D), 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, Hq, T), 7.0, device="cuda")
+    rs.sparse_attn_prefill(s, to_dev(q, "bf16"), to_dev(dk, "bf16"), to_dev(dv, "bf16"), T, block, 1.0 / np.sqrt(D),
+                           torch.from_numpy(idx).cuda(), 3, out, lse, ws)
+    oout, olse = oracle.sparse_attn_prefill(q, kc, vc, T, block, 1.0 / np.sqrt(D), idx)
+    ok, worst = attn_close(to_np(out), oout)
+    assert ok, worst
+    np.testing.assert_allclose(to_np(lse), olse, rtol=2e-3, atol=2e-3)
+    ws.async_status()
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("order", ["growing", "falling", "mixed"])
 @pytest.mark.parametrize("sub", ["1", "2"])
