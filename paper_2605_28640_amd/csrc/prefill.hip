@@ -47,7 +47,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kMT = 128;        // query rows per workgroup tile (4 waves x 32)
 constexpr uint32_t kSlotShift = 27;
 constexpr float kLazy = 8.f;    // slack (base-2 exponent) before the softmax reference point moves
-constexpr float kLarge = 4096.f;  // sum of a lane's 16 weights from which it is looked at
+constexpr float kLarge = 4096.f;  // 16 x 2^kLazy: above it one of a lane's 16 weights of a 32-key sub-tile has passed the slack
 
 // ------------------------------------------------------------------------------------
 // bucketing of (row, slot) pairs by picked block
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 // 15 of some 95 vector instructions fewer in a loop that power limits: 32 over 8 heads x 16001
                 // tokens 1774 -> 1710 us.  (Tiles of listed rows have too few steps: 690 -> 715 us.)
                 float ps = weights((m == -INFINITY) ? INFINITY : -m);
-                if (__any(!(ps <= kLarge))) {
+                if (__any(!(ps <= kLarge * SUB))) {  // some weight is above 2^kLazy: the reference is sure to move
                     scores(std::false_type{});
                     ps = weights_by_maximum();
                 }
