@@ -120,15 +120,13 @@ static int pick_splits(long units, long items, long min_items_per_split, long ta
 
 static int num_cus()
 {
-    static int n = 0;
-    if (n == 0) {
+    static const int n = [] {  // (thread-safe on first use)
         int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-            n = v;
-        else
-            n = 256;
-    }
+        return hipGetDevice(&dev) == hipSuccess &&
+                       hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0
+                   ? v
+                   : 256;
+    }();
     return n;
 }
 

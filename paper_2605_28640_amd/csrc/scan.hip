@@ -572,17 +572,17 @@ static int launch_scan(const void *k, const void *v, const float *g, float *stat
     const int n_chunks = (int)((T_new + lead + CHUNK - 1) / CHUNK);
     long grid = (long)BH * (D / DS) * n_chunks;
     if (n_chunks > 1) {
-        static int per_cu = 0, cus = 0;  // resident workgroups of this kernel
-        if (per_cu == 0) {
-            int dev = 0, n = 0;
+        // resident workgroups of this kernel: both factors at once, as several host threads may be the first here
+        static const long resident = [] {
+            int dev = 0, per_cu = 0, cus = 0;
             (void)hipGetDevice(&dev);
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE>, NW * 64, 0) != hipSuccess || n < 1) n = 1;
-            per_cu = n;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE>, NW * 64, 0) != hipSuccess || per_cu < 1) per_cu = 1;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-        }
-        long want = knob_or(knobs().scan_grid, per_cu * cus);
+            return (long)per_cu * cus;
+        }();
+        long want = knob_or(knobs().scan_grid, (int)resident);
+        if (want > resident) want = resident;  // the knob only narrows: every workgroup stays resident
         if (want < 1) want = 1;
-        if (want > (long)per_cu * cus) want = (long)per_cu * cus;  // the knob only narrows: every workgroup stays resident
         if (grid > want) grid = want;
     }
     rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(

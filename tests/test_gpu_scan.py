@@ -292,3 +292,57 @@ def test_odd_starts_leave_the_page_bounds(rs, dtype, D, P):
                 else:
                     x = gk[:, :, p * P:min((p + 1) * P, t0 + T)]
                     assert np.array_equal(gm[:, :, p, 0], x.min(2)) and np.array_equal(gm[:, :, p, 1], x.max(2)), (t0, T, p)
+
+
+_FIRST_CALLS = """
+import threading
+import torch
+from paper_2605_28640_amd import binding as rs
+
+rs.load()
+torch.zeros(1, device="cuda")
+runs = []
+for dtype, D, H, T in ((torch.bfloat16, 128, 4, 4096), (torch.float32, 64, 4, 4096), (torch.float32, 128, 40, 1024)):
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    k, v = (torch.randn(1, H, T, D, device="cuda", generator=gen).to(dtype) for _ in range(2))
+    g = torch.sigmoid(torch.randn(1, H, T, D, device="cuda", generator=gen))
+    s = rs.make_shape(1, H, H, D, T, 16, dtype)
+    calls = []
+    for _ in range(4):
+        state = [torch.zeros(1, H, D, device="cuda") for _ in range(2)]
+        cache = [torch.zeros(1, H, T, D, dtype=dtype, device="cuda") for _ in range(2)]
+        calls.append((state, cache, rs.Workspace(rs.rat_scan_workspace_bytes(s, T)), torch.cuda.Stream()))
+    runs.append((s, k, v, g, T, calls))
+torch.cuda.synchronize()
+for s, k, v, g, T, calls in runs:
+    gate, failed = threading.Barrier(len(calls)), []
+
+    def call(state, cache, ws, stream):
+        try:
+            with torch.cuda.stream(stream):
+                gate.wait()
+                rs.rat_scan(s, k, v, g, *state, *cache, 0, T, ws, None)
+        except Exception as e:
+            failed.append(repr(e))
+
+    threads = [threading.Thread(target=call, args=c) for c in calls]
+    [t.start() for t in threads], [t.join() for t in threads]
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for state, cache, ws, _ in calls:
+        assert all(torch.equal(a, b) for a, b in zip(state + cache, calls[0][0] + calls[0][1]))
+        assert cache[0].abs().sum() > 0
+print("first calls ok")
+"""
+
+
+def test_first_calls_from_several_threads():
+    """Each form's first call looks up how many of its workgroups the GPU holds; here several threads make it at once,
+    each with its own workspace and stream, in a fresh process: every call is launched and all get the same bits."""
+    import os
+    import subprocess
+    import sys
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _FIRST_CALLS], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "first calls ok" in r.stdout, r.stdout + r.stderr
