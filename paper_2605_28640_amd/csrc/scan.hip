@@ -30,20 +30,24 @@
 
 namespace rs {
 
-// PAGE > 0 (a power of two from 16 tokens to the chunk length; the chunks are laid out from the chunk
-// boundary at or below t0, `lead` tokens before the run, where they pass the state on): a wave's tokens (16 or 32 in bfloat16, 8 or 16 in float32, at 128 or 64
-// channels) are whole pages or an aligned part of one, so the page's channelwise min / max of the stored keys (App. A.1,
-// Quest) leave with the states -- in-lane over the lane's four tokens, shuffles over the row
+// LEAD: the run starts inside a chunk; the chunks are laid out from the chunk boundary below t0, `lead` tokens before
+// the run, where they pass the state on.  A form of its own, as its code takes 17 to 23 registers more: without it
+// float32 slabs fit a CU twice (8 heads x 64K 313 -> 301 us), and the form without page bounds, which reads the same
+// pieces, loses nothing to the tests against the run's start (bfloat16, 8 heads x 128K 403 -> 360 us).
+// PAGE > 0 (a power of two from 16 tokens to the chunk length; the run starts on a chunk boundary, or LEAD): a wave's
+// tokens (16 or 32 in bfloat16, 8 or 16 in float32, at 128 or 64 channels) are whole pages or an aligned part of one, so
+// the page's channelwise min / max of the stored keys (App. A.1, Quest) leave with the states -- in-lane over the lane's four tokens, shuffles over the row
 // groups of a page, and for pages longer than a wave's tokens a fold of the waves' bounds
 // through LDS -- and the keys need no second pass.
-template <typename ST, int D, int DS, int NT, int NW, int PAGE>
+template <typename ST, int D, int DS, int NT, int NW, int PAGE, bool LEAD>
 __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const ST *__restrict__ k, const ST *__restrict__ v, const float *__restrict__ g,
     float *__restrict__ state_k, float *__restrict__ state_v, ST *__restrict__ k_cache,
     ST *__restrict__ v_cache, int BH, long T_new, long t0, long Tcap, int n_chunks,
     uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit, ST *__restrict__ meta, int deep, int lead_arg)
 {
-    const int lead = DS < D ? lead_arg : 0;  // (the full-row form starts on a chunk boundary where it leaves bounds)
+    const int lead = LEAD ? lead_arg : 0;
+    const int rec_chunks = LEAD ? n_chunks - 1 : n_chunks;  // records per unit (a lead may add a chunk, the last one leaves none)
     constexpr bool META = PAGE > 0;
     constexpr int TW = (64 / (DS / 8)) * NT;  // tokens of a wave
     static_assert(!META || (PAGE >= 16 && (NW * TW) % (PAGE > 0 ? PAGE : 1) == 0), "pages tile the chunk");
@@ -102,7 +106,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             const long t = tbase + i;
             typename R::raw_t kq = R::zero_raw(), vq = R::zero_raw();
             float4 ga = make_float4(1.f, 1.f, 1.f, 1.f), gb = ga;  // outside the run: the identity element (g = 1 keeps the state)
-            if ((DS == D || t >= 0) && t < T_new) {
+            if ((!LEAD || t >= 0) && t < T_new) {
                 const long off = (in_row0 + t) * D + ch0 + c0;
                 if constexpr (DS == D) {
                     // whole rows, read once: streaming loads (a slab shares its cache lines with the
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     // its round trip overlaps the fold; the wait below re-polls only if it was not there yet
     uint64_t early0 = 0, early1 = 0;
     if (tid < DS && j > 0) {
-        const uint64_t *p = rec + (((long)unit * (n_chunks - 1) + (j - 1)) * 2) * DS + tid;
+        const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + tid;
         early0 = load_u64_agent(p);
         early1 = load_u64_agent(p + DS);
     }
@@ -278,7 +282,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             Sk = state_k[bh * D + ch0 + c];
             Sv = state_v[bh * D + ch0 + c];
         } else {
-            const uint64_t *p = rec + (((long)unit * (n_chunks - 1) + (j - 1)) * 2) * DS + c;
+            const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + c;
             uint64_t w0 = early0, w1 = early1;
             int spins = 0;
             bool ok = ((uint32_t)(w0 >> 32) == tag) && ((uint32_t)(w1 >> 32) == tag);
@@ -299,7 +303,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             state_k[bh * D + ch0 + c] = Ok;
             state_v[bh * D + ch0 + c] = Ov;
         } else {
-            uint64_t *p = rec + (((long)unit * (n_chunks - 1) + j) * 2) * DS + c;
+            uint64_t *p = rec + (((long)unit * rec_chunks + j) * 2) * DS + c;
             store_u64_agent(p, ((uint64_t)tag << 32) | __float_as_uint(Ok));
             store_u64_agent(p + DS, ((uint64_t)tag << 32) | __float_as_uint(Ov));
         }
@@ -334,7 +338,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         plo[c] = INFINITY;
         phi[c] = -INFINITY;
     }
-    if constexpr (META && DS < D) {
+    if constexpr (LEAD) {
         if (tbase < 0) {  // stored rows of the run's first page: only their bounds are wanted
             const int page0 = (int)(t0 & (PAGE - 1));
 #pragma unroll 1
@@ -352,7 +356,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         const long t = tbase + i;
-        if ((DS == D || t >= 0) && t < T_new) {
+        if ((!LEAD || t >= 0) && t < T_new) {
             float kx[8], vx[8];
             R::unpack(kr[i], kx);
             R::unpack(vr[i], vx);
@@ -400,7 +404,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                     phi[c] = fmaxf(phi[c], shfl_xor_f(phi[c], msk));
                 }
             const long tp = (long)j * CHUNK + (long)wave * TW + (long)(rg / RGP) * PAGE - lead;  // the page's first token
-            if (tp < T_new && (DS == D || tp + PAGE > 0) && rg % RGP < 2) {
+            if (tp < T_new && (!LEAD || tp + PAGE > 0) && rg % RGP < 2) {
                 const long page = (t0 + tp) / PAGE;
                 ST *mrow = meta + (((long)bh * (Tcap / PAGE) + page) * 2) * D + ch0 + c0;
                 if (rg % RGP == 0) R::store(mrow, plo);
@@ -426,7 +430,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             }
             __syncthreads();
             const long tp = (long)j * CHUNK + (long)wave * PAGE - lead;  // first token of page `wave` of this chunk
-            if (wave < NW / WPP && rg < 2 && tp < T_new && (DS == D || tp + PAGE > 0)) {
+            if (wave < NW / WPP && rg < 2 && tp < T_new && (!LEAD || tp + PAGE > 0)) {
                 float x[8];
 #pragma unroll
                 for (int c = 0; c < 8; ++c) x[c] = s_pg[wave * WPP][rg][c0 + c];
@@ -558,37 +562,58 @@ __global__ __launch_bounds__(256) void rat_step_kernel(
     state_v[e] = sv;
 }
 
-template <typename ST, int D, int DS, int PAGE_ARG>
-static int launch_scan(const void *k, const void *v, const float *g, float *state_k,
+template <typename ST, int D, int DS, int PAGE, bool LEAD>
+static void launch_scan_form(const void *k, const void *v, const float *g, float *state_k,
                        float *state_v, void *k_cache, void *v_cache, int BH, long T_new, long t0,
                        long Tcap, uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit,
-                       void *meta, hipStream_t stream)
+                       void *meta, int lead, hipStream_t stream)
 {
     constexpr int NT = sizeof(ST) == 2 ? 4 : 2;
     constexpr int NW = 8;
     constexpr int CHUNK = NW * (64 / (DS / 8)) * NT;
-    constexpr int PAGE = (PAGE_ARG <= CHUNK) ? PAGE_ARG : 0;  // larger pages never get here with the bounds asked for
-    const int lead = (PAGE > 0 && DS < D) ? (int)(t0 % CHUNK) : 0;
     const int n_chunks = (int)((T_new + lead + CHUNK - 1) / CHUNK);
     long grid = (long)BH * (D / DS) * n_chunks;
     if (n_chunks > 1) {
         // resident workgroups of this kernel: both factors at once, as several host threads may be the first here
-        static const long resident = [] {
+        struct Resident {
+            long cus, all;
+        };
+        static const Resident resident = [] {
             int dev = 0, per_cu = 0, cus = 0;
             (void)hipGetDevice(&dev);
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE>, NW * 64, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD>, NW * 64, 0) != hipSuccess || per_cu < 1) per_cu = 1;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-            return (long)per_cu * cus;
+            return Resident{cus, (long)per_cu * cus};
         }();
-        long want = knob_or(knobs().scan_grid, (int)resident);
-        if (want > resident) want = resident;  // the knob only narrows: every workgroup stays resident
+        // With 16 chains or fewer one workgroup per CU: a second one only slows the chains' links down (float32, which
+        // fits two; two / one per CU: 4 heads x 64K of 128 channels 243 / 199 us, 8 heads x 64K of 64 channels 226 / 197,
+        // 2 heads 194 / 171; 32 chains, 8 heads of 128 channels: 300 / 314)
+        long want = knob_or(knobs().scan_grid, (int)((long)BH * (D / DS) <= 16 ? resident.cus : resident.all));
+        if (want > resident.all) want = resident.all;  // the knob only narrows: every workgroup stays resident
         if (want < 1) want = 1;
         if (grid > want) grid = want;
     }
-    rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(
+    rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(
         (const ST *)k, (const ST *)v, g, state_k, state_v, (ST *)k_cache, (ST *)v_cache, BH, T_new,
         t0, Tcap, n_chunks, ctrl, rec, tag, spin_limit, (ST *)meta, (n_chunks > 1 && (long)BH * (D / DS) >= 128) ? 1 : 0, lead);
-    return 0;
+}
+
+template <typename ST, int D, int DS, int PAGE_ARG>
+static void launch_scan(const void *k, const void *v, const float *g, float *state_k, float *state_v, void *k_cache,
+                        void *v_cache, int BH, long T_new, long t0, long Tcap, uint32_t *ctrl, uint64_t *rec, uint32_t tag,
+                        int spin_limit, void *meta, hipStream_t stream)
+{
+    constexpr int CHUNK = 8 * (64 / (DS / 8)) * (sizeof(ST) == 2 ? 4 : 2);
+    constexpr int PAGE = (PAGE_ARG <= CHUNK) ? PAGE_ARG : 0;  // larger pages never get here with the bounds asked for
+    if constexpr (PAGE > 0 && DS < D) {
+        if (t0 % CHUNK != 0) {
+            launch_scan_form<ST, D, DS, PAGE, true>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec,
+                                                    tag, spin_limit, meta, (int)(t0 % CHUNK), stream);
+            return;
+        }
+    }
+    launch_scan_form<ST, D, DS, PAGE, false>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec, tag,
+                                             spin_limit, meta, 0, stream);
 }
 
 int scan_chunk_tokens(int dtype, int D)
