@@ -627,17 +627,22 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     int splits = pick_splits(units, tiles, 8, target);
     if (splits > L.splits_att_max) splits = L.splits_att_max;
     // Heads of a KV head that attend the same rows go through them together where fetching the rows per
-    // head is what takes the time: when the heads' reads come to 300 MB (200 MB for two heads), or when
+    // head is what takes the time: when the heads' reads come to 300 MB (200 MB for two heads; 700 MB for eight heads
+    // over more than 32 splits, whose partials take long to merge) and the KV heads' splits fill the chip, or when
     // the splits of a KV head are few enough (8) that merging their partials costs little.  Per head / shared, us,
     // bfloat16, 128 channels: batch 8, 32 over 8 heads, 1000 rows 24.0 / 13.1, 8000 rows 159 / 67; batch 4
     // x 32768 183 / 104; batch 1 x 1000 9.4 / 8.3, x 65536 86 / 54, and the other way at 4000 rows 11.2 / 14.3,
-    // at 16416 23.4 / 24.2 and at 200 rows 5.8 / 7.8; batch 1, 16 over 8 heads x 32768 40 / 30, 32 over 4 x 32768 36.5 / 33.8.
+    // at 16416 23.4 / 24.2 and at 200 rows 5.8 / 7.8; batch 1, 16 over 8 heads x 32768 40 / 30.  With the append: 32 over 4
+    // heads x 32768 36 / 42, x 65000 73 / 55, batch 2 x 32768 73 / 50; 16 over 2 heads x 65000 (128 splits in all) 38 / 54.
     if (s->Hq > s->Hkv && (group || !use_idx)) {
-        int sp = pick_splits((long)s->B * s->Hkv, tiles, 8, knob_or(knobs().attend_wgs, 256));
+        const int G = s->Hq / s->Hkv;
+        const long kv_units = (long)s->B * s->Hkv;
+        int sp = pick_splits(kv_units, tiles, 8, knob_or(knobs().attend_wgs, 256));
         if (sp > L.splits_att_max) sp = L.splits_att_max;
         const double read = (double)units * tiles * 16 * s->D * 2 * esize(s->dtype);
-        const bool pays = read >= (s->Hq == 2 * s->Hkv ? 200e6 : 300e6) || (sp <= 8 && tiles >= 32);
-        if (decode_attend_shared_fits(s->dtype, s->D, s->Hq / s->Hkv, sp) && knob_or(knobs().attend_shared, pays ? 1 : 0)) {
+        const double from = G == 2 ? 200e6 : G == 8 && sp > 32 ? 700e6 : 300e6;
+        const bool pays = (read >= from && kv_units * sp >= 256) || (sp <= 8 && tiles >= 32);
+        if (decode_attend_shared_fits(s->dtype, s->D, G, sp) && knob_or(knobs().attend_shared, pays ? 1 : 0)) {
             decode_attend_shared_dispatch(s->dtype, s->D, q, k_cache, v_cache, use_idx, out, lse_out,
                                           (uint64_t *)(w + L.off_partial), s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_valid, K,
                                           scale, sp, ctr_att, err, tag, g_spin_limit.load(), (hipStream_t)stream);

@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
 // point once per step and head.
 // Bound by memory from about a hundred megabytes on (8 x 32 over 8 heads x 8000 rows: 268 MB in 67 us against
 // 159 us with a workgroup per head, which took every row four times through the CUs at 40 bytes per ns
-// each), by the latency of the merge below that.
+// each), by the merge below that.
 // ------------------------------------------------------------------------------------
 constexpr int kSharedThreads = 512;
 constexpr int kSharedMaxSplits = 64;
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
     constexpr int PPW = G * RPW <= 16 ? RPW : 1, NP = NW * PPW;
     __shared__ float s_m[NP][G], s_l[NP][G];
     __shared__ __attribute__((aligned(16))) float s_o[NP][G][D];
-    __shared__ int s_role;
+    __shared__ int s_last;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rg = lane / LPR, c0 = (lane % LPR) * 8;
@@ -678,46 +678,72 @@ __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
     }
     if (splits == 1) return;
 
-    // The last G splits of the unit to arrive share the final merge, a head each (fewer splits: every
-    // splits-th head): one workgroup would take 0.33 us per split for four heads.  The first of them may still wait
-    // for the partials of the others, which are already running or next to be dispatched.
-    const int roles = G < splits ? G : splits;
+    // The last split of the unit to arrive merges them all: every word it reads has been sent by a workgroup that ran, so
+    // nothing here depends on the order in which workgroups start.  The words go by plain 16-byte loads, two channels a
+    // lane (8-byte agent-scope loads take them at a third of that rate); one whose tag is not this call's, because it is
+    // still on its way or a cache holds it from before, is polled at agent scope.  Four heads x 32 splits take about 3 us,
+    // eight x 64 about 10 (a fence that empties the caches first costs 10 us by itself).
     if (tid == 0) {
-        const int prev = (int)atomicAdd(&unit_ctr[unit], 1u);
-        s_role = prev - (splits - roles);
-        if (prev == splits - 1) atomicExch(&unit_ctr[unit], 0u);
+        const uint32_t prev = atomicAdd(&unit_ctr[unit], 1u);
+        s_last = (prev == (uint32_t)splits - 1u);
+        if (s_last) atomicExch(&unit_ctr[unit], 0u);
     }
     __syncthreads();
-    const int role = s_role;
-    if (role < 0) return;
-    constexpr int NG = kSharedThreads / D;  // thread groups, each over every NG-th split
-    const int gi = tid / D, c = tid % D;
-    for (int g = role; g < G; g += roles) {
-        const long head = (long)unit * G + g;
-        float M = -INFINITY, L = 0.f, O = 0.f;
-        merge_partials(partial + head * splits * (D + 2), splits, D + 2, c, tag, spin_limit, err, M, L, O, gi, NG);
-        if (c == 0) {
-            s_m[gi][0] = M;
-            s_l[gi][0] = L;
-        }
-        s_o[gi][0][c] = O;
-        __syncthreads();
-        if (gi == 0) {
-            M = -INFINITY;
+    if (!s_last) return;
+    constexpr int LR = D / 2, ROWS = kSharedThreads / LR;  // lanes per partial, partials at a time
+    constexpr int PARTS = ROWS / G, U = 8;                 // of which each head has PARTS; partials a lane has on their way
+    static_assert(PARTS >= 1 && PARTS <= NP, "the parts meet in the arrays above");
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const int g = (tid / LR) % G, part = tid / LR / G, c = (tid % LR) * 2;
+    const uint64_t *ph = partial + ((long)unit * G + g) * splits * (D + 2);
+    float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f;
+    for (int s0 = part; s0 < splits; s0 += U * PARTS) {
+        u64x2 ml[U], oo[U];
 #pragma unroll
-            for (int i = 0; i < NG; ++i) M = fmaxf(M, s_m[i][0]);
-            L = O = 0.f;
-#pragma unroll
-            for (int i = 0; i < NG; ++i) {
-                const float a = (s_m[i][0] == -INFINITY) ? 0.f : __expf(s_m[i][0] - M);
-                L += s_l[i][0] * a;
-                O += s_o[i][0][c] * a;
-            }
-            const float inv = (L > 0.f) ? 1.f / L : 0.f;
-            from_f32(out[head * D + c], O * inv);
-            if (c == 0 && lse_out) lse_out[head] = (L > 0.f) ? M + __logf(L) : -INFINITY;
+        for (int u = 0; u < U; ++u) {
+            const int sp = (s0 + u * PARTS < splits) ? s0 + u * PARTS : s0;
+            ml[u] = *reinterpret_cast<const u64x2 *>(ph + (long)sp * (D + 2));
+            oo[u] = *reinterpret_cast<const u64x2 *>(ph + (long)sp * (D + 2) + 2 + c);
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u * PARTS >= splits) break;
+            const uint64_t *p = ph + (long)(s0 + u * PARTS) * (D + 2);
+            auto value = [&](uint64_t w, int at) __attribute__((always_inline)) -> float {
+                return (uint32_t)(w >> 32) == tag ? __uint_as_float((uint32_t)w) : acquire_f32(p + at, tag, spin_limit, err);
+            };
+            const float ms = value(ml[u].x, 0), ls = value(ml[u].y, 1), o0 = value(oo[u].x, 2 + c), o1 = value(oo[u].y, 3 + c);
+            const float mn = fmaxf(M, ms);
+            const float a1 = (M == -INFINITY) ? 0.f : __expf(M - mn);
+            const float a2 = (ms == -INFINITY) ? 0.f : __expf(ms - mn);
+            L = L * a1 + ls * a2;
+            O0 = O0 * a1 + o0 * a2;
+            O1 = O1 * a1 + o1 * a2;
+            M = mn;
+        }
+    }
+    if (c == 0) {
+        s_m[part][g] = M;
+        s_l[part][g] = L;
+    }
+    *reinterpret_cast<float2 *>(&s_o[part][g][c]) = make_float2(O0, O1);
+    __syncthreads();
+    for (int e = tid; e < G * D; e += kSharedThreads) {
+        const int ge = e / D, ce = e % D;
+        const long head = (long)unit * G + ge;
+        M = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) M = fmaxf(M, s_m[i][ge]);
+        L = O0 = 0.f;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) {
+            const float a = (s_m[i][ge] == -INFINITY) ? 0.f : __expf(s_m[i][ge] - M);
+            L += s_l[i][ge] * a;
+            O0 += s_o[i][ge][ce] * a;
+        }
+        const float inv = (L > 0.f) ? 1.f / L : 0.f;
+        from_f32(out[head * D + ce], O0 * inv);
+        if (ce == 0 && lse_out) lse_out[head] = (L > 0.f) ? M + __logf(L) : -INFINITY;
     }
 }
 
