@@ -498,7 +498,7 @@ __global__ __launch_bounds__(kSelThreads) void snapkv_sel_hist_kernel(const floa
     }
     __syncthreads();
     if (tid < 256 && lh[tid]) atomicAdd(&hist[(bk * 4 + pass) * 256 + tid], lh[tid]);
-    if (LAST && tid < 256) {
+    if (LAST && tid < 256 && gridDim.x > 1) {  // (a single slice has none before it)
         uint32_t *mine = slice_bins + (bk * gridDim.x + blockIdx.x) * kSelBins;
         mine[tid] = lh[tid];
         if (tid == 0) mine[256] = s_above;
@@ -703,8 +703,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     }
     // votes exist for prefix keys only: chunks that start past the prefix are not needed
     const dim3 grid2((unsigned)((L + Ly.keys_per_wg - 1) / Ly.keys_per_wg), (unsigned)BK);
-    // knob 0: the spread-out selection at any length that its slices' bins leave room for
-    const bool one_wg = L <= kSnapOneWgKeys && (knobs().snap_one_wg != 0 || (long)Ly.n_slices * kSelBins > L);
+    const bool one_wg = L <= kSnapOneWgKeys && knobs().snap_one_wg != 0;  // (knob 0: the spread-out selection at any length)
     uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
     const long n_hist = one_wg ? 0 : BK * 1024;
 #define RS_VOTES(DD, SS) \
@@ -722,8 +721,9 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
             votes, votes_out, idx_out, (int)L, pool_kernel, K_keep);
     } else {
         const dim3 gs((unsigned)Ly.n_slices, (unsigned)BK);
-        // the raw votes are not needed past the pooling: the slices' bins take their place (one word for
-        // every 15 votes of a full slice, and there are several slices)
+        // the raw votes are not needed past the pooling: the slices' bins take their place (kSelBins words a slice
+        // where there are several, and all but the last of them have kSelSlice votes)
+        static_assert(2 * kSelBins <= kSelSlice, "two slices or more leave room for their bins");
         uint32_t *slice_bins = (uint32_t *)votes;
         snapkv_sel_hist_kernel<true, false><<<gs, kSelThreads, 0, stream>>>(votes, pooled, sel_hist, L, K_keep, 0, pool_kernel / 2, nullptr);
         if (K_keep > 0) {

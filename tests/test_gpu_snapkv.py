@@ -146,3 +146,80 @@ def test_snapkv_compress_then_decode(rs, knobs, case):
         assert attn_close(to_np(out), want2)[0]
     torch.cuda.synchronize()
     ws.async_status()
+
+
+def _compress(rs, q, kc, vc, T, W, keep, pool, scale, lse=None):
+    """One call on device tensors: (kept positions, pooled votes, kept K rows)."""
+    B, Hkv, Tcap, D = kc.shape
+    s = rs.make_shape(B, q.shape[1], Hkv, D, Tcap, 16, torch.bfloat16)
+    ws = rs.Workspace(rs.snapkv_compress_workspace_bytes(s, T, W))
+    k_out, v_out = (torch.zeros(B, Hkv, keep + W, D, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    idx = torch.full((B, Hkv, keep), -5, dtype=torch.int32, device="cuda")
+    votes = torch.full((B, Hkv, T - W), -1.0, device="cuda")
+    if lse is None:
+        rs.snapkv_compress(s, q, kc, vc, T, W, keep, pool, scale, k_out, v_out, keep + W, idx, votes, ws)
+    else:
+        rs.snapkv_compress_lse(s, q, kc, vc, T, W, keep, pool, scale, lse, k_out, v_out, keep + W, idx, votes, ws)
+    torch.cuda.synchronize()
+    ws.async_status()
+    return idx, votes, k_out
+
+
+@pytest.mark.parametrize("L", [1, 100, 259, 4095, 4096, 4097, 8191, 8192, 8193, 12289, 15359, 15360, 15361, 20481])
+def test_selection_over_slices(rs, knobs, L):
+    """The spread-out selection takes 4096 positions a workgroup.  Lengths around one slice, several and the longest that
+    one workgroup takes; pools without a halo, with one and the widest; keys that repeat, so that equal votes lie on
+    both sides of every border.  The kept positions are exactly the first K of a stable descending sort of the
+    pooled votes, the pooled votes are the raw ones pooled, and both forms of the selection give the same bits."""
+    W, D, Hkv = 16, 64, 2
+    T = L + W
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    period = 37  # of the keys: every vote comes L / 37 times
+    kc = torch.randn(1, Hkv, period, D, generator=gen, device="cuda").to(torch.bfloat16)
+    kc = kc.repeat(1, 1, -(-T // period), 1)[:, :, :T].contiguous()
+    vc = torch.randn(1, Hkv, T, D, generator=gen, device="cuda").to(torch.bfloat16)
+    if L > 1000:  # a few positions of their own, at the borders too
+        at = torch.tensor([p for p in (0, 1, 4094, 4095, 4096, 4097, 8191, 8192, 12288, L - 1, L // 2) if p < L], device="cuda")
+        kc[:, :, at] = torch.randn(1, Hkv, len(at), D, generator=gen, device="cuda").to(torch.bfloat16) * 1.5
+    q = torch.randn(1, 2 * Hkv, W, D, generator=gen, device="cuda").to(torch.bfloat16)
+    raw = None
+    for pool in (1, 7, 63):
+        for keep in sorted({1, L // 3 + 1, max(1, L - 1), L}):
+            knobs.setenv("RATSPARSE_SNAP_ONE_WG", "0")
+            idx, votes, k_out = _compress(rs, q, kc, vc, T, W, keep, pool, 0.3)
+            raw = votes if pool == 1 and raw is None else raw
+            want = torch.nn.functional.max_pool1d(raw, pool, 1, pool // 2) if pool > 1 else raw
+            assert torch.equal(votes, want), (pool, keep)
+            first = torch.sort(votes, dim=2, descending=True, stable=True).indices[:, :, :keep].sort(2).values
+            assert torch.equal(idx.long(), first), (pool, keep)
+            rows = torch.cat([first, torch.arange(L, T, device="cuda").expand(1, Hkv, W)], 2)
+            assert torch.equal(k_out, kc.gather(2, rows[..., None].expand(-1, -1, -1, D)))
+            if L <= 15360:
+                knobs.setenv("RATSPARSE_SNAP_ONE_WG", "1")
+                idx1, votes1, k1 = _compress(rs, q, kc, vc, T, W, keep, pool, 0.3)
+                assert torch.equal(idx1, idx) and torch.equal(votes1, votes) and torch.equal(k1, k_out), (pool, keep)
+
+
+def test_streaming_sweeps_at_64_channels(rs):
+    """100 MB of keys or more are read with streaming loads: eight heads at once against each head by itself (13 MB).
+    With the log-sum-exp given the votes are the same bits; without, they differ by the order in which the key
+    chunks' sums are added (32 bits, 50 partial sums: 1e-5 leaves a factor of three over 50 x 2^-24)."""
+    T, W, D, H, keep = 102433, 32, 64, 8, 1000
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    kc, vc = (torch.randn(1, H, T, D, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(1, 2 * H, W, D, generator=gen, device="cuda").to(torch.bfloat16)
+    lse = torch.randn(1, 2 * H, W, generator=gen, device="cuda") + 11.0
+    assert kc.numel() * 2 >= 100 << 20
+    idx, votes, k_out = _compress(rs, q, kc, vc, T, W, keep, 7, 0.125)
+    idx_l, votes_l, k_l = _compress(rs, q, kc, vc, T, W, keep, 7, 0.125, lse)
+    for h in range(H):
+        one = [x[:, h:h + 1].contiguous() for x in (kc, vc)]
+        qh, lh = q[:, 2 * h:2 * h + 2].contiguous(), lse[:, 2 * h:2 * h + 2].contiguous()
+        i1, v1, k1 = _compress(rs, qh, *one, T, W, keep, 7, 0.125, lh)
+        assert torch.equal(i1[0, 0], idx_l[0, h]) and torch.equal(v1[0, 0], votes_l[0, h]) and torch.equal(k1[0, 0], k_l[0, h])
+        _, v2, _ = _compress(rs, qh, *one, T, W, keep, 7, 0.125)
+        torch.testing.assert_close(v2[0, 0], votes[0, h], rtol=1e-5, atol=0.0)
+        first = torch.sort(votes[0, h], descending=True, stable=True).indices[:keep].sort().values
+        assert torch.equal(idx[0, h].long(), first)
+        rows = torch.cat([first, torch.arange(T - W, T, device="cuda")])
+        assert torch.equal(k_out[0, h], kc[0, h, rows])
