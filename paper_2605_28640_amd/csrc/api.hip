@@ -163,7 +163,6 @@ static void knobs_read()
     k.gate_shared = env_or_unset("RATSPARSE_GATE_SHARED");
     k.prefill_masked = env_or_unset("RATSPARSE_PREFILL_MASKED");
     k.prefill_sub = env_or_unset("RATSPARSE_PREFILL_SUB");
-    k.prefill_grid = env_or_unset("RATSPARSE_PREFILL_GRID");
     k.snap_one_wg = env_or_unset("RATSPARSE_SNAP_ONE_WG");
 }
 

@@ -22,7 +22,7 @@ struct Knobs {
     // MoBA gate
     int gate_waves, gate_wgs, gate_shared;
     // prefill attention
-    int prefill_masked, prefill_grid, prefill_sub;
+    int prefill_masked, prefill_sub;
     // SnapKV
     int snap_one_wg;
 };

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void prefill_fill_kernel(const int32_t *__rest
 struct PrefillParams {
     const bf16 *q, *k_cache, *v_cache;
     const int32_t *idx;        // NULL: dense causal
-    const uint32_t *off, *tile_off, *cnt, *list;
+    const uint32_t *tile_off, *list;
     const TileDesc *desc;
     long desc_stride;
     uint16_t *part_o;          // [units][T][K][D] bf16
@@ -877,7 +877,7 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     p.T = T;
     p.Tcap = s->Tcap;
     p.scale = scale;
-    p.off = p.tile_off = p.cnt = p.list = nullptr;
+    p.tile_off = p.list = nullptr;
     p.desc = nullptr;
     p.desc_stride = 0;
     p.part_o = nullptr;
@@ -913,9 +913,7 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
         TileDesc *desc = (TileDesc *)(ws + L.off_desc);
         prefill_scan_kernel<<<(unsigned)units, 256, 0, stream>>>(cnt, off, tile_off, cursor, desc, L.desc_stride, Nb);
         prefill_fill_kernel<<<gr, 256, 0, stream>>>(idx, off, cursor, list, T, block, Nb, K, L.list_stride);
-        p.off = off;
         p.tile_off = tile_off;
-        p.cnt = cnt;
         p.list = list;
         p.desc = desc;
         p.desc_stride = L.desc_stride;

@@ -487,7 +487,7 @@ constexpr int kSharedMaxSplits = 64;
 template <typename ST, int D, int G>
 __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
     const ST *__restrict__ q, const ST *__restrict__ k_cache, const ST *__restrict__ v_cache, const int32_t *idx,
-    ST *__restrict__ out, float *__restrict__ lse_out, uint64_t *partial, int Hkv, long Tcap, int P, long T_valid, int K,
+    ST *__restrict__ out, float *__restrict__ lse_out, uint64_t *partial, long Tcap, int P, long T_valid, int K,
     float scale, int splits, uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit)
 {
     constexpr int LPR = D / 8;
@@ -990,8 +990,8 @@ void decode_attend_shared_dispatch(int dtype, int D, const void *q, const void *
     const int G = Hq / Hkv;
 #define RS_LAUNCH(ST, DD, GG)                                                                                \
     decode_attend_shared_kernel<ST, DD, GG><<<grid, kSharedThreads, 0, stream>>>(                            \
-        (const ST *)q, (const ST *)k_cache, (const ST *)v_cache, idx, (ST *)out, lse_out, partial, Hkv,      \
-        Tcap, P, T_valid, K, scale, splits, unit_ctr, err, tag, spin_limit)
+        (const ST *)q, (const ST *)k_cache, (const ST *)v_cache, idx, (ST *)out, lse_out, partial, Tcap,     \
+        P, T_valid, K, scale, splits, unit_ctr, err, tag, spin_limit)
 #define RS_LAUNCH_G(ST, DD)                     \
     do {                                        \
         if (G == 2) RS_LAUNCH(ST, DD, 2);       \
