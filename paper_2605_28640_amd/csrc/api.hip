@@ -628,11 +628,12 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     // Heads of a KV head that attend the same rows go through them together where fetching the rows per
     // head is what takes the time: when the heads' reads come to 300 MB (200 MB for two heads; 700 MB for eight heads
     // over more than 32 splits, whose partials take long to merge) and the KV heads' splits fill the chip, or when
-    // the splits of a KV head are few enough (8) that merging their partials costs little.  Per head / shared, us,
-    // bfloat16, 128 channels: batch 8, 32 over 8 heads, 1000 rows 24.0 / 13.1, 8000 rows 159 / 67; batch 4
-    // x 32768 183 / 104; batch 1 x 1000 9.4 / 8.3, x 65536 86 / 54, and the other way at 4000 rows 11.2 / 14.3,
-    // at 16416 23.4 / 24.2 and at 200 rows 5.8 / 7.8; batch 1, 16 over 8 heads x 32768 40 / 30.  With the append: 32 over 4
-    // heads x 32768 36 / 42, x 65000 73 / 55, batch 2 x 32768 73 / 50; 16 over 2 heads x 65000 (128 splits in all) 38 / 54.
+    // the splits of a KV head are few enough (8) that merging their partials costs little.  Per head / shared, us of
+    // kernel time, 128 channels, bfloat16 but for the last: 32 over 8 heads, batch 8, 1000 rows 22.7 / 13.9, 8000 rows
+    // 153 / 67; batch 4 x 32768 186 / 106; batch 1 x 1000 9.4 / 8.8, x 32768 47 / 36, x 65536 89 / 56, and the other way at
+    // 200 rows 5.7 / 8.0, 2000 9.0 / 11.9, 4000 11.0 / 15.7, 16416 22.6 / 24.7; 16 over 8 heads x 32768 36 / 30; 32 over 4
+    // x 32768 36 / 42, x 65536 74 / 58, batch 2 x 32768 72 / 51; 16 over 2 heads x 65536 (128 splits in all) 40 / 54;
+    // float32, 32 over 8 x 32768 90 / 61.
     if (s->Hq > s->Hkv && (group || !use_idx)) {
         const int G = s->Hq / s->Hkv;
         const long kv_units = (long)s->B * s->Hkv;

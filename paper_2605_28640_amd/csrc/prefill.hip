@@ -18,18 +18,20 @@
 // at a time between the current tile's matrix instructions, one barrier per step that waits for
 // the next tile only.  Tiles are unpadded; an XOR permutation of the 16-byte chunks of each row
 // keeps both operand reads conflict-free.
-// What bounds it: the causal form holds the matrix units 65 % busy and is then limited by power (the
-// clock falls from 1.67 to 1.54 GHz against the 59 % of two waves per SIMD); the routed forms wait
-// for memory and for the fixed parts of a tile.  Hence 168 registers (steps of 32 keys, 48 KB of
+// What bounds it: the causal form holds the matrix units 73 % busy and is then limited by power (the
+// clock falls to 1.54 GHz, from 1.69 at the 60 % of two waves per SIMD); the routed forms wait
+// for memory and for the fixed parts of a tile (matrix units 46, 16 and 48 % busy in listed tiles, own-block
+// tiles and by bit sets; 37, 15 and 39 % with two waves).  Hence 168 registers (steps of 32 keys, 48 KB of
 // LDS) and three workgroups per CU instead of 64-key steps with two, every kind of tile as its own
-// instantiation with nothing spilled in its loop, and causal tiles launched heaviest first over all
-// heads of an XCD (head by head, the last head's long tiles started late and the chip drained for a
-// quarter of the launch).  Before / after: causal, 32 over 8 heads, 16001 tokens 1.86 / 1.71 ms;
-// bit sets, 2 x 32 heads x 4001, blocks of 64, top-8 0.285 / 0.24 ms; regrouped, 32 heads x 32768,
-// blocks of 512, top-3 1.19 / 1.09 ms (listed tiles 0.78 / 0.69).
+// instantiation with nothing spilled in its loop, and causal tiles launched heaviest first over a
+// group of heads per XCD (head by head, the last head's long tiles started late and the chip drained for a
+// quarter of the launch).  Before / after, in a kernel trace: causal, 32 over 8 heads, 16001 tokens 2.00 / 1.82 ms
+// (1.85 / 1.72 back to back); bit sets, 2 x 32 heads x 4001, blocks of 64, top-8 0.34 / 0.295 ms; regrouped, 32 heads
+// x 32768, blocks of 512, top-3 1.20 / 1.12 ms (listed tiles 0.69, own-block tiles 0.43).
 // The softmax runs in the base-2 domain (one FMA + one v_exp_f32 per score), moves its
 // reference point (and rescales the accumulators) only when a row maximum has grown by more
-// than 2^8, and masks only on steps a boundary crosses.  Partials are kept as bfloat16 o
+// than 2^8 (in the causal form: when a lane's weights of a step add up to more than 2^8 each), and masks only on
+// steps a boundary crosses.  Partials are kept as bfloat16 o
 // (float32 log-sum-exp).  Output rows and partial records pass through LDS on their way out
 // and in, so that global memory sees whole 2 D-byte rows.
 #include <cstdlib>
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("s_barrier" ::: "memory");
 
-    // One step: keys 32 it .. 32 it + 31 from ring slot BUF; with NEXT, the tile two steps ahead is
+    // One step: keys kKT it .. kKT it + kKT - 1 from ring slot BUF; with NEXT, the tile two steps ahead is
     // staged into the slot the previous step has left, one load at a time between the matrix
     // instructions (a wave that issues its loads in one burst stalls until the CU's vector memory
     // path has taken them).
@@ -506,8 +508,8 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 return sum;
             };
             // the reference point of the exponentials follows the running maximum lazily: it moves
-            // only when the maximum has grown by more than kLazy (p then stays below 2^kLazy,
-            // harmless in float32 and bfloat16), so the accumulators are rarely rescaled
+            // only when the maximum has grown by more than kLazy (p then stays below 2^kLazy, or below
+            // kLarge * SUB where a step did without the maximum: harmless in float32 and bfloat16), so the accumulators are rarely rescaled
             // (-inf -> finite counts as a move; -inf -> -inf compares false)
             auto weights_by_maximum = [&]() __attribute__((always_inline)) -> float {
                 float mx = sacc[0][0];
@@ -800,9 +802,10 @@ __global__ void prefill_zero_kernel(uint32_t *p, long n)
 }
 
 // causal tiles: steps of 64 keys while the launch leaves the chip idle (kSmallLaunch row tiles at most), else of 32.
-// Steps of 64 / 32 keys (and the two-wave kernel of 64-key steps this one replaced), us: 8 heads x 2000 36 / 47 (41),
-// x 4000 68 / 87 (77), 32 over 8 x 500 15.2 / 17.1 (15.8), x 1000 25.6 / 29.6 (26.0), x 2000 54 / 56 (59), 2 x 8 x 535
-// 14.9 / 16.7 (14.5), by bit sets 8 heads x 4000 84 / 113 (80); 768 tiles: 32 over 8 heads x 300, batch 8, 33 / 20 (25)
+// Steps of 64 / 32 keys, us in a kernel trace (in brackets the two-wave kernel of 64-key steps that this one replaced,
+// measured apart): 8 heads x 2000 33 / 49 (41), x 4000 64 / 92 (77), 32 over 8 x 500 13.9 / 17.3 (15.8), x 1000
+// 23.2 / 30.1 (26.0), x 2000 49 / 57 (59), 2 x 8 x 535 13.5 / 17.1 (14.5), by bit sets 8 heads x 4000 78 / 112 (80);
+// 768 tiles: 32 over 8 heads x 300, batch 8, 29 / 19 (25)
 constexpr unsigned kSmallLaunch = 512;
 template <int D, PrefillForm FORM>
 static void prefill_causal_launch(const PrefillParams &p, dim3 grid, hipStream_t stream)

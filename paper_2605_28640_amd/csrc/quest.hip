@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
 // the next step's on their way while it works on the current ones; the softmax moves its reference
 // point once per step and head.
 // Bound by memory from about a hundred megabytes on (8 x 32 over 8 heads x 8000 rows: 268 MB in 67 us against
-// 159 us with a workgroup per head, which took every row four times through the CUs at 40 bytes per ns
+// 153 us with a workgroup per head, which took every row four times through the CUs at 40 bytes per ns
 // each), by the merge below that.
 // ------------------------------------------------------------------------------------
 constexpr int kSharedThreads = 512;

@@ -603,8 +603,11 @@ __global__ void snapkv_gather_kernel(const ST *__restrict__ k_cache, const ST *_
 // Short prefixes (at most kSnapOneWgKeys positions per head): pooling, the top-K_keep selection
 // and the ascending output in one launch, one 1024-thread workgroup per (batch, KV head) with
 // the order-preserving keys of the pooled votes in LDS (the selection the decode kernels use:
-// keys above the K-th, then equal ones by lowest position).  At these sizes the seven launches
-// of the spread-out selection below cost more than the work in them.
+// keys above the K-th, then equal ones by lowest position).  At these sizes the five launches
+// of the spread-out selection above cost more than the work in them.  The whole compression, one workgroup
+// a head / spread out, us: 8 heads x 4096 31 / 44, x 8000 41 / 46, x 12000 54 / 51, x 15360 66 / 54; 8 x 32 heads
+// x 4096 154 / 167, x 15360 533 / 560.  (The line is where the keys still fit beside the selection's own LDS; few heads
+// would gain from one at about 10000.)
 constexpr int kSnapOneWgKeys = 15360;  // 60 KiB of keys
 constexpr int kSnapOneWgThreads = 1024;
 
