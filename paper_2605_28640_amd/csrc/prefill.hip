@@ -801,16 +801,26 @@ __global__ void prefill_zero_kernel(uint32_t *p, long n)
     if (i < n) p[i] = 0u;
 }
 
-// causal tiles: steps of 64 keys while the launch leaves the chip idle (kSmallLaunch row tiles at most), else of 32.
-// Steps of 64 / 32 keys, us in a kernel trace (in brackets the two-wave kernel of 64-key steps that this one replaced,
-// measured apart): 8 heads x 2000 33 / 49 (41), x 4000 64 / 92 (77), 32 over 8 x 500 13.9 / 17.3 (15.8), x 1000
-// 23.2 / 30.1 (26.0), x 2000 49 / 57 (59), 2 x 8 x 535 13.5 / 17.1 (14.5), by bit sets 8 heads x 4000 78 / 112 (80);
-// 768 tiles: 32 over 8 heads x 300, batch 8, 29 / 19 (25)
-constexpr unsigned kSmallLaunch = 512;
+// Causal tiles: steps of 64 keys while the launch leaves the chip idle, else of 32.  At 64 channels up to 512 tiles.  At
+// 128 channels a 64-key workgroup has a CU's LDS to itself: up to 256 tiles, one a CU; above that the lightest tiles wait
+// for a second turn, which pays as long as turn and fixed cost of a tile fit beside the heaviest tile: few such tiles, or long
+// heads (up to a share of (n - 3) / 6 of 256 more tiles at n tiles a head, 512 at most).
+// Steps of 64 / 32 keys, us in a kernel trace (in brackets the two-wave kernel of 64-key steps that this one replaced):
+// 8 heads x 2000 33 / 49 (41), x 4000 64 / 92 (77), x 8000 158 / 194 (173), 32 over 8 x 500 13.9 / 17.3 (15.8), x 1000
+// 23.2 / 30.1 (26.0), x 1300 28.6 / 37.2 (37.9), x 2000 49 / 57 (59), batch 2 x 600 19.3 / 21.7 (21.6), x 700 23.7 / 24.4 (22.6),
+// 2 x 8 x 535 13.5 / 17.1 (14.5), by bit sets 8 heads x 4000 78 / 112 (80); the other way 32 over 8 heads batch 2 x 900
+// 31.4 / 30.5 (31.0), batch 3 x 390 20.9 / 17.5 (18.2), x 640 25.7 / 24.8 (23.1), batch 4 x 390 23.1 / 18.5 (19.0), batch 8 x 200
+// 19.0 / 14.6 (16.1), x 300 (768 tiles) 29 / 19 (25).  64 channels: batch 3 x 390 10.8 / 11.4 (13.0), 2000 30 / 34 (43), the
+// other way batch 6 x 390 (768 tiles) 17.9 / 14.7 (21.2).
+static bool prefill_small_launch(int D, long n, long tiles)
+{
+    if (D == 64) return tiles <= 512;
+    return tiles <= 256 || (tiles <= 512 && 6 * (tiles - 256) <= (n - 3) * 256);
+}
 template <int D, PrefillForm FORM>
 static void prefill_causal_launch(const PrefillParams &p, dim3 grid, hipStream_t stream)
 {
-    const int sub = knob_or(knobs().prefill_sub, grid.x * grid.y <= kSmallLaunch ? 2 : 1);
+    const int sub = knob_or(knobs().prefill_sub, prefill_small_launch(D, grid.x, (long)grid.x * grid.y) ? 2 : 1);
     if (sub == 2) prefill_attn_kernel<D, FORM, 2><<<grid, 256, 0, stream>>>(p);
     else prefill_attn_kernel<D, FORM, 1><<<grid, 256, 0, stream>>>(p);
 }
