@@ -817,12 +817,22 @@ static bool prefill_small_launch(int D, long n, long tiles)
     if (D == 64) return tiles <= 512;
     return tiles <= 256 || (tiles <= 512 && 6 * (tiles - 256) <= (n - 3) * 256);
 }
+// 32-key workgroups of 128 channels come three to a CU.  From 513 to 768 tiles some CUs would hold three heavy ones and others
+// two: with more LDS asked for than used only two fit, and the lightest tiles fill the second turn.  Two / three a CU, us in a
+// kernel trace: 8 heads x 12000 317 / 335, 16 x 6000 172 / 177, 32 over 8 x 2200 63.5 / 64.4, by bit sets 3 x 16 heads x 1500
+// 53.4 / 54.7, 32 x 2500 84 / 86 (the two-wave kernel of 64-key steps: 321, 172, 61.8, 51.3, 77); the other way where heads are
+// short, batch 5 x 500 27 / 23, and from more tiles on, 32 x 4000 (1024) 142 / 134.
+static unsigned prefill_spare_lds(int D, long n, long tiles)
+{
+    return D == 128 && n >= 9 && tiles > 512 && tiles <= 768 ? 24 * 1024 : 0;
+}
+
 template <int D, PrefillForm FORM>
 static void prefill_causal_launch(const PrefillParams &p, dim3 grid, hipStream_t stream)
 {
     const int sub = knob_or(knobs().prefill_sub, prefill_small_launch(D, grid.x, (long)grid.x * grid.y) ? 2 : 1);
     if (sub == 2) prefill_attn_kernel<D, FORM, 2><<<grid, 256, 0, stream>>>(p);
-    else prefill_attn_kernel<D, FORM, 1><<<grid, 256, 0, stream>>>(p);
+    else prefill_attn_kernel<D, FORM, 1><<<grid, 256, prefill_spare_lds(D, grid.x, (long)grid.x * grid.y), stream>>>(p);
 }
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
