@@ -284,20 +284,10 @@ __device__ __forceinline__ LdsSource lds_source(const void *base)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0x7fffffff, 0x00020000);
 }
-// STREAM: as a non-temporal load, for rows that the caches would not hold until they are needed again
-template <bool STREAM = false>
 __device__ __forceinline__ void load16_to_lds(LdsSource src, uint32_t byte_offset, void *l)
 {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)l, 16, (int)byte_offset, 0, 0,
-                                             STREAM ? 2 : 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)l, 16, (int)byte_offset, 0, 0, 0);
 }
-// A sweep over this many bytes of keys or more reads them with streaming loads.  Cached loads of cold
-// memory run at 4.0 TB/s here and streaming ones at 5.0-5.6, but what a first sweep leaves in the
-// memory-side cache speeds up a second one.  Both sweeps of the SnapKV votes together, cached /
-// streaming: 268 MB of keys 122 / 115 us (8 heads x 128K), 121 / 105 us (8 x 32 heads x 4096); 201 MB
-// 92 / 89 us; 134 MB 68 / 66 and 67 / 62 us; 34 MB 28 / 29 us.  MoBA block means: 268 MB 60 / 47 us,
-// 34 MB 10.4 / 10.7 us.
-constexpr long kStreamBytes = 100l << 20;
 // the same with a descriptor that covers `bytes` bytes (lanes past them read zeros) and a
 // wave-uniform offset beside the lane's own
 __device__ __forceinline__ LdsSource lds_source_sized(const void *base, int bytes)

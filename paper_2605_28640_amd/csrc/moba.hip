@@ -9,7 +9,9 @@ namespace rs {
 // ------------------------------------------------------------------------------------
 // block means: one workgroup per (block, batch*KV head); float32 accumulation
 // ------------------------------------------------------------------------------------
-// Bound by memory: eight rows per lane are on their way at a time; STREAM: as streaming loads (kStreamBytes).
+// Bound by memory: eight rows per lane are on their way at a time; STREAM: as streaming loads, for keys that no cache
+// would hold until the attention comes for them (268 MB 60 -> 47 us, 34 MB 10.4 -> 10.7).
+constexpr long kStreamBytes = 100l << 20;
 template <typename ST, int D, bool STREAM>
 __global__ __launch_bounds__(256) void moba_block_means_kernel(const ST *__restrict__ k_cache,
                                                                float *__restrict__ means, uint16_t *__restrict__ split,

@@ -26,8 +26,11 @@ constexpr int kSnapKT = 128;          // keys per step: four 32-key sub-tiles
 // (unpadded rows, 16-byte chunks permuted by chunk_swizzle); the next tile's loads are issued
 // between the current tile's matrix instructions.  Pass i of a tile: a lane fetches 16 bytes
 // of row RPI i + srow; rows past the end of the keys repeat the last valid row (finite data,
-// masked or never stored).
-template <int D, bool STREAM>
+// masked or never stored).  Ordinary loads: streaming ones make the sweeps themselves faster from 100 MB of keys on (8
+// heads x 128K 122 -> 115 us), but leave nothing in the memory-side cache for the second sweep and the gather.  The whole
+// compression, ordinary / streaming, us: 4 x 8 heads x 13070 to 1/4 107.5 / 113.3, 8 heads x 52000 100 / 106, x 97492 150 / 156,
+// 8 x 32 heads x 2000 103 / 111, 8 heads x 128K 192.5 / 192.8; the other way 8 x 32 heads x 2000 to 1/16 84.6 / 82.4.
+template <int D>
 struct SnapStage {
     static constexpr int CR = D / 8;          // 16-byte chunks per row
     static constexpr int RW = 64 / CR;        // rows one wave-wide load covers
@@ -45,20 +48,20 @@ struct SnapStage {
     __device__ __forceinline__ void pass(const bf16 *kt, uint16_t *tile, int i, int rem) const
     {
         const int r = (i * RPI + srow < rem) ? i * RPI + srow : rem - 1;
-        load16_to_lds<STREAM>(lds_source(kt), (uint32_t)(r * D + gchunk * 8) * 2u, tile + (i * RPI + wave * RW) * D);
+        load16_to_lds(lds_source(kt), (uint32_t)(r * D + gchunk * 8) * 2u, tile + (i * RPI + wave * RW) * D);
     }
 };
 
 // sweep 1: partial softmax statistics (max, sum) per (query row, key chunk).  S^T = K Q^T: a
 // lane owns one query row (a column of S^T), so its max and sum are in-lane reductions plus
 // one cross-half shuffle.  Wave w holds rows 32 w .. 32 w + 31 of the 128-row tile.
-template <int D, bool STREAM>
+template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_stats_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, float *__restrict__ stats, int Hq, int Hkv, long T,
     long Tcap, int W, int n_chunks, float scale, int keys_per_wg)
 {
     constexpr int NC = D / 16;
-    using Stage = SnapStage<D, STREAM>;
+    using Stage = SnapStage<D>;
     __shared__ __attribute__((aligned(1024))) uint16_t sK0[kSnapKT * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sK1[kSnapKT * D];
 
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // sub-tile w of every 128-key step against all (up to 128) query rows of the row tile, so a
 // key's vote is an in-lane sum plus one cross-half shuffle and is written straight out.  Only
 // prefix keys (< L) are stored, and every window query sees all of them: no mask is needed.
-template <int D, bool STREAM>
+template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_votes_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, const float *__restrict__ lse,
     float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (long z = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; z < n_hist; z += (long)gridDim.x * gridDim.y * 256)
         sel_hist[z] = 0u;
     constexpr int NC = D / 16;
-    using Stage = SnapStage<D, STREAM>;
+    using Stage = SnapStage<D>;
     __shared__ __attribute__((aligned(1024))) uint16_t sK0[kSnapKT * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sK1[kSnapKT * D];
 
@@ -685,21 +688,15 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     float *pooled = votes_out ? votes_out : (float *)(ws + Ly.off_pooled);
     const dim3 grid((unsigned)Ly.n_chunks, (unsigned)BK);
     const bf16 *qw = (const bf16 *)q_win, *kc = (const bf16 *)k_cache;
-    const bool big = BK * T * s->D * 2 >= kStreamBytes && Ly.R <= 128;  // (more query rows: a workgroup walks over its keys again)
     // the rows' log-sum-exp over all visible keys: handed in by the caller (the prefill attention of
     // the window rows has it), or from a first sweep over the keys
     if (lse_in) {
         lse = const_cast<float *>(lse_in);  // [B, Hq, W] is [B * Hkv][G * W]: only read
     } else {
-#define RS_STATS(DD, SS) \
-    snapkv_stats_kernel<DD, SS><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
-        if (s->D == 128) {
-            if (big) RS_STATS(128, true);
-            else RS_STATS(128, false);
-        } else {
-            if (big) RS_STATS(64, true);
-            else RS_STATS(64, false);
-        }
+#define RS_STATS(DD) \
+    snapkv_stats_kernel<DD><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
+        if (s->D == 128) RS_STATS(128);
+        else RS_STATS(64);
 #undef RS_STATS
         const long rows_total = BK * Ly.R;
         snapkv_lse_kernel<<<(unsigned)((rows_total + 3) / 4), 256, 0, stream>>>(stats, lse, Ly.R, Ly.n_chunks, rows_total);
@@ -709,15 +706,10 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     const bool one_wg = L <= kSnapOneWgKeys && knobs().snap_one_wg != 0;  // (knob 0: the spread-out selection at any length)
     uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
     const long n_hist = one_wg ? 0 : BK * 1024;
-#define RS_VOTES(DD, SS) \
-    snapkv_votes_kernel<DD, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
-    if (s->D == 128) {
-        if (big) RS_VOTES(128, true);
-        else RS_VOTES(128, false);
-    } else {
-        if (big) RS_VOTES(64, true);
-        else RS_VOTES(64, false);
-    }
+#define RS_VOTES(DD) \
+    snapkv_votes_kernel<DD><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
+    if (s->D == 128) RS_VOTES(128);
+    else RS_VOTES(64);
 #undef RS_VOTES
     if (one_wg) {
         snapkv_pool_select_kernel<<<(unsigned)BK, kSnapOneWgThreads, (size_t)L * 4, stream>>>(
