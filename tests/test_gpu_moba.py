@@ -344,3 +344,32 @@ def test_tile_order_over_many_heads(rs, knobs, heads):
         for lo in range(0, heads, 5):
             few, few_lse = run(lo, min(lo + 5, heads), lists)
             assert torch.equal(out[:, lo:lo + 5], few) and torch.equal(lse[:, lo:lo + 5], few_lse), lo
+
+
+@pytest.mark.parametrize("T,units", [(1100, 28), (1100, 29), (1100, 56), (1100, 57), (1100, 85), (1100, 86), (390, 64), (390, 65), (390, 128)])
+def test_launches_around_the_lines_between_the_step_widths(rs, knobs, T, units):
+    """Which step width a causal launch takes, and how many workgroups share a CU, depends on its tiles in all and per head:
+    on either side of each line (one tile a CU, two turns, two workgroups a CU, three) the launch gives the bits of one of
+    the two widths forced, and both forced widths agree with each other as far as bfloat16 weights let them."""
+    D, block, K = 128, 64, 4
+    gen = torch.Generator(device="cuda").manual_seed(T + units)
+    q, k, v = (torch.randn(1, units, T, D, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    t = torch.arange(T, device="cuda")[:, None] // block
+    idx = torch.sort(torch.where(torch.arange(K, device="cuda") <= t, t - torch.arange(K, device="cuda"), -1), dim=1).values
+    idx = idx.to(torch.int32).expand(1, units, T, K).contiguous()
+    s = rs.make_shape(1, units, units, D, T, 16, torch.bfloat16)
+    ws = rs.Workspace(rs.sparse_attn_prefill_workspace_bytes(s, T, block, K))
+    knobs.setenv("RATSPARSE_PREFILL_MASKED", "1")
+    for lists in (None, idx):
+        got = {}
+        for sub in (None, "1", "2"):
+            knobs.delenv("RATSPARSE_PREFILL_SUB") if sub is None else knobs.setenv("RATSPARSE_PREFILL_SUB", sub)
+            out = torch.full((1, units, T, D), 7.0, dtype=torch.bfloat16, device="cuda")
+            lse = torch.full((1, units, T), 7.0, device="cuda")
+            rs.sparse_attn_prefill(s, q, k, v, T, block, D ** -0.5, lists, K, out, lse, ws)
+            got[sub] = (out, lse)
+        assert any(torch.equal(got[None][0], got[x][0]) and torch.equal(got[None][1], got[x][1]) for x in ("1", "2"))
+        ok, worst = attn_close(to_np(got["1"][0]), to_np(got["2"][0]))  # two roundings of the weights: within the 2e-2 of the others
+        assert ok, worst
+        torch.testing.assert_close(got["1"][1], got["2"][1], rtol=1e-5, atol=1e-5)  # 32-bit sums
+    ws.async_status()
