@@ -24,6 +24,7 @@
 // the chunks may be laid out from a chunk boundary before the run, so that a run that starts anywhere
 // leaves its pages' bounds too (8 heads x 3001 tokens from 5003: 19.6 -> 16.1 us, one launch for two).
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 #include "knobs.h"
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const ST *__restrict__ k, const ST *__restrict__ v, const float *__restrict__ g,
     float *__restrict__ state_k, float *__restrict__ state_v, ST *__restrict__ k_cache,
     ST *__restrict__ v_cache, int BH, long T_new, long t0, long Tcap, int n_chunks,
-    uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit, ST *__restrict__ meta, int deep, int lead_arg)
+    uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit, ST *__restrict__ meta, int lead_arg)
 {
     const int lead = LEAD ? lead_arg : 0;
     const int rec_chunks = LEAD ? n_chunks - 1 : n_chunks;  // records per unit (a lead may add a chunk, the last one leaves none)
@@ -69,16 +70,17 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const int rg = lane / LPR;
     const int c0 = (lane % LPR) * 8;
 
-    // deep (many units, so every chain has slack): the waves that do not handle the chain send the next
-    // chunk's loads out before the current chunk is touched, and the ticket after next is drawn a chunk
-    // ahead; otherwise all loads of the next chunk go out behind the chain step.
     // Persistent workgroups: each keeps taking the next chunk (by ticket) until none is left.  The raw
-    // inputs of a chunk live in registers from its loads to its replay; there are two such register sets,
-    // and the loads of the NEXT ticket are issued before the current chunk is folded, chained and stored,
-    // so that a workgroup always has a chunk's worth of reads in flight (one workgroup fills a CU: without
-    // this its memory pipe idles through every fold, chain wait and replay).  The prefetched ticket is
+    // inputs of a chunk live in registers from its loads to its replay; with whole rows there are two such register
+    // sets, and the loads of the NEXT ticket go out right behind the current chunk's chain step, under its replay
+    // and stores (one workgroup fills a CU).  The prefetched ticket is
     // larger than the one in work and tickets are handed out in increasing order, so the smallest
     // unfinished ticket is always some workgroup's chunk in work: the chain cannot deadlock.
+    // Bound by memory: 4 x 32 heads x 64K (13.2 GB) take 2.73 ms, the same traffic without the arithmetic 2.48.  Waits that
+    // count exactly are what the overlap hangs on: while the sets were copied into each other and loads and stores went
+    // by branches, every chunk's replay waited for the next chunk's loads (us, then / now, 128 channels with bounds in
+    // bfloat16: 4 x 32 heads x 64K 2763 / 2727, 32 x 64K 738 / 717, 4 x 32 x 700 44.9 / 42.9; 4 x 32 x 8000 of 64 channels
+    // 185 / 172; float32, 8 x 32 heads x 500 91 / 83).
     const int units = BH * NS;
     const int total = units * n_chunks;
     // (kept as 32-bit words: the sets are carried around the chunk loop, and this compiler's back end
@@ -94,36 +96,57 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         __syncthreads();
         return s_ticket;
     };
+    // Whole rows (DS == D) move by buffer instructions, their descriptors based at the chunk's first row and sized to its
+    // rows: what lies past the run reads as zeros and is dropped on the way out, so that nothing branches between a
+    // chunk's loads and the fold that waits for them, and the wait can count exactly.
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kStream = 2;  // the instructions' bits for streaming access
+    const uint32_t lane_el = (uint32_t)((wave * RPW + rg) * NT * D + c0);  // the lane's first channel in a whole-row chunk
+    auto rows_of = [&](auto *p, long row0, int rows) __attribute__((always_inline)) {
+        return lds_source_sized(p + row0 * D, rows * D * (int)sizeof(*p));
+    };
     auto load_chunk = [&](int ticket, ChunkRegs &r) __attribute__((always_inline)) {
         const int j = ticket / units;
         const int unit = ticket % units;
         const int bh = unit / NS;
         const int ch0 = (unit % NS) * DS;
-        const long tbase = (long)j * CHUNK + (long)(wave * RPW + rg) * NT - lead;
         const long in_row0 = (long)bh * T_new;
+        if constexpr (DS == D) {
+            const long first = (long)j * CHUNK;
+            const int rows = (int)((T_new - first < CHUNK) ? T_new - first : CHUNK);
+            const auto kd = rows_of(k, in_row0 + first, rows), vd = rows_of(v, in_row0 + first, rows);
+            const auto gd = rows_of(g, in_row0 + first, rows);
+            uint32_t el = lane_el;
+            asm volatile("" : "+v"(el));  // (worked out here: the constants below then become the instructions' own offsets)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                auto fetch = [&](const LdsSource &d, uint32_t byte, auto *w) __attribute__((always_inline)) {
+                    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(d, byte, 0, kStream);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) w[c] = __builtin_bit_cast(std::remove_reference_t<decltype(w[0])>, (uint32_t)x[c]);
+                };
+#pragma unroll
+                for (int c = 0; c < KW; c += 4) fetch(kd, el * (uint32_t)sizeof(ST) + i * D * (int)sizeof(ST) + 4 * c, r.kw[i] + c);
+#pragma unroll
+                for (int c = 0; c < KW; c += 4) fetch(vd, el * (uint32_t)sizeof(ST) + i * D * (int)sizeof(ST) + 4 * c, r.vw[i] + c);
+#pragma unroll
+                for (int c = 0; c < 8; c += 4) fetch(gd, el * 4u + i * D * 4 + 4 * c, r.gw[i] + c);
+            }
+            return;
+        }
+        const long tbase = (long)j * CHUNK + (long)(wave * RPW + rg) * NT - lead;
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             const long t = tbase + i;
             typename R::raw_t kq = R::zero_raw(), vq = R::zero_raw();
             float4 ga = make_float4(1.f, 1.f, 1.f, 1.f), gb = ga;  // outside the run: the identity element (g = 1 keeps the state)
             if ((!LEAD || t >= 0) && t < T_new) {
+                // (a slab shares its cache lines with the other slabs of the row, which come by other workgroups: cached loads)
                 const long off = (in_row0 + t) * D + ch0 + c0;
-                if constexpr (DS == D) {
-                    // whole rows, read once: streaming loads (a slab shares its cache lines with the
-                    // other slabs of the row, which come by other workgroups: those stay cached loads)
-                    kq = R::load_raw_nt(k + off);
-                    vq = R::load_raw_nt(v + off);
-                    typedef float f32x4 __attribute__((ext_vector_type(4)));
-                    const f32x4 xa = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(g + off));
-                    const f32x4 xb = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(g + off + 4));
-                    ga = make_float4(xa.x, xa.y, xa.z, xa.w);
-                    gb = make_float4(xb.x, xb.y, xb.z, xb.w);
-                } else {
-                    kq = R::load_raw(k + off);
-                    vq = R::load_raw(v + off);
-                    ga = *reinterpret_cast<const float4 *>(g + off);
-                    gb = *reinterpret_cast<const float4 *>(g + off + 4);
-                }
+                kq = R::load_raw(k + off);
+                vq = R::load_raw(v + off);
+                ga = *reinterpret_cast<const float4 *>(g + off);
+                gb = *reinterpret_cast<const float4 *>(g + off + 4);
             }
             __builtin_memcpy(r.kw[i], &kq, sizeof(kq));
             __builtin_memcpy(r.vw[i], &vq, sizeof(vq));
@@ -131,11 +154,15 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             r.gw[i][4] = gb.x; r.gw[i][5] = gb.y; r.gw[i][6] = gb.z; r.gw[i][7] = gb.w;
         }
     };
-    // nt / nr: the next ticket and its register set (nt >= total: none).  The waves that handle the chain
-    // (threads below DS) issue their share of the next chunk's loads only after the chain step: a wave's
-    // loads return in order, so its polls of the predecessor's record would otherwise wait behind them.
-    constexpr int kChainWaves = (DS + 63) / 64;
-    auto process_chunk = [&](int ticket, ChunkRegs &r, int nt, ChunkRegs &nr) __attribute__((always_inline)) {
+    // nr: the register set of the next chunk; returns its ticket (>= total: none)
+    constexpr int kTicketThread = NW * 64 - 64;  // whole rows: who draws (a wave that does not handle the chain)
+    int drawn = total;                           // ... and what it drew last
+    auto draw = [&]() __attribute__((always_inline)) -> int {
+        int at = kCtrlTicket;
+        asm volatile("" : "+v"(at));  // (not known to be one address for all lanes: else the result is waited for at once)
+        return (int)atomicAdd(&ctrl[at], 1u);
+    };
+    auto process_chunk = [&](int ticket, ChunkRegs &r, ChunkRegs &nr) __attribute__((always_inline)) -> int {
     const int j = ticket / units;   // chunk index along T
     const int unit = ticket % units;  // consecutive tickets walk the units first
     const int bh = unit / NS;
@@ -150,21 +177,24 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         g0[i] = make_float4(r.gw[i][0], r.gw[i][1], r.gw[i][2], r.gw[i][3]);
         g1[i] = make_float4(r.gw[i][4], r.gw[i][5], r.gw[i][6], r.gw[i][7]);
     }
-
-    // the ticket after next is drawn now and parked in LDS at the first barrier: its round trip runs
-    // under the fold (full-row form; the slab form draws its tickets one at a time)
-    int ticket_ahead = 0;
     if constexpr (DS == D) {
-        if (deep && tid == 0) ticket_ahead = (int)atomicAdd(&ctrl[kCtrlTicket], 1u);
+        if (j == n_chunks - 1 && T_new % CHUNK != 0) {  // past the run: the identity element (g = 1 keeps the state; x is 0)
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+                if (tbase + i >= T_new) g0[i] = g1[i] = make_float4(1.f, 1.f, 1.f, 1.f);
+        }
     }
 
-    // first look at the previous chunk's outgoing state, issued behind the data loads so that
-    // its round trip overlaps the fold; the wait below re-polls only if it was not there yet
+    // slabs: a first look at the previous chunk's outgoing state, issued behind the data loads so that its round trip
+    // overlaps the fold; the wait below re-polls only if it was not there yet.  (Whole rows do without: registers that may
+    // still be waiting for it would hold up every wave's next use of them until the next chunk's loads have landed.)
     uint64_t early0 = 0, early1 = 0;
-    if (tid < DS && j > 0) {
-        const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + tid;
-        early0 = load_u64_agent(p);
-        early1 = load_u64_agent(p + DS);
+    if constexpr (DS < D) {
+        if (tid < DS && j > 0) {
+            const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + tid;
+            early0 = load_u64_agent(p);
+            early1 = load_u64_agent(p + DS);
+        }
     }
 
     // fold own tokens: state -> a * state + b
@@ -187,6 +217,11 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             a[c] *= gg[c];
             bk[c] = fmaf(gg[c], bk[c], om * kx[c]);
             bv[c] = fmaf(gg[c], bv[c], om * vx[c]);
+        }
+        // (token by token: unpacked all at once they do not fit the registers)
+        if constexpr (DS == D) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(a[c]), "+v"(bk[c]), "+v"(bv[c]));
         }
     }
 
@@ -263,9 +298,11 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     }
     }
     if constexpr (DS == D) {
-        if (deep && tid == 0) s_ticket = ticket_ahead;
+        if (tid == kTicketThread) s_ticket = drawn;
     }
     __syncthreads();
+    int nt = total;
+    if constexpr (DS == D) nt = __builtin_amdgcn_readfirstlane(s_ticket);
 
     if (tid < DS) {
         const int c = tid;
@@ -285,6 +322,10 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + c;
             uint64_t w0 = early0, w1 = early1;
             int spins = 0;
+            if constexpr (DS == D) {
+                w0 = load_u64_agent(p);
+                w1 = load_u64_agent(p + DS);
+            }
             bool ok = ((uint32_t)(w0 >> 32) == tag) && ((uint32_t)(w1 >> 32) == tag);
             while (!ok) {
                 if (++spins > spin_limit) break;
@@ -317,15 +358,43 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             cv = fmaf(aw, cv, s_agg[w][2][c]);
         }
     }
-    // the next chunk's loads go out here, behind the chain step: a wave's loads return in order, so
-    // issued any earlier they would hold up the chain waves' polls of the predecessor's record
+    // The next chunk's loads go out here, behind the chain step: a wave's loads return in order, so issued any earlier
+    // they would hold up the chain waves' polls of the predecessor's record (the other waves come here at once).  Before them goes
+    // the draw of the ticket after it, which is thus there when those loads are.
     if constexpr (DS == D) {  // (the slab form works on one chunk at a time)
-        if ((wave < kChainWaves || !deep) && nt < total) load_chunk(nt, nr);
+        if (nt < total) {
+            if (tid == kTicketThread) drawn = draw();
+            load_chunk(nt, nr);
+        }
     }
     __syncthreads();
 
     // replay from the incoming state
     float sk[8], sv[8];
+    // a token's inputs as new values to the compiler, which would otherwise keep what the fold made of them (1 - g,
+    // unpacked keys) in registers until the replay; in whole rows one token behind the states of the one before, as all
+    // of them unpacked at once do not fit the registers beside the next chunk's
+    auto fresh_inputs = [&](int i) __attribute__((always_inline)) {
+        uint32_t w[2 * KW + 8];
+        __builtin_memcpy(w, &kr[i], sizeof(kr[i]));
+        __builtin_memcpy(w + KW, &vr[i], sizeof(vr[i]));
+        __builtin_memcpy(w + 2 * KW, &g0[i], 16);
+        __builtin_memcpy(w + 2 * KW + 4, &g1[i], 16);
+        if constexpr (DS == D) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(sk[c]), "+v"(sv[c]));
+        }
+#pragma unroll
+        for (int c = 0; c < 2 * KW + 8; ++c) asm volatile("" : "+v"(w[c]));
+        __builtin_memcpy(&kr[i], w, sizeof(kr[i]));
+        __builtin_memcpy(&vr[i], w + KW, sizeof(vr[i]));
+        __builtin_memcpy(&g0[i], w + 2 * KW, 16);
+        __builtin_memcpy(&g1[i], w + 2 * KW + 4, 16);
+    };
+    if constexpr (DS < D) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) fresh_inputs(i);
+    }
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         sk[c] = fmaf(a[c], s_carry[wave][0][c0 + c], bk[c]);
@@ -353,10 +422,28 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             }
         }
     }
+    const int rows_out = (DS == D) ? (int)((T_new - (long)j * CHUNK < CHUNK) ? T_new - (long)j * CHUNK : CHUNK) : 0;
+    const auto kd_out = rows_of(k_cache, out_row0 + (long)j * CHUNK, rows_out), vd_out = rows_of(v_cache, out_row0 + (long)j * CHUNK, rows_out);
+    uint32_t el_out = lane_el;
+    asm volatile("" : "+v"(el_out));
+    auto store_row = [&](const LdsSource &d, int i, const float (&x)[8]) __attribute__((always_inline)) {  // whole rows
+        const uint32_t byte = el_out * (uint32_t)sizeof(ST) + i * D * (int)sizeof(ST);
+        if constexpr (sizeof(ST) == 2) {
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
+                                                         pack_bf16x2(x[6], x[7])}, d, byte, 0, kStream);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; c += 4)
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(x[c]), __float_as_uint(x[c + 1]), __float_as_uint(x[c + 2]),
+                                                             __float_as_uint(x[c + 3])}, d, byte + 4 * c, 0, kStream);
+        }
+    };
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
         const long t = tbase + i;
-        if ((!LEAD || t >= 0) && t < T_new) {
+        // (whole rows past the run: their states go nowhere, and the bounds below leave them out)
+        if (DS == D || ((!LEAD || t >= 0) && t < T_new)) {
+            if constexpr (DS == D) fresh_inputs(i);
             float kx[8], vx[8];
             R::unpack(kr[i], kx);
             R::unpack(vr[i], vx);
@@ -367,9 +454,14 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                 sk[c] = fmaf(gg[c], sk[c], om * kx[c]);
                 sv[c] = fmaf(gg[c], sv[c], om * vx[c]);
             }
-            const long off = (out_row0 + t) * D + ch0 + c0;
-            R::store_nt(k_cache + off, sk);
-            R::store_nt(v_cache + off, sv);
+            if constexpr (DS == D) {
+                store_row(kd_out, i, sk);
+                store_row(vd_out, i, sv);
+            } else {
+                const long off = (out_row0 + t) * D + ch0 + c0;
+                R::store_nt(k_cache + off, sk);
+                R::store_nt(v_cache + off, sv);
+            }
             if constexpr (META) {
                 float xs[8];  // the values just stored
                 if constexpr (sizeof(ST) == 2) {
@@ -384,10 +476,11 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
 #pragma unroll
                     for (int c = 0; c < 8; ++c) xs[c] = sk[c];
                 }
+                const bool in = DS < D || t < T_new;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    plo[c] = fminf(plo[c], xs[c]);
-                    phi[c] = fmaxf(phi[c], xs[c]);
+                    plo[c] = fminf(plo[c], in ? xs[c] : INFINITY);
+                    phi[c] = fmaxf(phi[c], in ? xs[c] : -INFINITY);
                 }
             }
         }
@@ -403,12 +496,33 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                     plo[c] = fminf(plo[c], shfl_xor_f(plo[c], msk));
                     phi[c] = fmaxf(phi[c], shfl_xor_f(phi[c], msk));
                 }
-            const long tp = (long)j * CHUNK + (long)wave * TW + (long)(rg / RGP) * PAGE - lead;  // the page's first token
-            if (tp < T_new && (!LEAD || tp + PAGE > 0) && rg % RGP < 2) {
-                const long page = (t0 + tp) / PAGE;
-                ST *mrow = meta + (((long)bh * (Tcap / PAGE) + page) * 2) * D + ch0 + c0;
-                if (rg % RGP == 0) R::store(mrow, plo);
-                else R::store(mrow + D, phi);
+            if constexpr (DS == D) {
+                // (a lane without a row of bounds to write aims past the descriptor's end)
+                const long page0 = (t0 + (long)j * CHUNK) / PAGE;
+                const LdsSource md = lds_source_sized(meta + ((long)bh * (Tcap / PAGE) + page0) * 2 * D,
+                                                      (rows_out + PAGE - 1) / PAGE * 2 * D * (int)sizeof(ST));
+                const int row = (wave * TW / PAGE + rg / RGP) * 2 + rg % RGP;
+                const uint32_t byte = (rg % RGP < 2) ? (uint32_t)(row * D + c0) * (uint32_t)sizeof(ST) : 0x40000000u;
+                float x[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[c] = (rg % RGP == 0) ? plo[c] : phi[c];
+                if constexpr (sizeof(ST) == 2) {
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
+                                                                 pack_bf16x2(x[6], x[7])}, md, byte, 0, 0);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 8; c += 4)
+                        __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(x[c]), __float_as_uint(x[c + 1]), __float_as_uint(x[c + 2]),
+                                                                     __float_as_uint(x[c + 3])}, md, byte + 4 * c, 0, 0);
+                }
+            } else {
+                const long tp = (long)j * CHUNK + (long)wave * TW + (long)(rg / RGP) * PAGE - lead;  // the page's first token
+                if (tp < T_new && (!LEAD || tp + PAGE > 0) && rg % RGP < 2) {
+                    const long page = (t0 + tp) / PAGE;
+                    ST *mrow = meta + (((long)bh * (Tcap / PAGE) + page) * 2) * D + ch0 + c0;
+                    if (rg % RGP == 0) R::store(mrow, plo);
+                    else R::store(mrow + D, phi);
+                }
             }
         } else {
             // a page spans WPP waves: each folds all its row groups, their bounds meet in LDS, and
@@ -447,41 +561,31 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         }
     }
 
+    return nt;
     };  // process_chunk
 
-    // (one call site of process_chunk: the register sets change places by moves, which cost nothing next
-    // to a chunk's work and wait for the prefetched loads no earlier than the fold would)
     ChunkRegs A, B;
     int tA = (int)blockIdx.x;  // one chunk per unit: the grid is the units, no tickets
     if (n_chunks > 1) tA = next_ticket();
     if (tA < total) {
-        load_chunk(tA, A);
-        int tB = total;
         if constexpr (DS == D) {
-            if (n_chunks > 1) tB = next_ticket();
-        }
-        for (;;) {
-            if constexpr (DS == D) {
-                // the waves that do not handle the chain send the next chunk's loads ahead of everything
-                if (deep && wave >= kChainWaves && tB < total) load_chunk(tB, B);
-            }
-            process_chunk(tA, A, tB, B);
-            if constexpr (DS == D) {
+            // two register sets in turn, each under its own name: a set that changed its name at the end of a turn would be
+            // copied, and the copies would wait for its loads
+            if (n_chunks > 1 && tid == kTicketThread) drawn = draw();
+            load_chunk(tA, A);
+            for (;;) {
+                const int tB = process_chunk(tA, A, B);
                 if (tB >= total) break;
-                A = B;
-                tA = tB;
-                if (deep) {
-                    __syncthreads();  // s_ticket was parked before the first barrier of process_chunk and is read by all here
-                    tB = s_ticket;
-                    __syncthreads();  // ... before the next chunk's thread 0 parks the following one
-                } else {
-                    tB = next_ticket();
-                }
-            } else {
+                tA = process_chunk(tB, B, A);
+                if (tA >= total) break;
+            }
+        } else {
+            for (;;) {
+                load_chunk(tA, A);
+                (void)process_chunk(tA, A, B);
                 if (n_chunks == 1) break;
                 tA = next_ticket();
                 if (tA >= total) break;
-                load_chunk(tA, A);
             }
         }
     }
@@ -595,7 +699,7 @@ static void launch_scan_form(const void *k, const void *v, const float *g, float
     }
     rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(
         (const ST *)k, (const ST *)v, g, state_k, state_v, (ST *)k_cache, (ST *)v_cache, BH, T_new,
-        t0, Tcap, n_chunks, ctrl, rec, tag, spin_limit, (ST *)meta, (n_chunks > 1 && (long)BH * (D / DS) >= 128) ? 1 : 0, lead);
+        t0, Tcap, n_chunks, ctrl, rec, tag, spin_limit, (ST *)meta, lead);
 }
 
 template <typename ST, int D, int DS, int PAGE_ARG>

@@ -294,6 +294,46 @@ def test_odd_starts_leave_the_page_bounds(rs, dtype, D, P):
                     assert np.array_equal(gm[:, :, p, 0], x.min(2)) and np.array_equal(gm[:, :, p, 1], x.max(2)), (t0, T, p)
 
 
+@pytest.mark.parametrize("dtype,D,P", [("bf16", 128, 16), ("bf16", 128, 64), ("bf16", 64, 256), ("f32", 128, 64), ("f32", 64, 16)])
+def test_whole_rows_end_where_the_run_ends(rs, knobs, dtype, D, P):
+    """Whole-row chunks (128 or 256 tokens in bfloat16, half in float32) that the run fills, misses by one token or begins
+    with one: the states are Eq. 1's, every touched page has the bounds of its stored keys, and neither a row past the
+    run nor a page past its last is written."""
+    knobs.setenv("RATSPARSE_SCAN_SLAB", "0")
+    B, H = 2, 3
+    chunk = {("bf16", 128): 128, ("bf16", 64): 256, ("f32", 128): 64, ("f32", 64): 128}[dtype, D]
+    for t0, T in ((0, 9), (0, chunk), (chunk, chunk - 1), (2 * chunk, chunk + 1), (0, 7 * chunk + P + 1)):
+        say("whole-row scan end", dtype, D, P, t0, T)
+        r = np.random.default_rng(t0 * 31 + T)
+        Tcap = -(-(t0 + T + 2 * P) // P) * P
+        k, v = (r.standard_normal((B, H, T, D)).astype(np.float32) for _ in range(2))
+        if dtype == "bf16":
+            k, v = synth.to_bf16_grid(k), synth.to_bf16_grid(v)
+        g = _gate(r, (B, H, T, D))
+        s0 = r.standard_normal((B, H, D)).astype(np.float32)
+        s = rs.make_shape(B, H, H, D, Tcap, P, tdtype(dtype))
+        ws = rs.Workspace(rs.rat_scan_workspace_bytes(s, T))
+        sk, sv = to_dev(s0), to_dev(s0)
+        kc, vc = (torch.full((B, H, Tcap, D), 7.0, dtype=tdtype(dtype), device="cuda") for _ in range(2))
+        meta = torch.full((B, H, Tcap // P, 2, D), 99.0, dtype=tdtype(dtype), device="cuda")
+        rs.rat_scan(s, to_dev(k, dtype), to_dev(v, dtype), to_dev(g), sk, sv, kc, vc, t0, T, ws, meta)
+        torch.cuda.synchronize()
+        ws.async_status()
+        ko, vo, osk, osv = oracle.rat_scan(k, v, g, s0, s0)
+        assert scan_close(to_np(sk), osk)[0] and scan_close(to_np(sv), osv)[0]
+        gk, gv, gm = to_np(kc), to_np(vc), to_np(meta)
+        ok = (lambda x, y: scan_close(x, y)[0]) if dtype == "f32" else bf16_store_ok
+        assert ok(gk[:, :, t0:t0 + T], ko) and ok(gv[:, :, t0:t0 + T], vo)
+        for got in (gk, gv):
+            assert np.all(got[:, :, :t0] == 7.0) and np.all(got[:, :, t0 + T:] == 7.0)
+        for p in range(Tcap // P):
+            if p * P + P <= t0 or p * P >= t0 + T:
+                assert np.all(gm[:, :, p] == 99.0), (t0, T, p)
+            else:
+                x = gk[:, :, p * P:min((p + 1) * P, t0 + T)]
+                assert np.array_equal(gm[:, :, p, 0], x.min(2)) and np.array_equal(gm[:, :, p, 1], x.max(2)), (t0, T, p)
+
+
 _FIRST_CALLS = """
 import threading
 import torch
