@@ -294,10 +294,11 @@ __device__ __forceinline__ LdsSource lds_source_sized(const void *base, int byte
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
 }
+template <int AUX = 0>  // 2: a streaming load
 __device__ __forceinline__ void load16_to_lds_at(LdsSource src, uint32_t lane_offset, uint32_t offset, void *l)
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void *)l, 16, (int)lane_offset,
-                                             (int)offset, 0, 0);
+                                             (int)offset, 0, AUX);
 }
 
 // Tiles of K/V rows sit in LDS unpadded (a wave-wide load fills whole rows back to back), so the bank

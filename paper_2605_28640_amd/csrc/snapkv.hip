@@ -6,7 +6,7 @@
 //
 // The [G*W x T] score matrix of a KV head is a dense contraction, done on the matrix cores
 // (v_mfma_f32_32x32x16_bf16) in two sweeps over the keys: sweep 1 forms S^T = K Q^T so that
-// a lane owns one query row and gets its softmax max / sum cheaply; sweep 2 forms S = Q K^T
+// a lane owns one query row and gets its softmax statistics cheaply; sweep 2 forms S = Q K^T
 // so that a lane owns one key column and its vote is an in-lane sum over the query rows.
 #include "common.h"
 #include "knobs.h"
@@ -20,52 +20,133 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kSnapKeysPerWg = 2048;  // keys per workgroup, at most (fewer when that leaves the chip idle)
-constexpr int kSnapKT = 128;          // keys per step: four 32-key sub-tiles
+constexpr int kSnapKT = 128;          // a workgroup's share of the keys is a multiple of this
+constexpr int kSnapTile = 32;         // keys of a wave's tile
+constexpr float kSnapLarge = 4096.f;  // 16 x 2^8
 
-// K tiles of 128 keys are double-buffered in LDS and filled by direct global -> LDS loads
-// (unpadded rows, 16-byte chunks permuted by chunk_swizzle); the next tile's loads are issued
-// between the current tile's matrix instructions.  Pass i of a tile: a lane fetches 16 bytes
-// of row RPI i + srow; rows past the end of the keys repeat the last valid row (finite data,
-// masked or never stored).  Ordinary loads: streaming ones make the sweeps themselves faster from 100 MB of keys on (8
-// heads x 128K 122 -> 115 us), but leave nothing in the memory-side cache for the second sweep and the gather.  The whole
-// compression, ordinary / streaming, us: 4 x 8 heads x 13070 to 1/4 107.5 / 113.3, 8 heads x 52000 100 / 106, x 97492 150 / 156,
-// 8 x 32 heads x 2000 103 / 111, 8 heads x 128K 192.5 / 192.8; the other way 8 x 32 heads x 2000 to 1/16 84.6 / 82.4.
+// Both sweeps stream the keys by waves of their own: a wave takes every fourth 32-key tile of the workgroup's keys against
+// all query rows of the row tile (up to 128, as fragments in registers) through two private slots of LDS, filled by
+// direct global -> LDS loads (unpadded rows, 16-byte chunks permuted by chunk_swizzle).  A tile's fragments are read
+// into registers at once, the slot is free again and the loads of the tile after next go out before the first matrix
+// instruction, so that a wave has one to two tiles on their way all the time and waits for nobody but them (rows past
+// the end of the keys read as zeros: finite, masked or never stored).
+// Bound by memory: 268 MB of keys in 44-47 us a sweep with up to 64 rows, 5.7-6.1 TB/s where reads alone reach 6.3-7, 47-51
+// with 128 (before, all four waves worked on one tile of 128 keys and waited together for the next: 57-65 us).  The
+// statistics go by a reference point that rarely moves, which for 128 rows took them from 58 to 51 us.
 template <int D>
 struct SnapStage {
-    static constexpr int CR = D / 8;          // 16-byte chunks per row
-    static constexpr int RW = 64 / CR;        // rows one wave-wide load covers
-    static constexpr int RPI = 4 * RW;        // rows one pass of the four waves covers
-    static constexpr int NP = kSnapKT / RPI;  // passes per tile
-    int srow, gchunk, wave;
+    static constexpr int CR = D / 8;               // 16-byte chunks per row
+    static constexpr int RW = 64 / CR;             // rows one wave-wide load covers
+    static constexpr int NP = kSnapTile / RW;      // loads per tile
+    static constexpr int NO = 16 / RW;             // after this many loads the permutation of the rows' chunks repeats
+    uint32_t off[NO];                              // the lane's byte in its row of load i, i modulo NO
     __device__ __forceinline__ SnapStage()
     {
-        const int lane = threadIdx.x & 63;
-        wave = threadIdx.x >> 6;
-        srow = wave * RW + lane / CR;
-        gchunk = (lane % CR) ^ chunk_swizzle<D>(srow);
+        const int lane = threadIdx.x & 63, srow = lane / CR;
+#pragma unroll
+        for (int i = 0; i < NO; ++i) off[i] = (uint32_t)(srow * D + ((lane % CR) ^ chunk_swizzle<D>(i * RW + srow)) * 8) * 2u;
     }
-    // kt: first row of the tile in global memory; rem: valid rows of the tile (>= 1)
-    __device__ __forceinline__ void pass(const bf16 *kt, uint16_t *tile, int i, int rem) const
+    // rows row0 .. row0 + 31 of x into a slot, as far as they lie below `rows`
+    template <int AUX = 0>
+    __device__ __forceinline__ void tile(const bf16 *x, long row0, long rows, uint16_t *slot) const
     {
-        const int r = (i * RPI + srow < rem) ? i * RPI + srow : rem - 1;
-        load16_to_lds(lds_source(kt), (uint32_t)(r * D + gchunk * 8) * 2u, tile + (i * RPI + wave * RW) * D);
+        const int n = (int)((rows - row0 < kSnapTile) ? rows - row0 : kSnapTile);
+        const LdsSource src = lds_source_sized(x + row0 * D, (n > 0 ? n : 0) * D * 2);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) load16_to_lds_at<AUX>(src, off[i % NO], (uint32_t)(i * RW * D * 2), slot + i * RW * D);
     }
 };
 
-// sweep 1: partial softmax statistics (max, sum) per (query row, key chunk).  S^T = K Q^T: a
-// lane owns one query row (a column of S^T), so its max and sum are in-lane reductions plus
-// one cross-half shuffle.  Wave w holds rows 32 w .. 32 w + 31 of the 128-row tile.
+// A tile's fragments out of a slot: all but the other slot's loads have landed, and when this returns the reads have left
+// the slot, so that it can be loaded into again.  (One block with its own waits: the compiler would have these
+// reads wait for the loads into the other slot too.)
 template <int D>
+__device__ __forceinline__ void snap_read_tile(const uint16_t *slots, uint32_t koff, bf16x8 (&kf)[D / 16])
+{
+    uint32_t at = (uint32_t)(size_t)(__attribute__((address_space(3))) const uint16_t *)slots + 2u * koff;
+    asm volatile("" : "+v"(at));  // (the other places are worked out here and not held in registers)
+    if constexpr (D == 128) {
+        asm volatile("s_waitcnt vmcnt(%16)\n\t"
+                     "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                     "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7])
+                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u),
+                       "v"(at ^ 224u), "n"(SnapStage<D>::NP)
+                     : "memory");
+    } else {
+        asm volatile("s_waitcnt vmcnt(%8)\n\t"
+                     "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3])
+                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "n"(SnapStage<D>::NP)
+                     : "memory");
+    }
+}
+
+// The wave's tiles in turn: fragments to registers, the next loads, then use(kf, first key of the tile).
+// The workgroup's keys are kc0 .. kc1 - 1 of kb; koff: the place of the first operand in the slots' arrays, the wave's
+// slot included (operand c: chunk 2 c + h of row lq, permuted: 16 c away by exclusive or).
+template <int D, int AUX, typename Use>
+__device__ __forceinline__ void snap_stream_keys(const bf16 *kb, long kc0, long kc1, const SnapStage<D> &st, uint16_t *slots0,
+                                                 uint16_t *slots1, uint32_t koff, Use use)
+{
+    constexpr int NC = D / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tiles = (int)((kc1 - kc0 + kSnapTile - 1) / kSnapTile);
+    const int n = (tiles - wave + 3) / 4;  // tiles of this wave (<= 0: none)
+    const long k0 = kc0 + (long)wave * kSnapTile;
+    auto step = [&](uint16_t *slots, int it) __attribute__((always_inline)) {
+        bf16x8 kf[NC];
+        snap_read_tile<D>(slots, koff, kf);
+        st.template tile<AUX>(kb, k0 + (long)(it + 2) * 4 * kSnapTile, kc1, slots + wave * kSnapTile * D);
+        use(kf, k0 + (long)it * 4 * kSnapTile);
+    };
+    for (int it = 0; it < n; it += 2) {
+        step(slots0, it);
+        if (it + 1 >= n) break;
+        step(slots1, it + 1);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing is on its way into the slots any more
+}
+
+// the row tile's queries (the R rows of a KV head follow each other) by way of the slots as 128 rows: whole rows per load,
+// where fragments fetched directly touch 64 cache lines each; ends with the slots free
+template <int D, int NRG>
+__device__ __forceinline__ void snap_query_fragments(const bf16 *q, int rows, const SnapStage<D> &st, uint16_t *slots,
+                                                     bf16x8 (&qf)[NRG][D / 16])
+{
+    const int lane = threadIdx.x & 63, lq = lane & 31, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < NRG) st.tile(q, wave * kSnapTile, rows, slots + wave * kSnapTile * D);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __syncthreads();
+#pragma unroll
+    for (int rg = 0; rg < NRG; ++rg)
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) qf[rg][c] = *reinterpret_cast<const bf16x8 *>(slots + (rg * kSnapTile + lq) * D + (((2 * c + h) ^ chunk_swizzle<D>(lq)) * 8));
+#pragma unroll
+    for (int rg = 0; rg < NRG; ++rg)
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) asm volatile("" : "+v"(qf[rg][c]));
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __syncthreads();
+}
+
+// sweep 1: partial softmax statistics (max, sum) per (query row, key chunk).  S^T = K Q^T: a
+// lane owns one query row (a column of S^T) of each of the NRG groups of 32, so its max and sum are in-lane reductions
+// plus one cross-half shuffle; the waves' statistics meet in LDS at the end.
+template <int D, int NRG, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_stats_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, float *__restrict__ stats, int Hq, int Hkv, long T,
     long Tcap, int W, int n_chunks, float scale, int keys_per_wg)
 {
-    constexpr int NC = D / 16;
+    constexpr int NC = D / 16, ROWS = 32 * NRG, AUX = STREAM ? 2 : 0;
     using Stage = SnapStage<D>;
-    __shared__ __attribute__((aligned(1024))) uint16_t sK0[kSnapKT * D];
-    __shared__ __attribute__((aligned(1024))) uint16_t sK1[kSnapKT * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sK0[4 * kSnapTile * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sK1[4 * kSnapTile * D];
+    __shared__ float s_ml[4][ROWS][2];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, h = lane >> 5;
     const int chunk = blockIdx.x;
     const int bk = blockIdx.y;  // b * Hkv + kvh
@@ -75,131 +156,100 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bf16 *kb = k_cache + (long)bk * Tcap * D;
     const long kc0 = (long)chunk * keys_per_wg;
     const long kc1 = (kc0 + keys_per_wg < T) ? kc0 + keys_per_wg : T;
-    const int n_steps = (int)((kc1 - kc0 + kSnapKT - 1) / kSnapKT);
-    const int n_row_tiles = (R + 127) / 128;
+    const int n_row_tiles = (R + ROWS - 1) / ROWS;
     const Stage st;
-    uint32_t koff[NC];  // K operand: row lq of a sub-tile, chunk 2 c + h (elements)
-    {
-        const int sw = chunk_swizzle<D>(lq);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) koff[c] = (uint32_t)(lq * D + (((2 * c + h) ^ sw) * 8));
-    }
+    const uint32_t koff = (uint32_t)((wave * kSnapTile + lq) * D + ((h ^ chunk_swizzle<D>(lq)) * 8));
     const float cs = scale * 1.4426950408889634f;  // base-2 domain
+    uint16_t *slot0 = sK0 + wave * kSnapTile * D, *slot1 = sK1 + wave * kSnapTile * D;
 
     for (int rt = 0; rt < n_row_tiles; ++rt) {
-        const int r = rt * 128 + wave * 32 + lq;
-        const bool r_ok = r < R;
-        const int w = r_ok ? r % W : 0;
-        {
-            const int rem = (int)((kc1 - kc0 < kSnapKT) ? kc1 - kc0 : kSnapKT);
+        st.template tile<AUX>(kb, kc0 + wave * kSnapTile, kc1, slot0);  // (a wave without a tile loads nothing)
+        bf16x8 qf[NRG][NC];
+        snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
+        st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
+        float m[NRG], l[NRG];
 #pragma unroll
-            for (int i = 0; i < Stage::NP; ++i) st.pass(kb + kc0 * D, sK0, i, rem);
+        for (int rg = 0; rg < NRG; ++rg) {
+            m[rg] = -INFINITY;
+            l[rg] = 0.f;
         }
-        // the row tile's queries (the R rows of a KV head follow each other) by way of the second buffer:
-        // whole rows per load, where fragments fetched directly touch 64 cache lines each (32 heads x
-        // 4096 tokens, window 64: 45.5 -> 42.6 us for the whole compression; 8 heads x 64K 112 -> 110)
-        {
-            const int rem = (R - rt * 128 < 128) ? R - rt * 128 : 128;
+        snap_stream_keys<D, AUX>(kb, kc0, kc1, st, sK0, sK1, koff, [&](const bf16x8 (&kf)[NC], long k0) __attribute__((always_inline)) {
+            auto groups = [&](auto edge_tag) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < Stage::NP; ++i) st.pass(q_win + ((long)bk * R + rt * 128) * D, sK1, i, rem);
-        }
-        bf16x8 qf[NC];
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        __syncthreads();
+                for (int rg = 0; rg < NRG; ++rg) {
+                    f32x16 sacc;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) qf[c] = *reinterpret_cast<const bf16x8 *>(&sK1[32 * wave * D + koff[c]]);
-        const long pos = L + w;  // absolute position of the query: keys <= pos are visible
-        float m = -INFINITY, l = 0.f;
-        __syncthreads();  // the second buffer is free for keys
-
-        auto step = [&](auto next_tag, auto buf_tag, int it) {
-            constexpr bool NEXT = decltype(next_tag)::value;
-            constexpr int BUF = decltype(buf_tag)::value;
-            const uint16_t *cK = BUF ? sK1 : sK0;
-            uint16_t *nK = BUF ? sK0 : sK1;
-            const long k0 = kc0 + (long)it * kSnapKT;
-            const long kn = k0 + kSnapKT;
-            const int rem_n = (int)((kc1 - kn < kSnapKT) ? kc1 - kn : kSnapKT);
-            // keys of this tile a lane may see, as offsets from k0: 0 .. hi (all 128 in the bulk)
-            const long hi_l = ((pos < kc1 - 1) ? pos : kc1 - 1) - k0;
-            const bool edge = (k0 + kSnapKT > kc1) || (k0 + kSnapKT - 1 > L);  // uniform
+                    for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
 #pragma unroll
-            for (int sp = 0; sp < 2; ++sp) {  // pairs of 32-key sub-tiles
-                f32x16 sacc[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) sacc[u][v] = 0.f;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    if constexpr (NEXT) {
-                        constexpr int every = (2 * NC) / Stage::NP;  // matrix-instruction pairs per load
-                        if ((sp * NC + c) % every == 0) st.pass(kb + kn * D, nK, (sp * NC + c) / every, rem_n);
-                    }
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(&cK[32 * (2 * sp + u) * D + koff[c]]);
-                        sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], sacc[u], 0, 0, 0);  // [key][row]
-                    }
-                }
-                if (edge) {
-                    const int hi = (int)((hi_l > kSnapKT) ? kSnapKT : ((hi_l < -1) ? -1 : hi_l)) - 4 * h;
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
+                    for (int c = 0; c < NC; ++c) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c], qf[rg][c], sacc, 0, 0, 0);  // [key][row]
+                    if constexpr (decltype(edge_tag)::value) {
+                        // keys of this tile the row may see, as offsets from k0: 0 .. hi
+                        int r = rt * ROWS + 32 * rg + lq;
+                        asm volatile("" : "+v"(r));  // (worked out here, not held in registers for the tiles without an edge)
+                        const long pos = L + (r < R ? r % W : 0);  // absolute position of the query: keys <= pos are visible
+                        const long hi_l = ((pos < kc1 - 1) ? pos : kc1 - 1) - k0;
+                        const int hi = (int)((hi_l > kSnapTile) ? kSnapTile : ((hi_l < -1) ? -1 : hi_l)) - 4 * h;
 #pragma unroll
                         for (int v = 0; v < 16; ++v) {
-                            const int e = 32 * (2 * sp + u) + 8 * (v / 4) + (v % 4);  // + 4 h: folded into hi
-                            if (e > hi) sacc[u][v] = -INFINITY;
+                            const int e = 8 * (v / 4) + (v % 4);  // + 4 h: folded into hi
+                            if (e > hi) sacc[v] = -INFINITY;
                         }
+                    }
+                    // Weights against the reference point as it is (none yet: its negative is +inf, and so are they);
+                    // the point moves to the maximum only where a lane's 16 weights add up to more than kSnapLarge.
+                    // (Each half of a row's lanes keeps its own sum; they meet at the end.)
+                    auto weights = [&](float ref) __attribute__((always_inline)) -> float {
+                        float p4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) p4[v % 4] += __builtin_amdgcn_exp2f(fmaf(sacc[v], cs, -ref));
+                        return (p4[0] + p4[1]) + (p4[2] + p4[3]);
+                    };
+                    float ps = weights(m[rg]);
+                    if (__any(!(ps <= kSnapLarge))) {
+                        float mx = sacc[0];
+#pragma unroll
+                        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
+                        const float m_new = fmaxf(m[rg], half_pair_max(mx) * cs);
+                        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+                        l[rg] *= (m[rg] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[rg] - m_safe);
+                        ps = weights(m_safe);
+                        m[rg] = m_new;
+                    }
+                    l[rg] += ps;
                 }
-                float mx = -INFINITY;
+            };
+            if (k0 + kSnapTile > kc1 || k0 + kSnapTile - 1 > L) groups(std::true_type{});  // (uniform)
+            else groups(std::false_type{});
+        });
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[u][v]);
-                mx = half_pair_max(mx) * cs;
-                const float m_new = fmaxf(m, mx);
-                const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-                float psum = 0.f;
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(fmaf(sacc[u][v], cs, -m_safe));
-                psum = half_pair_sum(psum);
-                l = l * ((m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_safe)) + psum;
-                m = m_new;
-            }
-            if constexpr (NEXT) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's loads have landed
-            __syncthreads();
-        };
-        {
-            using B0 = std::integral_constant<int, 0>;
-            using B1 = std::integral_constant<int, 1>;
-            int it = 0;
-            for (; it + 2 < n_steps; it += 2) {
-                step(std::true_type{}, B0{}, it);
-                step(std::true_type{}, B1{}, it + 1);
-            }
-            if (it + 2 == n_steps) {
-                step(std::true_type{}, B0{}, it);
-                step(std::false_type{}, B1{}, it + 1);
-            } else {
-                step(std::false_type{}, B0{}, it);
+        for (int rg = 0; rg < NRG; ++rg) {
+            const float ls = half_pair_sum(l[rg]);
+            if (h == 0) {
+                s_ml[wave][32 * rg + lq][0] = m[rg];
+                s_ml[wave][32 * rg + lq][1] = ls;
             }
         }
-        if (r_ok && h == 0) {  // (max, sum) back in the natural-log domain
+        __syncthreads();
+        const int r = rt * ROWS + tid;
+        if (tid < ROWS && r < R) {  // (max, sum) back in the natural-log domain
+            float M = -INFINITY, S = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) M = fmaxf(M, s_ml[w][tid][0]);
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                if (s_ml[w][tid][0] != -INFINITY) S += s_ml[w][tid][1] * __builtin_amdgcn_exp2f(s_ml[w][tid][0] - M);
             float *sp = stats + (((long)bk * n_chunks + chunk) * R + r) * 2;
-            sp[0] = m * 0.6931471805599453f;
-            sp[1] = l;
+            sp[0] = M * 0.6931471805599453f;
+            sp[1] = S;
         }
+        // (the next row tile's barriers come before its statistics)
     }
 }
 
-// sweep 2: the votes.  S = Q K^T: a lane owns one key column, and wave w takes the keys of
-// sub-tile w of every 128-key step against all (up to 128) query rows of the row tile, so a
-// key's vote is an in-lane sum plus one cross-half shuffle and is written straight out.  Only
+// sweep 2: the votes.  S = Q K^T: a lane owns one key column of the wave's tile against all query rows of the
+// row tile, so a key's vote is an in-lane sum plus one cross-half shuffle and is written straight out.  Only
 // prefix keys (< L) are stored, and every window query sees all of them: no mask is needed.
-template <int D>
+template <int D, int NRG, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_votes_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, const float *__restrict__ lse,
     float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
@@ -208,14 +258,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // the selection's bins start at zero
     for (long z = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; z < n_hist; z += (long)gridDim.x * gridDim.y * 256)
         sel_hist[z] = 0u;
-    constexpr int NC = D / 16;
+    constexpr int NC = D / 16, ROWS = 32 * NRG, AUX = STREAM ? 2 : 0;
     using Stage = SnapStage<D>;
-    __shared__ __attribute__((aligned(1024))) uint16_t sK0[kSnapKT * D];
-    __shared__ __attribute__((aligned(1024))) uint16_t sK1[kSnapKT * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sK0[4 * kSnapTile * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sK1[4 * kSnapTile * D];
+    __shared__ __attribute__((aligned(16))) float s_lse2[ROWS];  // row log-sum-exp, base-2 domain
 
-    __shared__ __attribute__((aligned(16))) float s_lse2[128];  // row log-sum-exp, base-2 domain
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, h = lane >> 5;
     const int chunk = blockIdx.x;
     const int bk = blockIdx.y;  // b * Hkv + kvh
@@ -225,78 +274,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bf16 *kb = k_cache + (long)bk * Tcap * D;
     const long kc0 = (long)chunk * keys_per_wg;
     const long kc1 = (kc0 + keys_per_wg < L) ? kc0 + keys_per_wg : L;  // prefix keys only
-    const int n_steps = (int)((kc1 - kc0 + kSnapKT - 1) / kSnapKT);
-    const int n_row_tiles = (R + 127) / 128;
+    const int n_row_tiles = (R + ROWS - 1) / ROWS;
     const Stage st;
-    uint32_t koff[NC];
-    {
-        const int sw = chunk_swizzle<D>(lq);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) koff[c] = (uint32_t)((32 * wave + lq) * D + (((2 * c + h) ^ sw) * 8));
-    }
+    const uint32_t koff = (uint32_t)((wave * kSnapTile + lq) * D + ((h ^ chunk_swizzle<D>(lq)) * 8));
     const float cs = scale * 1.4426950408889634f;
+    uint16_t *slot0 = sK0 + wave * kSnapTile * D, *slot1 = sK1 + wave * kSnapTile * D;
 
     for (int rt = 0; rt < n_row_tiles; ++rt) {
-        {
-            const int rem = (int)((kc1 - kc0 < kSnapKT) ? kc1 - kc0 : kSnapKT);
-#pragma unroll
-            for (int i = 0; i < Stage::NP; ++i) st.pass(kb + kc0 * D, sK0, i, rem);
-        }
-        // A operands: query rows 32 rg + lq of the row tile, rg = 0..3 (by way of the second buffer, as in the
-        // first sweep); and the log-sum-exp of all rows of the tile in LDS (base-2 domain; +inf for
-        // padding rows: their votes vanish)
-        {
-            const int rem = (R - rt * 128 < 128) ? R - rt * 128 : 128;
-#pragma unroll
-            for (int i = 0; i < Stage::NP; ++i) st.pass(q_win + ((long)bk * R + rt * 128) * D, sK1, i, rem);
-        }
+        st.template tile<AUX>(kb, kc0 + wave * kSnapTile, kc1, slot0);
         if (rt > 0) __syncthreads();  // the previous row tile's readers are done with s_lse2
-        if (tid < 128) {
-            const int rr = rt * 128 + tid;
+        // the log-sum-exp of all rows of the tile in LDS (base-2 domain; +inf for padding rows: their votes vanish)
+        if (tid < ROWS) {
+            const int rr = rt * ROWS + tid;
             s_lse2[tid] = (rr < R) ? lse[(long)bk * R + rr] * 1.4426950408889634f : INFINITY;
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        __syncthreads();
-        bf16x8 qf[4][NC];
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) qf[rg][c] = *reinterpret_cast<const bf16x8 *>(&sK1[32 * rg * D + koff[c] - 32 * wave * D]);
-        __syncthreads();  // the second buffer is free for keys
-
-        auto step = [&](auto next_tag, auto buf_tag, int it) {
-            constexpr bool NEXT = decltype(next_tag)::value;
-            constexpr int BUF = decltype(buf_tag)::value;
-            const uint16_t *cK = BUF ? sK1 : sK0;
-            uint16_t *nK = BUF ? sK0 : sK1;
-            const long k0 = kc0 + (long)it * kSnapKT;
-            const long kn = k0 + kSnapKT;
-            const int rem_n = (int)((kc1 - kn < kSnapKT) ? kc1 - kn : kSnapKT);
+        bf16x8 qf[NRG][NC];
+        snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
+        st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
+        snap_stream_keys<D, AUX>(kb, kc0, kc1, st, sK0, sK1, koff, [&](const bf16x8 (&kf)[NC], long k0) __attribute__((always_inline)) {
             float vsum = 0.f;
+            constexpr int PR = NRG < 2 ? 1 : 2;  // row groups at a time
 #pragma unroll
-            for (int rp = 0; rp < 2; ++rp) {  // pairs of 32-row groups
-                f32x16 sacc[2];
+            for (int rp = 0; rp < NRG; rp += PR) {
+                f32x16 sacc[PR];
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+                for (int u = 0; u < PR; ++u)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) sacc[u][v] = 0.f;
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    if constexpr (NEXT) {
-                        constexpr int every = (2 * NC) / Stage::NP;
-                        if ((rp * NC + c) % every == 0) st.pass(kb + kn * D, nK, (rp * NC + c) / every, rem_n);
-                    }
-                    const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(&cK[koff[c]]);
+                for (int c = 0; c < NC; ++c)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
-                        sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[2 * rp + u][c], kf, sacc[u], 0, 0, 0);  // [row][key]
-                }
+                    for (int u = 0; u < PR; ++u)
+                        sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[rp + u][c], kf[c], sacc[u], 0, 0, 0);  // [row][key]
                 // accumulator value v: row 8 (v / 4) + 4 h + v % 4 of the group
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+                for (int u = 0; u < PR; ++u)
 #pragma unroll
                     for (int qd = 0; qd < 4; ++qd) {
-                        const float4 ls = *reinterpret_cast<const float4 *>(&s_lse2[(2 * rp + u) * 32 + 8 * qd + 4 * h]);
+                        const float4 ls = *reinterpret_cast<const float4 *>(&s_lse2[(rp + u) * 32 + 8 * qd + 4 * h]);
                         vsum += __builtin_amdgcn_exp2f(fmaf(sacc[u][4 * qd], cs, -ls.x));
                         vsum += __builtin_amdgcn_exp2f(fmaf(sacc[u][4 * qd + 1], cs, -ls.y));
                         vsum += __builtin_amdgcn_exp2f(fmaf(sacc[u][4 * qd + 2], cs, -ls.z));
@@ -304,29 +319,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     }
             }
             vsum = half_pair_sum(vsum);
-            const long key = k0 + 32 * wave + lq;
+            const long key = k0 + lq;
             if (h == 0 && key < kc1) {
                 float *dst = votes + (long)bk * L + key;
                 *dst = (rt == 0) ? vsum : *dst + vsum;
             }
-            if constexpr (NEXT) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-            __syncthreads();
-        };
-        {
-            using B0 = std::integral_constant<int, 0>;
-            using B1 = std::integral_constant<int, 1>;
-            int it = 0;
-            for (; it + 2 < n_steps; it += 2) {
-                step(std::true_type{}, B0{}, it);
-                step(std::true_type{}, B1{}, it + 1);
-            }
-            if (it + 2 == n_steps) {
-                step(std::true_type{}, B0{}, it);
-                step(std::false_type{}, B1{}, it + 1);
-            } else {
-                step(std::false_type{}, B0{}, it);
-            }
-        }
+        });
     }
 }
 
@@ -582,8 +580,9 @@ __global__ __launch_bounds__(kSelThreads) void snapkv_sel_emit_kernel(const floa
     }
 }
 
-// copy the kept rows, then the window rows: one 16-byte chunk per thread
-template <typename ST>
+// copy the kept rows, then the window rows: one 16-byte chunk per thread.  STREAM: the rows are not in the memory-side
+// cache (the sweeps streamed), ordinary loads would only evict others for them: 8 x 32 heads x 4096 to 512 33 -> 26 us
+template <typename ST, bool STREAM>
 __global__ void snapkv_gather_kernel(const ST *__restrict__ k_cache, const ST *__restrict__ v_cache,
                                      const int32_t *__restrict__ idx, ST *__restrict__ kc_out, ST *__restrict__ vc_out,
                                      long T, long Tcap, long Tcap_out, int W, int K_keep, int D, long total)
@@ -597,10 +596,12 @@ __global__ void snapkv_gather_kernel(const ST *__restrict__ k_cache, const ST *_
     const long r = rem / cpr;
     const int c = (int)(rem % cpr);
     const long srow = (r < K_keep) ? idx[bk * K_keep + r] : (T - W) + (r - K_keep);
-    const uint4 *ks = reinterpret_cast<const uint4 *>(k_cache + (bk * Tcap + srow) * D) + c;
-    const uint4 *vs = reinterpret_cast<const uint4 *>(v_cache + (bk * Tcap + srow) * D) + c;
-    reinterpret_cast<uint4 *>(kc_out + (bk * Tcap_out + r) * D)[c] = *ks;
-    reinterpret_cast<uint4 *>(vc_out + (bk * Tcap_out + r) * D)[c] = *vs;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 *ks = reinterpret_cast<const u32x4 *>(k_cache + (bk * Tcap + srow) * D) + c;
+    const u32x4 *vs = reinterpret_cast<const u32x4 *>(v_cache + (bk * Tcap + srow) * D) + c;
+    const u32x4 kx = STREAM ? __builtin_nontemporal_load(ks) : *ks, vx = STREAM ? __builtin_nontemporal_load(vs) : *vs;
+    reinterpret_cast<u32x4 *>(kc_out + (bk * Tcap_out + r) * D)[c] = kx;
+    reinterpret_cast<u32x4 *>(vc_out + (bk * Tcap_out + r) * D)[c] = vx;
 }
 
 // Short prefixes (at most kSnapOneWgKeys positions per head): pooling, the top-K_keep selection
@@ -688,15 +689,33 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     float *pooled = votes_out ? votes_out : (float *)(ws + Ly.off_pooled);
     const dim3 grid((unsigned)Ly.n_chunks, (unsigned)BK);
     const bf16 *qw = (const bf16 *)q_win, *kc = (const bf16 *)k_cache;
+    // groups of 32 query rows a wave holds at a time
+#define RS_SNAP_ROWS1(LAUNCH, DD, SS)           \
+    do {                                        \
+        if (Ly.R <= 32) LAUNCH(DD, 1, SS);      \
+        else if (Ly.R <= 64) LAUNCH(DD, 2, SS); \
+        else LAUNCH(DD, 4, SS);                 \
+    } while (0)
+#define RS_SNAP_ROWS(LAUNCH, DD)                    \
+    do {                                            \
+        if (streaming) RS_SNAP_ROWS1(LAUNCH, DD, true); \
+        else RS_SNAP_ROWS1(LAUNCH, DD, false);      \
+    } while (0)
+    // From about 80 MB of keys on streaming loads: ordinary ones have the memory-side cache make room for every line (cold
+    // keys 64 us a sweep against 47 at 268 MB), and what the first sweep leaves there saves the second one and the gather
+    // less than that.  The whole compression, ordinary / streaming, us: 8 heads x 128K 168 / 156, x 97492 141 / 133, x 41000
+    // (84 MB) 90.3 / 89.1, 8 x 32 heads x 4096 154 / 134, x 2000 92 / 81, 4 x 8 x 13070 101 / 93; the other way 8 heads x 32768
+    // (67 MB) to 1/8 62.6 / 63.3, to 1/16 58.3 / 60.7.
+    const bool streaming = BK * T * s->D * 2 >= 80l << 20;
     // the rows' log-sum-exp over all visible keys: handed in by the caller (the prefill attention of
     // the window rows has it), or from a first sweep over the keys
     if (lse_in) {
         lse = const_cast<float *>(lse_in);  // [B, Hq, W] is [B * Hkv][G * W]: only read
     } else {
-#define RS_STATS(DD) \
-    snapkv_stats_kernel<DD><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
-        if (s->D == 128) RS_STATS(128);
-        else RS_STATS(64);
+#define RS_STATS(DD, GG, SS) \
+    snapkv_stats_kernel<DD, GG, SS><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
+        if (s->D == 128) RS_SNAP_ROWS(RS_STATS, 128);
+        else RS_SNAP_ROWS(RS_STATS, 64);
 #undef RS_STATS
         const long rows_total = BK * Ly.R;
         snapkv_lse_kernel<<<(unsigned)((rows_total + 3) / 4), 256, 0, stream>>>(stats, lse, Ly.R, Ly.n_chunks, rows_total);
@@ -706,11 +725,13 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     const bool one_wg = L <= kSnapOneWgKeys && knobs().snap_one_wg != 0;  // (knob 0: the spread-out selection at any length)
     uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
     const long n_hist = one_wg ? 0 : BK * 1024;
-#define RS_VOTES(DD) \
-    snapkv_votes_kernel<DD><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
-    if (s->D == 128) RS_VOTES(128);
-    else RS_VOTES(64);
+#define RS_VOTES(DD, GG, SS) \
+    snapkv_votes_kernel<DD, GG, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
+    if (s->D == 128) RS_SNAP_ROWS(RS_VOTES, 128);
+    else RS_SNAP_ROWS(RS_VOTES, 64);
 #undef RS_VOTES
+#undef RS_SNAP_ROWS
+#undef RS_SNAP_ROWS1
     if (one_wg) {
         snapkv_pool_select_kernel<<<(unsigned)BK, kSnapOneWgThreads, (size_t)L * 4, stream>>>(
             votes, votes_out, idx_out, (int)L, pool_kernel, K_keep);
@@ -730,9 +751,13 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     }
     const int cpr = s->D * 2 / 16;
     const long total = BK * (long)(K_keep + W) * cpr;
-    snapkv_gather_kernel<bf16><<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(
-        (const bf16 *)k_cache, (const bf16 *)v_cache, idx_out, (bf16 *)kc_out, (bf16 *)vc_out, T, s->Tcap, Tcap_out, W,
-        K_keep, s->D, total);
+#define RS_GATHER(SS)                                                                                                  \
+    snapkv_gather_kernel<bf16, SS><<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(                               \
+        (const bf16 *)k_cache, (const bf16 *)v_cache, idx_out, (bf16 *)kc_out, (bf16 *)vc_out, T, s->Tcap, Tcap_out, W, \
+        K_keep, s->D, total)
+    if (streaming) RS_GATHER(true);
+    else RS_GATHER(false);
+#undef RS_GATHER
     return hipGetLastError() == hipSuccess ? RS_OK : RS_LAUNCH_FAILED;
 }
 

@@ -222,3 +222,43 @@ def test_long_sweeps_at_64_channels(rs):
         assert torch.equal(idx[0, h].long(), first)
         rows = torch.cat([first, torch.arange(T - W, T, device="cuda")])
         assert torch.equal(k_out[0, h], kc[0, h, rows])
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,W", [(2, 2, 128, 20), (2, 2, 64, 64), (4, 2, 128, 33), (4, 1, 64, 40), (8, 2, 128, 64)])
+@pytest.mark.parametrize("grow", [0.0, 0.05])
+def test_sweeps_at_the_edges_of_tiles(rs, Hq, Hkv, D, W, grow):
+    """One, two and four groups of 32 window rows and more than one tile of them; lengths that leave waves without a tile,
+    a tile with one key, and several chunks of keys; scores that keep growing along the keys (the softmax reference moves)
+    and ones that don't; the last length also with enough heads for streaming loads.  Against 64-bit softmax sums: the
+    votes are sums of W * G weights, each within a few units of float32 rounding of exp2 and of a log-sum-exp of
+    magnitude below 2^10, 2^10 * 2^-23 = 1.2e-4 at worst."""
+    scale = 1.0 / np.sqrt(D)
+    for T, B in ((W + 1, 1), (W + 31, 2), (W + 97, 1), (W + 128, 1), (2048 + W + 1, 1), (2 * 2048 + 5, 2), (4001, -(-(81 << 20) // (Hkv * 4001 * D * 2)))):
+        say("snapkv edges", Hq, Hkv, D, W, grow, T, B)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(T)
+        k = torch.randn(B, Hkv, T, D, generator=gen, device="cuda")
+        q = torch.randn(B, Hq, W, D, generator=gen, device="cuda")
+        k[..., 0] += grow * torch.arange(T, device="cuda")
+        q[..., 0] = 1.0
+        k, q = k.bfloat16(), q.bfloat16()
+        v = torch.randn(B, Hkv, T, D, generator=gen, device="cuda").bfloat16()
+        L = T - W
+        keep = max(1, L // 3)
+        s = rs.make_shape(B, Hq, Hkv, D, T, 16, torch.bfloat16)
+        ws = rs.Workspace(rs.snapkv_compress_workspace_bytes(s, T, W))
+        ko, vo = (torch.zeros(B, Hkv, keep + W, D, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        idx = torch.full((B, Hkv, keep), -5, dtype=torch.int32, device="cuda")
+        votes = torch.zeros(B, Hkv, L, device="cuda")
+        rs.snapkv_compress(s, q, k, v, T, W, keep, 1, scale, ko, vo, keep + W, idx, votes, ws)
+        later = torch.arange(T, device="cuda")[None] > L + torch.arange(W, device="cuda")[:, None]
+        for b, h in {(0, 0), (B - 1, Hkv - 1), (B // 2, 0)}:
+            want = torch.zeros(L, dtype=torch.float64, device="cuda")
+            for g in range(Hq // Hkv):
+                x = q[b, h * (Hq // Hkv) + g].double() @ k[b, h].double().T * scale
+                want += torch.softmax(x.masked_fill_(later, -torch.inf), 1).sum(0)[:L]
+            np.testing.assert_allclose(to_np(votes[b, h]), to_np(want), rtol=2e-4, atol=1e-9)
+        best = torch.sort(votes, dim=2, descending=True, stable=True).indices[:, :, :keep].sort(2).values
+        assert torch.equal(best.int(), idx)
+        rows = torch.cat([best, torch.arange(L, T, device="cuda").expand(B, Hkv, W)], 2)[..., None].expand(-1, -1, -1, D)
+        assert torch.equal(ko, k.gather(2, rows)) and torch.equal(vo, v.gather(2, rows))
