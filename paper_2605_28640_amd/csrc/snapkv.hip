@@ -132,7 +132,7 @@ __device__ __forceinline__ void snap_query_fragments(const bf16 *q, int rows, co
     __syncthreads();
 }
 
-// sweep 1: partial softmax statistics (max, sum) per (query row, key chunk).  S^T = K Q^T: a
+// sweep 1: partial softmax statistics (reference point, sum) per (query row, key chunk).  S^T = K Q^T: a
 // lane owns one query row (a column of S^T) of each of the NRG groups of 32, so its max and sum are in-lane reductions
 // plus one cross-half shuffle; the waves' statistics meet in LDS at the end.
 template <int D, int NRG, bool STREAM>
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
         __syncthreads();
         const int r = rt * ROWS + tid;
-        if (tid < ROWS && r < R) {  // (max, sum) back in the natural-log domain
+        if (tid < ROWS && r < R) {  // (reference point in the base-2 domain, sum)
             float M = -INFINITY, S = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) M = fmaxf(M, s_ml[w][tid][0]);
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int w = 0; w < 4; ++w)
                 if (s_ml[w][tid][0] != -INFINITY) S += s_ml[w][tid][1] * __builtin_amdgcn_exp2f(s_ml[w][tid][0] - M);
             float *sp = stats + (((long)bk * n_chunks + chunk) * R + r) * 2;
-            sp[0] = M * 0.6931471805599453f;
+            sp[0] = M;
             sp[1] = S;
         }
         // (the next row tile's barriers come before its statistics)
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 template <int D, int NRG, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_votes_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, const float *__restrict__ lse,
-    float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
+    const float *__restrict__ stats, int n_chunks, float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
     uint32_t *__restrict__ sel_hist, long n_hist)
 {
     // the selection's bins start at zero
@@ -263,6 +263,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(1024))) uint16_t sK0[4 * kSnapTile * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sK1[4 * kSnapTile * D];
     __shared__ __attribute__((aligned(16))) float s_lse2[ROWS];  // row log-sum-exp, base-2 domain
+    constexpr int PARTS = 256 / ROWS;  // threads that share a row's statistics
+    __shared__ float s_part[PARTS][ROWS][2];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, h = lane >> 5;
@@ -282,14 +284,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     for (int rt = 0; rt < n_row_tiles; ++rt) {
         st.template tile<AUX>(kb, kc0 + wave * kSnapTile, kc1, slot0);
-        if (rt > 0) __syncthreads();  // the previous row tile's readers are done with s_lse2
-        // the log-sum-exp of all rows of the tile in LDS (base-2 domain; +inf for padding rows: their votes vanish)
-        if (tid < ROWS) {
-            const int rr = rt * ROWS + tid;
-            s_lse2[tid] = (rr < R) ? lse[(long)bk * R + rr] * 1.4426950408889634f : INFINITY;
+        // The rows' log-sum-exp: handed in, or from the statistics of the first sweep's chunks, which every workgroup folds
+        // for itself in a fixed order, beside its first loads (as a launch of its own: 5-6 us).
+        const int rr = rt * ROWS + tid % ROWS;
+        if (!lse) {
+            float M = -INFINITY, S = 0.f;
+            const float2 *sp = reinterpret_cast<const float2 *>(stats) + (long)bk * n_chunks * R + (rr < R ? rr : 0);
+            constexpr int U = 8;  // chunks on their way at a time
+            for (int c0 = tid / ROWS; c0 < n_chunks; c0 += U * PARTS) {
+                float2 x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int c = c0 + u * PARTS;
+                    x[u] = sp[(long)(c < n_chunks ? c : c0) * R];
+                    if (c >= n_chunks) x[u] = make_float2(-INFINITY, 0.f);
+                }
+                float Mn = M;
+#pragma unroll
+                for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, x[u].x);
+                if (Mn != -INFINITY) {
+                    S *= (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) S += (x[u].x == -INFINITY) ? 0.f : x[u].y * __builtin_amdgcn_exp2f(x[u].x - Mn);
+                    M = Mn;
+                }
+            }
+            s_part[tid / ROWS][tid % ROWS][0] = M;
+            s_part[tid / ROWS][tid % ROWS][1] = S;
         }
         bf16x8 qf[NRG][NC];
         snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
+        // (base-2 domain; +inf for padding rows: their votes vanish.  The previous row tile's readers are two barriers back.)
+        if (tid < ROWS) {
+            float x = INFINITY;
+            if (rr < R && lse) x = lse[(long)bk * R + rr] * 1.4426950408889634f;
+            if (rr < R && !lse) {
+                float M = -INFINITY, S = 0.f;
+#pragma unroll
+                for (int p = 0; p < PARTS; ++p) M = fmaxf(M, s_part[p][tid][0]);
+#pragma unroll
+                for (int p = 0; p < PARTS; ++p) S += (s_part[p][tid][0] == -INFINITY) ? 0.f : s_part[p][tid][1] * __builtin_amdgcn_exp2f(s_part[p][tid][0] - M);
+                // M + log2(S), rounded once: the exponent of S joins M first, what that rounds off joins the rest (log2 of
+                // S itself, up to 2^17, would carry an error of that size into every vote)
+                const int e = ilogbf(S);
+                const float hi = M + (float)e, rounded = (float)e - (hi - M);
+                x = hi + (__log2f(scalbnf(S, -e)) + rounded);
+            }
+            s_lse2[tid] = x;
+        }
+        __syncthreads();
         st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
         snap_stream_keys<D, AUX>(kb, kc0, kc1, st, sK0, sK1, koff, [&](const bf16x8 (&kf)[NC], long k0) __attribute__((always_inline)) {
             float vsum = 0.f;
@@ -326,30 +369,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         });
     }
-}
-
-// log-sum-exp of each row over its key chunks: one wave per row, lanes over chunks
-__global__ __launch_bounds__(256) void snapkv_lse_kernel(const float *__restrict__ stats, float *__restrict__ lse, int R,
-                                                         int n_chunks, long rows_total)
-{
-    const long i = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (i >= rows_total) return;
-    const long bk = i / R;
-    const int r = (int)(i % R);
-    float M = -INFINITY;
-    for (int c = lane; c < n_chunks; c += 64) M = fmaxf(M, stats[((bk * n_chunks + c) * R + r) * 2]);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, shfl_xor_f(M, m));
-    float Ls = 0.f;
-    for (int c = lane; c < n_chunks; c += 64) {
-        const float mc = stats[((bk * n_chunks + c) * R + r) * 2];
-        if (mc != -INFINITY) Ls += stats[((bk * n_chunks + c) * R + r) * 2 + 1] * __expf(mc - M);
-    }
-    // fixed butterfly order: the same bits on every run
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) Ls += shfl_xor_f(Ls, m);
-    if (lane == 0) lse[i] = M + __logf(Ls);
 }
 
 // ------------------------------------------------------------------------------------
@@ -643,7 +662,7 @@ static size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct SnapLayout {
     int n_chunks, R, keys_per_wg;
-    size_t off_stats, off_lse, off_votes, off_pooled, off_hist, total;
+    size_t off_stats, off_votes, off_pooled, off_hist, total;
     int n_slices;
 };
 
@@ -661,8 +680,6 @@ static SnapLayout snap_layout(const rs_shape *s, long T, int W)
     size_t o = RS_WS_CTRL_BYTES;
     L.off_stats = o;
     o += al256s((size_t)BK * L.n_chunks * L.R * 2 * 4);
-    L.off_lse = o;
-    o += al256s((size_t)BK * L.R * 4);
     L.off_votes = o;
     o += al256s((size_t)BK * (T - W) * 4);
     L.off_pooled = o;
@@ -684,7 +701,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     const SnapLayout Ly = snap_layout(s, T, W);
     const long BK = (long)s->B * s->Hkv;
     const long L = T - W;
-    float *stats = (float *)(ws + Ly.off_stats), *lse = (float *)(ws + Ly.off_lse);
+    float *stats = (float *)(ws + Ly.off_stats);
     float *votes = (float *)(ws + Ly.off_votes);
     float *pooled = votes_out ? votes_out : (float *)(ws + Ly.off_pooled);
     const dim3 grid((unsigned)Ly.n_chunks, (unsigned)BK);
@@ -709,16 +726,13 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     const bool streaming = BK * T * s->D * 2 >= 80l << 20;
     // the rows' log-sum-exp over all visible keys: handed in by the caller (the prefill attention of
     // the window rows has it), or from a first sweep over the keys
-    if (lse_in) {
-        lse = const_cast<float *>(lse_in);  // [B, Hq, W] is [B * Hkv][G * W]: only read
-    } else {
+    // ([B, Hq, W] is [B * Hkv][G * W])
+    if (!lse_in) {
 #define RS_STATS(DD, GG, SS) \
     snapkv_stats_kernel<DD, GG, SS><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
         if (s->D == 128) RS_SNAP_ROWS(RS_STATS, 128);
         else RS_SNAP_ROWS(RS_STATS, 64);
 #undef RS_STATS
-        const long rows_total = BK * Ly.R;
-        snapkv_lse_kernel<<<(unsigned)((rows_total + 3) / 4), 256, 0, stream>>>(stats, lse, Ly.R, Ly.n_chunks, rows_total);
     }
     // votes exist for prefix keys only: chunks that start past the prefix are not needed
     const dim3 grid2((unsigned)((L + Ly.keys_per_wg - 1) / Ly.keys_per_wg), (unsigned)BK);
@@ -726,7 +740,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
     const long n_hist = one_wg ? 0 : BK * 1024;
 #define RS_VOTES(DD, GG, SS) \
-    snapkv_votes_kernel<DD, GG, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
+    snapkv_votes_kernel<DD, GG, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse_in, stats, Ly.n_chunks, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
     if (s->D == 128) RS_SNAP_ROWS(RS_VOTES, 128);
     else RS_SNAP_ROWS(RS_VOTES, 64);
 #undef RS_VOTES
