@@ -301,6 +301,24 @@ __device__ __forceinline__ void load16_to_lds_at(LdsSource src, uint32_t lane_of
                                              (int)offset, 0, AUX);
 }
 
+// this lane's 8 channels of a row through a sized descriptor: bytes past its end read as zeros, without a branch, so that
+// the wait for a load can count exactly what was issued after it (a load under a branch makes that unknown, and the wait one
+// for every load on its way).  AUX: 0, or 2 for a streaming load.
+template <typename ST, int AUX>
+__device__ __forceinline__ typename Row8<ST>::raw_t load_row8(LdsSource src, uint32_t byte)
+{
+    typename Row8<ST>::raw_t w;
+    uint32_t x[sizeof(w) / 4];
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(w) / 16; ++i) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(src, byte + 16 * i, 0, AUX);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[4 * i + c] = (uint32_t)v[c];
+    }
+    __builtin_memcpy(&w, x, sizeof(w));
+    return w;
+}
+
 // Tiles of K/V rows sit in LDS unpadded (a wave-wide load fills whole rows back to back), so the bank
 // spread comes from permuting the 16-byte chunks inside each row: chunk c of row r is kept at
 // position c ^ chunk_swizzle(r).  The permutation is chosen so that (a) 16 lanes reading the

@@ -6,6 +6,7 @@
 // 8 channels (one 16-byte bf16 load) each, so a wave touches RPW = 64/LPR rows per load
 // instruction and every global access is a run of full 128/256-byte rows.
 #include <cstdlib>
+#include "attend.h"
 #include "common.h"
 #include "knobs.h"
 #include "select.h"
@@ -263,9 +264,9 @@ int score_select_dispatch(int dtype, int D, int GQ, const void *q, const void *m
 // decode attention over a list of 16-row tiles (selected pages, or all rows), split over
 // workgroups; partial (m, l, o) per split; the last split to arrive merges them.
 // ------------------------------------------------------------------------------------
-template <typename ST, int D, int kAttThreads>
+template <typename ST, int D, int kAttThreads, bool STREAM>
 __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
-    const ST *__restrict__ q, const ST *__restrict__ k_cache, const ST *__restrict__ v_cache, const int32_t *idx,
+    const ST *__restrict__ q, const ST *k_cache, const ST *v_cache, const int32_t *idx,
     ST *__restrict__ out, float *__restrict__ lse_out, uint64_t *partial, int Hq, int Hkv, long Tcap, int P,
     long T_valid, int K, float scale, int splits, uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit,
     int idx_per_kv, uint32_t *state, long T_max)
@@ -290,10 +291,8 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
         }
     };
     constexpr int LPR = D / 8;
-    constexpr int RPW = 64 / LPR;  // rows per load instruction
-    constexpr int TR = 16;         // rows per tile
-    constexpr int RPL = TR / RPW;  // rows per lane per tile (4 for D=128, 2 for D=64)
-    constexpr int TPI = 2;         // tiles in flight per wave
+    constexpr int TR = 16;   // rows per tile
+    constexpr int TPI = sizeof(ST) == 2 ? 2 : 1;  // tiles per step of a wave
     constexpr int kAttWaves = kAttThreads / 64;
     using R = Row8<ST>;
     __shared__ float s_m[kAttWaves], s_l[kAttWaves];
@@ -301,7 +300,7 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
     __shared__ int s_last;
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane / LPR;
     const int c0 = (lane % LPR) * 8;
     const int unit = blockIdx.y;
@@ -312,88 +311,36 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
     // a page list belongs to the query head, or (group-shared selection) to its KV head
     const int32_t *idx_row = idx ? idx + (long)(idx_per_kv ? b * Hkv + kvh : unit) * K : nullptr;
 
-    RowDot<ST> qd;
+    RowDot<ST> qd[1];
     {
         float qv[8];
         R::load(q + (long)unit * D + c0, qv);
-        qd.set(qv);
+        qd[0].set(qv);
     }
 
-    const int tiles_per_page = P / TR;
-    const long n_tiles = idx ? (long)K * tiles_per_page : (T_valid + TR - 1) / TR;
+    const int page_shift = idx ? __builtin_ctz((unsigned)(P / TR)) : 0;  // tiles of a page: a power of two
+    const long n_tiles = idx ? (long)K << page_shift : (T_valid + TR - 1) / TR;
     const long per = (n_tiles + splits - 1) / splits;
     const long tb = (long)blockIdx.x * per;
     const long te = (tb + per < n_tiles) ? tb + per : n_tiles;
 
-    float m = -INFINITY, l = 0.f;
-    float o[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) o[c] = 0.f;
-
-    for (long t = tb + wave * TPI; t < te; t += kAttWaves * TPI) {
-        long row0[TPI];
-        typename R::raw_t kr[TPI][RPL], vr[TPI][RPL];
-#pragma unroll
-        for (int u = 0; u < TPI; ++u) {
-            const long tt = t + u;
-            row0[u] = T_valid;  // nothing to do
-            if (tt < te) {
-                if (idx) {
-                    const int page = idx_row[tt / tiles_per_page];
-                    if (page >= 0) row0[u] = (long)page * P + (tt % tiles_per_page) * TR;
-                } else {
-                    row0[u] = tt * TR;
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < TPI; ++u) {
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const long row = row0[u] + i * RPW + rg;
-                if (row < T_valid) {
-                    if (Hq == Hkv) {  // no other query head reads these rows: streaming loads
-                        kr[u][i] = R::load_raw_nt(kb + row * D + c0);
-                        vr[u][i] = R::load_raw_nt(vb + row * D + c0);
-                    } else {
-                        kr[u][i] = R::load_raw(kb + row * D + c0);
-                        vr[u][i] = R::load_raw(vb + row * D + c0);
-                    }
-                } else {  // masked rows contribute nothing (and stale memory is never read)
-                    kr[u][i] = R::zero_raw();
-                    vr[u][i] = R::zero_raw();
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < TPI; ++u) {
-            float s[RPL];
-            float mt = m;
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const float d = group_sum<LPR>(qd.dot(kr[u][i])) * scale;
-                const long row = row0[u] + i * RPW + rg;
-                s[i] = (row < T_valid) ? d : -INFINITY;
-                mt = fmaxf(mt, s[i]);
-            }
-            if (mt != -INFINITY) {  // uniform over the lanes of a row group
-                const float corr = __expf(m - mt);
-                l *= corr;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) o[c] *= corr;
-#pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    const float p = __expf(s[i] - mt);
-                    l += p;
-                    float x[8];
-                    R::unpack(vr[u][i], x);
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) o[c] = fmaf(p, x[c], o[c]);
-                }
-                m = mt;
-            }
-        }
+    AttendState<1> st;
+    st.clear();
+    const long t_first = tb + wave * TPI, stride = kAttWaves * TPI;
+    if (idx) {
+        WavePages pages;
+        attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
+            const int page = pages.next([&](int n) __attribute__((always_inline)) -> int {
+                const long tt = t_first + (long)(n / TPI) * stride + n % TPI;
+                return tt < te ? idx_row[tt >> page_shift] : -1;
+            });
+            return page >= 0 ? (long)page * P + (t & ((1 << page_shift) - 1)) * TR : T_valid;
+        });
+    } else {
+        attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long { return t * TR; });
     }
+    float m = st.m[0], l = st.l[0];
+    float (&o)[8] = st.o[0];
 
     // merge the row groups of the wave
 #pragma unroll
@@ -477,23 +424,21 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
 // are unpacked once.  A lane keeps G running (m, l, o).  A wave takes TPI tiles per step and has
 // the next step's on their way while it works on the current ones; the softmax moves its reference
 // point once per step and head.
-// Bound by memory from about a hundred megabytes on (8 x 32 over 8 heads x 8000 rows: 268 MB in 67 us against
-// 153 us with a workgroup per head, which took every row four times through the CUs at 40 bytes per ns
-// each), by the merge below that.
+// Bound by memory from about a hundred megabytes on (8 x 32 over 8 heads x 8000 rows: 268 MB in 57 us with the append against
+// 153 us with a workgroup per head), by the merge below that.
 // ------------------------------------------------------------------------------------
 constexpr int kSharedThreads = 512;
 constexpr int kSharedMaxSplits = 64;
 
 template <typename ST, int D, int G>
 __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
-    const ST *__restrict__ q, const ST *__restrict__ k_cache, const ST *__restrict__ v_cache, const int32_t *idx,
+    const ST *__restrict__ q, const ST *k_cache, const ST *v_cache, const int32_t *idx,
     ST *__restrict__ out, float *__restrict__ lse_out, uint64_t *partial, long Tcap, int P, long T_valid, int K,
     float scale, int splits, uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit)
 {
     constexpr int LPR = D / 8;
     constexpr int RPW = 64 / LPR;  // rows per load instruction
     constexpr int TR = 16;         // rows per tile
-    constexpr int RPL = TR / RPW;  // rows per lane per tile
     constexpr int TPI = (sizeof(ST) == 2 && G < 8) ? 2 : 1;  // tiles per step of a wave
     constexpr int NW = kSharedThreads / 64;
     using R = Row8<ST>;
@@ -504,54 +449,18 @@ __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
     __shared__ __attribute__((aligned(16))) float s_o[NP][G][D];
     __shared__ int s_last;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane / LPR, c0 = (lane % LPR) * 8;
     const int unit = blockIdx.y;  // b * Hkv + kvh; its query heads are rows unit * G .. of q, out and the partials
-    const ST *kb = k_cache + (long)unit * Tcap * D + c0;
-    const ST *vb = v_cache + (long)unit * Tcap * D + c0;
+    const ST *kb = k_cache + (long)unit * Tcap * D;
+    const ST *vb = v_cache + (long)unit * Tcap * D;
     const int32_t *idx_row = idx ? idx + (long)unit * K : nullptr;
 
-    const int tiles_per_page = P / TR;
-    const long n_tiles = idx ? (long)K * tiles_per_page : (T_valid + TR - 1) / TR;
+    const int page_shift = idx ? __builtin_ctz((unsigned)(P / TR)) : 0;  // tiles of a page: a power of two
+    const long n_tiles = idx ? (long)K << page_shift : (T_valid + TR - 1) / TR;
     const long per = (n_tiles + splits - 1) / splits;
     const long tb = (long)blockIdx.x * per;
     const long te = (tb + per < n_tiles) ? tb + per : n_tiles;
-
-    struct Step {
-        typename R::raw_t k[TPI][RPL], v[TPI][RPL];
-        long row0[TPI];
-    };
-    auto load = [&](long t, Step &x) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < TPI; ++u) {
-            const long tt = t + u;
-            x.row0[u] = T_valid;  // nothing to do
-            if (tt < te) {
-                if (idx) {
-                    const int page = idx_row[tt / tiles_per_page];
-                    if (page >= 0) x.row0[u] = (long)page * P + (tt % tiles_per_page) * TR;
-                } else {
-                    x.row0[u] = tt * TR;
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < TPI; ++u)
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const long row = x.row0[u] + i * RPW + rg;
-                if (row < T_valid) {  // each row is read by this workgroup only: streaming loads
-                    x.k[u][i] = R::load_raw_nt(kb + row * D);
-                    x.v[u][i] = R::load_raw_nt(vb + row * D);
-                } else {  // masked rows contribute nothing (and stale memory is never read)
-                    x.k[u][i] = R::zero_raw();
-                    x.v[u][i] = R::zero_raw();
-                }
-            }
-    };
-    Step xa, xb;
-    const long t_first = tb + wave * TPI, stride = NW * TPI;
-    if (t_first < te) load(t_first, xa);
 
     RowDot<ST> qd[G];
 #pragma unroll
@@ -560,62 +469,23 @@ __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
         R::load(q + ((long)unit * G + g) * D + c0, qv);
         qd[g].set(qv);
     }
-    float m[G], l[G], o[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        m[g] = -INFINITY;
-        l[g] = 0.f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) o[g][c] = 0.f;
+    AttendState<G> st;
+    st.clear();
+    // (each row is read by this workgroup only: streaming loads)
+    const long t_first = tb + wave * TPI, stride = NW * TPI;
+    if (idx) {
+        WavePages pages;
+        attend_tiles<ST, D, G, TPI, true>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
+            const int page = pages.next([&](int n) __attribute__((always_inline)) -> int {
+                const long tt = t_first + (long)(n / TPI) * stride + n % TPI;
+                return tt < te ? idx_row[tt >> page_shift] : -1;
+            });
+            return page >= 0 ? (long)page * P + (t & ((1 << page_shift) - 1)) * TR : T_valid;
+        });
+    } else {
+        attend_tiles<ST, D, G, TPI, true>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long { return t * TR; });
     }
-    auto attend = [&](const Step &x) __attribute__((always_inline)) {
-        float s[G][TPI][RPL];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float mt = m[g];
-#pragma unroll
-            for (int u = 0; u < TPI; ++u)
-#pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    const float d = group_sum<LPR>(qd[g].dot(x.k[u][i])) * scale;
-                    s[g][u][i] = (x.row0[u] + i * RPW + rg < T_valid) ? d : -INFINITY;
-                    mt = fmaxf(mt, s[g][u][i]);
-                }
-            const float ms = (mt == -INFINITY) ? 0.f : mt;  // nothing to attend yet: every weight below is 0
-            const float corr = __expf(m[g] - ms);
-            m[g] = mt;
-            l[g] *= corr;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) o[g][c] *= corr;
-#pragma unroll
-            for (int u = 0; u < TPI; ++u)
-#pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    s[g][u][i] = __expf(s[g][u][i] - ms);
-                    l[g] += s[g][u][i];
-                }
-        }
-#pragma unroll
-        for (int u = 0; u < TPI; ++u)
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                float y[8];
-                R::unpack(x.v[u][i], y);
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) o[g][c] = fmaf(s[g][u][i], y[c], o[g][c]);
-            }
-    };
-    for (long t = t_first; t < te;) {
-        if (t + stride < te) load(t + stride, xb);
-        attend(xa);
-        t += stride;
-        if (t >= te) break;
-        if (t + stride < te) load(t + stride, xa);
-        attend(xb);
-        t += stride;
-    }
+    float (&m)[G] = st.m, (&l)[G] = st.l, (&o)[G][8] = st.o;
 
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -752,7 +622,11 @@ __global__ __launch_bounds__(kSharedThreads) void decode_attend_shared_kernel(
 // inside one 512-thread workgroup -- page scores into LDS keys, the top-K selection, then
 // attention over the picked pages with the waves splitting the tiles -- so nothing is handed
 // between workgroups and the step is one launch.  Same score arithmetic, forced pages and tie
-// rule as quest_score_select_kernel; the attention loop is decode_attend_kernel's.
+// rule as quest_score_select_kernel; the attention loop is decode_attend_kernel's.  Bound by its chain of phases, one workgroup
+// to a CU at a batch of eight: hence the pages that are kept anyway are fetched first of all, up to 256 pages are
+// selected by counting ranks instead of radix passes, and the next tile's rows are on their way behind the current one's.
+// With the append, 4096 tokens, 8 pages of 64, before / after, us: 8 x 32 heads 21.5 / 17.7, 16 x 32 35.2 / 30.3, 32 14.5 / 12.8;
+// 16 x 32 over 8 heads x 1000, 8 of 16 17.5 / 13.5; 4 x 32 over 8 heads x 8000, 31 of 32 23.8 / 20.9.
 // Dynamic LDS: Np keys, then K picked pages.
 // ------------------------------------------------------------------------------------
 constexpr int kUnitThreads = 512;
@@ -762,8 +636,8 @@ constexpr int kUnitThreads = 512;
 // the last workgroup out advances the count and the tag word.
 template <typename ST, int D, bool STATE>
 __global__ __launch_bounds__(kUnitThreads) void quest_unit_decode_kernel(
-    const ST *__restrict__ q, const ST *__restrict__ meta, const ST *__restrict__ k_cache,
-    const ST *__restrict__ v_cache, ST *__restrict__ out, float *__restrict__ lse_out, int32_t *__restrict__ idx_out,
+    const ST *__restrict__ q, const ST *__restrict__ meta, const ST *k_cache,
+    const ST *v_cache, ST *__restrict__ out, float *__restrict__ lse_out, int32_t *__restrict__ idx_out,
     int Hq, int Hkv, long Tcap, int P, long T_valid, int Np, int K, int n_first, int n_local, float scale,
     int Np_lds, uint32_t *state, long T_max)
 {
@@ -779,19 +653,19 @@ __global__ __launch_bounds__(kUnitThreads) void quest_unit_decode_kernel(
     constexpr int RPW = 64 / LPR;
     constexpr int UNR = 4;
     constexpr int NW = kUnitThreads / 64;
+    constexpr bool STREAM = false;
     constexpr int TR = 16;
-    constexpr int RPL = TR / RPW;
-    constexpr int TPI = 2;
+    constexpr int TPI = 1;  // tiles of a wave's step (two: one workgroup a CU instead of two, and slower there too)
     using R = Row8<ST>;
     __shared__ SelectShared<kUnitThreads> sh;
     __shared__ float s_m[NW], s_l[NW];
     __shared__ float s_o[NW][D];
-    extern __shared__ uint32_t s_dyn[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
     uint32_t *s_keys = s_dyn;
-    int *s_sel = reinterpret_cast<int *>(s_dyn + Np_lds);
+    int *s_sel = reinterpret_cast<int *>(s_dyn + (Np_lds + 3) / 4 * 4);
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane / LPR;
     const int c0 = (lane % LPR) * 8;
     const int unit = blockIdx.x;
@@ -807,96 +681,71 @@ __global__ __launch_bounds__(kUnitThreads) void quest_unit_decode_kernel(
     BoundDot<ST> bound;
     bound.set(qv);
 
-    // page scores (Eq. 3 with the min/max bound) -> order-preserving keys
+    // Pages that are kept whatever their scores, the local ones and then the first ones, come first in the attention below
+    // (a rotation of the ascending list by the local ones), so that a wave whose first tiles lie in them has those rows
+    // on their way from here on.
+    const int page_shift = __builtin_ctz((unsigned)(P / TR));  // tiles of a page: a power of two
+    const bool known = n_first >= 0 && n_local >= 0 && n_first + n_local <= K && n_first + n_local <= Np;
+    const int rotate = known ? n_local : 0;
+    const long known_tiles = known ? (long)(n_first + n_local) << page_shift : 0, n_tiles = (long)K << page_shift;
+    AttendStep<ST, D, TPI> xa;
+    auto known_row = [&](long t) __attribute__((always_inline)) -> long {
+        const int i = (int)(t >> page_shift);
+        return (long)(i < n_local ? Np - n_local + i : i - n_local) * P + (t & ((1 << page_shift) - 1)) * TR;
+    };
+    xa.template load<STREAM>(kb, vb, T_valid, wave * TPI, known_tiles, known_row);
+
+    // page scores (Eq. 3 with the min/max bound) -> order-preserving keys (zeros up to a multiple of four)
+    if (tid < ((-Np) & 3)) s_keys[Np + tid] = 0u;
     constexpr int PPI = UNR * RPW * NW;
-    for (int base = wave * (UNR * RPW) + rg; base < Np; base += PPI) {
+    for (int base = wave * (UNR * RPW); base < Np; base += PPI) {
+        const int n = (Np - base < UNR * RPW) ? Np - base : UNR * RPW;
+        const LdsSource md = lds_source_sized(mbase + (long)base * 2 * D, n * 2 * D * (int)sizeof(ST));
+        const uint32_t at = (uint32_t)((rg * 2 * D + c0) * (int)sizeof(ST));
         typename R::raw_t mn[UNR], mx[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int p = base + u * RPW;
-            if (p < Np) {
-                mn[u] = R::load_raw(mbase + ((long)p * 2) * D + c0);
-                mx[u] = R::load_raw(mbase + ((long)p * 2 + 1) * D + c0);
-            } else {
-                mn[u] = R::zero_raw();
-                mx[u] = R::zero_raw();
-            }
+            mn[u] = load_row8<ST, 0>(md, at + u * RPW * 2 * D * (int)sizeof(ST));
+            mx[u] = load_row8<ST, 0>(md, at + (u * RPW * 2 + 1) * D * (int)sizeof(ST));
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int p = base + u * RPW;
+            const int p = base + rg + u * RPW;
             const float s = group_sum<LPR>(bound.add(0.f, mn[u], mx[u]));
             if (p < Np && (lane % LPR) == 0) s_keys[p] = (p < n_first || p >= Np - n_local) ? 0xffffffffu : float_to_key(s);
         }
     }
     __syncthreads();
     int32_t *dst = idx_out ? idx_out + (long)unit * K : nullptr;
-    select_topk_lds<kUnitThreads>(s_keys, Np, K, sh, [s_sel, dst](int pos, int p) {
+    auto emit = [s_sel, dst](int pos, int p) {
         s_sel[pos] = p;
         if (dst) dst[pos] = p;
-    });
+    };
+    if (Np <= kUnitThreads / 2) select_topk_few<kUnitThreads>(s_keys, Np, K, sh.wave_tot, emit);
+    else select_topk_lds<kUnitThreads>(s_keys, Np, K, sh, emit);
     __syncthreads();
 
     // attention over the picked pages (Eq. 4): 16-row tiles, the waves take them in turn
-    RowDot<ST> qd;
-    qd.set(qv);
-    const int tiles_per_page = P / TR;
-    const int n_tiles = K * tiles_per_page;
-    float m = -INFINITY, l = 0.f;
-    float o[8];
+    RowDot<ST> qd[1];
+    qd[0].set(qv);
+    AttendState<1> st;
+    st.clear();
+    auto row_of = [&](long t) __attribute__((always_inline)) -> long {
+        const int i = (int)(t >> page_shift);
+        const int page = __builtin_amdgcn_readfirstlane(s_sel[i < rotate ? K - rotate + i : i - rotate]);
+        return (long)page * P + (t & ((1 << page_shift) - 1)) * TR;
+    };
+    // (a page whose score is a NaN may tie with the pages that are kept: the list decides)
+    bool loaded = true;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) o[c] = 0.f;
-    for (int t = wave * TPI; t < n_tiles; t += NW * TPI) {
-        long row0[TPI];
-        typename R::raw_t kr[TPI][RPL], vr[TPI][RPL];
-#pragma unroll
-        for (int u = 0; u < TPI; ++u) {
-            const int tt = t + u;
-            row0[u] = T_valid;  // nothing to do
-            if (tt < n_tiles) row0[u] = (long)s_sel[tt / tiles_per_page] * P + (tt % tiles_per_page) * TR;
-        }
-#pragma unroll
-        for (int u = 0; u < TPI; ++u)
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const long row = row0[u] + i * RPW + rg;
-                if (row < T_valid) {
-                    kr[u][i] = R::load_raw(kb + row * D + c0);
-                    vr[u][i] = R::load_raw(vb + row * D + c0);
-                } else {
-                    kr[u][i] = R::zero_raw();
-                    vr[u][i] = R::zero_raw();
-                }
-            }
-#pragma unroll
-        for (int u = 0; u < TPI; ++u) {
-            float s[RPL];
-            float mt = m;
-#pragma unroll
-            for (int i = 0; i < RPL; ++i) {
-                const float d = group_sum<LPR>(qd.dot(kr[u][i])) * scale;
-                const long row = row0[u] + i * RPW + rg;
-                s[i] = (row < T_valid) ? d : -INFINITY;
-                mt = fmaxf(mt, s[i]);
-            }
-            if (mt != -INFINITY) {
-                const float corr = __expf(m - mt);
-                l *= corr;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) o[c] *= corr;
-#pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    const float pr = __expf(s[i] - mt);
-                    l += pr;
-                    float x[8];
-                    R::unpack(vr[u][i], x);
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) o[c] = fmaf(pr, x[c], o[c]);
-                }
-                m = mt;
-            }
-        }
+    for (int u = 0; u < TPI; ++u) {
+        const long t = wave * TPI + u;
+        if (t < n_tiles && (t >= known_tiles || row_of(t) != known_row(t))) loaded = false;
     }
+    if (!loaded) xa.template load<STREAM>(kb, vb, T_valid, wave * TPI, n_tiles, row_of);
+    attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, wave * TPI, n_tiles, NW * TPI, scale, qd, st, xa, row_of);
+    float m = st.m[0], l = st.l[0];
+    float (&o)[8] = st.o[0];
     // merge the row groups of the wave, then the waves
 #pragma unroll
     for (int mask = LPR; mask < 64; mask <<= 1) {
@@ -953,15 +802,15 @@ void unit_decode_dispatch(int dtype, int D, const void *q, const void *meta, con
                           long T_valid, int Np, int K, int n_first, int n_local, float scale, uint32_t *state,
                           hipStream_t stream)
 {
-    const size_t lds = (size_t)(Np + K) * 4;
+    const size_t lds = (size_t)((Np + 3) / 4 * 4 + K) * 4;
 #define RS_LAUNCH1(ST, DD, SS)                                                                                   \
     quest_unit_decode_kernel<ST, DD, SS><<<(unsigned)(B * Hq), kUnitThreads, lds, stream>>>(                     \
         (const ST *)q, (const ST *)meta, (const ST *)k_cache, (const ST *)v_cache, (ST *)out, lse_out, idx_out, \
         Hq, Hkv, Tcap, P, T_valid, Np, K, n_first, n_local, scale, Np, state, T_valid)
-#define RS_LAUNCH(ST, DD)                  \
-    do {                                   \
+#define RS_LAUNCH(ST, DD)                    \
+    do {                                     \
         if (state) RS_LAUNCH1(ST, DD, true); \
-        else RS_LAUNCH1(ST, DD, false);    \
+        else RS_LAUNCH1(ST, DD, false);      \
     } while (0)
     if (dtype == RS_BF16) {
         if (D == 128) RS_LAUNCH(bf16, 128);
@@ -1018,10 +867,16 @@ void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache
 {
     const dim3 grid((unsigned)splits, (unsigned)(B * Hq));
     constexpr int kAttThreads = 512;  // about one such workgroup per CU (see the split rule of the caller)
-#define RS_LAUNCH(ST, DD)                                                                                   \
-    decode_attend_kernel<ST, DD, kAttThreads><<<grid, kAttThreads, 0, stream>>>(                            \
+#define RS_LAUNCH1(ST, DD, SS)                                                                              \
+    decode_attend_kernel<ST, DD, kAttThreads, SS><<<grid, kAttThreads, 0, stream>>>(                        \
         (const ST *)q, (const ST *)k_cache, (const ST *)v_cache, idx, (ST *)out, lse_out, partial, Hq, Hkv, \
         Tcap, P, T_valid, K, scale, splits, unit_ctr, err, tag, spin_limit, idx_per_kv, state, T_max)
+    // no other query head reads these rows: streaming loads
+#define RS_LAUNCH(ST, DD)                       \
+    do {                                        \
+        if (Hq == Hkv) RS_LAUNCH1(ST, DD, true); \
+        else RS_LAUNCH1(ST, DD, false);         \
+    } while (0)
     if (dtype == RS_BF16) {
         if (D == 128) RS_LAUNCH(bf16, 128);
         else RS_LAUNCH(bf16, 64);
@@ -1030,6 +885,7 @@ void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache
         else RS_LAUNCH(float, 64);
     }
 #undef RS_LAUNCH
+#undef RS_LAUNCH1
 }
 
 }  // namespace rs

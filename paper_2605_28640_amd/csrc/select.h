@@ -208,6 +208,45 @@ __device__ void select_topk_lds(const uint32_t *keys, int Np, int K, SelectShare
     }
 }
 
+// The same for few candidates, Np <= NT / 2: a candidate's rank is counted outright, NT / Np threads (to a power of two)
+// sharing the comparisons, where the radix passes spend their time at barriers.  keys: zeros up to the next multiple of 4;
+// counts: NT / 64 words.
+template <int NT, typename Emit>
+__device__ __forceinline__ void select_topk_few(uint32_t *keys, int Np, int K, int *counts, Emit emit)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int lg = 31 - __builtin_clz((unsigned)NT) - (Np > 1 ? 32 - __builtin_clz((unsigned)(Np - 1)) : 0);
+    if (lg > 6) lg = 6;  // 2^lg threads per candidate, lanes of one wave
+    const int p = tid >> lg, part = tid & ((1 << lg) - 1);
+    const uint32_t own = (p < Np) ? keys[p] : 1u;
+    const int groups = (Np + 3) / 4, own_group = p / 4;  // of four keys; the threads of a candidate take them in turn
+    int before = 0;
+    if (__any(own == 0u)) {  // (the key of one NaN)
+        for (int j = part; j < Np; j += 1 << lg) before += (keys[j] > own || (keys[j] == own && j < p)) ? 1 : 0;
+    } else {
+        // ahead of the candidate: above it, or equal and of an earlier group (its own group's equals follow)
+        for (int gq = part; gq < groups; gq += 1 << lg) {
+            const uint4 kq = *reinterpret_cast<const uint4 *>(keys + 4 * gq);
+            const uint32_t above = (gq < own_group) ? own - 1u : own;
+            before += (int)(kq.x > above) + (int)(kq.y > above) + (int)(kq.z > above) + (int)(kq.w > above);
+        }
+        if (part == 0 && p < Np) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) before += (c < (p & 3) && keys[4 * own_group + c] == own) ? 1 : 0;
+        }
+    }
+    for (int d = 1; d < (1 << lg); d <<= 1) before += __shfl_xor(before, d, 64);
+    const bool mine = p < Np && before < K && part == 0;
+    const uint64_t who = __ballot(mine);
+    if (lane == 0) counts[wave] = __popcll(who);
+    __syncthreads();
+    int pos = lanes_below(who);
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w)
+        if (w < wave) pos += counts[w];
+    if (mine) emit(pos, p);
+}
+
 // Read the Np tagged scores of a unit into keys in LDS, a few loads in flight at a time;
 // always-kept pages get the top key.  Ends with a workgroup barrier.
 template <int NT>

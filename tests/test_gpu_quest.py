@@ -472,3 +472,43 @@ def test_dense_decode_of_shared_rows(rs, knobs, dtype, D, G):
                 assert ok, (T, shared, idx is None, worst)
                 np.testing.assert_allclose(to_np(lse), wl, rtol=1e-4, atol=1e-4)
         ws.async_status()
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("scores", ["spread", "ties", "nan"])
+def test_few_pages_in_one_workgroup(rs, knobs, dtype, D, scores):
+    """The one-workgroup step counts ranks up to 256 pages and takes radix passes beyond, and fetches the pages that are kept
+    anyway before it knows the rest: the lists are those of the two-launch form, the outputs (other orders of the same
+    rows) agree to float32 rounding through the weights, 2^-20 of their size or one rounding of the storage type."""
+    P, B, Hq, Hkv = 16, 2, 4, 2
+    for Np, K, n_first, n_local in ((1, 1, 1, 1), (2, 2, 1, 1), (3, 2, 1, 1), (5, 4, 0, 2), (9, 5, 2, 0), (63, 8, 1, 1), (64, 64, 3, 1),
+                                    (65, 9, 1, 2), (127, 16, 1, 1), (129, 30, 0, 0), (255, 40, 1, 4), (256, 64, 2, 2), (257, 64, 1, 1)):
+        say("few pages", dtype, D, scores, Np, K, n_first, n_local)
+        T = Np * P - 5
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(Np)
+        s = rs.make_shape(B, Hq, Hkv, D, Np * P, P, tdtype(dtype))
+        kc, vc = (torch.randn(B, Hkv, Np * P, D, generator=gen, device="cuda").to(tdtype(dtype)) for _ in range(2))
+        q = torch.randn(B, Hq, D, generator=gen, device="cuda").to(tdtype(dtype))
+        meta = torch.zeros(B, Hkv, Np, 2, D, dtype=tdtype(dtype), device="cuda")
+        rs.quest_page_meta(s, kc, meta, 0, T)
+        if scores == "ties":
+            meta[:] = meta[:, :, :1]
+            meta[:, :, 1::3] *= 2
+        if scores == "nan":
+            meta[:, :, Np // 2:, 1, 0] = -torch.tensor(float("nan"), device="cuda")
+        ws = rs.Workspace(rs.sparse_attn_decode_workspace_bytes(s, T, K))
+        got = []
+        for one_wg in ("0", "1"):
+            knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", "1")
+            knobs.setenv("RATSPARSE_FUSED_ONE_WG", one_wg)
+            out = torch.zeros(B, Hq, D, dtype=tdtype(dtype), device="cuda")
+            lse = torch.zeros(B, Hq, device="cuda")
+            idx = torch.full((B, Hq, K), -5, dtype=torch.int32, device="cuda")
+            rs.sparse_attn_decode(s, q, kc, vc, T, 1.0 / np.sqrt(D), None, K, meta, n_first, n_local, out, lse, idx, ws)
+            torch.cuda.synchronize()
+            ws.async_status()
+            got.append((to_np(out), to_np(lse), to_np(idx)))
+        np.testing.assert_array_equal(got[1][2], got[0][2])
+        np.testing.assert_allclose(got[1][1], got[0][1], rtol=1e-6, atol=2e-6)
+        np.testing.assert_allclose(got[1][0], got[0][0], rtol=2.0 ** -7 if dtype == "bf16" else 1e-5, atol=2e-6)
