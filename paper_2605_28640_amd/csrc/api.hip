@@ -150,7 +150,6 @@ static void knobs_read()
     k.fused_satt = env_or_unset("RATSPARSE_FUSED_SATT");
     k.fused_fine = env_or_unset("RATSPARSE_FUSED_FINE");
     k.fused_fine_pct = env_or_unset("RATSPARSE_FUSED_FINE_PCT");
-    k.fused_nt = env_or_unset("RATSPARSE_FUSED_NT");
     k.fused_pingpong = env_or_unset("RATSPARSE_FUSED_PINGPONG");
     k.fused_two_launch = env_or_unset("RATSPARSE_FUSED_TWO_LAUNCH");
     k.fused_one_wg = env_or_unset("RATSPARSE_FUSED_ONE_WG");
@@ -250,7 +249,6 @@ static long fused_setup(FusedParams &prm, const rs_shape *s, const DecodeLayout 
     prm.units_fine = (int)(units * fine_pct / 100);
     prm.S_max = kMaxAttSplits;
     prm.reverse = knob_or(kn.fused_pingpong, 1) ? (int)(T_valid & 1) : 0;
-    prm.nt_kv = knob_or(kn.fused_nt, 1);  // bit 0: K/V pages, bit 1: page metadata
     prm.scale = scale; prm.tag = 0; prm.spin_limit = g_spin_limit.load();
 #ifdef RS_FUSED_TRACE
     prm.trace = (uint64_t *)(w + L.off_trace);

@@ -61,76 +61,101 @@ struct AttendStep {
     }
 };
 
-// Tiles t0, t0 + 1, ... + TPI - 1, whose rows are on their way in xa, then `stride` on, as far as they lie below te.  A wave
-// has the next step's rows on their way while it works on the current ones: 16 KB of bfloat16 rows of 128 channels at
-// TPI = 2 and twice that at the peak.  The softmax moves its reference point once per step and head.
-// (kb, vb: not through restricted pointers, which would let the compiler move the loads.)
-template <typename ST, int D, int G, int TPI, bool STREAM, typename RowOf>
-__device__ __forceinline__ void attend_tiles(const ST *kb, const ST *vb, long T_valid, long t0, long te, long stride, float scale,
-                                             const RowDot<ST> (&qd)[G], AttendState<G> &st, AttendStep<ST, D, TPI> &xa, RowOf row_of)
+// the rows of a step into a lane's state; the softmax moves its reference point once per step and head
+template <typename ST, int D, int G, int TPI>
+__device__ __forceinline__ void attend_one(const AttendStep<ST, D, TPI> &x, float scale, const RowDot<ST> (&qd)[G], AttendState<G> &st)
 {
-    using Step = AttendStep<ST, D, TPI>;
-    constexpr int LPR = D / 8, RPW = Step::RPW, RPL = Step::RPL;
+    constexpr int LPR = D / 8, RPW = 64 / LPR, RPL = 16 / RPW;
     const int rg = (threadIdx.x & 63) / LPR;
-    auto attend = [&](const Step &x) __attribute__((always_inline)) {
-        float s[G][TPI][RPL];
+    float s[G][TPI][RPL];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float mt = st.m[g];
-#pragma unroll
-            for (int u = 0; u < TPI; ++u)
-#pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    const float d = group_sum<LPR>(qd[g].dot(x.k[u][i])) * scale;
-                    s[g][u][i] = (i * RPW + rg < x.rows[u]) ? d : -INFINITY;
-                    mt = fmaxf(mt, s[g][u][i]);
-                }
-            const float ms = (mt == -INFINITY) ? 0.f : mt;  // nothing to attend yet: every weight below is 0
-            const float corr = __expf(st.m[g] - ms);
-            st.m[g] = mt;
-            st.l[g] *= corr;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) st.o[g][c] *= corr;
-#pragma unroll
-            for (int u = 0; u < TPI; ++u)
-#pragma unroll
-                for (int i = 0; i < RPL; ++i) {
-                    s[g][u][i] = __expf(s[g][u][i] - ms);
-                    st.l[g] += s[g][u][i];
-                }
-        }
+    for (int g = 0; g < G; ++g) {
+        float mt = st.m[g];
 #pragma unroll
         for (int u = 0; u < TPI; ++u)
 #pragma unroll
             for (int i = 0; i < RPL; ++i) {
-                float y[8];
-                Row8<ST>::unpack(x.v[u][i], y);
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) st.o[g][c] = fmaf(s[g][u][i], y[c], st.o[g][c]);
+                const float d = group_sum<LPR>(qd[g].dot(x.k[u][i])) * scale;
+                s[g][u][i] = (i * RPW + rg < x.rows[u]) ? d : -INFINITY;
+                mt = fmaxf(mt, s[g][u][i]);
             }
-    };
+        const float ms = (mt == -INFINITY) ? 0.f : mt;  // nothing to attend yet: every weight below is 0
+        const float corr = __expf(st.m[g] - ms);
+        st.m[g] = mt;
+        st.l[g] *= corr;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) st.o[g][c] *= corr;
+#pragma unroll
+        for (int u = 0; u < TPI; ++u)
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                s[g][u][i] = __expf(s[g][u][i] - ms);
+                st.l[g] += s[g][u][i];
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < TPI; ++u)
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            float y[8];
+            Row8<ST>::unpack(x.v[u][i], y);
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) st.o[g][c] = fmaf(s[g][u][i], y[c], st.o[g][c]);
+        }
+}
+
+// Tiles t0, t0 + 1, ... + TPI - 1, whose rows are on their way in xa, then `stride` on, as far as they lie below te.  A wave
+// has the next step's rows on their way while it works on the current ones: 16 KB of bfloat16 rows of 128 channels at
+// TPI = 2 and twice that at the peak.
+// (kb, vb: not through restricted pointers, which would let the compiler move the loads.)  in_last_step(): called before the
+// arithmetic of the wave's last step.
+struct NoLastStep {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <typename ST, int D, int G, int TPI, bool STREAM, typename RowOf, typename Last = NoLastStep>
+__device__ __forceinline__ void attend_tiles(const ST *kb, const ST *vb, long T_valid, long t0, long te, long stride, float scale,
+                                             const RowDot<ST> (&qd)[G], AttendState<G> &st, AttendStep<ST, D, TPI> &xa, RowOf row_of,
+                                             Last in_last_step = Last())
+{
+    using Step = AttendStep<ST, D, TPI>;
+    auto attend = [&](const Step &x) __attribute__((always_inline)) { attend_one<ST, D, G, TPI>(x, scale, qd, st); };
     if (t0 >= te) return;
     Step xb;
     for (long t = t0;;) {
         xb.template load<STREAM>(kb, vb, T_valid, t + stride, te, row_of);
+        if (t + stride >= te) in_last_step();
         attend(xa);
         t += stride;
         if (t >= te) break;
         xa.template load<STREAM>(kb, vb, T_valid, t + stride, te, row_of);
+        if (t + stride >= te) in_last_step();
         attend(xb);
         t += stride;
         if (t >= te) break;
     }
 }
-template <typename ST, int D, int G, int TPI, bool STREAM, typename RowOf>
+template <typename ST, int D, int G, int TPI, bool STREAM, typename RowOf, typename Last = NoLastStep>
 __device__ __forceinline__ void attend_tiles(const ST *kb, const ST *vb, long T_valid, long t0, long te, long stride, float scale,
-                                             const RowDot<ST> (&qd)[G], AttendState<G> &st, RowOf row_of)
+                                             const RowDot<ST> (&qd)[G], AttendState<G> &st, RowOf row_of, Last in_last_step = Last())
 {
     AttendStep<ST, D, TPI> xa;
     xa.template load<STREAM>(kb, vb, T_valid, t0, te, row_of);
-    attend_tiles<ST, D, G, TPI, STREAM>(kb, vb, T_valid, t0, te, stride, scale, qd, st, xa, row_of);
+    attend_tiles<ST, D, G, TPI, STREAM>(kb, vb, T_valid, t0, te, stride, scale, qd, st, xa, row_of, in_last_step);
+}
+
+// The same a step at a time, for kernels whose other waves on the SIMD (four in all) fill the wait.
+template <typename ST, int D, int G, int TPI, bool STREAM, typename RowOf, typename Last = NoLastStep>
+__device__ __forceinline__ void attend_tiles_in_turn(const ST *kb, const ST *vb, long T_valid, long t0, long te, long stride, float scale,
+                                                     const RowDot<ST> (&qd)[G], AttendState<G> &st, RowOf row_of, Last in_last_step = Last())
+{
+    for (long t = t0; t < te; t += stride) {
+        AttendStep<ST, D, TPI> x;
+        x.template load<STREAM>(kb, vb, T_valid, t, te, row_of);
+        if (t + stride >= te) in_last_step();
+        attend_one<ST, D, G, TPI>(x, scale, qd, st);
+    }
 }
 
 // A wave's entries of a page list, one per lane, fetched 64 at a time: entry n is that of the n-th tile the wave takes.

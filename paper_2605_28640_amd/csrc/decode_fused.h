@@ -22,7 +22,6 @@ struct FusedParams {
     int units_fine, S_att_fine;  // the last units_fine units (in ticket order) use S_att_fine slices
     int S_max;                   // slices the partial buffer holds per unit
     int reverse;            // walk the units from the last to the first
-    int nt_kv;              // stream K/V pages with non-temporal loads
     float scale;
     uint32_t tag;
     int spin_limit;

@@ -16,13 +16,14 @@
 // an already-running workgroup is producing: whoever waits holds a larger ticket than the
 // item it waits for, tickets are handed out in increasing order to running workgroups,
 // and the item with the smallest outstanding ticket never waits.
+#include "attend.h"
 #include "common.h"
 #include "select.h"
 #include "decode_fused.h"
 
 namespace rs {
 
-template <typename ST, int D, int kFusedThreads, bool STATE>
+template <typename ST, int D, int kFusedThreads, bool STATE, bool STREAM>
 __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_fused_kernel(const FusedParams P_)
 {
     constexpr int kFusedWaves = kFusedThreads / 64;
@@ -58,7 +59,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
     extern __shared__ uint32_t s_keys[];  // Np keys for the selection
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = lane / LPR;
     const int cl = lane % LPR;
     const int c0 = cl * 8;
@@ -109,45 +110,48 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
             BoundDot<ST> bound;
             bound.set(qv);
 
-            constexpr int UNR = 4;
+            constexpr int UNR = sizeof(ST) == 2 ? 4 : 2;  // pages of a lane per step
             constexpr int PPI = UNR * RPW * kFusedWaves;  // pages per workgroup step
             const int per = (Np_ + a.S_score - 1) / a.S_score;
             const int pb = slice * per;
             const int pe = (pb + per < Np_) ? pb + per : Np_;
             const bool sel_here = (slice == a.S_score - 1);
-            for (int base = pb + wave * (UNR * RPW) + rg; base < pe; base += PPI) {
-                if (!sel_here && base + PPI >= pe) fetch_next();
+            // a wave's 8 to 32 pages of a step on their way (bounds rows follow each other; pages past the slice come as zeros)
+            struct PageStep {
                 typename R::raw_t mn[UNR], mx[UNR];
+            };
+            constexpr int PPW = UNR * RPW, ROW = D * (int)sizeof(ST);
+            auto load_pages = [&](int base, PageStep &x) __attribute__((always_inline)) {
+                const int n = (pe - base < PPW) ? pe - base : PPW;
+                const LdsSource md = lds_source_sized(mbase + (n > 0 ? (long)base : 0) * 2 * D, (n > 0 ? n : 0) * 2 * ROW);
+                const uint32_t at = (uint32_t)(rg * 2 * ROW + c0 * (int)sizeof(ST));
 #pragma unroll
                 for (int u = 0; u < UNR; ++u) {
-                    const int p = base + u * RPW;
-                    if (p < pe) {
-                        if (a.nt_kv & 2) {
-                            mn[u] = R::load_raw_nt(mbase + ((long)p * 2) * D + c0);
-                            mx[u] = R::load_raw_nt(mbase + ((long)p * 2 + 1) * D + c0);
-                        } else {
-                            mn[u] = R::load_raw(mbase + ((long)p * 2) * D + c0);
-                            mx[u] = R::load_raw(mbase + ((long)p * 2 + 1) * D + c0);
-                        }
-                    } else {
-                        mn[u] = R::zero_raw();
-                        mx[u] = R::zero_raw();
-                    }
+                    x.mn[u] = load_row8<ST, 0>(md, at + u * RPW * 2 * ROW);
+                    x.mx[u] = load_row8<ST, 0>(md, at + (u * RPW * 2 + 1) * ROW);
                 }
-                // the wave's UNR * RPW pages are consecutive.  Every lane of a row group holds the group's
-                // sums; lane u of the group keeps page u's, and the UNR first lanes of the RPW groups then
-                // publish the wave's scores with ONE store instruction of adjacent 8-byte words (whole lines
-                // on the write-through path; which lane writes which word of a line does not matter)
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" ::: "memory");
+            };
+            // The wave's pages are consecutive.  Every lane of a row group holds the group's sums; lane u of the group keeps page
+            // u's, and the UNR first lanes of the RPW groups then publish the wave's scores with ONE store of adjacent
+            // 8-byte words (whole lines on the write-through path; which lane writes which word of a line does not matter).
+            auto score_pages = [&](int base, const PageStep &x) __attribute__((always_inline)) {
                 float mine = 0.f;
 #pragma unroll
                 for (int u = 0; u < UNR; ++u) {
-                    const float s = group_sum<LPR>(bound.add(0.f, mn[u], mx[u]));
+                    const float s = group_sum<LPR>(bound.add(0.f, x.mn[u], x.mx[u]));
                     if (cl == u) mine = s;
                 }
-                {
-                    const int p = base + cl * RPW;
-                    if (cl < UNR && p < pe) publish_f32(&srow[p], mine, tag_);
-                }
+                const int p = rg + cl * RPW;  // of the wave's
+                const int n = (pe - base < PPW) ? pe - base : PPW;
+                if (cl < UNR && p < n) publish_f32(&srow[base + p], mine, tag_);
+            };
+            for (int base = pb + wave * PPW; base < pe; base += PPI) {
+                PageStep xa;
+                load_pages(base, xa);
+                if (!sel_here && base + PPI >= pe) fetch_next();
+                score_pages(base, xa);
             }
             mark(item, 1);
             // the unit's last slice carries the largest ticket: every other slice is already
@@ -187,110 +191,49 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
             const uint64_t *sel = a.idx_tagged + (long)unit * a.K;
 
             constexpr int TR = 16;
-            constexpr int RPL = TR / RPW;
-            constexpr int TPI = 2;
-            RowDot<ST> qd;
+            constexpr int TPI = sizeof(ST) == 2 ? 2 : 1;
+            RowDot<ST> qd[1];
             {
                 float qv[8];
                 R::load((const ST *)a.q + (long)unit * D + c0, qv);
-                qd.set(qv);
+                qd[0].set(qv);
             }
 
-            const int tiles_per_page = a.P / TR;
-            const int n_tiles = a.K * tiles_per_page;
+            const int page_shift = __builtin_ctz((unsigned)(a.P / TR));  // tiles of a page: a power of two
+            const int n_tiles = a.K << page_shift;
             const int per = (n_tiles + S_att - 1) / S_att;
             const int tb = slice * per;
             const int te = (tb + per < n_tiles) ? tb + per : n_tiles;
-
-            float m = -INFINITY, l = 0.f;
-            float o[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) o[c] = 0.f;
-
             const bool finish = (slice == S_att - 1);  // largest ticket of the unit: folds the others
-            // The list entries of the tiles this wave will take come in at once, one per lane (lane j: step
-            // j / TPI, tile j % TPI of the step), each lane waiting for its own word if the selection is
-            // still being written; the steps then read them lane to scalar.  Otherwise every step would
-            // begin with a trip to memory for its entries before it can ask for the rows.
-            constexpr int SPC = 64 / TPI;  // steps one such fetch covers
-            uint32_t my_page = 0xffffffffu;
-            int step_i = 0;
-            for (int t = tb + wave * TPI; t < te; t += kFusedWaves * TPI, ++step_i) {
-                if (!finish && t + kFusedWaves * TPI >= te) fetch_next();
-                if (step_i % SPC == 0) {
-                    const int mt = t + (lane / TPI) * (kFusedWaves * TPI) + (lane % TPI);
-                    my_page = 0xffffffffu;
-                    if (mt < te) {
-                        const uint64_t *wp = &sel[mt / tiles_per_page];
-                        uint64_t w2 = load_u64_agent(wp);
-                        int spins = 0;
-                        while ((uint32_t)(w2 >> 32) != tag_) {  // the selection is still being written
-                            if (++spins > a.spin_limit) {
-                                atomicExch(a.err, 1u);
-                                break;
-                            }
-                            __builtin_amdgcn_s_sleep(2);
-                            w2 = load_u64_agent(wp);
+
+            // The list entries of the tiles this wave will take come in at once, one per lane, each lane waiting for its own word
+            // if the selection is still being written.  Otherwise every step would begin with a trip to memory for its
+            // entries before it can ask for the rows.
+            AttendState<1> st;
+            st.clear();
+            WavePages pages;
+            const int t_first = tb + wave * TPI, stride = kFusedWaves * TPI;
+            attend_tiles_in_turn<ST, D, 1, TPI, STREAM>(kb, vb, T_valid_, t_first, te, stride, a.scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
+                const int page = pages.next([&](int n) __attribute__((always_inline)) -> int {
+                    const int mt = t_first + (n / TPI) * stride + n % TPI;
+                    if (mt >= te) return -1;
+                    const uint64_t *wp = &sel[mt >> page_shift];
+                    uint64_t w2 = load_u64_agent(wp);
+                    int spins = 0;
+                    while ((uint32_t)(w2 >> 32) != tag_) {  // the selection is still being written
+                        if (++spins > a.spin_limit) {
+                            atomicExch(a.err, 1u);
+                            break;
                         }
-                        if ((uint32_t)(w2 >> 32) == tag_) my_page = (uint32_t)w2;  // else gave up: skip
+                        __builtin_amdgcn_s_sleep(2);
+                        w2 = load_u64_agent(wp);
                     }
-                }
-                long row0[TPI];
-                typename R::raw_t kr[TPI][RPL], vr[TPI][RPL];
-#pragma unroll
-                for (int u = 0; u < TPI; ++u) {
-                    row0[u] = T_valid_;
-                    const uint32_t page = (uint32_t)__builtin_amdgcn_readlane((int)my_page, (step_i % SPC) * TPI + u);
-                    if (t + u < te && page < (uint32_t)Np_) row0[u] = (long)page * a.P + ((t + u) % tiles_per_page) * TR;
-                }
-#pragma unroll
-                for (int u = 0; u < TPI; ++u) {
-#pragma unroll
-                    for (int i = 0; i < RPL; ++i) {
-                        const long row = row0[u] + i * RPW + rg;
-                        if (row < T_valid_) {
-                            if (a.nt_kv & 1) {
-                                kr[u][i] = R::load_raw_nt(kb + row * D + c0);
-                                vr[u][i] = R::load_raw_nt(vb + row * D + c0);
-                            } else {
-                                kr[u][i] = R::load_raw(kb + row * D + c0);
-                                vr[u][i] = R::load_raw(vb + row * D + c0);
-                            }
-                        } else {
-                            kr[u][i] = R::zero_raw();
-                            vr[u][i] = R::zero_raw();
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < TPI; ++u) {
-                    float s[RPL];
-                    float mt = m;
-#pragma unroll
-                    for (int i = 0; i < RPL; ++i) {
-                        const float d = group_sum<LPR>(qd.dot(kr[u][i])) * a.scale;
-                        const long row = row0[u] + i * RPW + rg;
-                        s[i] = (row < T_valid_) ? d : -INFINITY;
-                        mt = fmaxf(mt, s[i]);
-                    }
-                    if (mt != -INFINITY) {
-                        const float corr = __expf(m - mt);
-                        l *= corr;
-#pragma unroll
-                        for (int c = 0; c < 8; ++c) o[c] *= corr;
-#pragma unroll
-                        for (int i = 0; i < RPL; ++i) {
-                            const float p = __expf(s[i] - mt);
-                            l += p;
-                            float x[8];
-                            R::unpack(vr[u][i], x);
-#pragma unroll
-                            for (int c = 0; c < 8; ++c) o[c] = fmaf(p, x[c], o[c]);
-                        }
-                        m = mt;
-                    }
-                }
-            }
+                    return (uint32_t)(w2 >> 32) == tag_ ? (int)(uint32_t)w2 : -1;  // else gave up: skip
+                });
+                return ((uint32_t)page < (uint32_t)Np_) ? (long)page * a.P + (t & ((1 << page_shift) - 1)) * TR : T_valid_;
+            }, [&]() __attribute__((always_inline)) { if (!finish) fetch_next(); });
+            float m = st.m[0], l = st.l[0];
+            float (&o)[8] = st.o[0];
 
             mark(item, 5);
             // merge the row groups of the wave, then the waves through LDS
@@ -406,8 +349,18 @@ template <typename ST, int D, int NT>
 static int launch_fused(const FusedParams &prm, int np_lds, int grid, hipStream_t stream)
 {
     if (np_lds > 15360) return RS_UNSUPPORTED;  // keys must fit 60 KiB of LDS
-    if (prm.state) decode_fused_kernel<ST, D, NT, true><<<grid, NT, (size_t)np_lds * 4, stream>>>(prm);
-    else decode_fused_kernel<ST, D, NT, false><<<grid, NT, (size_t)np_lds * 4, stream>>>(prm);
+    // Rows that one query head reads: streaming loads.  Query heads that share rows find them in the caches: ordinary loads
+    // (4 x 32 over 8 heads x 64K, 1/4 of the pages, with the append 206 / 180 us).  The page bounds go by ordinary loads, of
+    // which the next step on the same cache finds most in the memory-side cache (4 x 32 heads x 64K, 1/16, a step after
+    // another on one cache 96 us, streamed 103; over three caches in turn 106.5 and 101.5).
+#define RS_LAUNCH(SS)                                                                                   \
+    do {                                                                                                \
+        if (prm.state) decode_fused_kernel<ST, D, NT, true, SS><<<grid, NT, (size_t)np_lds * 4, stream>>>(prm); \
+        else decode_fused_kernel<ST, D, NT, false, SS><<<grid, NT, (size_t)np_lds * 4, stream>>>(prm);  \
+    } while (0)
+    if (prm.Hq == prm.Hkv) RS_LAUNCH(true);
+    else RS_LAUNCH(false);
+#undef RS_LAUNCH
     return RS_OK;
 }
 

@@ -13,7 +13,7 @@ constexpr int kKnobUnset = -2147483647 - 1;
 struct Knobs {
     // decode (api.hip)
     int score_wgs, attend_wgs, attend_shared;
-    int fused_grid, fused_sscore, fused_satt, fused_fine, fused_fine_pct, fused_nt, fused_pingpong;
+    int fused_grid, fused_sscore, fused_satt, fused_fine, fused_fine_pct, fused_pingpong;
     int fused_two_launch, fused_one_wg;
     // scan
     int scan_grid, scan_slab, scan_meta;
