@@ -171,6 +171,7 @@ struct PrefillParams {
     float *lse_out;
     int Hq, Hkv, Nb, K, block, n_diag;
     int group;                 // causal tiles: units of an XCD whose tiles go out together
+    int stream_records;        // partial records past the caches, both ways
     long T, Tcap, list_stride;
     float scale;
 };
@@ -686,7 +687,8 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             const int row = i * RW + ln / CR, c = ln % CR;
             bf16 *dst = dest_of_row(i, row);
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * D + ((c ^ chunk_swizzle<D>(row)) * 8));
-            if (dst) *reinterpret_cast<uint4 *>(dst + c * 8) = v;
+            if (dst && FORM == kListed && a.stream_records) __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(dst + c * 8));
+            else if (dst) *reinterpret_cast<uint4 *>(dst + c * 8) = v;
         }
     };
     long tq;
@@ -748,7 +750,8 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int j = 0; j < 32 / RW; ++j) {
                     const int rr = j * RW + frow;
                     const int rc = (rr < rows_here) ? rr : rows_here - 1;
-                    rec[i][j] = *reinterpret_cast<const u32x4 *>(src + (uint32_t)(rc * a.K * D + fchunk * 8));
+                    const u32x4 *p = reinterpret_cast<const u32x4 *>(src + (uint32_t)(rc * a.K * D + fchunk * 8));
+                    rec[i][j] = a.stream_records ? __builtin_nontemporal_load(p) : *p;
                 }
             }
             float Mn = M;
@@ -901,6 +904,7 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     p.Tcap = s->Tcap;
     p.scale = scale;
     p.tile_off = p.list = nullptr;
+    p.stream_records = 0;
     p.desc = nullptr;
     p.desc_stride = 0;
     p.part_o = nullptr;
@@ -943,6 +947,11 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
         p.part_o = (uint16_t *)(ws + L.off_part_o);
         p.part_lse = (float *)(ws + L.off_part_lse);
         p.list_stride = L.list_stride;
+        // Records that the memory-side cache would lose before they are read anyway (written and read once, K - 1 a row) go
+        // past it; smaller ones are found there.  Routing and attention, plain / streamed, us: 2 x 32 over 8 heads x 16000, blocks of
+        // 256, top-4 (786 MB) 1053 / 1021, 16 heads x 20000 (246 MB) 415 / 398, 32 x 13000, 512, top-3 (213 MB) 479 / 473, 32 x
+        // 32768 (537 MB) 1166 / 1160; the other way 8 x 16000, 256, top-4 (98 MB) 169 / 175.
+        p.stream_records = units * T * (K - 1) * s->D * 2 >= 150l << 20;
     }
     if (idx) {
         // launch 1: tiles of listed rows leave partials; launch 2: own-block tiles fold them in
