@@ -35,7 +35,12 @@ void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache
                             const int32_t *idx, void *out, float *lse_out, uint64_t *partial, int B, int Hq,
                             int Hkv, long Tcap, int P, long T_valid, int K, float scale, int splits,
                             uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit, int idx_per_kv,
-                            uint32_t *state, long T_max, hipStream_t stream);
+                            uint32_t *state, long T_max, const uint32_t *keys, long key_stride, int32_t *idx_out,
+                            hipStream_t stream);
+size_t attend_select_lds(long key_stride, int K, int P, int splits);
+void score_keys_dispatch(int dtype, int D, const void *q, const void *meta, uint32_t *keys, int B, int Hq, int Hkv, long Np_cap,
+                         int Np, int K, int n_first, int n_local, int splits, uint32_t *err, const uint32_t *state, long T_max,
+                         int P, long key_stride, hipStream_t stream);
 bool decode_attend_shared_fits(int dtype, int D, int G, int splits);
 void decode_attend_shared_dispatch(int dtype, int D, const void *q, const void *k_cache, const void *v_cache,
                                    const int32_t *idx, void *out, float *lse_out, uint64_t *partial, int B, int Hq, int Hkv,
@@ -182,7 +187,13 @@ constexpr int kMaxAttSplits = 64;
 struct DecodeLayout {
     int Np, splits_score, splits_att_max;
     size_t off_scores, off_idx, off_idx_tagged, off_partial, off_trace, total;
+    // Page keys of the attention that selects for itself: the last keys_bytes of the workspace, whatever length they are for, so
+    // that at no other length of the same shape tagged words live there, which a plain word might pass for.  A
+    // workspace without room for them behind `total` is enough: the selection is then a launch of its own.
+    size_t keys_bytes, total_keys;
 };
+
+static long key_row(int Np) { return (Np + 3) / 4 * 4; }  // keys of a unit, 16-byte rows
 
 static DecodeLayout decode_layout(const rs_shape *s, long T_valid, int K)
 {
@@ -208,7 +219,35 @@ static DecodeLayout decode_layout(const rs_shape *s, long T_valid, int K)
     off += (size_t)4096 * 64 * 8;
 #endif
     L.total = off;
+    L.keys_bytes = align256((size_t)units * key_row(L.Np) * 4);
+    L.total_keys = align256(L.total) + L.keys_bytes + 256;
     return L;
+}
+
+// splits of a unit's tiles in the attention that is a launch of its own:
+// 512-thread workgroups, about one per CU: fewer, fuller workgroups start sooner and leave fewer
+// partials to merge than many small ones (32 query / 8 KV heads, batch 1: dense over 16.5K rows
+// 29 -> 25 us, over 32K rows 45 -> 41 us, 128 listed pages 13.7 -> 10.1 us against 256 threads
+// and 512 workgroups).  A wave takes two tiles per step: past 16 steps per wave, twice the splits.
+static int attend_splits(const DecodeLayout &L, long units, long tiles)
+{
+    int target = knob_or(knobs().attend_wgs, 0);
+    if (target <= 0) {
+        target = 256;
+        if (tiles > (long)pick_splits(units, tiles, 8, 256) * 8 * 2 * 16) target = 512;
+    }
+    const int splits = pick_splits(units, tiles, 8, target);
+    return splits > L.splits_att_max ? L.splits_att_max : splits;
+}
+
+// Whether that attention selects its pages itself, every split for its own: where the keys and a split's part of the list
+// fit beside its other LDS (12000 pages).  The launch before it then only scores: no arrival counter, no tagged words to
+// gather, no workgroup that selects while the rest of the chip is idle, no list to read back.  Append + decode, selection by
+// the last arrival / by every split, us: 32 over 8 heads x 32768, 1/8 of the pages 29.2 / 27.2, 32 heads x 32768, 1/16 32.5 / 30.4,
+// 2 x 16 over 8 of 64 channels x 30000 26.1 / 22.9, 4 x 32 over 8 x 16000, 1/4 61.2 / 60.6, 2 heads x 60000 48.6 / 47.4.
+static bool attend_selects(int Np, int K, int P, int splits)
+{
+    return Np >= 64 && attend_select_lds(key_row(Np), K, P, splits) <= 48 * 1024;
 }
 
 // work split and buffers of the one-launch decode (score -> select -> attend) for a sequence of
@@ -535,7 +574,7 @@ int32_t quest_select_decode_group(const rs_shape *s, const void *q, const void *
 size_t sparse_attn_decode_workspace_bytes(const rs_shape *s, int64_t T_valid, int32_t K)
 {
     if (check_shape(s, true) != RS_OK || T_valid <= 0) return 0;
-    return decode_layout(s, T_valid, K).total;
+    return decode_layout(s, T_valid, K).total_keys;
 }
 
 static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, const void *k_cache, const void *v_cache,
@@ -602,6 +641,22 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
         if (st != RS_OK) return st;
         return launch_status();
     }
+    int key_splits = 0;  // > 0: the attention selects for itself, in that many splits
+    const long key_stride = key_row(L.Np);
+    if (fused && !group && ws_bytes >= L.total_keys) {
+        key_splits = attend_splits(L, units, (long)K * (s->P / 16));
+        if (!attend_selects(L.Np, K, s->P, key_splits)) key_splits = 0;
+    }
+    if (key_splits > 0) {
+        uint32_t *keys = (uint32_t *)(w + ((ws_bytes - L.keys_bytes) & ~(size_t)255));
+        score_keys_dispatch(s->dtype, s->D, q, meta, keys, s->B, s->Hq, s->Hkv, s->Tcap / s->P, L.Np, K, n_first, n_local,
+                            L.splits_score, err, nullptr, 0, s->P, key_stride, (hipStream_t)stream);
+        if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
+        decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, nullptr, out, lse_out, (uint64_t *)(w + L.off_partial), s->B,
+                               s->Hq, s->Hkv, s->Tcap, s->P, T_valid, K, scale, key_splits, ctr_att, err, tag,
+                               g_spin_limit.load(), 0, nullptr, 0, keys, key_stride, idx_out, (hipStream_t)stream);
+        return launch_status();
+    }
     if (fused) {
         int32_t *sel = idx_out ? idx_out : (int32_t *)(w + L.off_idx);
         st = score_select_dispatch(s->dtype, s->D, GQ, q, meta, (uint64_t *)(w + L.off_scores), nullptr, sel, s->B,
@@ -612,17 +667,7 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
         use_idx = sel;
     }
     const long tiles = use_idx ? (long)K * (s->P / 16) : (T_valid + 15) / 16;
-    // 512-thread workgroups, about one per CU: fewer, fuller workgroups start sooner and leave fewer
-    // partials to merge than many small ones (32 query / 8 KV heads, batch 1: dense over 16.5K rows
-    // 29 -> 25 us, over 32K rows 45 -> 41 us, 128 listed pages 13.7 -> 10.1 us against 256 threads
-    // and 512 workgroups).  A wave takes two tiles per step: past 16 steps per wave, twice the splits.
-    int target = knob_or(knobs().attend_wgs, 0);
-    if (target <= 0) {
-        target = 256;
-        if (tiles > (long)pick_splits(units, tiles, 8, 256) * 8 * 2 * 16) target = 512;
-    }
-    int splits = pick_splits(units, tiles, 8, target);
-    if (splits > L.splits_att_max) splits = L.splits_att_max;
+    const int splits = attend_splits(L, units, tiles);
     // Heads of a KV head that attend the same rows go through them together where fetching the rows per
     // head is what takes the time: when the heads' reads come to 300 MB (200 MB for two heads; 700 MB for eight heads
     // over more than 32 splits, whose partials take long to merge) and the KV heads' splits fill the chip, or when
@@ -649,7 +694,8 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     }
     decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, use_idx, out, lse_out,
                            (uint64_t *)(w + L.off_partial), s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_valid, K, scale,
-                           splits, ctr_att, err, tag, g_spin_limit.load(), group ? 1 : 0, nullptr, 0, (hipStream_t)stream);
+                           splits, ctr_att, err, tag, g_spin_limit.load(), group ? 1 : 0, nullptr, 0, nullptr, 0, nullptr,
+                           (hipStream_t)stream);
     return launch_status();
 }
 
@@ -734,7 +780,7 @@ int32_t sparse_attn_decode_static(const rs_shape *s, const void *q, const void *
 size_t rat_decode_step_workspace_bytes(const rs_shape *s, int64_t T_max, int32_t K)
 {
     if (check_shape(s, true) != RS_OK || T_max <= 0 || T_max > s->Tcap) return 0;
-    return decode_layout(s, T_max, K).total;
+    return decode_layout(s, T_max, K).total_keys;
 }
 
 int32_t rat_decode_state_set(void *ws, size_t ws_bytes, int64_t T, void *stream)
@@ -794,23 +840,27 @@ int32_t rat_decode_step(const rs_shape *s, const void *k, const void *v, const f
         uint32_t *ctr_score = (uint32_t *)w + kCtrlUnit0;
         uint32_t *ctr_att = ctr_score + kMaxUnits;
         uint32_t *err = (uint32_t *)w + kCtrlAsyncErr;
+        const int splits = attend_splits(L, units, (long)K * (s->P / 16));
+        uint32_t *state = (uint32_t *)w;
+        if (ws_bytes >= L.total_keys && attend_selects(L.Np, K, s->P, splits)) {
+            uint32_t *keys = (uint32_t *)(w + ((ws_bytes - L.keys_bytes) & ~(size_t)255));
+            score_keys_dispatch(s->dtype, s->D, q, meta, keys, s->B, s->Hq, s->Hkv, s->Tcap / s->P, L.Np, K, n_first, n_local,
+                                L.splits_score, err, state, T_max, s->P, key_row(L.Np), (hipStream_t)stream);
+            if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
+            decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, nullptr, out, lse_out, (uint64_t *)(w + L.off_partial),
+                                   s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_max, K, scale, splits, ctr_att, err, 0u,
+                                   g_spin_limit.load(), 0, state, T_max, keys, key_row(L.Np), idx_out, (hipStream_t)stream);
+            return launch_status();
+        }
         int32_t *sel = idx_out ? idx_out : (int32_t *)(w + L.off_idx);
         st = score_select_dispatch(s->dtype, s->D, 1, q, meta, (uint64_t *)(w + L.off_scores), nullptr, sel, s->B, s->Hq,
                                    s->Hkv, s->Tcap / s->P, L.Np, K, n_first, n_local, L.splits_score, ctr_score, err, 0u,
-                                   g_spin_limit.load(), (const uint32_t *)w, T_max, s->P, (hipStream_t)stream);
+                                   g_spin_limit.load(), state, T_max, s->P, (hipStream_t)stream);
         if (st != RS_OK) return st;
         if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
-        const long tiles = (long)K * (s->P / 16);
-        int target = knob_or(knobs().attend_wgs, 0);
-        if (target <= 0) {
-            target = 256;
-            if (tiles > (long)pick_splits(units, tiles, 8, 256) * 8 * 2 * 16) target = 512;
-        }
-        int splits = pick_splits(units, tiles, 8, target);
-        if (splits > L.splits_att_max) splits = L.splits_att_max;
         decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, sel, out, lse_out, (uint64_t *)(w + L.off_partial),
                                s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_max, K, scale, splits, ctr_att, err, 0u,
-                               g_spin_limit.load(), 0, (uint32_t *)w, T_max, (hipStream_t)stream);
+                               g_spin_limit.load(), 0, state, T_max, nullptr, 0, nullptr, (hipStream_t)stream);
         return launch_status();
     }
     FusedParams prm;

@@ -261,15 +261,89 @@ int score_select_dispatch(int dtype, int D, int GQ, const void *q, const void *m
 }
 
 // ------------------------------------------------------------------------------------
+// The same scores as order-preserving keys (pages that are always kept: the top key) for an attention kernel that selects
+// for itself: no hand-over inside the launch, and the chip does not idle while one workgroup of a unit selects.
+// ------------------------------------------------------------------------------------
+template <typename ST, int D>
+__global__ __launch_bounds__(kSelThreads) void quest_score_keys_kernel(const ST *__restrict__ q, const ST *meta, uint32_t *keys,
+                                                                       int Hq, int Hkv, long Np_cap, int Np, int K, int n_first,
+                                                                       int n_local, int splits, uint32_t *err,
+                                                                       const uint32_t *state, long T_max, int P, long key_stride)
+{
+    if (state) {  // the replayable decode step: tokens in the cache + 1 (the step's append has run)
+        const long T_valid = *reinterpret_cast<const long *>(state + kCtrlStateT) + 1;
+        Np = (int)((T_valid + P - 1) / P);
+        if (T_valid > T_max || K > Np) {  // outside what the buffers were sized for: report, do nothing
+            if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) atomicExch(err, 1u);
+            return;
+        }
+    }
+    constexpr int LPR = D / 8, RPW = 64 / LPR, ROW = D * (int)sizeof(ST);
+    constexpr int UNR = 4, PPW = UNR * RPW;  // pages of a lane and of a wave per step
+    using R = Row8<ST>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rg = lane / LPR, cl = lane % LPR;
+    const int unit = blockIdx.y, b = unit / Hq, kvh = (unit % Hq) / (Hq / Hkv);
+    const ST *mbase = meta + ((long)(b * Hkv + kvh) * Np_cap) * 2 * D;
+    uint32_t *krow = keys + unit * key_stride;
+    float qv[8];
+    R::load(q + (long)unit * D + cl * 8, qv);
+    BoundDot<ST> bound;
+    bound.set(qv);
+    const int per = (Np + splits - 1) / splits;
+    const int pb = blockIdx.x * per;
+    const int pe = (pb + per < Np) ? pb + per : Np;
+    for (int base = pb + wave * PPW; base < pe; base += PPW * (kSelThreads / 64)) {
+        const int n = (pe - base < PPW) ? pe - base : PPW;
+        const LdsSource md = lds_source_sized(mbase + (long)base * 2 * D, n * 2 * ROW);
+        const uint32_t at = (uint32_t)(rg * 2 * ROW + cl * 8 * (int)sizeof(ST));
+        typename R::raw_t mn[UNR], mx[UNR];
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            mn[u] = load_row8<ST, 0>(md, at + u * RPW * 2 * ROW);
+            mx[u] = load_row8<ST, 0>(md, at + (u * RPW * 2 + 1) * ROW);
+        }
+        float mine = 0.f;  // lane u of a row group keeps page u's sum, and the wave's keys leave with one store
+#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const float x = group_sum<LPR>(bound.add(0.f, mn[u], mx[u]));
+            if (cl == u) mine = x;
+        }
+        const int p = base + rg + cl * RPW;
+        if (cl < UNR && p < pe) krow[p] = (p < n_first || p >= Np - n_local) ? 0xffffffffu : float_to_key(mine);
+    }
+}
+
+void score_keys_dispatch(int dtype, int D, const void *q, const void *meta, uint32_t *keys, int B, int Hq, int Hkv, long Np_cap,
+                         int Np, int K, int n_first, int n_local, int splits, uint32_t *err, const uint32_t *state, long T_max,
+                         int P, long key_stride, hipStream_t stream)
+{
+    const dim3 grid((unsigned)splits, (unsigned)(B * Hq));
+#define RS_LAUNCH(ST, DD)                                                                                                       \
+    quest_score_keys_kernel<ST, DD><<<grid, kSelThreads, 0, stream>>>((const ST *)q, (const ST *)meta, keys, Hq, Hkv, Np_cap, Np, \
+                                                                      K, n_first, n_local, splits, err, state, T_max, P, key_stride)
+    if (dtype == RS_BF16) {
+        if (D == 128) RS_LAUNCH(bf16, 128);
+        else RS_LAUNCH(bf16, 64);
+    } else {
+        if (D == 128) RS_LAUNCH(float, 128);
+        else RS_LAUNCH(float, 64);
+    }
+#undef RS_LAUNCH
+}
+
+// ------------------------------------------------------------------------------------
 // decode attention over a list of 16-row tiles (selected pages, or all rows), split over
 // workgroups; partial (m, l, o) per split; the last split to arrive merges them.
 // ------------------------------------------------------------------------------------
-template <typename ST, int D, int kAttThreads, bool STREAM>
+// SELECT: the list is not given; every split selects it from the unit's page keys (keys, key_stride of them per unit) and
+// keeps its own part in LDS, the first split writes it to idx_out.  Dynamic LDS then: key_stride keys, and the part.
+template <typename ST, int D, int kAttThreads, bool STREAM, bool SELECT>
 __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
     const ST *__restrict__ q, const ST *k_cache, const ST *v_cache, const int32_t *idx,
     ST *__restrict__ out, float *__restrict__ lse_out, uint64_t *partial, int Hq, int Hkv, long Tcap, int P,
     long T_valid, int K, float scale, int splits, uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit,
-    int idx_per_kv, uint32_t *state, long T_max)
+    int idx_per_kv, uint32_t *state, long T_max, const uint32_t *keys, long key_stride, int32_t *idx_out)
 {
     // state (the replayable decode step, listed pages): length and tag come from the workspace's words; the
     // last workgroup out of the grid advances them (every workgroup has read them by then)
@@ -318,8 +392,8 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
         qd[0].set(qv);
     }
 
-    const int page_shift = idx ? __builtin_ctz((unsigned)(P / TR)) : 0;  // tiles of a page: a power of two
-    const long n_tiles = idx ? (long)K << page_shift : (T_valid + TR - 1) / TR;
+    const int page_shift = (SELECT || idx) ? __builtin_ctz((unsigned)(P / TR)) : 0;  // tiles of a page: a power of two
+    const long n_tiles = (SELECT || idx) ? (long)K << page_shift : (T_valid + TR - 1) / TR;
     const long per = (n_tiles + splits - 1) / splits;
     const long tb = (long)blockIdx.x * per;
     const long te = (tb + per < n_tiles) ? tb + per : n_tiles;
@@ -327,7 +401,35 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
     AttendState<1> st;
     st.clear();
     const long t_first = tb + wave * TPI, stride = kAttWaves * TPI;
-    if (idx) {
+    if constexpr (SELECT) {
+        __shared__ SelectShared<kAttThreads> sh;
+        extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
+        uint32_t *s_keys = s_dyn;
+        int *s_sel = reinterpret_cast<int *>(s_dyn + key_stride);
+        const int Np = (int)((T_valid + P - 1) / P);
+        const uint4 *src = reinterpret_cast<const uint4 *>(keys + unit * key_stride);
+        for (int i = tid; i < (Np + 3) / 4; i += kAttThreads) {
+            uint4 x = src[i];
+            if (4 * i + 1 >= Np) x.y = 0u;  // (zeros up to a multiple of four)
+            if (4 * i + 2 >= Np) x.z = 0u;
+            if (4 * i + 3 >= Np) x.w = 0u;
+            reinterpret_cast<uint4 *>(s_keys)[i] = x;
+        }
+        __syncthreads();
+        const int first = (int)(tb >> page_shift), past = tb < te ? (int)((te - 1) >> page_shift) + 1 : first;  // this split's part
+        int32_t *whole = (blockIdx.x == 0 && idx_out) ? idx_out + (long)unit * K : nullptr;
+        auto emit = [=](int pos, int p) {
+            if (pos >= first && pos < past) s_sel[pos - first] = p;
+            if (whole) whole[pos] = p;
+        };
+        if (Np <= kAttThreads / 2) select_topk_few<kAttThreads>(s_keys, Np, K, sh.wave_tot, emit);
+        else select_topk_lds<kAttThreads>(s_keys, Np, K, sh, emit);
+        __syncthreads();
+        attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
+            const int page = __builtin_amdgcn_readfirstlane(s_sel[(int)(t >> page_shift) - first]);
+            return (long)page * P + (t & ((1 << page_shift) - 1)) * TR;
+        });
+    } else if (idx) {
         WavePages pages;
         attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
             const int page = pages.next([&](int n) __attribute__((always_inline)) -> int {
@@ -859,23 +961,35 @@ void decode_attend_shared_dispatch(int dtype, int D, const void *q, const void *
 #undef RS_LAUNCH
 }
 
+// LDS of a split that selects for itself: the keys, and its part of the list (a part may begin and end inside a page)
+size_t attend_select_lds(long key_stride, int K, int P, int splits)
+{
+    const long tiles = (long)K * (P / 16), per = (tiles + splits - 1) / splits;
+    return (size_t)(key_stride + per / (P / 16) + 2) * 4;
+}
+
+// keys != NULL: the kernel selects for itself (idx is not read; idx_out may be NULL)
 void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache, const void *v_cache,
                             const int32_t *idx, void *out, float *lse_out, uint64_t *partial, int B, int Hq,
                             int Hkv, long Tcap, int P, long T_valid, int K, float scale, int splits,
                             uint32_t *unit_ctr, uint32_t *err, uint32_t tag, int spin_limit, int idx_per_kv,
-                            uint32_t *state, long T_max, hipStream_t stream)
+                            uint32_t *state, long T_max, const uint32_t *keys, long key_stride, int32_t *idx_out,
+                            hipStream_t stream)
 {
     const dim3 grid((unsigned)splits, (unsigned)(B * Hq));
     constexpr int kAttThreads = 512;  // about one such workgroup per CU (see the split rule of the caller)
-#define RS_LAUNCH1(ST, DD, SS)                                                                              \
-    decode_attend_kernel<ST, DD, kAttThreads, SS><<<grid, kAttThreads, 0, stream>>>(                        \
+    const size_t lds = keys ? attend_select_lds(key_stride, K, P, splits) : 0;
+#define RS_LAUNCH1(ST, DD, SS, LL)                                                                          \
+    decode_attend_kernel<ST, DD, kAttThreads, SS, LL><<<grid, kAttThreads, lds, stream>>>(                  \
         (const ST *)q, (const ST *)k_cache, (const ST *)v_cache, idx, (ST *)out, lse_out, partial, Hq, Hkv, \
-        Tcap, P, T_valid, K, scale, splits, unit_ctr, err, tag, spin_limit, idx_per_kv, state, T_max)
+        Tcap, P, T_valid, K, scale, splits, unit_ctr, err, tag, spin_limit, idx_per_kv, state, T_max, keys, key_stride, idx_out)
     // no other query head reads these rows: streaming loads
-#define RS_LAUNCH(ST, DD)                       \
-    do {                                        \
-        if (Hq == Hkv) RS_LAUNCH1(ST, DD, true); \
-        else RS_LAUNCH1(ST, DD, false);         \
+#define RS_LAUNCH(ST, DD)                                       \
+    do {                                                        \
+        if (keys && Hq == Hkv) RS_LAUNCH1(ST, DD, true, true);  \
+        else if (keys) RS_LAUNCH1(ST, DD, false, true);         \
+        else if (Hq == Hkv) RS_LAUNCH1(ST, DD, true, false);    \
+        else RS_LAUNCH1(ST, DD, false, false);                  \
     } while (0)
     if (dtype == RS_BF16) {
         if (D == 128) RS_LAUNCH(bf16, 128);

@@ -512,3 +512,38 @@ def test_few_pages_in_one_workgroup(rs, knobs, dtype, D, scores):
         np.testing.assert_array_equal(got[1][2], got[0][2])
         np.testing.assert_allclose(got[1][1], got[0][1], rtol=1e-6, atol=2e-6)
         np.testing.assert_allclose(got[1][0], got[0][0], rtol=2.0 ** -7 if dtype == "bf16" else 1e-5, atol=2e-6)
+
+
+@pytest.mark.parametrize("P,T,K,Hq,Hkv,D,dtype", [(16, 1024, 5, 2, 2, 128, "bf16"), (16, 1040 - 3, 64, 4, 2, 64, "bf16"), (64, 9001, 100, 2, 1, 128, "f32"),
+                                                   (16, 70000, 700, 2, 2, 64, "bf16"), (16, 16 * 12100, 300, 1, 1, 64, "bf16")])
+def test_selection_by_every_split_or_by_a_launch_of_its_own(rs, knobs, P, T, K, Hq, Hkv, D, dtype):
+    """As two launches the attention's splits select for themselves (a split's part of the list may begin and end inside a
+    page); with more keys than fit the LDS, and with a workspace that has no room for them, the first launch selects: the
+    same lists, log-sum-exps and outputs bit for bit, with and without the list asked for."""
+    say("selection by split", P, T, K, Hq, Hkv, D, dtype)
+    knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", "1")
+    knobs.setenv("RATSPARSE_FUSED_ONE_WG", "0")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T)
+    Np, B = -(-T // P), 1
+    s = rs.make_shape(B, Hq, Hkv, D, Np * P, P, tdtype(dtype))
+    kc, vc = (torch.randn(B, Hkv, Np * P, D, generator=gen, device="cuda").to(tdtype(dtype)) for _ in range(2))
+    q = torch.randn(B, Hq, D, generator=gen, device="cuda").to(tdtype(dtype))
+    meta = torch.zeros(B, Hkv, Np, 2, D, dtype=tdtype(dtype), device="cuda")
+    rs.quest_page_meta(s, kc, meta, 0, T)
+    need = rs.sparse_attn_decode_workspace_bytes(s, T, K)
+    keys = -(-(B * Hq * (-(-Np // 4) * 4) * 4) // 256) * 256
+    got = []
+    for size, with_list in ((need, True), (need - keys - 256, True), (need, False)):
+        ws = rs.Workspace(size)
+        out = torch.zeros(B, Hq, D, dtype=tdtype(dtype), device="cuda")
+        lse = torch.zeros(B, Hq, device="cuda")
+        idx = torch.full((B, Hq, K), -5, dtype=torch.int32, device="cuda")
+        for _ in range(2):  # (the second time on a workspace that holds the first one's words)
+            rs.sparse_attn_decode(s, q, kc, vc, T, 1.0 / np.sqrt(D), None, K, meta, 1, 1, out, lse, idx if with_list else None, ws)
+        torch.cuda.synchronize()
+        ws.async_status()
+        got.append((out, lse, idx))
+    assert torch.equal(got[0][2], got[1][2]) and int(got[0][2].min()) == 0 and int(got[0][2].max()) == Np - 1
+    for o in got[1:]:
+        assert torch.equal(o[0], got[0][0]) and torch.equal(o[1], got[0][1])
