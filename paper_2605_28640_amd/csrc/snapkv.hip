@@ -132,7 +132,7 @@ __device__ __forceinline__ void snap_query_fragments(const bf16 *q, int rows, co
     __syncthreads();
 }
 
-// sweep 1: partial softmax statistics (reference point, sum) per (query row, key chunk).  S^T = K Q^T: a
+// sweep 1: partial softmax statistics (max, sum) per (query row, key chunk).  S^T = K Q^T: a
 // lane owns one query row (a column of S^T) of each of the NRG groups of 32, so its max and sum are in-lane reductions
 // plus one cross-half shuffle; the waves' statistics meet in LDS at the end.
 template <int D, int NRG, bool STREAM>
@@ -167,10 +167,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         bf16x8 qf[NRG][NC];
         snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
         st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
-        float m[NRG], l[NRG];
+        float m[NRG], l[NRG], top[NRG];  // reference point, sum, and the largest score (unscaled) of this lane's keys
 #pragma unroll
         for (int rg = 0; rg < NRG; ++rg) {
-            m[rg] = -INFINITY;
+            m[rg] = top[rg] = -INFINITY;
             l[rg] = 0.f;
         }
         snap_stream_keys<D, AUX>(kb, kc0, kc1, st, sK0, sK1, koff, [&](const bf16x8 (&kf)[NC], long k0) __attribute__((always_inline)) {
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         }
                     }
                     // Weights against the reference point as it is (none yet: its negative is +inf, and so are they);
-                    // the point moves to the maximum only where a lane's 16 weights add up to more than kSnapLarge.
+                    // the point moves to the maximum so far only where a lane's 16 weights add up to more than kSnapLarge.
                     // (Each half of a row's lanes keeps its own sum; they meet at the end.)
                     auto weights = [&](float ref) __attribute__((always_inline)) -> float {
                         float p4[4] = {0.f, 0.f, 0.f, 0.f};
@@ -205,11 +205,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         return (p4[0] + p4[1]) + (p4[2] + p4[3]);
                     };
                     float ps = weights(m[rg]);
-                    if (__any(!(ps <= kSnapLarge))) {
-                        float mx = sacc[0];
 #pragma unroll
-                        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
-                        const float m_new = fmaxf(m[rg], half_pair_max(mx) * cs);
+                    for (int v = 0; v < 16; v += 2) top[rg] = fmaxf(fmaxf(top[rg], sacc[v]), sacc[v + 1]);
+                    if (__any(!(ps <= kSnapLarge))) {
+                        const float m_new = half_pair_max(top[rg]) * cs;
                         const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
                         l[rg] *= (m[rg] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[rg] - m_safe);
                         ps = weights(m_safe);
@@ -223,15 +222,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         });
 #pragma unroll
         for (int rg = 0; rg < NRG; ++rg) {
-            const float ls = half_pair_sum(l[rg]);
+            // (the statistics are those of the maximum: what the normaliser is rounded to does not hang on the reference)
+            const float mt = half_pair_max(top[rg]) * cs, ls = half_pair_sum(l[rg]);
             if (h == 0) {
-                s_ml[wave][32 * rg + lq][0] = m[rg];
-                s_ml[wave][32 * rg + lq][1] = ls;
+                s_ml[wave][32 * rg + lq][0] = mt;
+                s_ml[wave][32 * rg + lq][1] = (mt == -INFINITY) ? 0.f : ls * __builtin_amdgcn_exp2f(m[rg] - mt);
             }
         }
         __syncthreads();
         const int r = rt * ROWS + tid;
-        if (tid < ROWS && r < R) {  // (reference point in the base-2 domain, sum)
+        if (tid < ROWS && r < R) {  // (max, sum) back in the natural-log domain
             float M = -INFINITY, S = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) M = fmaxf(M, s_ml[w][tid][0]);
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int w = 0; w < 4; ++w)
                 if (s_ml[w][tid][0] != -INFINITY) S += s_ml[w][tid][1] * __builtin_amdgcn_exp2f(s_ml[w][tid][0] - M);
             float *sp = stats + (((long)bk * n_chunks + chunk) * R + r) * 2;
-            sp[0] = M;
+            sp[0] = M * 0.6931471805599453f;
             sp[1] = S;
         }
         // (the next row tile's barriers come before its statistics)
@@ -303,9 +303,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, x[u].x);
                 if (Mn != -INFINITY) {
-                    S *= (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+                    S *= (M == -INFINITY) ? 0.f : __expf(M - Mn);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) S += (x[u].x == -INFINITY) ? 0.f : x[u].y * __builtin_amdgcn_exp2f(x[u].x - Mn);
+                    for (int u = 0; u < U; ++u) S += (x[u].x == -INFINITY) ? 0.f : x[u].y * __expf(x[u].x - Mn);
                     M = Mn;
                 }
             }
@@ -323,12 +323,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int p = 0; p < PARTS; ++p) M = fmaxf(M, s_part[p][tid][0]);
 #pragma unroll
-                for (int p = 0; p < PARTS; ++p) S += (s_part[p][tid][0] == -INFINITY) ? 0.f : s_part[p][tid][1] * __builtin_amdgcn_exp2f(s_part[p][tid][0] - M);
-                // M + log2(S), rounded once: the exponent of S joins M first, what that rounds off joins the rest (log2 of
-                // S itself, up to 2^17, would carry an error of that size into every vote)
-                const int e = ilogbf(S);
-                const float hi = M + (float)e, rounded = (float)e - (hi - M);
-                x = hi + (__log2f(scalbnf(S, -e)) + rounded);
+                for (int p = 0; p < PARTS; ++p) S += (s_part[p][tid][0] == -INFINITY) ? 0.f : s_part[p][tid][1] * __expf(s_part[p][tid][0] - M);
+                x = (M + __logf(S)) * 1.4426950408889634f;
             }
             s_lse2[tid] = x;
         }
