@@ -22,17 +22,16 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kSnapKeysPerWg = 2048;  // keys per workgroup, at most (fewer when that leaves the chip idle)
 constexpr int kSnapKT = 128;          // a workgroup's share of the keys is a multiple of this
 constexpr int kSnapTile = 32;         // keys of a wave's tile
-constexpr float kSnapLarge = 4096.f;  // 16 x 2^8
+constexpr int kSnapStep = 64;         // keys of a step of the first sweep
 
-// Both sweeps stream the keys by waves of their own: a wave takes every fourth 32-key tile of the workgroup's keys against
-// all query rows of the row tile (up to 128, as fragments in registers) through two private slots of LDS, filled by
-// direct global -> LDS loads (unpadded rows, 16-byte chunks permuted by chunk_swizzle).  A tile's fragments are read
-// into registers at once, the slot is free again and the loads of the tile after next go out before the first matrix
-// instruction, so that a wave has one to two tiles on their way all the time and waits for nobody but them (rows past
-// the end of the keys read as zeros: finite, masked or never stored).
-// Bound by memory: 268 MB of keys in 44-47 us a sweep with up to 64 rows, 5.7-6.1 TB/s where reads alone reach 6.3-7, 47-51
-// with 128 (before, all four waves worked on one tile of 128 keys and waited together for the next: 57-65 us).  The
-// statistics go by a reference point that rarely moves, which for 128 rows took them from 58 to 51 us.
+// Both sweeps bring the keys by direct global -> LDS loads (unpadded rows, 16-byte chunks permuted by chunk_swizzle; rows
+// past the end of the keys read as zeros: finite, masked or never stored) that are counted, never drained, while keys are left.
+// The second streams them by waves of their own: a wave takes every fourth 32-key tile of the workgroup's keys against
+// all query rows of the row tile (up to 128, as fragments in registers) through two private slots of LDS.  A tile's
+// fragments are read into registers at once, the slot is free again and the loads of the tile after next go out before the
+// first matrix instruction, so that a wave has one to two tiles on their way all the time and waits for nobody but them.
+// Bound by memory: 268 MB of keys in 43 us with 64 rows, 48 with 128 (8 heads x 128K, 8 x 32 heads x 4096), where reads alone
+// take 38-43; all four waves on one tile of 128 keys, waiting together for the next, took 55-57.
 template <int D>
 struct SnapStage {
     static constexpr int CR = D / 8;               // 16-byte chunks per row
@@ -46,21 +45,21 @@ struct SnapStage {
 #pragma unroll
         for (int i = 0; i < NO; ++i) off[i] = (uint32_t)(srow * D + ((lane % CR) ^ chunk_swizzle<D>(i * RW + srow)) * 8) * 2u;
     }
-    // rows row0 .. row0 + 31 of x into a slot, as far as they lie below `rows`
-    template <int AUX = 0>
+    // rows row0 .. row0 + N - 1 of x into a slot, as far as they lie below `rows`
+    template <int AUX = 0, int N = kSnapTile>
     __device__ __forceinline__ void tile(const bf16 *x, long row0, long rows, uint16_t *slot) const
     {
-        const int n = (int)((rows - row0 < kSnapTile) ? rows - row0 : kSnapTile);
+        const int n = (int)((rows - row0 < N) ? rows - row0 : N);
         const LdsSource src = lds_source_sized(x + row0 * D, (n > 0 ? n : 0) * D * 2);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) load16_to_lds_at<AUX>(src, off[i % NO], (uint32_t)(i * RW * D * 2), slot + i * RW * D);
+        for (int i = 0; i < N / RW; ++i) load16_to_lds_at<AUX>(src, off[i % NO], (uint32_t)(i * RW * D * 2), slot + i * RW * D);
     }
 };
 
-// A tile's fragments out of a slot: all but the other slot's loads have landed, and when this returns the reads have left
+// A tile's fragments out of a slot: all but the wave's last VM loads have landed, and when this returns the reads have left
 // the slot, so that it can be loaded into again.  (One block with its own waits: the compiler would have these
-// reads wait for the loads into the other slot too.)
-template <int D>
+// reads wait for the loads into the other slots too.)
+template <int D, int VM>
 __device__ __forceinline__ void snap_read_tile(const uint16_t *slots, uint32_t koff, bf16x8 (&kf)[D / 16])
 {
     uint32_t at = (uint32_t)(size_t)(__attribute__((address_space(3))) const uint16_t *)slots + 2u * koff;
@@ -72,14 +71,14 @@ __device__ __forceinline__ void snap_read_tile(const uint16_t *slots, uint32_t k
                      "s_waitcnt lgkmcnt(0)"
                      : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7])
                      : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "v"(at ^ 128u), "v"(at ^ 160u), "v"(at ^ 192u),
-                       "v"(at ^ 224u), "n"(SnapStage<D>::NP)
+                       "v"(at ^ 224u), "n"(VM)
                      : "memory");
     } else {
         asm volatile("s_waitcnt vmcnt(%8)\n\t"
                      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
                      "s_waitcnt lgkmcnt(0)"
                      : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3])
-                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "n"(SnapStage<D>::NP)
+                     : "v"(at), "v"(at ^ 32u), "v"(at ^ 64u), "v"(at ^ 96u), "n"(VM)
                      : "memory");
     }
 }
@@ -98,7 +97,7 @@ __device__ __forceinline__ void snap_stream_keys(const bf16 *kb, long kc0, long 
     const long k0 = kc0 + (long)wave * kSnapTile;
     auto step = [&](uint16_t *slots, int it) __attribute__((always_inline)) {
         bf16x8 kf[NC];
-        snap_read_tile<D>(slots, koff, kf);
+        snap_read_tile<D, SnapStage<D>::NP>(slots, koff, kf);
         st.template tile<AUX>(kb, k0 + (long)(it + 2) * 4 * kSnapTile, kc1, slots + wave * kSnapTile * D);
         use(kf, k0 + (long)it * 4 * kSnapTile);
     };
@@ -133,18 +132,24 @@ __device__ __forceinline__ void snap_query_fragments(const bf16 *q, int rows, co
 }
 
 // sweep 1: partial softmax statistics (max, sum) per (query row, key chunk).  S^T = K Q^T: a
-// lane owns one query row (a column of S^T) of each of the NRG groups of 32, so its max and sum are in-lane reductions
-// plus one cross-half shuffle; the waves' statistics meet in LDS at the end.
-template <int D, int NRG, bool STREAM>
+// lane owns one query row (a column of S^T), so its max and sum are in-lane reductions plus
+// one cross-half shuffle.  Wave w holds rows 32 w .. 32 w + 31 of the 128-row tile and goes over all keys of the chunk,
+// 64 at a time and in order: which positions are kept can hang on the last place of these sums (votes that tie to seven
+// digits are not rare among thousands), so their order does not follow the shape of the launch.
+// The keys of a step lie in one of four slots, loaded by all four waves three steps ahead.
+// Bound by memory with up to 64 rows (268 MB of keys in 50 us), by the weights' arithmetic with 128 (60 us); two slots of 128
+// keys, loaded during a step and waited for at its end, took 64-68.  (Tiles of the waves' own, as in the second sweep, take 44-51
+// us, and give the sums another order.)
+template <int D, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_stats_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, float *__restrict__ stats, int Hq, int Hkv, long T,
     long Tcap, int W, int n_chunks, float scale, int keys_per_wg)
 {
-    constexpr int NC = D / 16, ROWS = 32 * NRG, AUX = STREAM ? 2 : 0;
+    constexpr int NC = D / 16, AUX = STREAM ? 2 : 0;
     using Stage = SnapStage<D>;
-    __shared__ __attribute__((aligned(1024))) uint16_t sK0[4 * kSnapTile * D];
-    __shared__ __attribute__((aligned(1024))) uint16_t sK1[4 * kSnapTile * D];
-    __shared__ float s_ml[4][ROWS][2];
+    constexpr int SLOT = kSnapStep * D, OWN = kSnapStep / 4;  // a slot's elements, a wave's rows of a step
+    constexpr int LPS = OWN / Stage::RW;                      // a wave's loads of a step
+    __shared__ __attribute__((aligned(1024))) uint16_t sK[4 * SLOT];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, h = lane >> 5;
@@ -156,93 +161,84 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bf16 *kb = k_cache + (long)bk * Tcap * D;
     const long kc0 = (long)chunk * keys_per_wg;
     const long kc1 = (kc0 + keys_per_wg < T) ? kc0 + keys_per_wg : T;
-    const int n_row_tiles = (R + ROWS - 1) / ROWS;
+    const int n_steps = (int)((kc1 - kc0 + kSnapStep - 1) / kSnapStep);
+    const int n_row_tiles = (R + 127) / 128;
     const Stage st;
-    const uint32_t koff = (uint32_t)((wave * kSnapTile + lq) * D + ((h ^ chunk_swizzle<D>(lq)) * 8));
+    const uint32_t koff = (uint32_t)(lq * D + ((h ^ chunk_swizzle<D>(lq)) * 8));  // K operand: row lq of a sub-tile, chunk h (chunk 2 c + h: 16 c away by exclusive or)
     const float cs = scale * 1.4426950408889634f;  // base-2 domain
-    uint16_t *slot0 = sK0 + wave * kSnapTile * D, *slot1 = sK1 + wave * kSnapTile * D;
+    // a step's loads always go out (past the end of the keys: as zeros), so that the waits can count them
+    auto load_step = [&](int it) __attribute__((always_inline)) {
+        st.template tile<AUX, OWN>(kb, kc0 + (long)it * kSnapStep + wave * OWN, kc1, sK + (it & 3) * SLOT + wave * OWN * D);
+    };
 
     for (int rt = 0; rt < n_row_tiles; ++rt) {
-        st.template tile<AUX>(kb, kc0 + wave * kSnapTile, kc1, slot0);  // (a wave without a tile loads nothing)
-        bf16x8 qf[NRG][NC];
-        snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
-        st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
-        float m[NRG], l[NRG], top[NRG];  // reference point, sum, and the largest score (unscaled) of this lane's keys
+        const int r = rt * 128 + wave * 32 + lq;
+        const bool wave_ok = rt * 128 + wave * 32 < R, r_ok = r < R;
+        const long pos = L + (r_ok ? r % W : 0);  // absolute position of the query: keys <= pos are visible
+        // the row tile's queries (the R rows of a KV head follow each other) by way of the last two slots: whole rows per
+        // load, where fragments fetched directly touch 64 cache lines each
+        uint16_t *sq = sK + 2 * SLOT + wave * 32 * D;
+        st.tile(q_win + ((long)bk * R + rt * 128) * D, wave * 32, R - rt * 128, sq);
+        load_step(0);
+        load_step(1);
+        bf16x8 qf[NC];
+        snap_read_tile<D, 2 * LPS>(sq, koff, qf);
+        asm volatile("s_barrier" ::: "memory");  // every wave has its queries: the last two slots are free for keys
+        load_step(2);
+        float m = -INFINITY, l = 0.f;
+        for (int it = 0; it < n_steps; ++it) {
+            // this wave's loads of the step have landed; behind the barrier everybody's have, and nobody reads the step before
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * LPS) : "memory");
+            load_step(it + 3);
+            if (!wave_ok) continue;
+            const uint16_t *slot = sK + (it & 3) * SLOT;
+            f32x16 sacc[2];
 #pragma unroll
-        for (int rg = 0; rg < NRG; ++rg) {
-            m[rg] = top[rg] = -INFINITY;
-            l[rg] = 0.f;
-        }
-        snap_stream_keys<D, AUX>(kb, kc0, kc1, st, sK0, sK1, koff, [&](const bf16x8 (&kf)[NC], long k0) __attribute__((always_inline)) {
-            auto groups = [&](auto edge_tag) __attribute__((always_inline)) {
+            for (int u = 0; u < 2; ++u) {
+                bf16x8 kf[NC];
+                snap_read_tile<D, 63>(slot + u * 32 * D, koff, kf);
 #pragma unroll
-                for (int rg = 0; rg < NRG; ++rg) {
-                    f32x16 sacc;
+                for (int v = 0; v < 16; ++v) sacc[u][v] = 0.f;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c], qf[rg][c], sacc, 0, 0, 0);  // [key][row]
-                    if constexpr (decltype(edge_tag)::value) {
-                        // keys of this tile the row may see, as offsets from k0: 0 .. hi
-                        int r = rt * ROWS + 32 * rg + lq;
-                        asm volatile("" : "+v"(r));  // (worked out here, not held in registers for the tiles without an edge)
-                        const long pos = L + (r < R ? r % W : 0);  // absolute position of the query: keys <= pos are visible
-                        const long hi_l = ((pos < kc1 - 1) ? pos : kc1 - 1) - k0;
-                        const int hi = (int)((hi_l > kSnapTile) ? kSnapTile : ((hi_l < -1) ? -1 : hi_l)) - 4 * h;
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int e = 8 * (v / 4) + (v % 4);  // + 4 h: folded into hi
-                            if (e > hi) sacc[v] = -INFINITY;
-                        }
-                    }
-                    // Weights against the reference point as it is (none yet: its negative is +inf, and so are they);
-                    // the point moves to the maximum so far only where a lane's 16 weights add up to more than kSnapLarge.
-                    // (Each half of a row's lanes keeps its own sum; they meet at the end.)
-                    auto weights = [&](float ref) __attribute__((always_inline)) -> float {
-                        float p4[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) p4[v % 4] += __builtin_amdgcn_exp2f(fmaf(sacc[v], cs, -ref));
-                        return (p4[0] + p4[1]) + (p4[2] + p4[3]);
-                    };
-                    float ps = weights(m[rg]);
-#pragma unroll
-                    for (int v = 0; v < 16; v += 2) top[rg] = fmaxf(fmaxf(top[rg], sacc[v]), sacc[v + 1]);
-                    if (__any(!(ps <= kSnapLarge))) {
-                        const float m_new = half_pair_max(top[rg]) * cs;
-                        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-                        l[rg] *= (m[rg] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[rg] - m_safe);
-                        ps = weights(m_safe);
-                        m[rg] = m_new;
-                    }
-                    l[rg] += ps;
-                }
-            };
-            if (k0 + kSnapTile > kc1 || k0 + kSnapTile - 1 > L) groups(std::true_type{});  // (uniform)
-            else groups(std::false_type{});
-        });
-#pragma unroll
-        for (int rg = 0; rg < NRG; ++rg) {
-            // (the statistics are those of the maximum: what the normaliser is rounded to does not hang on the reference)
-            const float mt = half_pair_max(top[rg]) * cs, ls = half_pair_sum(l[rg]);
-            if (h == 0) {
-                s_ml[wave][32 * rg + lq][0] = mt;
-                s_ml[wave][32 * rg + lq][1] = (mt == -INFINITY) ? 0.f : ls * __builtin_amdgcn_exp2f(m[rg] - mt);
+                for (int c = 0; c < NC; ++c) sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c], qf[c], sacc[u], 0, 0, 0);  // [key][row]
             }
+            const long k0 = kc0 + (long)it * kSnapStep;
+            if (k0 + kSnapStep > kc1 || k0 + kSnapStep - 1 > L) {  // (uniform)
+                // keys of this step a lane may see, as offsets from k0: 0 .. hi
+                const long hi_l = ((pos < kc1 - 1) ? pos : kc1 - 1) - k0;
+                const int hi = (int)((hi_l > kSnapStep) ? kSnapStep : ((hi_l < -1) ? -1 : hi_l)) - 4 * h;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int e = 32 * u + 8 * (v / 4) + (v % 4);  // + 4 h: folded into hi
+                        if (e > hi) sacc[u][v] = -INFINITY;
+                    }
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[u][v]);
+            mx = half_pair_max(mx) * cs;
+            const float m_new = fmaxf(m, mx);
+            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+            float psum = 0.f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(fmaf(sacc[u][v], cs, -m_safe));
+            psum = half_pair_sum(psum);
+            l = l * ((m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_safe)) + psum;
+            m = m_new;
         }
-        __syncthreads();
-        const int r = rt * ROWS + tid;
-        if (tid < ROWS && r < R) {  // (max, sum) back in the natural-log domain
-            float M = -INFINITY, S = 0.f;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) M = fmaxf(M, s_ml[w][tid][0]);
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-                if (s_ml[w][tid][0] != -INFINITY) S += s_ml[w][tid][1] * __builtin_amdgcn_exp2f(s_ml[w][tid][0] - M);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing is on its way into the slots any more
+        asm volatile("s_barrier" ::: "memory");  // ... nor read out of them
+        if (r_ok && h == 0) {  // (max, sum) back in the natural-log domain
             float *sp = stats + (((long)bk * n_chunks + chunk) * R + r) * 2;
-            sp[0] = M * 0.6931471805599453f;
-            sp[1] = S;
+            sp[0] = m * 0.6931471805599453f;
+            sp[1] = l;
         }
-        // (the next row tile's barriers come before its statistics)
     }
 }
 
@@ -252,7 +248,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 template <int D, int NRG, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_votes_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, const float *__restrict__ lse,
-    const float *__restrict__ stats, int n_chunks, float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
+    float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
     uint32_t *__restrict__ sel_hist, long n_hist)
 {
     // the selection's bins start at zero
@@ -263,8 +259,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(1024))) uint16_t sK0[4 * kSnapTile * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sK1[4 * kSnapTile * D];
     __shared__ __attribute__((aligned(16))) float s_lse2[ROWS];  // row log-sum-exp, base-2 domain
-    constexpr int PARTS = 256 / ROWS;  // threads that share a row's statistics
-    __shared__ float s_part[PARTS][ROWS][2];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, h = lane >> 5;
@@ -284,49 +278,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     for (int rt = 0; rt < n_row_tiles; ++rt) {
         st.template tile<AUX>(kb, kc0 + wave * kSnapTile, kc1, slot0);
-        // The rows' log-sum-exp: handed in, or from the statistics of the first sweep's chunks, which every workgroup folds
-        // for itself in a fixed order, beside its first loads (as a launch of its own: 5-6 us).
-        const int rr = rt * ROWS + tid % ROWS;
-        if (!lse) {
-            float M = -INFINITY, S = 0.f;
-            const float2 *sp = reinterpret_cast<const float2 *>(stats) + (long)bk * n_chunks * R + (rr < R ? rr : 0);
-            constexpr int U = 8;  // chunks on their way at a time
-            for (int c0 = tid / ROWS; c0 < n_chunks; c0 += U * PARTS) {
-                float2 x[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int c = c0 + u * PARTS;
-                    x[u] = sp[(long)(c < n_chunks ? c : c0) * R];
-                    if (c >= n_chunks) x[u] = make_float2(-INFINITY, 0.f);
-                }
-                float Mn = M;
-#pragma unroll
-                for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, x[u].x);
-                if (Mn != -INFINITY) {
-                    S *= (M == -INFINITY) ? 0.f : __expf(M - Mn);
-#pragma unroll
-                    for (int u = 0; u < U; ++u) S += (x[u].x == -INFINITY) ? 0.f : x[u].y * __expf(x[u].x - Mn);
-                    M = Mn;
-                }
-            }
-            s_part[tid / ROWS][tid % ROWS][0] = M;
-            s_part[tid / ROWS][tid % ROWS][1] = S;
-        }
         bf16x8 qf[NRG][NC];
         snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
         // (base-2 domain; +inf for padding rows: their votes vanish.  The previous row tile's readers are two barriers back.)
         if (tid < ROWS) {
-            float x = INFINITY;
-            if (rr < R && lse) x = lse[(long)bk * R + rr] * 1.4426950408889634f;
-            if (rr < R && !lse) {
-                float M = -INFINITY, S = 0.f;
-#pragma unroll
-                for (int p = 0; p < PARTS; ++p) M = fmaxf(M, s_part[p][tid][0]);
-#pragma unroll
-                for (int p = 0; p < PARTS; ++p) S += (s_part[p][tid][0] == -INFINITY) ? 0.f : s_part[p][tid][1] * __expf(s_part[p][tid][0] - M);
-                x = (M + __logf(S)) * 1.4426950408889634f;
-            }
-            s_lse2[tid] = x;
+            const int rr = rt * ROWS + tid;
+            s_lse2[tid] = (rr < R) ? lse[(long)bk * R + rr] * 1.4426950408889634f : INFINITY;
         }
         __syncthreads();
         st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
@@ -365,6 +322,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         });
     }
+}
+
+// log-sum-exp of each row over its key chunks: one wave per row, lanes over chunks
+__global__ __launch_bounds__(256) void snapkv_lse_kernel(const float *__restrict__ stats, float *__restrict__ lse, int R,
+                                                         int n_chunks, long rows_total)
+{
+    const long i = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (i >= rows_total) return;
+    const long bk = i / R;
+    const int r = (int)(i % R);
+    float M = -INFINITY;
+    for (int c = lane; c < n_chunks; c += 64) M = fmaxf(M, stats[((bk * n_chunks + c) * R + r) * 2]);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, shfl_xor_f(M, m));
+    float Ls = 0.f;
+    for (int c = lane; c < n_chunks; c += 64) {
+        const float mc = stats[((bk * n_chunks + c) * R + r) * 2];
+        if (mc != -INFINITY) Ls += stats[((bk * n_chunks + c) * R + r) * 2 + 1] * __expf(mc - M);
+    }
+    // fixed butterfly order: the same bits on every run
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) Ls += shfl_xor_f(Ls, m);
+    if (lane == 0) lse[i] = M + __logf(Ls);
 }
 
 // ------------------------------------------------------------------------------------
@@ -658,7 +639,7 @@ static size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct SnapLayout {
     int n_chunks, R, keys_per_wg;
-    size_t off_stats, off_votes, off_pooled, off_hist, total;
+    size_t off_stats, off_lse, off_votes, off_pooled, off_hist, total;
     int n_slices;
 };
 
@@ -676,6 +657,8 @@ static SnapLayout snap_layout(const rs_shape *s, long T, int W)
     size_t o = RS_WS_CTRL_BYTES;
     L.off_stats = o;
     o += al256s((size_t)BK * L.n_chunks * L.R * 2 * 4);
+    L.off_lse = o;
+    o += al256s((size_t)BK * L.R * 4);
     L.off_votes = o;
     o += al256s((size_t)BK * (T - W) * 4);
     L.off_pooled = o;
@@ -697,7 +680,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     const SnapLayout Ly = snap_layout(s, T, W);
     const long BK = (long)s->B * s->Hkv;
     const long L = T - W;
-    float *stats = (float *)(ws + Ly.off_stats);
+    float *stats = (float *)(ws + Ly.off_stats), *lse = (float *)(ws + Ly.off_lse);
     float *votes = (float *)(ws + Ly.off_votes);
     float *pooled = votes_out ? votes_out : (float *)(ws + Ly.off_pooled);
     const dim3 grid((unsigned)Ly.n_chunks, (unsigned)BK);
@@ -716,7 +699,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     } while (0)
     // From about 80 MB of keys on streaming loads: ordinary ones have the memory-side cache make room for every line (cold
     // keys 64 us a sweep against 47 at 268 MB), and what the first sweep leaves there saves the second one and the gather
-    // less than that.  The whole compression, ordinary / streaming, us: 8 heads x 128K 168 / 156, x 97492 141 / 133, x 41000
+    // less than that.  The whole compression (with a first sweep by the waves' own tiles), ordinary / streaming, us: 8 heads x 128K 168 / 156, x 97492 141 / 133, x 41000
     // (84 MB) 90.3 / 89.1, 8 x 32 heads x 4096 154 / 134, x 2000 92 / 81, 4 x 8 x 13070 101 / 93; the other way 8 heads x 32768
     // (67 MB) to 1/8 62.6 / 63.3, to 1/16 58.3 / 60.7.
     const bool streaming = BK * T * s->D * 2 >= 80l << 20;
@@ -724,11 +707,15 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     // the window rows has it), or from a first sweep over the keys
     // ([B, Hq, W] is [B * Hkv][G * W])
     if (!lse_in) {
-#define RS_STATS(DD, GG, SS) \
-    snapkv_stats_kernel<DD, GG, SS><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
-        if (s->D == 128) RS_SNAP_ROWS(RS_STATS, 128);
-        else RS_SNAP_ROWS(RS_STATS, 64);
+#define RS_STATS(DD, SS) \
+    snapkv_stats_kernel<DD, SS><<<grid, 256, 0, stream>>>(qw, kc, stats, s->Hq, s->Hkv, T, s->Tcap, W, Ly.n_chunks, scale, Ly.keys_per_wg)
+        if (s->D == 128 && streaming) RS_STATS(128, true);
+        else if (s->D == 128) RS_STATS(128, false);
+        else if (streaming) RS_STATS(64, true);
+        else RS_STATS(64, false);
 #undef RS_STATS
+        const long rows_total = BK * Ly.R;
+        snapkv_lse_kernel<<<(unsigned)((rows_total + 3) / 4), 256, 0, stream>>>(stats, lse, Ly.R, Ly.n_chunks, rows_total);
     }
     // votes exist for prefix keys only: chunks that start past the prefix are not needed
     const dim3 grid2((unsigned)((L + Ly.keys_per_wg - 1) / Ly.keys_per_wg), (unsigned)BK);
@@ -736,7 +723,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
     const long n_hist = one_wg ? 0 : BK * 1024;
 #define RS_VOTES(DD, GG, SS) \
-    snapkv_votes_kernel<DD, GG, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse_in, stats, Ly.n_chunks, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
+    snapkv_votes_kernel<DD, GG, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse_in ? lse_in : lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
     if (s->D == 128) RS_SNAP_ROWS(RS_VOTES, 128);
     else RS_SNAP_ROWS(RS_VOTES, 64);
 #undef RS_VOTES

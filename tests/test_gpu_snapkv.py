@@ -1,5 +1,7 @@
 """GPU parity of SnapKV compression (window votes, pooling, top-K positions, gather) and of
 dense decode over the compressed cache, against the float64 oracle, through the C ABI."""
+import hashlib
+
 import numpy as np
 import pytest
 import torch
@@ -262,3 +264,60 @@ def test_sweeps_at_the_edges_of_tiles(rs, Hq, Hkv, D, W, grow):
         assert torch.equal(best.int(), idx)
         rows = torch.cat([best, torch.arange(L, T, device="cuda").expand(B, Hkv, W)], 2)[..., None].expand(-1, -1, -1, D)
         assert torch.equal(ko, k.gather(2, rows)) and torch.equal(vo, v.gather(2, rows))
+
+
+def _of_integers(shape, seed):
+    """bf16 values of about unit variance from integer arithmetic alone: the same bits wherever they are made."""
+    n = int(np.prod(shape))
+    x = torch.arange(n, dtype=torch.int64, device="cuda") + (seed << 40)
+    total = torch.zeros_like(x)
+    for _ in range(2):
+        x = (x ^ (x >> 29)) * 0x2545F4914F6CDD1D + 0x1234567
+        x = (x ^ (x >> 32)) * 0x5851F42D4C957F2D
+        for shift in (0, 16, 32, 48):
+            total += (x >> shift) & 0xFFFF
+    return ((total.float() - 4 * 65535.0) / 65536.0 * 1.2247449).to(torch.bfloat16).view(shape)
+
+
+VOTE_DIGESTS = {
+    (2, 2, 2, 128, 1000, 20): "67db2d1de6e47aa6",
+    (1, 4, 2, 128, 3001, 40): "2b9369875b0263ed",
+    (1, 4, 1, 64, 65, 64): "2f535acbdc114ba3",
+    (1, 8, 2, 128, 9001, 64): "94001a61917985a4",
+    (3, 6, 3, 64, 20001, 64): "628e2acac47f6885",
+    (8, 32, 32, 128, 4096, 64): "7c6a547590751ff4",
+    (1, 8, 8, 64, 102433, 32): "c675b59fdfd0aee0",
+    (1, 8, 1, 128, 131072, 32): "f0a351f9c41bee8b",
+}
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,W", list(VOTE_DIGESTS))
+def test_votes_keep_their_bits(rs, B, Hq, Hkv, D, T, W):
+    """Which of thousands of positions are kept hangs on the last place of the votes: two on either side of the cut
+    often tie to seven digits, and one swapped tie moves a hundred entries of the ascending list.  So the votes' bits do
+    not change with the way the sweeps are laid out: these are the digests of the votes that 128-key steps by whole workgroups
+    gave, for one and several row tiles, waves without rows, a single key, up to 8, up to 64 and more chunks, with and without
+    streaming loads."""
+    say("snapkv bits", B, Hq, Hkv, D, T, W)
+    k, q = _of_integers((B, Hkv, T, D), 109), _of_integers((B, Hq, W, D), 110)
+    _, votes, _ = _compress(rs, q, k, k, T, W, 1, 1, D ** -0.5)
+    assert hashlib.sha1(votes.cpu().numpy().tobytes()).hexdigest()[:16] == VOTE_DIGESTS[B, Hq, Hkv, D, T, W]
+
+
+def test_kept_positions_are_those_of_64_bit_votes(rs):
+    """256 heads of 4096 tokens to 512 with pooling: plateaus of seven equal votes, and a cut that falls among thousands of
+    votes a part in a million apart.  For these inputs the votes in float32 (3.3e-7 off in the mean, a log-sum-exp of about 9
+    rounded to float32 being most of it) select what the 64-bit ones select, in every head."""
+    B, H, T, W, D, keep, pool = 8, 32, 4096, 64, 128, 512, 7
+    k, q = _of_integers((B, H, T, D), 109), _of_integers((B, H, W, D), 110)
+    idx, votes, _ = _compress(rs, q, k, k, T, W, keep, pool, D ** -0.5)
+    L = T - W
+    later = torch.arange(T, device="cuda")[None] > L + torch.arange(W, device="cuda")[:, None]
+    for b in range(B):
+        x = torch.matmul(q[b].double(), k[b].double().transpose(1, 2).contiguous()) * D ** -0.5
+        want = torch.softmax(x.masked_fill_(later, -torch.inf), 2).sum(1)[:, :L]
+        want = torch.nn.functional.max_pool1d(want[None], pool, 1, pool // 2)[0]
+        # (64 weights a vote, each exp2 and its argument within a few times 2^-24 x 16)
+        assert ((votes[b].double() - want).abs() <= 4e-6 * want).all()
+        first = torch.sort(want, dim=1, descending=True, stable=True).indices[:, :keep].sort(1).values
+        assert torch.equal(idx[b].long(), first), b
