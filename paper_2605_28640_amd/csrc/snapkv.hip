@@ -22,6 +22,11 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kSnapKeysPerWg = 2048;  // keys per workgroup, at most (fewer when that leaves the chip idle)
 constexpr int kSnapKT = 128;          // a workgroup's share of the keys is a multiple of this
 constexpr int kSnapTile = 32;         // keys of a wave's tile
+// Up to this many chunks the second sweep's workgroups fold the first one's statistics for themselves, 8 KB at most for 128
+// rows, and the launch between the sweeps falls away: 8 x 32 heads x 4096 (2 chunks) 134.8 -> 130.2 us, 4 x 8 x 2000 (8 chunks)
+// 31.9 -> 30.1.  Every workgroup reads the statistics of all chunks of its head, so that the reads grow with the square of the
+// chunks: without the line 2 heads x 128K (256 chunks of 256 rows) took 79 us for 67, one head 120 for 66.
+constexpr int kSnapFoldChunks = 8;
 constexpr int kSnapStep = 64;         // keys of a step of the first sweep
 
 // Both sweeps bring the keys by direct global -> LDS loads (unpadded rows, 16-byte chunks permuted by chunk_swizzle; rows
@@ -245,10 +250,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // sweep 2: the votes.  S = Q K^T: a lane owns one key column of the wave's tile against all query rows of the
 // row tile, so a key's vote is an in-lane sum plus one cross-half shuffle and is written straight out.  Only
 // prefix keys (< L) are stored, and every window query sees all of them: no mask is needed.
-template <int D, int NRG, bool STREAM>
+template <int D, int NRG, bool STREAM, bool FOLD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_votes_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, const float *__restrict__ lse,
-    float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
+    const float *__restrict__ stats, int n_chunks, float *__restrict__ votes, int Hq, int Hkv, long T, long Tcap, int W, float scale, int keys_per_wg,
     uint32_t *__restrict__ sel_hist, long n_hist)
 {
     // the selection's bins start at zero
@@ -278,12 +283,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     for (int rt = 0; rt < n_row_tiles; ++rt) {
         st.template tile<AUX>(kb, kc0 + wave * kSnapTile, kc1, slot0);
+        // the rows' log-sum-exp: from lse, or (FOLD) from the statistics of the first sweep's few chunks
+        const int rr = rt * ROWS + tid;
+        float2 part[kSnapFoldChunks];
+        if (FOLD && tid < ROWS) {
+            const float2 *sp = reinterpret_cast<const float2 *>(stats) + (long)bk * n_chunks * R + (rr < R ? rr : 0);
+#pragma unroll
+            for (int c = 0; c < kSnapFoldChunks; ++c) part[c] = (c < n_chunks) ? sp[(long)c * R] : make_float2(-INFINITY, 0.f);
+        }
         bf16x8 qf[NRG][NC];
         snap_query_fragments<D, NRG>(q_win + ((long)bk * R + rt * ROWS) * D, R - rt * ROWS, st, sK1, qf);
         // (base-2 domain; +inf for padding rows: their votes vanish.  The previous row tile's readers are two barriers back.)
         if (tid < ROWS) {
-            const int rr = rt * ROWS + tid;
-            s_lse2[tid] = (rr < R) ? lse[(long)bk * R + rr] * 1.4426950408889634f : INFINITY;
+            float x = INFINITY;
+            if (!FOLD && rr < R) x = lse[(long)bk * R + rr] * 1.4426950408889634f;
+            if (FOLD && rr < R) {
+                float M = -INFINITY;
+#pragma unroll
+                for (int c = 0; c < kSnapFoldChunks; ++c) M = fmaxf(M, part[c].x);
+                // (the launch's order of sums, whose lanes beyond the chunks add zeros: the same bits)
+#pragma unroll
+                for (int c = 0; c < kSnapFoldChunks; ++c) part[c].y = (part[c].x == -INFINITY) ? 0.f : part[c].y * __expf(part[c].x - M);
+#pragma unroll
+                for (int d = kSnapFoldChunks / 2; d >= 1; d /= 2)
+#pragma unroll
+                    for (int c = 0; c < d; ++c) part[c].y += part[c + d].y;
+                x = (M + __logf(part[0].y)) * 1.4426950408889634f;
+            }
+            s_lse2[tid] = x;
         }
         __syncthreads();
         st.template tile<AUX>(kb, kc0 + (wave + 4) * kSnapTile, kc1, slot1);
@@ -703,6 +730,7 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
     // (84 MB) 90.3 / 89.1, 8 x 32 heads x 4096 154 / 134, x 2000 92 / 81, 4 x 8 x 13070 101 / 93; the other way 8 heads x 32768
     // (67 MB) to 1/8 62.6 / 63.3, to 1/16 58.3 / 60.7.
     const bool streaming = BK * T * s->D * 2 >= 80l << 20;
+    const bool fold = !lse_in && Ly.n_chunks <= kSnapFoldChunks;
     // the rows' log-sum-exp over all visible keys: handed in by the caller (the prefill attention of
     // the window rows has it), or from a first sweep over the keys
     // ([B, Hq, W] is [B * Hkv][G * W])
@@ -715,18 +743,24 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
         else RS_STATS(64, false);
 #undef RS_STATS
         const long rows_total = BK * Ly.R;
-        snapkv_lse_kernel<<<(unsigned)((rows_total + 3) / 4), 256, 0, stream>>>(stats, lse, Ly.R, Ly.n_chunks, rows_total);
+        if (!fold) snapkv_lse_kernel<<<(unsigned)((rows_total + 3) / 4), 256, 0, stream>>>(stats, lse, Ly.R, Ly.n_chunks, rows_total);
     }
     // votes exist for prefix keys only: chunks that start past the prefix are not needed
     const dim3 grid2((unsigned)((L + Ly.keys_per_wg - 1) / Ly.keys_per_wg), (unsigned)BK);
     const bool one_wg = L <= kSnapOneWgKeys && knobs().snap_one_wg != 0;  // (knob 0: the spread-out selection at any length)
     uint32_t *sel_hist = (uint32_t *)(ws + Ly.off_hist);
     const long n_hist = one_wg ? 0 : BK * 1024;
-#define RS_VOTES(DD, GG, SS) \
-    snapkv_votes_kernel<DD, GG, SS><<<grid2, 256, 0, stream>>>(qw, kc, lse_in ? lse_in : lse, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
+#define RS_VOTES1(DD, GG, SS, FF) \
+    snapkv_votes_kernel<DD, GG, SS, FF><<<grid2, 256, 0, stream>>>(qw, kc, lse_in ? lse_in : lse, stats, Ly.n_chunks, votes, s->Hq, s->Hkv, T, s->Tcap, W, scale, Ly.keys_per_wg, sel_hist, n_hist)
+#define RS_VOTES(DD, GG, SS)                    \
+    do {                                        \
+        if (fold) RS_VOTES1(DD, GG, SS, true);  \
+        else RS_VOTES1(DD, GG, SS, false);      \
+    } while (0)
     if (s->D == 128) RS_SNAP_ROWS(RS_VOTES, 128);
     else RS_SNAP_ROWS(RS_VOTES, 64);
 #undef RS_VOTES
+#undef RS_VOTES1
 #undef RS_SNAP_ROWS
 #undef RS_SNAP_ROWS1
     if (one_wg) {

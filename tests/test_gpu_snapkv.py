@@ -281,6 +281,9 @@ def _of_integers(shape, seed):
 
 VOTE_DIGESTS = {
     (2, 2, 2, 128, 1000, 20): "67db2d1de6e47aa6",
+    (1, 4, 1, 128, 2048, 32): "e0580499a646cead",
+    (1, 4, 1, 128, 2049, 32): "04ff56d1c8dd338a",
+    (2, 16, 2, 64, 1800, 20): "2e991ac47f2ca60b",
     (1, 4, 2, 128, 3001, 40): "2b9369875b0263ed",
     (1, 4, 1, 64, 65, 64): "2f535acbdc114ba3",
     (1, 8, 2, 128, 9001, 64): "94001a61917985a4",
