@@ -27,11 +27,13 @@ template <typename ST, int D, int TPI>
 struct AttendStep {
     static constexpr int RPW = 64 / (D / 8), TR = 16, RPL = TR / RPW;
     typename Row8<ST>::raw_t k[TPI][RPL], v[TPI][RPL];
-    int rows[TPI];  // valid rows of the tile (0: none)
+    int rows[TPI];  // valid rows of the tile, 0 .. 16 (0: none)
 
     // Tiles t .. t + TPI - 1 as far as they lie below te.  row_of(t): the tile's first row, or T_valid for none; called once
     // per tile, in order, by the whole wave (t, te: the same in all lanes).  The loads go through descriptors that end
     // with the last valid row of their tile, unconditionally: rows that do not exist come as zeros and count for nothing.
+    // (Tiles of a last page may begin past T_valid, and a listed page may lie anywhere past it: a count below 0, which the
+    // descriptor would take for 4 GB, or one cut to 32 bits would bring rows that are there, 0 times NaN among them.)
     template <bool STREAM, typename RowOf>
     __device__ __forceinline__ void load(const ST *kb, const ST *vb, long T_valid, long t, long te, RowOf row_of)
     {
@@ -42,7 +44,7 @@ struct AttendStep {
         for (int u = 0; u < TPI; ++u) {
             const long row0 = (t + u < te) ? row_of(t + u) : T_valid;
             const long left = T_valid - row0;
-            rows[u] = (int)(left < TR ? left : TR);
+            rows[u] = left >= TR ? TR : left > 0 ? (int)left : 0;
             const long from = left > 0 ? row0 : 0;
             kd[u] = lds_source_sized(kb + from * D, rows[u] * ROW);
             vd[u] = lds_source_sized(vb + from * D, rows[u] * ROW);

@@ -547,3 +547,71 @@ def test_selection_by_every_split_or_by_a_launch_of_its_own(rs, knobs, P, T, K, 
     assert torch.equal(got[0][2], got[1][2]) and int(got[0][2].min()) == 0 and int(got[0][2].max()) == Np - 1
     for o in got[1:]:
         assert torch.equal(o[0], got[0][0]) and torch.equal(o[1], got[0][1])
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("P", [32, 64, 512])
+@pytest.mark.parametrize("form", ["one_wg", "select_by_split", "select_by_launch", "persistent", "step", "listed", "group", "group_listed"])
+def test_rows_that_are_not_attended_count_for_nothing(rs, knobs, form, P, dtype, D):
+    """Only rows below T_valid of kept pages may reach the result.  Rows from T_valid on hold NaN (tiles of the last page
+    begin past it wherever P >= 32), page 0 is not kept and the values of its first 16 rows are infinite or NaN, and given
+    lists also name pages past the end: the first one, and one whose first row is 2^32."""
+    G = 2 if form.startswith("group") else 1
+    B, Hkv, dt, tol = 1, 2, tdtype(dtype), 2e-2 if dtype == "bf16" else 1e-4  # (the tolerances of the tests above)
+    Hq, scale = Hkv * G, 1.0 / np.sqrt(D)
+    knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", "0" if form == "persistent" else "1")
+    knobs.setenv("RATSPARSE_FUSED_ONE_WG", "1" if form == "one_wg" else "0")
+    knobs.setenv("RATSPARSE_ATTEND_SHARED", "1")
+    for T in (1, 5, 15, 17, P + 1, 2 * P + 3, 63 * P + 17, 70 * P + 16):
+        Np = -(-T // P)
+        K = min(3, Np - 1) if Np > 1 else 1  # (page 0 is left out where there is another)
+        say("rows not attended", form, P, dtype, T, K)
+        Tcap = (Np + 1) * P
+        gen = torch.Generator(device="cuda").manual_seed(T)
+        kc, vc = (torch.randn(B, Hkv, Tcap, D, generator=gen, device="cuda") for _ in range(2))
+        q = (torch.randn(B, Hq, D, generator=gen, device="cuda").abs() + 0.1).to(dt)
+        meta = torch.zeros(B, Hkv, Tcap // P, 2, D, dtype=dt, device="cuda")
+        if Np > 1:
+            kc[:, :, :P] = -4.0
+            vc[:, :, :16:3], vc[:, :, 1:16:3] = torch.inf, torch.nan
+        kc[:, :, T:], vc[:, :, T:] = torch.nan, torch.nan
+        kc, vc = kc.to(dt), vc.to(dt)
+        s = rs.make_shape(B, Hq, Hkv, D, Tcap, P, dt)
+        rs.quest_page_meta(s, kc, meta, 0, T)
+        heads = Hkv if G > 1 else Hq
+        idx = torch.full((B, heads, K), -5, dtype=torch.int32, device="cuda")
+        out, lse = torch.full((B, Hq, D), 7.0, dtype=dt, device="cuda"), torch.full((B, Hq), 7.0, device="cuda")
+        need = rs.sparse_attn_decode_workspace_bytes(s, T, max(K, 3))
+        if form == "select_by_launch":
+            need = rs.sparse_attn_decode_workspace_bytes(s, T, K) - -(-(B * Hq * (-(-Np // 4) * 4) * 4) // 256) * 256 - 256
+        ws = rs.Workspace(need)
+        if form == "step":
+            ws = rs.Workspace(rs.rat_decode_step_workspace_bytes(s, T, K))
+            rs.rat_decode_state_set(ws, T - 1)
+            state = [torch.randn(B, Hkv, D, generator=gen, device="cuda") for _ in range(2)]
+            k, v = (torch.randn(B, Hkv, 1, D, generator=gen, device="cuda").to(dt) for _ in range(2))
+            g = torch.rand(B, Hkv, 1, D, generator=gen, device="cuda")
+            rs.rat_decode_step(s, k, v, g, *state, kc, vc, meta, q, scale, K, 0, 1, T, out, lse, idx, ws)
+        elif form.endswith("listed"):
+            if Np > 2:
+                K = 3
+                idx = torch.tensor([Np - 1, Np, 2 ** 32 // P], dtype=torch.int32, device="cuda").repeat(B, heads, 1)
+            else:
+                idx[:] = Np - 1
+            call = rs.sparse_attn_decode_group if G > 1 else rs.sparse_attn_decode
+            call(s, q, kc, vc, T, scale, idx, K, None, 0, 0, out, lse, None, ws)
+        else:
+            call = rs.sparse_attn_decode_group if G > 1 else rs.sparse_attn_decode
+            call(s, q, kc, vc, T, scale, None, K, meta, 0, 1, out, lse, idx, ws)
+        torch.cuda.synchronize()
+        ws.async_status()
+        for b in range(B):
+            for h in range(Hq):
+                pages = [p for p in idx[b, h // G].tolist() if p < Np]
+                assert pages[-1] == Np - 1 and (Np == 1 or 0 not in pages), pages
+                rows = torch.cat([torch.arange(p * P, min((p + 1) * P, T)) for p in pages]).cuda()
+                x = kc[b, h // G, rows].double() @ q[b, h].double() * scale
+                want = torch.softmax(x, 0) @ vc[b, h // G, rows].double()
+                ok, worst = attn_close(to_np(out[b, h]), to_np(want), tol)
+                assert ok, (T, h, worst)
+                np.testing.assert_allclose(float(lse[b, h]), float(torch.logsumexp(x, 0)), rtol=1e-4, atol=1e-4)
