@@ -61,6 +61,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     using R = Row8<ST>;
 
     __shared__ int s_ticket;
+    __shared__ int s_drawn;  // (a word of its own: s_ticket is still being read when the first chunk parks its drawn ticket)
     __shared__ float s_agg[NW][3][DS];
     __shared__ float s_carry[NW][2][DS];
 
@@ -298,11 +299,11 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     }
     }
     if constexpr (DS == D) {
-        if (tid == kTicketThread) s_ticket = drawn;
+        if (tid == kTicketThread) s_drawn = drawn;  // read behind the barrier below; the chain step's barrier lies before the next write
     }
     __syncthreads();
     int nt = total;
-    if constexpr (DS == D) nt = __builtin_amdgcn_readfirstlane(s_ticket);
+    if constexpr (DS == D) nt = __builtin_amdgcn_readfirstlane(s_drawn);
 
     if (tid < DS) {
         const int c = tid;
