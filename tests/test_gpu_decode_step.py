@@ -67,6 +67,8 @@ def _force_form(knobs, form):
 
 
 FORMS = ["persistent", "one_wg", "two_launch"]
+# (from 64 pages at T_max on, the third case here, the second of two launches selects for itself)
+CASE_FORMS = [pytest.param(0, form, id=form) for form in FORMS] + [pytest.param(2, "two_launch", id="two_launch_long")]
 
 
 @pytest.mark.parametrize("form", FORMS)
@@ -131,11 +133,11 @@ def test_step_equals_scan_then_fused_decode(rs, knobs, case, form):
     assert ok, worst
 
 
-@pytest.mark.parametrize("form", FORMS)
-def test_step_past_the_sized_length_changes_nothing_and_reports(rs, knobs, form):
+@pytest.mark.parametrize("case,form", CASE_FORMS)
+def test_step_past_the_sized_length_changes_nothing_and_reports(rs, knobs, case, form):
     _force_form(knobs, form)
-    w, T0, steps, Tcap, P, K, n_first, n_local = CASES[0]
-    w, s, pre, a, b = _setup(rs, 0)
+    w, T0, steps, Tcap, P, K, n_first, n_local = CASES[case]
+    w, s, pre, a, b = _setup(rs, case)
     dt = tdtype(w.dtype)
     scale = 1.0 / np.sqrt(w.D)
     T_max = T0 + 1
@@ -160,15 +162,15 @@ def test_step_past_the_sized_length_changes_nothing_and_reports(rs, knobs, form)
     assert torch.equal(keep[3], out)
 
 
-@pytest.mark.parametrize("form", FORMS)
-def test_step_with_fewer_pages_than_K_changes_nothing_and_reports(rs, knobs, form):
+@pytest.mark.parametrize("case,form", CASE_FORMS)
+def test_step_with_fewer_pages_than_K_changes_nothing_and_reports(rs, knobs, case, form):
     """A step taken while the sequence still has fewer pages than K must select (right after
     rat_decode_state_set with a short T) is refused by the attention kernel; the append of the same
     call must then leave the carries, the caches and the page bounds alone too, or a later replay
     would apply the gate to the carry a second time."""
     _force_form(knobs, form)
-    w, T0, steps, Tcap, P, K, n_first, n_local = CASES[0]
-    w, s, pre, a, b = _setup(rs, 0)
+    w, T0, steps, Tcap, P, K, n_first, n_local = CASES[case]
+    w, s, pre, a, b = _setup(rs, case)
     dt = tdtype(w.dtype)
     scale = 1.0 / np.sqrt(w.D)
     T_max = Tcap
@@ -198,11 +200,11 @@ def test_step_with_fewer_pages_than_K_changes_nothing_and_reports(rs, knobs, for
     np.testing.assert_array_equal(to_np(idx), np.broadcast_to(np.arange(K, dtype=np.int32), (w.B, w.Hq, K)))
 
 
-@pytest.mark.parametrize("form", FORMS)
-def test_step_replays_from_a_captured_graph(rs, knobs, form):
+@pytest.mark.parametrize("case,form", CASE_FORMS)
+def test_step_replays_from_a_captured_graph(rs, knobs, case, form):
     _force_form(knobs, form)
-    _, T0, steps, Tcap, P, K, n_first, n_local = CASES[0]
-    w, s, pre, a, b = _setup(rs, 0)
+    _, T0, steps, Tcap, P, K, n_first, n_local = CASES[case]
+    w, s, pre, a, b = _setup(rs, case)
     dt = tdtype(w.dtype)
     T_max = T0 + steps + 1
     scale = 1.0 / np.sqrt(w.D)
@@ -243,8 +245,15 @@ def test_step_replays_from_a_captured_graph(rs, knobs, form):
         torch.cuda.synchronize()
         assert torch.equal(idx_a, idx_b), t
         assert torch.equal(out_a, out_b), t
-    assert a.same_as(b)
     assert rs.rat_decode_state_get(ws_a) == T0 + steps + 1
+    for T in (K * P + 5, max(K * P, T0 // 8)):  # the same graph, at lengths far below the one the launches are laid out for
+        rs.rat_decode_state_set(ws_a, T)
+        graph.replay()
+        eager(T - T0)
+        torch.cuda.synchronize()
+        assert torch.equal(idx_a, idx_b) and torch.equal(out_a, out_b), T
+        assert rs.rat_decode_state_get(ws_a) == T + 1
+    assert a.same_as(b)
     ws_a.async_status()
 
 

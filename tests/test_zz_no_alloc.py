@@ -101,9 +101,31 @@ def test_size_limit_is_refused_before_anything_runs(rs):
     # batch 4, 32 heads, 64K tokens + 512 steps, K = 1024: the largest configured decode shape
     s = rs.make_shape(4, 32, 32, 128, 66048, 16, torch.bfloat16)
     assert rs.sparse_attn_decode_workspace_bytes(s, 66048, 1024) <= rs.RS_STATIC_SCRATCH_BYTES
+    keys = -(-(4 * 32 * 4128 * 4) // 256) * 256 + 256  # (that count takes in the page keys, which need not fit)
+    assert round((rs.sparse_attn_decode_workspace_bytes(s, 66048, 1024) - keys) / 2 ** 20, 1) == 13.7
     big = rs.make_shape(16, 32, 32, 128, 66048, 16, torch.bfloat16)
     assert rs.sparse_attn_decode_workspace_bytes(big, 66048, 1024) > rs.RS_STATIC_SCRATCH_BYTES
     st = lib.sparse_attn_decode_static(ctypes.byref(big), A, A, A, 66048, 0.1, None, 1024, A, 1, 1, A, None, None, A, None)
     assert st == 6 and b"static" in lib.ratsparse_status_string(st)
     assert lib.sparse_attn_decode_static(ctypes.byref(s), A, A, A, 66048, 0.1, None, 1024, A, 1, 1, A, None, None, None,
                                          None) == 1  # the error word is required
+
+
+def test_between_the_scratch_without_and_with_page_keys(rs, knobs):
+    """The static array has no room for the page keys of this list but for everything else: the first launch selects,
+    where the workspace entry point's attention selects for itself, with the same bits; a list that leaves no room
+    for the rest is refused."""
+    knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", "1")
+    knobs.setenv("RATSPARSE_FUSED_ONE_WG", "0")
+    B, Hq, Hkv, D, T, P = 8, 16, 2, 64, 80000, 16
+    s = rs.make_shape(B, Hq, Hkv, D, T, P, torch.bfloat16)
+    keys = B * Hq * (T // P) * 4 + 256
+    need = lambda K: rs.sparse_attn_decode_workspace_bytes(s, T, K) - keys
+    K = max(k for k in range(3000, T // P) if need(k) <= rs.RS_STATIC_SCRATCH_BYTES)
+    assert need(K) + keys > rs.RS_STATIC_SCRATCH_BYTES and need(K + 1) > rs.RS_STATIC_SCRATCH_BYTES
+    say("no-alloc between", K)
+    a, b = _both(rs, (B, Hq, Hkv, D, T, P), T, K, "fused", 5)
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    A = 1 << 20  # made-up aligned addresses: refused before any launch
+    st = rs.load().sparse_attn_decode_static(ctypes.byref(s), A, A, A, T, 0.1, None, K + 1, A, 1, 1, A, None, None, A, None)
+    assert st == 6
