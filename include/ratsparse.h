@@ -21,7 +21,7 @@
  *     default stream) and the call returns without waiting for it.  Arguments are
  *     validated synchronously before anything is enqueued.
  *   - Scratch memory is a caller buffer `ws` of at least <entry>_workspace_bytes()
- *     bytes.  Its first RS_WS_CTRL_BYTES are control words that must be zero when a
+ *     bytes (sparse_attn_decode, its _group form and rat_decode_step also take less, see there).  Its first RS_WS_CTRL_BYTES are control words that must be zero when a
  *     call starts: zero them once with ratsparse_workspace_init(); every entry
  *     point leaves them zero again when its kernels have finished.  One workspace
  *     must not be used by two calls that can run at the same time.
@@ -61,7 +61,7 @@ enum {
     RS_OK = 0,
     RS_INVALID_ARG = 1,         /* null / misaligned pointer, non-positive size, K out of range, T > Tcap */
     RS_UNSUPPORTED = 2,         /* D not in {64,128}, page / block size not supported, dtype unknown */
-    RS_WORKSPACE_TOO_SMALL = 3, /* ws == NULL or ws_bytes below <entry>_workspace_bytes() */
+    RS_WORKSPACE_TOO_SMALL = 3, /* ws == NULL or ws_bytes below what the entry point needs */
     RS_LAUNCH_FAILED = 4,       /* hipGetLastError() after a launch */
     RS_ASYNC_TIMEOUT = 5,       /* reported by ratsparse_async_status(): a bounded in-kernel wait expired */
     RS_SCRATCH_LIMIT = 6        /* sparse_attn_decode_static: the shape needs more than RS_STATIC_SCRATCH_BYTES */
@@ -177,7 +177,12 @@ int32_t quest_select_decode(const rs_shape *s, const void *q, const void *meta,
  *                               idx_out ([B, Hq, K] or NULL) receives the selection;
  *   idx == NULL, meta == NULL   dense attention over all tokens t < T_valid (full budget).
  *   out     [B, Hq, D] dtype
- *   lse_out [B, Hq] float32 or NULL: log-sum-exp of the scaled logits */
+ *   lse_out [B, Hq] float32 or NULL: log-sum-exp of the scaled logits
+ * Workspace: sparse_attn_decode_workspace_bytes() counts the page keys of the select-then-attend mode,
+ * RS_PAGE_KEY_BYTES of them, which lie at the end of whatever workspace is given.  One smaller by these is enough
+ * (RS_WORKSPACE_TOO_SMALL only below that): where the step goes as two launches, the first one then selects,
+ * with the same results in a little more time.  The same holds for rat_decode_step. */
+#define RS_PAGE_KEY_BYTES(B, Hq, Np) ((((size_t)(B) * (Hq) * (((Np) + 3) / 4 * 4) * 4 + 255) & ~(size_t)255) + 256)
 size_t sparse_attn_decode_workspace_bytes(const rs_shape *s, int64_t T_valid, int32_t K);
 int32_t sparse_attn_decode(const rs_shape *s, const void *q, const void *k_cache,
                            const void *v_cache, int64_t T_valid, float scale,
@@ -189,16 +194,16 @@ int32_t sparse_attn_decode(const rs_shape *s, const void *q, const void *k_cache
  * For callers that cannot allocate or size device memory at the call: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same three modes, same
  * kernels and same results as sparse_attn_decode; the scratch (control words, tagged scores,
- * tagged page lists, split partials) is a device array of RS_STATIC_SCRATCH_BYTES inside the
+ * tagged page lists, split partials, page keys) is a device array of RS_STATIC_SCRATCH_BYTES inside the
  * library instead of the caller's workspace.  The call itself allocates and frees nothing
  * (no hipMalloc, no hipFree, no library routine that allocates); the first call on a
  * device looks up that device's copy of the array.
  *   async_err  device uint32, caller-owned, required: set to 1 by a kernel whose bounded wait
  *              expired (outputs then undefined); the caller zeroes it and reads it after
  *              synchronising.  It stands in for ratsparse_async_status(), which needs a workspace.
- * Limit: sparse_attn_decode_workspace_bytes(s, T_valid, K) (K = 0 in the dense mode) must not
- * exceed RS_STATIC_SCRATCH_BYTES, else RS_SCRATCH_LIMIT and nothing is enqueued.  B = 4 with
- * 32 heads at 64K tokens, 16-token pages, K = 1024 needs 14.2 MiB.
+ * Limit: sparse_attn_decode_workspace_bytes(s, T_valid, K) (K = 0 in the dense mode) less the page keys
+ * must not exceed RS_STATIC_SCRATCH_BYTES, else RS_SCRATCH_LIMIT and nothing is enqueued; the page keys have
+ * room where the whole fits.  B = 4 with 32 heads at 66048 tokens, 16-token pages, K = 1024 needs 13.7 MiB, 15.7 with them.
  * Every call on a GPU uses that GPU's one array: calls that can overlap on one GPU (two
  * streams, two host threads) race and must be serialised by the caller.  The array keeps
  * the previous call's contents; each call first clears the control words with a small

@@ -187,9 +187,11 @@ constexpr int kMaxAttSplits = 64;
 struct DecodeLayout {
     int Np, splits_score, splits_att_max;
     size_t off_scores, off_idx, off_idx_tagged, off_partial, off_trace, total;
-    // Page keys of the attention that selects for itself: the last keys_bytes of the workspace, whatever length they are for, so
-    // that at no other length of the same shape tagged words live there, which a plain word might pass for.  A
-    // workspace without room for them behind `total` is enough: the selection is then a launch of its own.
+    // Page keys of the attention that selects for itself: the last keys_bytes of the workspace, whatever length they are for.
+    // In a workspace of at least total_keys for the largest length and list of one shape no tagged word ever lies there.
+    // In others (less room, several shapes in turn, the static array) a key can lie where a later call polls for a tagged
+    // word; like anything else a workspace may hold it passes for one only if it equals that call's tag, a fresh 32-bit value.
+    // A workspace without room for them behind `total` is enough: the selection is then a launch of its own.
     size_t keys_bytes, total_keys;
 };
 
@@ -219,8 +221,8 @@ static DecodeLayout decode_layout(const rs_shape *s, long T_valid, int K)
     off += (size_t)4096 * 64 * 8;
 #endif
     L.total = off;
-    L.keys_bytes = align256((size_t)units * key_row(L.Np) * 4);
-    L.total_keys = align256(L.total) + L.keys_bytes + 256;
+    L.keys_bytes = RS_PAGE_KEY_BYTES(s->B, s->Hq, L.Np) - 256;
+    L.total_keys = align256(L.total) + RS_PAGE_KEY_BYTES(s->B, s->Hq, L.Np);  // (256: the keys begin at a multiple of it)
     return L;
 }
 
