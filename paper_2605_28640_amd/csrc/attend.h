@@ -109,8 +109,8 @@ __device__ __forceinline__ void attend_one(const AttendStep<ST, D, TPI> &x, floa
 }
 
 // Tiles t0, t0 + 1, ... + TPI - 1, whose rows are on their way in xa, then `stride` on, as far as they lie below te.  A wave
-// has the next step's rows on their way while it works on the current ones: 16 KB of bfloat16 rows of 128 channels at
-// TPI = 2 and twice that at the peak.
+// has the next step's rows on their way while it works on the current ones: a tile of bfloat16 rows of 128 channels is 8 KB and
+// 32 registers a step.
 // (kb, vb: not through restricted pointers, which would let the compiler move the loads.)  in_last_step(): called before the
 // arithmetic of the wave's last step.
 struct NoLastStep {

@@ -366,7 +366,13 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
     };
     constexpr int LPR = D / 8;
     constexpr int TR = 16;   // rows per tile
-    constexpr int TPI = sizeof(ST) == 2 ? 2 : 1;  // tiles per step of a wave
+    // One tile to a wave's step, and the next one's rows on their way where a tile's K and V are 32 registers (64 with float32
+    // rows of 128 channels): at most 128 registers in all, so that two workgroups share a CU and a grid that is not a
+    // multiple of the CUs has no second turn.  Two tiles, or 64-register steps ahead (157-165 registers, one workgroup to a CU):
+    // append + decode of 7 x 8 heads x 7055, 55 of 441 pages 22.9 -> 32.0 us, 5 x 8 x 20000, 156 of 1250 31.3 -> 40.0, 3 x 4 x 7473 dense
+    // 21.1 -> 23.4, float32 7 x 16 x 8252 35.7 -> 42.1; where the grid is 256 workgroups anyway 32 over 8 heads x 16416 19.8 -> 21.5.
+    constexpr int TPI = 1;
+    constexpr bool AHEAD = D * (int)sizeof(ST) < 512;
     constexpr int kAttWaves = kAttThreads / 64;
     using R = Row8<ST>;
     __shared__ float s_m[kAttWaves], s_l[kAttWaves];
@@ -401,6 +407,10 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
     AttendState<1> st;
     st.clear();
     const long t_first = tb + wave * TPI, stride = kAttWaves * TPI;
+    auto attend = [&](auto row_of) __attribute__((always_inline)) {
+        if constexpr (AHEAD) attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, row_of);
+        else attend_tiles_in_turn<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, row_of);
+    };
     if constexpr (SELECT) {
         __shared__ SelectShared<kAttThreads> sh;
         extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
@@ -425,13 +435,13 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
         if (Np <= kAttThreads / 2) select_topk_few<kAttThreads>(s_keys, Np, K, sh.wave_tot, emit);
         else select_topk_lds<kAttThreads>(s_keys, Np, K, sh, emit);
         __syncthreads();
-        attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
+        attend([&](long t) __attribute__((always_inline)) -> long {
             const int page = __builtin_amdgcn_readfirstlane(s_sel[(int)(t >> page_shift) - first]);
             return (long)page * P + (t & ((1 << page_shift) - 1)) * TR;
         });
     } else if (idx) {
         WavePages pages;
-        attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long {
+        attend([&](long t) __attribute__((always_inline)) -> long {
             const int page = pages.next([&](int n) __attribute__((always_inline)) -> int {
                 const long tt = t_first + (long)(n / TPI) * stride + n % TPI;
                 return tt < te ? idx_row[tt >> page_shift] : -1;
@@ -439,7 +449,7 @@ __global__ __launch_bounds__(kAttThreads) void decode_attend_kernel(
             return page >= 0 ? (long)page * P + (t & ((1 << page_shift) - 1)) * TR : T_valid;
         });
     } else {
-        attend_tiles<ST, D, 1, TPI, STREAM>(kb, vb, T_valid, t_first, te, stride, scale, qd, st, [&](long t) __attribute__((always_inline)) -> long { return t * TR; });
+        attend([&](long t) __attribute__((always_inline)) -> long { return t * TR; });
     }
     float m = st.m[0], l = st.l[0];
     float (&o)[8] = st.o[0];
