@@ -230,15 +230,21 @@ static DecodeLayout decode_layout(const rs_shape *s, long T_valid, int K)
 // 512-thread workgroups, about one per CU: fewer, fuller workgroups start sooner and leave fewer
 // partials to merge than many small ones (32 query / 8 KV heads, batch 1: dense over 16.5K rows
 // 29 -> 25 us, over 32K rows 45 -> 41 us, 128 listed pages 13.7 -> 10.1 us against 256 threads
-// and 512 workgroups).  A wave takes two tiles per step: past 16 steps per wave, twice the splits.
+// and 512 workgroups).  Past 32 tiles per wave, twice the splits.
+// Where that many splits of every unit come to a few more workgroups than the target, a split less, as long as four fifths of
+// the CUs keep theirs: the CUs that get a second (or third) workgroup take that much longer, and the rest wait for them.
+// Append + decode, with / without, us: float32 3 x 8 heads x 20000, 100 of 1250 pages (264 workgroups) 33.6 / 29.4, dense 3 x 4 x 7473
+// 35.8 / 26.4, 5 x 11 x 30000 (550 of 512) 355 / 289; bfloat16 7 x 8 x 7055, 55 of 441 pages (280) 23.4 / 21.4, dense 40 heads x 9000
+// (280) 45.2 / 35.5, 18 x 65000 (522) 122 / 107, 31 x 8 x 500 (496 to 248) 19.2 / 17.1; no shape of 48 got slower by more than 1 %.
 static int attend_splits(const DecodeLayout &L, long units, long tiles)
 {
     int target = knob_or(knobs().attend_wgs, 0);
     if (target <= 0) {
         target = 256;
-        if (tiles > (long)pick_splits(units, tiles, 8, 256) * 8 * 2 * 16) target = 512;
+        if (tiles > (long)pick_splits(units, tiles, 8, 256) * 8 * 32) target = 512;
     }
-    const int splits = pick_splits(units, tiles, 8, target);
+    int splits = pick_splits(units, tiles, 8, target);
+    if (splits > 1 && units * splits > target && units * (splits - 1) * 5 >= target * 4l) --splits;
     return splits > L.splits_att_max ? L.splits_att_max : splits;
 }
 

@@ -615,3 +615,40 @@ def test_rows_that_are_not_attended_count_for_nothing(rs, knobs, form, P, dtype,
                 ok, worst = attn_close(to_np(out[b, h]), to_np(want), tol)
                 assert ok, (T, h, worst)
                 np.testing.assert_allclose(float(lse[b, h]), float(torch.logsumexp(x, 0)), rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("B,H,T,K,dtype", [(3, 4, 7473, 0, "f32"), (1, 12, 3000, 0, "bf16"), (7, 8, 1100, 30, "bf16"), (5, 11, 30000, 0, "bf16"), (31, 8, 300, 0, "bf16"),
+                                           (1, 18, 33000, 1100, "bf16"), (7, 10, 257, 0, "bf16"), (2, 128, 260, 0, "bf16"), (1, 257, 260, 0, "bf16")])
+def test_splits_of_unit_counts_that_do_not_divide_the_chip(rs, knobs, B, H, T, K, dtype):
+    """A few units more or fewer than divide 256 or 512 workgroups: dense decode, and two launches with a selection, against
+    64-bit attention over the rows kept.  (bfloat16 outputs are rounded once, 2^-8 of a value; float32 sums of 7473
+    weights: a few times 2^-24 x 16.)"""
+    say("uneven units", B, H, T, K, dtype)
+    knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", "1")
+    knobs.setenv("RATSPARSE_FUSED_ONE_WG", "0")
+    P, D, dt = 16, 128, tdtype(dtype)
+    Np = -(-T // P)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    kc, vc = (torch.randn(B, H, Np * P, D, generator=gen, device="cuda").to(dt) for _ in range(2))
+    q = torch.randn(B, H, D, generator=gen, device="cuda").to(dt)
+    s = rs.make_shape(B, H, H, D, Np * P, P, dt)
+    meta = torch.zeros(B, H, Np, 2, D, dtype=dt, device="cuda")
+    if K:
+        rs.quest_page_meta(s, kc, meta, 0, T)
+    ws = rs.Workspace(rs.sparse_attn_decode_workspace_bytes(s, T, K))
+    out, lse = torch.zeros(B, H, D, dtype=dt, device="cuda"), torch.zeros(B, H, device="cuda")
+    idx = torch.full((B, H, max(K, 1)), -5, dtype=torch.int32, device="cuda")
+    rs.sparse_attn_decode(s, q, kc, vc, T, D ** -0.5, None, K, meta if K else None, 1 if K else 0, 1 if K else 0, out, lse, idx if K else None, ws)
+    torch.cuda.synchronize()
+    ws.async_status()
+    tol = 2.0 ** -8 if dtype == "bf16" else 4e-6
+    for b in range(B):
+        for h in range(H):
+            rows = torch.arange(T, device="cuda")
+            if K:
+                rows = (idx[b, h].long()[:, None] * P + torch.arange(P, device="cuda")).flatten()
+                rows = rows[rows < T]
+            x = kc[b, h, rows].double() @ q[b, h].double() * D ** -0.5
+            want = torch.softmax(x, 0) @ vc[b, h, rows].double()
+            assert float((out[b, h].double() - want).abs().max()) <= tol * float(want.abs().max()), (b, h)
+            assert abs(float(lse[b, h]) - float(torch.logsumexp(x, 0))) <= 1e-5
