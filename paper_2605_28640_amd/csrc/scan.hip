@@ -40,13 +40,23 @@ namespace rs {
 // the page's channelwise min / max of the stored keys (App. A.1, Quest) leave with the states -- in-lane over the lane's four tokens, shuffles over the row
 // groups of a page, and for pages longer than a wave's tokens a fold of the waves' bounds
 // through LDS -- and the keys need no second pass.
-template <typename ST, int D, int DS, int NT, int NW, int PAGE, bool LEAD>
+// TURN: when a workgroup learns which chunk comes next, and sends its loads out.
+enum ScanTurn {
+    kOneAtATime,  // when the chunk in work is done: slabs, and whole rows in runs of one chunk
+    kNextAtEnd,   // whole rows: the next chunk is known from the end of the one before, its loads go out under the replay
+    kNextAhead,   // ... and drawn a chunk earlier still, so that nobody waits for the draw
+};
+template <typename ST, int D, int DS, int NT, int NW, int PAGE, bool LEAD, ScanTurn TURN>
 __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const ST *__restrict__ k, const ST *__restrict__ v, const float *__restrict__ g,
     float *__restrict__ state_k, float *__restrict__ state_v, ST *__restrict__ k_cache,
     ST *__restrict__ v_cache, int BH, long T_new, long t0, long Tcap, int n_chunks,
     uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit, ST *__restrict__ meta, int lead_arg)
 {
+    constexpr bool PIPE = TURN != kOneAtATime, AHEAD = TURN == kNextAhead;
+    constexpr bool ROOM = TURN == kNextAtEnd && sizeof(ST) == 4;  // registers to spare beside the two sets
+    constexpr bool EARLY = !PIPE || ROOM, FENCE = PIPE && !ROOM;
+    static_assert(!PIPE || (DS == D && !LEAD), "");
     const int lead = LEAD ? lead_arg : 0;
     const int rec_chunks = LEAD ? n_chunks - 1 : n_chunks;  // records per unit (a lead may add a chunk, the last one leaves none)
     constexpr bool META = PAGE > 0;
@@ -72,7 +82,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const int c0 = (lane % LPR) * 8;
 
     // Persistent workgroups: each keeps taking the next chunk (by ticket) until none is left.  The raw
-    // inputs of a chunk live in registers from its loads to its replay; with whole rows there are two such register
+    // inputs of a chunk live in registers from its loads to its replay; with whole rows (PIPE) there are two such register
     // sets, and the loads of the NEXT ticket go out right behind the current chunk's chain step, under its replay
     // and stores (one workgroup fills a CU).  The prefetched ticket is
     // larger than the one in work and tickets are handed out in increasing order, so the smallest
@@ -80,8 +90,8 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     // Bound by memory: 4 x 32 heads x 64K (13.2 GB) take 2.73 ms, the same traffic without the arithmetic 2.48.  Waits that
     // count exactly are what the overlap hangs on: while the sets were copied into each other and loads and stores went
     // by branches, every chunk's replay waited for the next chunk's loads (us, then / now, 128 channels with bounds in
-    // bfloat16: 4 x 32 heads x 64K 2763 / 2727, 32 x 64K 738 / 717, 4 x 32 x 700 44.9 / 42.9; 4 x 32 x 8000 of 64 channels
-    // 185 / 172; float32, 8 x 32 heads x 500 91 / 83).
+    // bfloat16: 4 x 32 heads x 64K 2763 / 2727, 32 x 64K 738 / 717; 4 x 32 x 8000 of 64 channels
+    // 185 / 170; float32, 8 x 32 heads x 500 91 / 83).
     const int units = BH * NS;
     const int total = units * n_chunks;
     // (kept as 32-bit words: the sets are carried around the chunk loop, and this compiler's back end
@@ -97,7 +107,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         __syncthreads();
         return s_ticket;
     };
-    // Whole rows (DS == D) move by buffer instructions, their descriptors based at the chunk's first row and sized to its
+    // Whole rows (PIPE) move by buffer instructions, their descriptors based at the chunk's first row and sized to its
     // rows: what lies past the run reads as zeros and is dropped on the way out, so that nothing branches between a
     // chunk's loads and the fold that waits for them, and the wait can count exactly.
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -112,7 +122,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         const int bh = unit / NS;
         const int ch0 = (unit % NS) * DS;
         const long in_row0 = (long)bh * T_new;
-        if constexpr (DS == D) {
+        if constexpr (PIPE) {
             const long first = (long)j * CHUNK;
             const int rows = (int)((T_new - first < CHUNK) ? T_new - first : CHUNK);
             const auto kd = rows_of(k, in_row0 + first, rows), vd = rows_of(v, in_row0 + first, rows);
@@ -142,12 +152,21 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             typename R::raw_t kq = R::zero_raw(), vq = R::zero_raw();
             float4 ga = make_float4(1.f, 1.f, 1.f, 1.f), gb = ga;  // outside the run: the identity element (g = 1 keeps the state)
             if ((!LEAD || t >= 0) && t < T_new) {
-                // (a slab shares its cache lines with the other slabs of the row, which come by other workgroups: cached loads)
                 const long off = (in_row0 + t) * D + ch0 + c0;
-                kq = R::load_raw(k + off);
-                vq = R::load_raw(v + off);
-                ga = *reinterpret_cast<const float4 *>(g + off);
-                gb = *reinterpret_cast<const float4 *>(g + off + 4);
+                if constexpr (DS == D) {
+                    kq = R::load_raw_nt(k + off);
+                    vq = R::load_raw_nt(v + off);
+                    typedef float f32x4 __attribute__((ext_vector_type(4)));
+                    const f32x4 xa = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(g + off));
+                    const f32x4 xb = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(g + off + 4));
+                    ga = make_float4(xa.x, xa.y, xa.z, xa.w);
+                    gb = make_float4(xb.x, xb.y, xb.z, xb.w);
+                } else {  // (a slab shares its cache lines with the other slabs of the row, which come by other workgroups: cached loads)
+                    kq = R::load_raw(k + off);
+                    vq = R::load_raw(v + off);
+                    ga = *reinterpret_cast<const float4 *>(g + off);
+                    gb = *reinterpret_cast<const float4 *>(g + off + 4);
+                }
             }
             __builtin_memcpy(r.kw[i], &kq, sizeof(kq));
             __builtin_memcpy(r.vw[i], &vq, sizeof(vq));
@@ -155,7 +174,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             r.gw[i][4] = gb.x; r.gw[i][5] = gb.y; r.gw[i][6] = gb.z; r.gw[i][7] = gb.w;
         }
     };
-    // nr: the register set of the next chunk; returns its ticket (>= total: none)
+    // nr: the register set of the next chunk, next: its ticket, unless it was drawn ahead; returns it (>= total: none)
     constexpr int kTicketThread = NW * 64 - 64;  // whole rows: who draws (a wave that does not handle the chain)
     int drawn = total;                           // ... and what it drew last
     auto draw = [&]() __attribute__((always_inline)) -> int {
@@ -163,7 +182,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         asm volatile("" : "+v"(at));  // (not known to be one address for all lanes: else the result is waited for at once)
         return (int)atomicAdd(&ctrl[at], 1u);
     };
-    auto process_chunk = [&](int ticket, ChunkRegs &r, ChunkRegs &nr) __attribute__((always_inline)) -> int {
+    auto process_chunk = [&](int ticket, ChunkRegs &r, ChunkRegs &nr, int next) __attribute__((always_inline)) -> int {
     const int j = ticket / units;   // chunk index along T
     const int unit = ticket % units;  // consecutive tickets walk the units first
     const int bh = unit / NS;
@@ -178,7 +197,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         g0[i] = make_float4(r.gw[i][0], r.gw[i][1], r.gw[i][2], r.gw[i][3]);
         g1[i] = make_float4(r.gw[i][4], r.gw[i][5], r.gw[i][6], r.gw[i][7]);
     }
-    if constexpr (DS == D) {
+    if constexpr (PIPE) {
         if (j == n_chunks - 1 && T_new % CHUNK != 0) {  // past the run: the identity element (g = 1 keeps the state; x is 0)
 #pragma unroll
             for (int i = 0; i < NT; ++i)
@@ -186,11 +205,12 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         }
     }
 
-    // slabs: a first look at the previous chunk's outgoing state, issued behind the data loads so that its round trip
-    // overlaps the fold; the wait below re-polls only if it was not there yet.  (Whole rows do without: registers that may
-    // still be waiting for it would hold up every wave's next use of them until the next chunk's loads have landed.)
+    // A first look at the previous chunk's outgoing state, issued behind the data loads so that its round trip
+    // overlaps the fold; the wait below re-polls only if it was not there yet.  (Bfloat16 whole rows, and those drawn ahead, do
+    // without: registers that may still be waiting for it hold up every wave's next use of them until the next chunk's
+    // loads have landed.)
     uint64_t early0 = 0, early1 = 0;
-    if constexpr (DS < D) {
+    if constexpr (EARLY) {
         if (tid < DS && j > 0) {
             const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + tid;
             early0 = load_u64_agent(p);
@@ -220,7 +240,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             bv[c] = fmaf(gg[c], bv[c], om * vx[c]);
         }
         // (token by token: unpacked all at once they do not fit the registers)
-        if constexpr (DS == D) {
+        if constexpr (FENCE) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(a[c]), "+v"(bk[c]), "+v"(bv[c]));
         }
@@ -298,12 +318,12 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         bv[c] = (rg == 0) ? 0.f : pv;
     }
     }
-    if constexpr (DS == D) {
+    if constexpr (AHEAD) {
         if (tid == kTicketThread) s_drawn = drawn;  // read behind the barrier below; the chain step's barrier lies before the next write
     }
     __syncthreads();
-    int nt = total;
-    if constexpr (DS == D) nt = __builtin_amdgcn_readfirstlane(s_drawn);
+    int nt = next;
+    if constexpr (AHEAD) nt = __builtin_amdgcn_readfirstlane(s_drawn);
 
     if (tid < DS) {
         const int c = tid;
@@ -323,7 +343,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             const uint64_t *p = rec + (((long)unit * rec_chunks + (j - 1)) * 2) * DS + c;
             uint64_t w0 = early0, w1 = early1;
             int spins = 0;
-            if constexpr (DS == D) {
+            if constexpr (!EARLY) {
                 w0 = load_u64_agent(p);
                 w1 = load_u64_agent(p + DS);
             }
@@ -361,10 +381,10 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     }
     // The next chunk's loads go out here, behind the chain step: a wave's loads return in order, so issued any earlier
     // they would hold up the chain waves' polls of the predecessor's record (the other waves come here at once).  Before them goes
-    // the draw of the ticket after it, which is thus there when those loads are.
-    if constexpr (DS == D) {  // (the slab form works on one chunk at a time)
+    // the draw of the ticket after it (AHEAD), which is thus there when those loads are.
+    if constexpr (PIPE) {
         if (nt < total) {
-            if (tid == kTicketThread) drawn = draw();
+            if (AHEAD && tid == kTicketThread) drawn = draw();
             load_chunk(nt, nr);
         }
     }
@@ -381,7 +401,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         __builtin_memcpy(w + KW, &vr[i], sizeof(vr[i]));
         __builtin_memcpy(w + 2 * KW, &g0[i], 16);
         __builtin_memcpy(w + 2 * KW + 4, &g1[i], 16);
-        if constexpr (DS == D) {
+        if constexpr (FENCE) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(sk[c]), "+v"(sv[c]));
         }
@@ -392,7 +412,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         __builtin_memcpy(&g0[i], w + 2 * KW, 16);
         __builtin_memcpy(&g1[i], w + 2 * KW + 4, 16);
     };
-    if constexpr (DS < D) {
+    if constexpr (!PIPE) {
 #pragma unroll
         for (int i = 0; i < NT; ++i) fresh_inputs(i);
     }
@@ -423,7 +443,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
             }
         }
     }
-    const int rows_out = (DS == D) ? (int)((T_new - (long)j * CHUNK < CHUNK) ? T_new - (long)j * CHUNK : CHUNK) : 0;
+    const int rows_out = PIPE ? (int)((T_new - (long)j * CHUNK < CHUNK) ? T_new - (long)j * CHUNK : CHUNK) : 0;
     const auto kd_out = rows_of(k_cache, out_row0 + (long)j * CHUNK, rows_out), vd_out = rows_of(v_cache, out_row0 + (long)j * CHUNK, rows_out);
     uint32_t el_out = lane_el;
     asm volatile("" : "+v"(el_out));
@@ -443,8 +463,8 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     for (int i = 0; i < NT; ++i) {
         const long t = tbase + i;
         // (whole rows past the run: their states go nowhere, and the bounds below leave them out)
-        if (DS == D || ((!LEAD || t >= 0) && t < T_new)) {
-            if constexpr (DS == D) fresh_inputs(i);
+        if (PIPE || ((!LEAD || t >= 0) && t < T_new)) {
+            if constexpr (PIPE) fresh_inputs(i);
             float kx[8], vx[8];
             R::unpack(kr[i], kx);
             R::unpack(vr[i], vx);
@@ -455,7 +475,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                 sk[c] = fmaf(gg[c], sk[c], om * kx[c]);
                 sv[c] = fmaf(gg[c], sv[c], om * vx[c]);
             }
-            if constexpr (DS == D) {
+            if constexpr (PIPE) {
                 store_row(kd_out, i, sk);
                 store_row(vd_out, i, sv);
             } else {
@@ -477,7 +497,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
 #pragma unroll
                     for (int c = 0; c < 8; ++c) xs[c] = sk[c];
                 }
-                const bool in = DS < D || t < T_new;
+                const bool in = !PIPE || t < T_new;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
                     plo[c] = fminf(plo[c], in ? xs[c] : INFINITY);
@@ -497,7 +517,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                     plo[c] = fminf(plo[c], shfl_xor_f(plo[c], msk));
                     phi[c] = fmaxf(phi[c], shfl_xor_f(phi[c], msk));
                 }
-            if constexpr (DS == D) {
+            if constexpr (PIPE) {
                 // (a lane without a row of bounds to write aims past the descriptor's end)
                 const long page0 = (t0 + (long)j * CHUNK) / PAGE;
                 const LdsSource md = lds_source_sized(meta + ((long)bh * (Tcap / PAGE) + page0) * 2 * D,
@@ -569,21 +589,25 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     int tA = (int)blockIdx.x;  // one chunk per unit: the grid is the units, no tickets
     if (n_chunks > 1) tA = next_ticket();
     if (tA < total) {
-        if constexpr (DS == D) {
+        if constexpr (PIPE) {
             // two register sets in turn, each under its own name: a set that changed its name at the end of a turn would be
             // copied, and the copies would wait for its loads
-            if (n_chunks > 1 && tid == kTicketThread) drawn = draw();
+            if (AHEAD && tid == kTicketThread) drawn = draw();
             load_chunk(tA, A);
+            int next = total;
+            if constexpr (!AHEAD) next = next_ticket();
             for (;;) {
-                const int tB = process_chunk(tA, A, B);
+                const int tB = process_chunk(tA, A, B, next);
                 if (tB >= total) break;
-                tA = process_chunk(tB, B, A);
+                if constexpr (!AHEAD) next = next_ticket();
+                tA = process_chunk(tB, B, A, next);
                 if (tA >= total) break;
+                if constexpr (!AHEAD) next = next_ticket();
             }
         } else {
             for (;;) {
                 load_chunk(tA, A);
-                (void)process_chunk(tA, A, B);
+                (void)process_chunk(tA, A, B, total);
                 if (n_chunks == 1) break;
                 tA = next_ticket();
                 if (tA >= total) break;
@@ -667,7 +691,7 @@ __global__ __launch_bounds__(256) void rat_step_kernel(
     state_v[e] = sv;
 }
 
-template <typename ST, int D, int DS, int PAGE, bool LEAD>
+template <typename ST, int D, int DS, int PAGE, bool LEAD, ScanTurn TURN>
 static void launch_scan_form(const void *k, const void *v, const float *g, float *state_k,
                        float *state_v, void *k_cache, void *v_cache, int BH, long T_new, long t0,
                        long Tcap, uint32_t *ctrl, uint64_t *rec, uint32_t tag, int spin_limit,
@@ -686,7 +710,7 @@ static void launch_scan_form(const void *k, const void *v, const float *g, float
         static const Resident resident = [] {
             int dev = 0, per_cu = 0, cus = 0;
             (void)hipGetDevice(&dev);
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD>, NW * 64, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD, TURN>, NW * 64, 0) != hipSuccess || per_cu < 1) per_cu = 1;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
             return Resident{cus, (long)per_cu * cus};
         }();
@@ -698,7 +722,7 @@ static void launch_scan_form(const void *k, const void *v, const float *g, float
         if (want < 1) want = 1;
         if (grid > want) grid = want;
     }
-    rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(
+    rat_scan_chunk_kernel<ST, D, DS, NT, NW, PAGE, LEAD, TURN><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(
         (const ST *)k, (const ST *)v, g, state_k, state_v, (ST *)k_cache, (ST *)v_cache, BH, T_new,
         t0, Tcap, n_chunks, ctrl, rec, tag, spin_limit, (ST *)meta, lead);
 }
@@ -712,13 +736,30 @@ static void launch_scan(const void *k, const void *v, const float *g, float *sta
     constexpr int PAGE = (PAGE_ARG <= CHUNK) ? PAGE_ARG : 0;  // larger pages never get here with the bounds asked for
     if constexpr (PAGE > 0 && DS < D) {
         if (t0 % CHUNK != 0) {
-            launch_scan_form<ST, D, DS, PAGE, true>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec,
+            launch_scan_form<ST, D, DS, PAGE, true, kOneAtATime>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec,
                                                     tag, spin_limit, meta, (int)(t0 % CHUNK), stream);
             return;
         }
     }
-    launch_scan_form<ST, D, DS, PAGE, false>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec, tag,
-                                             spin_limit, meta, 0, stream);
+#define RS_TURN(TT)                                                                                                                   \
+    launch_scan_form<ST, D, DS, PAGE, false, TT>(k, v, g, state_k, state_v, k_cache, v_cache, BH, T_new, t0, Tcap, ctrl, rec, tag, \
+                                                 spin_limit, meta, 0, stream)
+    if constexpr (DS < D) {
+        RS_TURN(kOneAtATime);
+    } else {
+        // Runs of one chunk have nothing to send ahead, and waves without rows then skip loads, replay and stores (kernel alone, 96 heads
+        // x 31 tokens 7.1 / 5.8 us).  A ticket drawn a chunk ahead saves a round trip to memory a chunk, and ties a chunk to a
+        // workgroup that has two others to do first, which the chunk's successors wait for: it pays from eight chunks a CU on,
+        // with 128 channels only for 48 chains and more.  Drawn ahead / at the end, us (with page bounds from t0 = 0, bfloat16 but for the last):
+        // 4 x 32 heads x 64K 2293 / 2382, x 16000 571 / 577, x 2500 109 / 110, 2 x 32 x 64K 1196 / 1210, 64 channels 4 x 32 x 32000 593 / 624,
+        // x 4000 93 / 94; the other way 4 x 32 x 700 42.9 / 38.9, x 1500 72.0 / 70.7, 8 x 32 x 400 46.1 / 43.8, 64 x 1000 from an odd start
+        // 35.7 / 33.1, 44 x 1637 42.9 / 38.6, 24 x 32000 316 / 292, 32 x 64K 678 / 657, float32 24 x 20000 245 / 233.
+        const long n_chunks = (T_new + CHUNK - 1) / CHUNK;
+        if (n_chunks == 1) RS_TURN(kOneAtATime);
+        else if ((D == 128 && BH < 48) || BH * n_chunks < 2048) RS_TURN(kNextAtEnd);
+        else RS_TURN(kNextAhead);
+    }
+#undef RS_TURN
 }
 
 int scan_chunk_tokens(int dtype, int D)

@@ -386,3 +386,39 @@ def test_first_calls_from_several_threads():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", _FIRST_CALLS], cwd=root, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "first calls ok" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+def test_whole_row_forms_give_the_same_bits(rs, knobs, dtype, D):
+    """Whole rows have a form for runs of one chunk, one that learns its next chunk at the end of each, and one that draws it ahead
+    (from 48 chains and 2048 chunks on).  Chunks are folded and chained alike in all three, so a run cut at chunk boundaries into
+    pieces of one chunk, of several, or not at all gives the same states, rows and page bounds."""
+    knobs.setenv("RATSPARSE_SCAN_SLAB", "0")
+    chunk = {("bf16", 128): 128, ("bf16", 64): 256, ("f32", 128): 64, ("f32", 64): 128}[dtype, D]
+    B, H, P, dt = 1, 64, 16, tdtype(dtype)
+    T = 32 * chunk - 37  # 2048 chunks, the last one ragged
+    Tcap = -(-T // P) * P
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    k, v = (torch.randn(B, H, T, D, generator=gen, device="cuda").to(dt) for _ in range(2))
+    g = torch.sigmoid(torch.randn(B, H, T, D, generator=gen, device="cuda") + 3)
+    s = rs.make_shape(B, H, H, D, Tcap, P, dt)
+    ws = rs.Workspace(rs.rat_scan_workspace_bytes(s, T))
+    got = []
+    for piece in (T, 5 * chunk, chunk):
+        say("scan forms", dtype, D, piece)
+        sk, sv = torch.zeros(B, H, D, device="cuda"), torch.ones(B, H, D, device="cuda")
+        kc, vc = (torch.zeros(B, H, Tcap, D, dtype=dt, device="cuda") for _ in range(2))
+        meta = torch.zeros(B, H, Tcap // P, 2, D, dtype=dt, device="cuda")
+        for t in range(0, T, piece):
+            n = min(piece, T - t)
+            rs.rat_scan(s, *(x[:, :, t:t + n].contiguous() for x in (k, v, g)), sk, sv, kc, vc, t, n, ws, meta)
+        torch.cuda.synchronize()
+        ws.async_status()
+        got.append((sk, sv, kc, vc, meta))
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+    want = torch.zeros(B, H, D, device="cuda", dtype=torch.float64)
+    for t in range(T):
+        want = g[:, :, t].double() * want + (1 - g[:, :, t].double()) * k[:, :, t].double()
+    # (a state is a mean of inputs with weights that sum to 1: each of the last hundred or so steps rounds it by 2^-24)
+    assert float((got[0][0].double() - want).norm() / want.norm()) <= 1e-5
