@@ -233,7 +233,7 @@ static DecodeLayout decode_layout(const rs_shape *s, long T_valid, int K)
 // and 512 workgroups).  Past 32 tiles per wave, twice the splits.
 // Where that many splits of every unit come to a few more workgroups than the target, a split less, as long as four fifths of
 // the CUs keep theirs: the CUs that get a second (or third) workgroup take that much longer, and the rest wait for them.
-// Append + decode, with / without, us: float32 3 x 8 heads x 20000, 100 of 1250 pages (264 workgroups) 33.6 / 29.4, dense 3 x 4 x 7473
+// Append + decode, rounded up / a split less, us: float32 3 x 8 heads x 20000, 100 of 1250 pages (264 workgroups) 33.6 / 29.4, dense 3 x 4 x 7473
 // 35.8 / 26.4, 5 x 11 x 30000 (550 of 512) 355 / 289; bfloat16 7 x 8 x 7055, 55 of 441 pages (280) 23.4 / 21.4, dense 40 heads x 9000
 // (280) 45.2 / 35.5, 18 x 65000 (522) 122 / 107, 31 x 8 x 500 (496 to 248) 19.2 / 17.1; no shape of 48 got slower by more than 1 %.
 static int attend_splits(const DecodeLayout &L, long units, long tiles)
@@ -251,8 +251,9 @@ static int attend_splits(const DecodeLayout &L, long units, long tiles)
 // Whether that attention selects its pages itself, every split for its own: where the keys and a split's part of the list
 // fit beside its other LDS (12000 pages).  The launch before it then only scores: no arrival counter, no tagged words to
 // gather, no workgroup that selects while the rest of the chip is idle, no list to read back.  Append + decode, selection by
-// the last arrival / by every split, us: 32 over 8 heads x 32768, 1/8 of the pages 29.2 / 27.2, 32 heads x 32768, 1/16 32.5 / 30.4,
-// 2 x 16 over 8 of 64 channels x 30000 26.1 / 22.9, 4 x 32 over 8 x 16000, 1/4 61.2 / 60.6, 2 heads x 60000 48.6 / 47.4.
+// the last arrival / by every split, us: 32 over 8 heads x 32768, 1/8 of the pages 27.2 / 25.2, 32 heads x 32768, 1/16 32.1 / 30.4,
+// 2 x 16 over 8 of 64 channels x 30000 24.0 / 22.1, 4 x 32 over 8 x 16000, 1/4 63.5 / 61.5, 2 heads x 60000 33.0 / 31.6, float32 3 x 8 x
+// 20000 30.4 / 29.2, 4 heads x 1100 17.9 / 17.4, 32 over 8 x 160000 46.2 / 43.2.
 static bool attend_selects(int Np, int K, int P, int splits)
 {
     return Np >= 64 && attend_select_lds(key_row(Np), K, P, splits) <= 48 * 1024;
@@ -618,19 +619,20 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     if (group && !listed && !fused) return RS_INVALID_ARG;  // the dense path has no selection to share
     // One persistent launch when the step is long enough to be bound by bandwidth: at least about
     // 450 MB of page metadata and selected pages (some 90 us) over at least 512 pages per sequence.
-    // Shorter steps are bound by latency, and there the two plain launches below measured faster:
-    // 32 heads at 4096 tokens, batch 8, 8 of 64 pages 23 against 38 us; batch 64 117 against 130 us;
-    // 32 query over 8 KV heads at 32K, batch 1, 29 against 33 us.  Long ones the other way: batch 4
-    // at 64K (538 MB) 95 against 143 us, batch 32 at 8K 98 against 112 us.
+    // Shorter steps are bound by latency, and there the two plain launches are mostly faster.  Append + decode, two launches / persistent,
+    // us: 32 over 8 heads at 32K, batch 1 (75 MB) 25 / 35, 32 heads at 32K, batch 2 (151 MB) 40 / 47, 16K, batch 8 (302 MB) 60 / 68,
+    // float32 at 32K, batch 2 (393 MB) 82 / 92; the other way 64K, batch 4 (537 MB) 109 / 106, 32 over 8 at 64K, batch 4 (604 MB)
+    // 133 / 113, at 16K, batch 8 (570 MB) 110 / 96.  (The two forms cross between 300 and 550 MB, by shape: 64K, batch 3 (403 MB)
+    // 107 / 88 and 32 over 8 at 32K, batch 4 (302 MB) 74 / 67 are on the wrong side of the line; 8K, batch 32 (537 MB) 110 / 110.)
     const double step_bytes = ((double)s->B * s->Hkv * Np * 2 + (double)units * K * s->P * 2) * s->D * esize(s->dtype);
     const int two_launch = knob_or(knobs().fused_two_launch, (step_bytes >= 450e6 && Np >= 512) ? 0 : 1);
     // Short contexts (the paper's 4096 tokens): the whole step of a (batch, query head) inside one
     // workgroup, one launch, nothing handed between workgroups.  Taken when a unit's metadata and
     // picked pages are small (at most 1.5 MB, and at most 512 KB unless there are 128 units or
-    // more) and the step is not one of the long ones above.  32 heads at 4096 tokens, 64-token
-    // pages, top-8 (one workgroup per unit / two launches / persistent launch, us): batch 1
-    // 13 / 16 / 21, batch 8 20 / 24 / 39, batch 64 112 / 123 / 130; 8K and 16K at batch 8:
-    // 28 / 32 / 44 and 47 / 52 / 59; the other way at 32K, batch 2: 51 / 34 / 47.
+    // more) and the step is not one of the long ones above.  Append + decode, 32 heads, 64-token pages, 8 of 64 at 4096 tokens (one
+    // workgroup per unit / two launches / persistent launch, us): batch 1 14 / 17 / 21, batch 8 18 / 22 / 33; 8K at batch 8 34 / 34 / 45,
+    // 16K 63 / 60 / 68; 16-token pages, 8K, batch 16 54 / 60 / 64; the other way at 32K, batch 2: 60 / 40 / 47.  (At batch 64 and 4096
+    // tokens two launches have become the faster form: 106 / 96 / 125.)
     const double unit_bytes = ((double)Np * 2 + (double)K * s->P * 2) * s->D * esize(s->dtype);
     const bool unit_rule = two_launch && unit_bytes <= 1.5e6 && (units >= 128 || unit_bytes <= 512e3);
     const int one_wg = knob_or(knobs().fused_one_wg, unit_rule ? 1 : 0);
@@ -679,12 +681,12 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     // Heads of a KV head that attend the same rows go through them together where fetching the rows per
     // head is what takes the time: when the heads' reads come to 300 MB (200 MB for two heads; 700 MB for eight heads
     // over more than 32 splits, whose partials take long to merge) and the KV heads' splits fill the chip, or when
-    // the splits of a KV head are few enough (8) that merging their partials costs little.  Per head / shared, us of
-    // kernel time, 128 channels, bfloat16 but for the last: 32 over 8 heads, batch 8, 1000 rows 22.7 / 13.9, 8000 rows
-    // 153 / 67; batch 4 x 32768 186 / 106; batch 1 x 1000 9.4 / 8.8, x 32768 47 / 36, x 65536 89 / 56, and the other way at
-    // 200 rows 5.7 / 8.0, 2000 9.0 / 11.9, 4000 11.0 / 15.7, 16416 22.6 / 24.7; 16 over 8 heads x 32768 36 / 30; 32 over 4
-    // x 32768 36 / 42, x 65536 74 / 58, batch 2 x 32768 72 / 51; 16 over 2 heads x 65536 (128 splits in all) 40 / 54;
-    // float32, 32 over 8 x 32768 90 / 61.
+    // the splits of a KV head are few enough (8) that merging their partials costs little.  Append + decode, per head / shared, us,
+    // 128 channels, bfloat16 but for the last: 32 over 8 heads, batch 8, 1000 rows 26 / 16, 8000 rows 158 / 56; batch 4 x 32768
+    // 166 / 101; batch 1 x 24000 35 / 27, x 32768 48 / 34, x 65536 84 / 52, and the other way at 4000 13.6 / 16.6, 16416
+    // 20 / 23 (up to 2000 rows the two calls bound both: 13); 16 over 8 heads x 32768 39 / 30; 32 over 4 x 32768 32 / 40,
+    // x 65536 72 / 53, batch 2 x 32768 69 / 47; 16 over 2 heads x 65536 (128 splits in all) 36 / 51; 8 over 2 x 65000 26 / 30; float32,
+    // 32 over 8 x 32768 77 / 57.
     if (s->Hq > s->Hkv && (group || !use_idx)) {
         const int G = s->Hq / s->Hkv;
         const long kv_units = (long)s->B * s->Hkv;
