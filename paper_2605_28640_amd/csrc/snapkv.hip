@@ -142,9 +142,9 @@ __device__ __forceinline__ void snap_query_fragments(const bf16 *q, int rows, co
 // 64 at a time and in order: which positions are kept can hang on the last place of these sums (votes that tie to seven
 // digits are not rare among thousands), so their order does not follow the shape of the launch.
 // The keys of a step lie in one of four slots, loaded by all four waves three steps ahead.
-// Bound by memory with up to 64 rows (268 MB of keys in 50 us), by the weights' arithmetic with 128 (60 us); two slots of 128
-// keys, loaded during a step and waited for at its end, took 64-68.  (Tiles of the waves' own, as in the second sweep, take 44-51
-// us, and give the sums another order.)
+// Bound by memory with up to 64 rows (268 MB of keys in 50 us), partly by the weights' arithmetic with 128 (51-60 us, by
+// machine); two slots of 128 keys, loaded during a step and waited for at its end, took 60-68.  (Tiles of the waves' own, as in
+// the second sweep, take 44-51 us, and give the sums another order.)
 template <int D, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void snapkv_stats_kernel(
     const bf16 *__restrict__ q_win, const bf16 *__restrict__ k_cache, float *__restrict__ stats, int Hq, int Hkv, long T,

@@ -233,7 +233,8 @@ def test_sweeps_at_the_edges_of_tiles(rs, Hq, Hkv, D, W, grow):
     a tile with one key, and several chunks of keys; scores that keep growing along the keys (the softmax reference moves)
     and ones that don't; the last length also with enough heads for streaming loads.  Against 64-bit softmax sums: the
     votes are sums of W * G weights, each within a few units of float32 rounding of exp2 and of a log-sum-exp of
-    magnitude below 2^10, 2^10 * 2^-23 = 1.2e-4 at worst."""
+    magnitude below 2^10, 2^10 * 2^-23 = 1.2e-4 at worst; where the scores don't grow it stays below 16, and its two roundings,
+    the exponent's and a few of the sums come to 16 * 2^-24 * 4 = 4e-6."""
     scale = 1.0 / np.sqrt(D)
     for T, B in ((W + 1, 1), (W + 31, 2), (W + 97, 1), (W + 128, 1), (2048 + W + 1, 1), (2 * 2048 + 5, 2), (4001, -(-(81 << 20) // (Hkv * 4001 * D * 2)))):
         say("snapkv edges", Hq, Hkv, D, W, grow, T, B)
@@ -259,7 +260,7 @@ def test_sweeps_at_the_edges_of_tiles(rs, Hq, Hkv, D, W, grow):
             for g in range(Hq // Hkv):
                 x = q[b, h * (Hq // Hkv) + g].double() @ k[b, h].double().T * scale
                 want += torch.softmax(x.masked_fill_(later, -torch.inf), 1).sum(0)[:L]
-            np.testing.assert_allclose(to_np(votes[b, h]), to_np(want), rtol=2e-4, atol=1e-9)
+            np.testing.assert_allclose(to_np(votes[b, h]), to_np(want), rtol=2e-4 if grow else 4e-6, atol=1e-9)
         best = torch.sort(votes, dim=2, descending=True, stable=True).indices[:, :, :keep].sort(2).values
         assert torch.equal(best.int(), idx)
         rows = torch.cat([best, torch.arange(L, T, device="cuda").expand(B, Hkv, W)], 2)[..., None].expand(-1, -1, -1, D)
