@@ -392,9 +392,11 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
 
     // replay from the incoming state
     float sk[8], sv[8];
-    // a token's inputs as new values to the compiler, which would otherwise keep what the fold made of them (1 - g,
-    // unpacked keys) in registers until the replay; in whole rows one token behind the states of the one before, as all
-    // of them unpacked at once do not fit the registers beside the next chunk's
+    // Whole rows with two sets: a token's inputs as new values to the compiler, which would otherwise keep what the fold made of
+    // them (1 - g, unpacked keys) in registers until the replay; one token behind the states of the one before, as all
+    // of them unpacked at once do not fit the registers beside the next chunk's.  (Slabs keep them: worked out again they cost
+    // a short run 0.4 us, 2 x 8 heads x 600 in float32 17.7 / 18.7.  Float32 slabs sit at 120 to 128 registers, two workgroups to a
+    // CU; two more and pages of 32 tokens lose the second: 8 heads x 64K 284 / 310, 128 x 6000 393 / 444.)
     auto fresh_inputs = [&](int i) __attribute__((always_inline)) {
         uint32_t w[2 * KW + 8];
         __builtin_memcpy(w, &kr[i], sizeof(kr[i]));
@@ -412,10 +414,6 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
         __builtin_memcpy(&g0[i], w + 2 * KW, 16);
         __builtin_memcpy(&g1[i], w + 2 * KW + 4, 16);
     };
-    if constexpr (!PIPE) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i) fresh_inputs(i);
-    }
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         sk[c] = fmaf(a[c], s_carry[wave][0][c0 + c], bk[c]);
@@ -446,7 +444,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     const int rows_out = PIPE ? (int)((T_new - (long)j * CHUNK < CHUNK) ? T_new - (long)j * CHUNK : CHUNK) : 0;
     const auto kd_out = rows_of(k_cache, out_row0 + (long)j * CHUNK, rows_out), vd_out = rows_of(v_cache, out_row0 + (long)j * CHUNK, rows_out);
     uint32_t el_out = lane_el;
-    asm volatile("" : "+v"(el_out));
+    if constexpr (PIPE) asm volatile("" : "+v"(el_out));
     auto store_row = [&](const LdsSource &d, int i, const float (&x)[8]) __attribute__((always_inline)) {  // whole rows
         const uint32_t byte = el_out * (uint32_t)sizeof(ST) + i * D * (int)sizeof(ST);
         if constexpr (sizeof(ST) == 2) {
@@ -605,12 +603,13 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
                 if constexpr (!AHEAD) next = next_ticket();
             }
         } else {
+            load_chunk(tA, A);
             for (;;) {
-                load_chunk(tA, A);
                 (void)process_chunk(tA, A, B, total);
                 if (n_chunks == 1) break;
                 tA = next_ticket();
                 if (tA >= total) break;
+                load_chunk(tA, A);
             }
         }
     }
