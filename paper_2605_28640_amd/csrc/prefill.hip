@@ -830,6 +830,26 @@ static unsigned prefill_spare_lds(int D, long n, long tiles)
     return D == 128 && n >= 9 && tiles > 512 && tiles <= 768 ? 24 * 1024 : 0;
 }
 
+// Units of an XCD whose causal tiles go out together.  The tiles of a group keep the XCD's 96 workgroups busy for about as
+// long as its heaviest tile takes (group * n_diag^2 / 2 steps over 96, against n_diag), and never fewer than four units or than
+// the query heads of a KV head; more units than that only widen what its 4 MB of L2 see at a time: 8 x 32 heads x 4096
+// tokens by bit sets, 32 units at a time 1530 us, 6 at a time 1213, one after the other 1270; 9 and 12 at a time no better.
+// A remainder is a group that does not fill the XCD, so the units are divided evenly (the heads of a KV head together) where that
+// is possible with more than half as many at a time.  As above with the remainder / divided evenly, us: 2 x 32 heads x 4001 (8 units: 2 + 6 / 4 + 4) 262 / 249,
+// by bit sets with routing 315 / 306, 8 x 32 x 4096 (32: 2 + 5 of 6 / 8 of 4) 1040 / 1008 and 1232 / 1213, 3 x 32 x 2500
+// (12: 2 + 10 / 6 + 6) 170 / 166; four at least instead of two: 32 over 8 heads x 16001 1752 / 1735, 32 x 16000 1760 / 1740.
+static int prefill_group(long units, int heads_per_kv, int n_diag)
+{
+    int want = (192 + n_diag - 1) / n_diag;
+    if (want < 4) want = 4;
+    want = (want + heads_per_kv - 1) / heads_per_kv * heads_per_kv;
+    if (units % 8) return want;
+    const long u = units / 8;
+    for (int g = want; 2 * g > want; g -= heads_per_kv)
+        if (u % g == 0) return g;
+    return want;
+}
+
 template <int D, PrefillForm FORM>
 static void prefill_causal_launch(const PrefillParams &p, dim3 grid, hipStream_t stream)
 {
@@ -895,11 +915,7 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     p.K = K;
     p.block = block;
     p.n_diag = (int)((T + kMT - 1) / kMT);
-    // the tiles of a group keep the XCD's 96 workgroups busy for about as long as its heaviest tile takes
-    // (group * n_diag^2 / 2 steps over 96, against n_diag); more units than that only widen what its 4 MB of
-    // L2 see at a time: 8 x 32 heads x 4096 tokens by bit sets, 32 units at a time 1530 us, 6 at a time 1213,
-    // one after the other 1270; 9 and 12 at a time measured no better
-    p.group = (192 + p.n_diag - 1) / p.n_diag;
+    p.group = prefill_group(units, s->Hq / s->Hkv, p.n_diag);
     p.T = T;
     p.Tcap = s->Tcap;
     p.scale = scale;
