@@ -224,6 +224,13 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     constexpr int RW = 64 / CR;    // rows one wave-wide load covers
     constexpr int RPI = 4 * RW;    // rows one pass of the four waves covers
     constexpr int CPT = kKT / RPI; // passes per tile (loads per thread per tile, for K and for V)
+    // Operands read this many matrix instructions ahead of their use, the order pinned; 0: in the compiler's order, which
+    // under 168 registers reads most of them right before they are used, and every matrix instruction waits for an LDS trip.
+    // Tiles of listed rows and own-block tiles wait longer than they multiply: 32 heads x 32768, blocks of 512, top-3
+    // 1155 -> 1132 us with routing, 16 heads x 20000 380 -> 369, 2 x 32 over 8 heads x 16000, blocks of 256, top-4 1012 -> 1000.  (Three
+    // ahead: 1154; six: 1156.)  Causal tiles are limited by power and have fewer registers left (2 x 32 heads x 4001 260 -> 270, by
+    // bit sets 326 -> 325, 32 over 8 heads x 16001 1743 -> 1725), 64 channels have few operands (2 x 16 over 8 heads x 20000 392 -> 394).
+    constexpr int kAhead = (D == 128 && (FORM == kListed || FORM == kOwn)) ? 4 : 0;
     // a ring of three K and three V tiles as separate objects, addressed with a compile-time index:
     // the compiler then knows that a step's operand reads and the direct loads into another slot
     // cannot overlap, and puts no wait between them
@@ -457,6 +464,27 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int sub = 0; sub < SUB; ++sub)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) sacc[sub][v] = 0.f;
+                if constexpr (kAhead > 0) {
+                    bf16x8 kf[kAhead];
+                    auto read = [&](int n) __attribute__((always_inline)) {
+                        kf[n % kAhead] = *reinterpret_cast<const bf16x8 *>(&cK[koff[n]]);
+                    };
+#pragma unroll
+                    for (int n = 0; n < kAhead; ++n) read(n);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) {
+                        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[n % kAhead], qf[n], sacc[0], 0, 0, 0);
+                        if (n + kAhead < NC) read(n + kAhead);
+                        if constexpr (LOAD) {
+                            if (n % (NC / CPT) == 0) stage(kb, gk, nK, n / (NC / CPT), it + 2);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    __builtin_amdgcn_s_setprio(0);
+                    return;
+                }
+                // kAhead = 0
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     if constexpr (LOAD) {
@@ -560,39 +588,67 @@ __global__ __launch_bounds__(SUB == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             // P^T as the B operand: accumulator values 8c .. 8c+7 are this lane's keys
             // 16c + 4h + {0..3} and 16c + 8 + 4h + {0..3}; V^T is read in the same key order
             __builtin_amdgcn_s_setprio(1);
+            if constexpr (kAhead > 0) {
+                union {
+                    s16x4 s[2];
+                    bf16x8 f;
+                } vf[kAhead];
+                auto read = [&](int n) __attribute__((always_inline)) {
+                    const uint16_t *vq = &cV[16 * (n / NDT) * D] + voff[n % NDT];
+                    vf[n % kAhead].s[0] = lds_read_tr16(vq);
+                    vf[n % kAhead].s[1] = lds_read_tr16(vq + 8 * D);
+                };
 #pragma unroll
-            for (int sub = 0; sub < SUB; ++sub) {
-                bf16x8 pf[2];
+                for (int n = 0; n < kAhead; ++n) read(n);
+                bf16x8 pf;
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int n = 0; n < 2 * NDT; ++n) {
+                    if (n % NDT == 0) {
 #pragma unroll
-                    for (int s8 = 0; s8 < 8; ++s8) pf[c][s8] = (__bf16)sacc[sub][8 * c + s8];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    if constexpr (NEXT) {
-                        if (2 * sub + c < CPT) stage(vb, gv, nV, 2 * sub + c, it + 2);
+                        for (int s8 = 0; s8 < 8; ++s8) pf[s8] = (__bf16)sacc[0][8 * (n / NDT) + s8];
+                        if constexpr (NEXT) {
+                            if (n / NDT < CPT) stage(vb, gv, nV, n / NDT, it + 2);
+                        }
                     }
+                    oacc[n % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n % kAhead].f, pf, oacc[n % NDT], 0, 0, 0);
+                    if (n + kAhead < 2 * NDT) read(n + kAhead);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
 #pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) {
-                        const uint16_t *vq = &cV[(32 * sub + 16 * c) * D];
-                        union {
-                            s16x4 s[2];
-                            bf16x8 f;
-                        } vf;
-                        vf.s[0] = lds_read_tr16(vq + voff[dt]);
-                        vf.s[1] = lds_read_tr16(vq + voff[dt] + 8 * D);
-                        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f, pf[c], oacc[dt], 0, 0, 0);
+                for (int sub = 0; sub < SUB; ++sub) {
+                    bf16x8 pf[2];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+#pragma unroll
+                        for (int s8 = 0; s8 < 8; ++s8) pf[c][s8] = (__bf16)sacc[sub][8 * c + s8];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        if constexpr (NEXT) {
+                            if (2 * sub + c < CPT) stage(vb, gv, nV, 2 * sub + c, it + 2);
+                        }
+#pragma unroll
+                        for (int dt = 0; dt < NDT; ++dt) {
+                            const uint16_t *vq = &cV[(32 * sub + 16 * c) * D];
+                            union {
+                                s16x4 s[2];
+                                bf16x8 f;
+                            } vf;
+                            vf.s[0] = lds_read_tr16(vq + voff[dt]);
+                            vf.s[1] = lds_read_tr16(vq + voff[dt] + 8 * D);
+                            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f, pf[c], oacc[dt], 0, 0, 0);
+                        }
                     }
                 }
-            }
-            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
-            for (int g = 0; g < SUB * 2 * NDT - 3; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                if (NEXT && g < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                for (int g = 0; g < SUB * 2 * NDT - 3; ++g) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    if (NEXT && g < CPT) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
             __builtin_amdgcn_s_setprio(0);
         }
         if constexpr (FORM == kBitSets) {  // block of the next step (wave-uniform counters, no division)
