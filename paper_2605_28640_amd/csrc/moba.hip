@@ -174,31 +174,37 @@ typedef float gate_f32x16 __attribute__((ext_vector_type(16)));
 // NWV > 1 (register picks only): the waves of a workgroup share the unit's block-mean operands
 // through LDS (at most 64 blocks: 48 KB at D = 128), fetched once per workgroup instead of once per
 // 64-token tile from L2 -- with operands two chunks ahead, a wave otherwise waits an L2 round
-// trip every other chunk.
+// trip every other chunk.  Twelve waves with 32 query rows each, three to a SIMD: with six waves of 64 rows two SIMDs of a CU had
+// twice the work of the others and vector work lay bare (means and gate of 32 heads x 32768, blocks of 512, top-3: 123 -> 112 us,
+// of which the means are 47; 8 x 32 heads x 4096, blocks of 64, top-8 145 -> 132).  What is left is bound by memory: without
+// the matrix instructions 107, without the picks 111.  (Queries as streaming loads: 108, but the attention then finds none in the
+// memory-side cache, 2 x 32 heads x 4001 with attention 304 -> 319.  The next tile's rows sent for before the matrix work: 113.)
 template <int D, int KL, bool WIDE, int NWV>
-__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV == 1 ? 2 : 1, 2))) void moba_gate_mfma_kernel(const bf16 *__restrict__ q, const uint16_t *__restrict__ split,
+__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV == 1 ? 2 : 3, NWV == 1 ? 2 : 3))) void moba_gate_mfma_kernel(const bf16 *__restrict__ q, const uint16_t *__restrict__ split,
                                                            int32_t *__restrict__ idx_out, int Hq, int Hkv, long T,
                                                            int block, int Nb, int K, int n_first)
 {
     constexpr int NC = D / 16;
     constexpr int CR = D / 8;    // 16-byte chunks per query row
     constexpr int RW = 64 / CR;  // rows one wave-wide direct load covers
-    constexpr int NP = 64 / RW;  // direct loads per 64-row tile
-    // A workgroup is one wave; it walks over tiles of 64 query tokens of one (batch, head).  The
+    constexpr int QT = NWV == 1 ? 2 : 1;  // 32-row query tiles a wave takes at a time
+    constexpr int ROWS = 32 * QT;
+    constexpr int NP = ROWS / RW;  // direct loads per tile
+    // A wave walks over tiles of ROWS query tokens of one (batch, head).  The
     // tile's query rows come through LDS: row-contiguous direct loads (a lane fetching its own
     // row in 16-byte pieces would touch 64 cache lines per instruction), issued one tile ahead --
     // once the current tile's operands sit in registers and its matrix work is done -- so that
     // they land under the picks of the current tile.
     static_assert(NWV == 1 || (KL > 0 && !WIDE), "shared operands: register picks only");
-    __shared__ __attribute__((aligned(1024))) uint16_t sQ_all[NWV * 64 * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t sQ_all[NWV * ROWS * D];
     __shared__ __attribute__((aligned(1024))) uint16_t sM[NWV == 1 ? 8 : 2 * 3 * 32 * D];  // [group][term][chunk][lane][8]
     extern __shared__ float s_score[];  // [Nb rounded up to 32][64], only for the LDS picks
     const int lane = threadIdx.x & 63, lq = lane & 31, h = lane >> 5;
     const int wave = (NWV == 1) ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint16_t *sQ = sQ_all + wave * 64 * D;
+    uint16_t *sQ = sQ_all + wave * ROWS * D;
     const int unit = blockIdx.y;  // b * Hq + h
     const int b = unit / Hq, hq = unit % Hq, kvh = hq / (Hq / Hkv);
-    const long n_tiles = (T + 63) / 64;
+    const long n_tiles = (T + ROWS - 1) / ROWS;
     const long tile0 = (long)blockIdx.x * NWV + wave, tile_step = (long)gridDim.x * NWV;
     if constexpr (NWV > 1) {
         // the unit's operands into LDS: 1 KB per direct load, the waves take turns
@@ -213,7 +219,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
     const int srow = lane / CR;
     auto stage_q = [&](long t_tile) __attribute__((always_inline)) {
         const LdsSource src = lds_source(q + ((long)unit * T + t_tile) * D);
-        const int last = (int)((T - 1 - t_tile < 63) ? T - 1 - t_tile : 63);  // rows past the end repeat the last one
+        const int last = (int)((T - 1 - t_tile < ROWS - 1) ? T - 1 - t_tile : ROWS - 1);  // rows past the end repeat the last one
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int row = i * RW + srow;
@@ -221,14 +227,14 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
             load16_to_lds(src, (uint32_t)(r * D + (((lane % CR) ^ chunk_swizzle<D>(row)) * 8)) * 2u, sQ + i * RW * D);
         }
     };
-    stage_q(tile0 * 64);
+    stage_q(tile0 * ROWS);
 
     const uint16_t *sbase = split + (long)(b * Hkv + kvh) * ((Nb + 31) / 32) * 3 * 32 * D;  // wave-uniform
     const LdsSource means_src = lds_source(sbase);  // operand loads: descriptor + scalar offset + 16 bytes per lane
-    // scores of blocks j0 .. j0 + 31 against this wave's 64 queries
-    auto scores = [&](int j0, const gate_bf16x8 (&qf)[2][NC], gate_f32x16 (&acc)[2]) __attribute__((always_inline)) {
+    // scores of blocks j0 .. j0 + 31 against this wave's queries
+    auto scores = [&](int j0, const gate_bf16x8 (&qf)[QT][NC], gate_f32x16 (&acc)[QT]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
+        for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[qt][v] = 0.f;
         const int frag = (j0 / 32) * 3 * 32 * D * 2;  // byte offset of the group's [term][chunk][lane][8]: 1 KB per operand
@@ -249,7 +255,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         for (int c = 0; c < NC; ++c) {
             if (c + 2 < NC) fetch(c + 2);
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt) {
+            for (int qt = 0; qt < QT; ++qt) {
                 acc[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m[c % 3][2], qf[qt][c], acc[qt], 0, 0, 0);
                 acc[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m[c % 3][1], qf[qt][c], acc[qt], 0, 0, 0);
                 acc[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m[c % 3][0], qf[qt][c], acc[qt], 0, 0, 0);
@@ -258,20 +264,25 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         }
     };
     for (long tile = tile0; tile < n_tiles; tile += tile_step) {
-    const long t_tile = tile * 64;
-    const long t_last = (t_tile + 63 < T) ? t_tile + 63 : T - 1;
-    const int own_max = (int)(t_last / block);  // uniform over the wave
+    const long t_tile = tile * ROWS;
+    // own blocks of the tile's rows: that of the first row by a division (T < 2^32: longer caches don't fit the memory), the
+    // others from their distance to it
+    const uint32_t own_min = (uint32_t)t_tile / (uint32_t)block, rest = (uint32_t)t_tile - own_min * (uint32_t)block;
+    const int n_rows = (T - t_tile < ROWS) ? (int)(T - t_tile) : ROWS;
+    auto own_of = [&](int row) __attribute__((always_inline)) -> int {  // rows past the end repeat the last one
+        const uint32_t x = rest + (uint32_t)(row < n_rows ? row : n_rows - 1);
+        return (int)(own_min + (block >= ROWS ? (x >= (uint32_t)block ? 1u : 0u) : x / (uint32_t)block));
+    };
+    const int own_max = own_of(ROWS - 1);  // uniform over the wave
     const bool more = tile + tile_step < n_tiles;
-    // B operands: this lane's two query rows (tokens t_tile + lq and t_tile + 32 + lq, clamped)
-    gate_bf16x8 qf[2][NC];
-    int own_q[2];
+    // B operands: this lane's query rows (tokens t_tile + 32 qt + lq, clamped)
+    gate_bf16x8 qf[QT][NC];
+    int own_q[QT];
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile's rows are in LDS
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-        const long t = t_tile + 32 * qt + lq;
-        const long tc = (t < T) ? t : T - 1;
-        own_q[qt] = (int)(tc / block);
+    for (int qt = 0; qt < QT; ++qt) {
         const int row = 32 * qt + lq;
+        own_q[qt] = own_of(row);
         const int sw = chunk_swizzle<D>(row);
 #pragma unroll
         for (int c = 0; c < NC; ++c) qf[qt][c] = *reinterpret_cast<const gate_bf16x8 *>(&sQ[row * D + (((2 * c + h) ^ sw) * 8)]);
@@ -279,33 +290,39 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the operands are in registers, the LDS tile is free again
     // accumulator value v of lane (lq, h): block j0 + 8 (v / 4) + 4 h + v % 4, query lq
     if constexpr (KL > 0 && !WIDE) {
-        float sc[2][2][16];  // [block group][query tile][value]; -inf: not a candidate
+        float sc[2][QT][16];  // [block group][query tile][value]; -inf: not a candidate
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             if (32 * g <= own_max) {
-                gate_f32x16 acc[2];
+                gate_f32x16 acc[QT];
                 scores(32 * g, qf, acc);
 #pragma unroll
-                for (int qt = 0; qt < 2; ++qt)
+                for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int j = 32 * g + 8 * (v / 4) + 4 * h + (v % 4);
-                        float x = acc[qt][v];
-                        if (j == own_q[qt] || j < n_first) x = INFINITY;  // always kept
-                        sc[g][qt][v] = (j <= own_q[qt]) ? x : -INFINITY;
-                    }
+                    for (int v = 0; v < 16; ++v) sc[g][qt][v] = acc[qt][v];
+                if (32 * g + 31 >= (int)own_min || n_first > 32 * g) {  // blocks that are kept anyway or no candidates (uniform)
+#pragma unroll
+                    for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int j = 32 * g + 8 * (v / 4) + 4 * h + (v % 4);
+                            float x = sc[g][qt][v];
+                            if (j == own_q[qt] || j < n_first) x = INFINITY;  // always kept
+                            sc[g][qt][v] = (j <= own_q[qt]) ? x : -INFINITY;
+                        }
+                }
             } else {
 #pragma unroll
-                for (int qt = 0; qt < 2; ++qt)
+                for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) sc[g][qt][v] = -INFINITY;
             }
         }
-        if (more) stage_q((tile + tile_step) * 64);  // lands under the picks
-        // half h writes the picks of query tile h (token t_tile + 32 h + lq) as a 64-bit mask of blocks
+        if (more) stage_q((tile + tile_step) * ROWS);  // lands under the picks
+        // half h writes the picks of query tile h (token t_tile + 32 h + lq; of one tile the first half) from a 64-bit mask of blocks
         uint64_t picks = 0;
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
+        for (int qt = 0; qt < QT; ++qt) {
             // the KL largest of this half-lane's values, then of both halves: a descending list,
             // a new value x enters by top[i] <- median(top[i-1], top[i], x) (old values), top[0] <- max
             float top[KL];
@@ -340,10 +357,12 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
                 uint32_t w[2];
 #pragma unroll
                 for (int g = 0; g < 2; ++g) {
+                    // value v in bit v first (a doubling with carry each), then every four of them to their eight blocks
                     uint32_t m = 0u;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        if (test(sc[g][qt][v], thr)) m |= 1u << (8 * (v / 4) + (v % 4));
+                    for (int v = 15; v >= 0; --v) m = m + m + (test(sc[g][qt][v], thr) ? 1u : 0u);
+                    m = (m | m << 8) & 0x00ff00ffu;
+                    m = (m | m << 4) & 0x0f0f0f0fu;
                     m <<= 4 * h;
                     w[g] = m | (uint32_t)__shfl_xor((int)m, 32, 64);
                 }
@@ -360,10 +379,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
                     tied &= tied - 1;
                 }
             }
-            if (qt == h) picks = sel;
+            if (QT == 1 || qt == h) picks = sel;
         }
-        const long t = t_tile + 32 * h + lq;
-        if (t < T) {
+        const long t = t_tile + (QT == 1 ? 0 : 32 * h) + lq;
+        if (t < T && (QT == 2 || h == 0)) {
             int32_t *dst = idx_out + ((long)unit * T + t) * K;
             for (int n = 0; n < K; ++n) {
                 dst[n] = picks ? (int32_t)__builtin_ctzll(picks) : -1;
@@ -373,9 +392,9 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         continue;
     } else if constexpr (KL > 0) {
         // more than 64 blocks: sorted top lists per query tile while the scores go to LDS columns
-        float top[2][KL];
+        float top[QT][KL];
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt)
+        for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
             for (int i = 0; i < KL; ++i) top[qt][i] = -INFINITY;
         auto put = [&](float (&tl)[KL], float x) __attribute__((always_inline)) {
@@ -389,10 +408,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
             }
         };
         for (int j0 = 0; j0 <= own_max; j0 += 32) {
-            gate_f32x16 acc[2];
+            gate_f32x16 acc[QT];
             scores(j0, qf, acc);
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt)
+            for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int j = j0 + 8 * (v / 4) + 4 * h + (v % 4);
@@ -402,9 +421,9 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
                     put(top[qt], (j <= own_q[qt]) ? x : -INFINITY);
                 }
         }
-        if (more) stage_q((tile + tile_step) * 64);  // lands under the picks
+        if (more) stage_q((tile + tile_step) * ROWS);  // lands under the picks
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
+        for (int qt = 0; qt < QT; ++qt) {
             float other[KL];
 #pragma unroll
             for (int i = 0; i < KL; ++i) other[i] = shfl_xor_f(top[qt][i], 32);
@@ -413,12 +432,12 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         }
         // from here thread = query token t_tile + lane = query tile h, row lq
         const long t = t_tile + lane;
-        const int own = h ? own_q[1] : own_q[0];
+        const int own = h ? own_q[QT - 1] : own_q[0];
         const int avail = own + 1;
         const int take = (K < avail) ? K : avail;
-        float thr = h ? top[1][0] : top[0][0];
+        float thr = h ? top[QT - 1][0] : top[0][0];
 #pragma unroll
-        for (int i = 1; i < KL; ++i) thr = (take > i) ? (h ? top[1][i] : top[0][i]) : thr;  // top[take - 1]
+        for (int i = 1; i < KL; ++i) thr = (take > i) ? (h ? top[QT - 1][i] : top[0][i]) : thr;  // top[take - 1]
         __syncthreads();  // the score columns are complete
         uint64_t ge[4] = {0ull, 0ull, 0ull, 0ull}, gt[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
@@ -473,10 +492,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
         continue;
     } else {
         for (int j0 = 0; j0 <= own_max; j0 += 32) {
-            gate_f32x16 acc[2];
+            gate_f32x16 acc[QT];
             scores(j0, qf, acc);
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt)
+            for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int j = j0 + 8 * (v / 4) + 4 * h + (v % 4);
@@ -486,14 +505,13 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(NWV ==
                 }
         }
     }
-    if (more) stage_q((tile + tile_step) * 64);  // lands under the picks
+    if (more) stage_q((tile + tile_step) * ROWS);  // lands under the picks
     __syncthreads();
     // the picks: thread = query token, candidates 0 .. own.  The sweeps run to the wave-uniform
     // bound own_max in steps of four (rows up to the next multiple of 32 exist in LDS), so that
     // four LDS reads are in flight at a time; entries past the thread's own block are skipped.
     const long t = t_tile + lane;
-    const long tq = (t < T) ? t : T - 1;
-    const int own = (int)(tq / block);
+    const int own = h ? own_q[QT - 1] : own_q[0];
     const int avail = own + 1;
     const int take = (K < avail) ? K : avail;
     for (int r = 0; r < take; ++r) {
@@ -560,17 +578,18 @@ int moba_select_dispatch(const rs_shape *s, const void *q, const void *k_cache, 
     if (knobs().gate_waves != kKnobUnset) per_unit = ((long)knobs().gate_waves + units - 1) / units;
     if (per_unit < 1) per_unit = 1;
     const dim3 g3((unsigned)(n_tiles < per_unit ? n_tiles : per_unit), (unsigned)units);
-    // six-wave workgroups with the operands in LDS (48 KB + 6 x 16 KB of query rows): one per CU
-    long wg_per_unit = (256 + units - 1) / units;
-    if (knobs().gate_wgs != kKnobUnset) wg_per_unit = ((long)knobs().gate_wgs + units - 1) / units;
+    // twelve-wave workgroups with the operands in LDS (48 KB + 12 x 8 KB of query rows): one per CU
+    constexpr int nwv = 12;
+    long wg_per_unit = (knobs().gate_wgs != kKnobUnset ? (long)knobs().gate_wgs : 256) / units;
     if (wg_per_unit < 1) wg_per_unit = 1;
-    constexpr int nwv = 6;
-    if (wg_per_unit > (n_tiles + nwv - 1) / nwv) wg_per_unit = (n_tiles + nwv - 1) / nwv;
+    const long n_tiles32 = (T + 31) / 32;
+    if (wg_per_unit > (n_tiles32 + nwv - 1) / nwv) wg_per_unit = (n_tiles32 + nwv - 1) / nwv;
     const dim3 g4((unsigned)wg_per_unit, (unsigned)units);
     const int eso = knobs().gate_shared;
-    // worth its set-up from about 8192 tiles on (C4 0.148 -> 0.138 ms; 8 x 32 heads x 4096 tokens, blocks of 64,
-    // top-8: 0.184 -> 0.150 ms; 32 heads x 4096 tokens: 0.026 against 0.031 ms the other way)
-    const bool shared_ops = in_registers && (eso != kKnobUnset ? eso != 0 : units * n_tiles >= 8192);
+    // Worth its set-up from about 4000 tiles of 64 rows on.  Means and gate, one wave / shared, us: 8 x 32 heads x 4096 tokens,
+    // blocks of 64, top-8 (16384 tiles) 182 / 132, 4 x 32 x 4096 86 / 74, 2 x 32 x 4001 (4032) 45.8 / 44.0; the other way 32 over 8
+    // heads x 4096, top-16 (2048) 27.6 / 32.2.
+    const bool shared_ops = in_registers && (eso != kKnobUnset ? eso != 0 : units * n_tiles >= 4000);
     const bool big = (long)s->B * s->Hkv * T * s->D * (s->dtype == RS_BF16 ? 2 : 4) >= kStreamBytes;
 #define RS_MEANS(ST, DD, GRID, SPLIT)                                                                                          \
     do {                                                                                                                       \
@@ -587,7 +606,7 @@ int moba_select_dispatch(const rs_shape *s, const void *q, const void *k_cache, 
         if (s->D == 128) {
             RS_MEANS(bf16, 128, g1p, split);
 #define RS_GATE1(DD, KLL, WW, LDS) moba_gate_mfma_kernel<DD, KLL, WW, 1><<<g3, 64, LDS, stream>>>((const bf16 *)q, split, idx_out, s->Hq, s->Hkv, T, block, Nb, K, n_first)
-#define RS_GATE4(DD, KLL) moba_gate_mfma_kernel<DD, KLL, false, 6><<<g4, 384, 0, stream>>>((const bf16 *)q, split, idx_out, s->Hq, s->Hkv, T, block, Nb, K, n_first)
+#define RS_GATE4(DD, KLL) moba_gate_mfma_kernel<DD, KLL, false, nwv><<<g4, 64 * nwv, 0, stream>>>((const bf16 *)q, split, idx_out, s->Hq, s->Hkv, T, block, Nb, K, n_first)
 #define RS_GATE(DD)                                            \
     do {                                                       \
         if (kl == 0) RS_GATE1(DD, 0, true, lds_mfma);          \
