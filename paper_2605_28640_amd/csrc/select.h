@@ -4,6 +4,8 @@
 
 #include "common.h"
 
+#include <type_traits>
+
 namespace rs {
 
 // ------------------------------------------------------------------------------------
@@ -42,9 +44,9 @@ __device__ __forceinline__ float acquire_f32(const uint64_t *p, uint32_t tag, in
 // ------------------------------------------------------------------------------------
 template <int NT>
 struct SelectShared {
-    uint32_t hist[4][256];  // one histogram per radix pass, zeroed once
+    __attribute__((aligned(16))) uint32_t hist[4][256];  // one histogram per radix pass, zeroed once
     int wave_tot[NT / 64];
-    int ex_cnt[NT];  // (row, wave) table: greater-than count | equal count << 16
+    __attribute__((aligned(16))) int ex_cnt[NT];  // (row, wave) table: greater-than count | equal count << 16
 };
 
 // wave64 inclusive prefix sum over ascending lanes, with DPP row shifts and row broadcasts
@@ -68,9 +70,180 @@ struct NoMark {
     __device__ __forceinline__ void operator()(int) const {}
 };
 
+// wave64 minimum, in lane 63: the same lane pattern
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t min_step_dpp(uint32_t x)
+{
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROWS, 0xf, false);
+    return y < x ? y : x;
+}
+__device__ __forceinline__ uint32_t wave_min_dpp(uint32_t x)
+{
+    x = min_step_dpp<0x111, 0xf>(x);
+    x = min_step_dpp<0x112, 0xf>(x);
+    x = min_step_dpp<0x114, 0xf>(x);
+    x = min_step_dpp<0x118, 0xf>(x);
+    x = min_step_dpp<0x142, 0xa>(x);
+    return min_step_dpp<0x143, 0xc>(x);
+}
+
+// The same selection by one histogram, where the keys' numbers spread over their range: 1023 bins of equal width between the
+// smallest and the largest number (the last bin: keys of 0xffffffff, the pages that are kept anyway), and the K-th largest is
+// ranked among the few keys of its bin.  The keys stay in registers; four barriers, where the radix passes take nine, read the keys
+// anew each time and spend their first pass on a handful of distinct top bytes.  Bound by the vector instructions of two waves
+// a SIMD: 2049 keys by 512 threads 8.2 -> 3.2 us.  False, with nothing emitted, where it does not apply: infinities, NaN or an
+// extreme range among the numbers, or more than 64 keys in the bin.  Requires Np <= kSpreadRows * NT, 512 threads.
+constexpr int kSpreadRows = 10;
+template <int R0, int R, typename Body>
+__device__ __forceinline__ void rows_from(int rows, Body body)
+{
+    if constexpr (R0 < R) {
+        if (R0 < rows) {
+            body(std::integral_constant<int, R0>{});
+            rows_from<R0 + 1, R>(rows, body);
+        }
+    }
+}
+template <int NT, typename Emit>
+__device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np, int K, SelectShared<NT> &sh, Emit emit)
+{
+    constexpr int W = NT / 64, kBins = 4 * 256, R = kSpreadRows;
+    static_assert(W == 8, "the layout of the ranges and counts below");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rows = (Np + NT - 1) / NT;
+    uint32_t *bins = &sh.hist[0][0];
+    uint32_t *range = reinterpret_cast<uint32_t *>(sh.ex_cnt);  // W minima, W complements of maxima; later the table of counts
+    uint32_t *near_k = range + 256, *near_p = near_k + 64, *n_near = near_k + 128;  // the keys of the bin, their indices, how many
+    reinterpret_cast<uint2 *>(bins)[tid] = make_uint2(0u, 0u);
+    if (tid == 0) *n_near = 0u;
+    // body(integral_constant<r>) for the rows that hold candidates (uniform)
+    auto each_row = [&](auto body) __attribute__((always_inline)) { rows_from<0, R>(rows, body); };
+    uint32_t kq[R];
+    uint32_t lo = 0xffffffffu, nhi = 0xffffffffu;  // the smallest key, and the complement of the largest below 0xffffffff
+    each_row([&](auto row) __attribute__((always_inline)) {
+        constexpr int r = decltype(row)::value;
+        const int p = r * NT + tid;
+        kq[r] = keys[p < Np ? p : Np - 1];
+        lo = kq[r] < lo ? kq[r] : lo;
+        const uint32_t nk = kq[r] == 0xffffffffu ? 0xffffffffu : ~kq[r];
+        nhi = nk < nhi ? nk : nhi;
+    });
+    lo = wave_min_dpp(lo);
+    nhi = wave_min_dpp(nhi);
+    if (lane == 63) {
+        range[wave] = lo;
+        range[W + wave] = nhi;
+    }
+    __syncthreads();
+    {
+        uint32_t x = range[lane & 15];  // minima over each half of a row of 16 lanes: lanes 7 and 15
+        x = min_step_dpp<0x111, 0xf>(x);
+        x = min_step_dpp<0x112, 0xf>(x);
+        uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x114, 0xf, 0xf, false);  // lanes 3, 11 into 7, 15
+        x = y < x ? y : x;
+        lo = (uint32_t)__builtin_amdgcn_readlane((int)x, 7);
+        nhi = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+    }
+    auto number = [](uint32_t k) __attribute__((always_inline)) {
+        return __uint_as_float(k ^ (~(uint32_t)((int32_t)k >> 31) | 0x80000000u));
+    };
+    // finite numbers only: between the keys of the largest negative and positive ones
+    const float f_lo = number(lo), width = number(~nhi) - f_lo;
+    if (lo < 0x00800000u || nhi < ~0xff7fffffu || !(width > 1e-30f && width < 1e38f)) {
+        __syncthreads();
+        return false;
+    }
+    const float per = (float)(kBins - 1) / width;
+    // ascending with the number: difference and product are rounded monotonically
+    int bn[R];
+    each_row([&](auto row) __attribute__((always_inline)) {
+        constexpr int r = decltype(row)::value;
+        const int x = (int)((number(kq[r]) - f_lo) * per);
+        bn[r] = kq[r] == 0xffffffffu ? kBins - 1 : x < kBins - 1 ? x : kBins - 2;
+        if (r * NT + tid < Np) atomicAdd(&bins[bn[r]], 1u);
+        else bn[r] = -1;
+    });
+    __syncthreads();
+    // lane l owns bins 16 (63 - l) .. + 15: a prefix sum over ascending lanes counts its bins and every higher one; then the same
+    // among the 16 bins of the lane that the K-th largest falls to
+    int bin, rank, n;  // rank: of the wanted key in its bin, from 0; n: keys in the bin
+    {
+        const uint4 *mine = reinterpret_cast<const uint4 *>(bins + 16 * (63 - lane));
+        int own = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 x = mine[i];
+            own += (int)(x.x + x.y) + (int)(x.z + x.w);
+        }
+        const int incl = wave_incl_scan_dpp(own);
+        const uint64_t who = __ballot(incl - own < K && K <= incl);  // exactly one lane
+        const int src = (int)__builtin_ctzll(who ? who : 1ull);
+        const int above = __builtin_amdgcn_readlane(incl - own, src);
+        const int b = 16 * (63 - src) + 15 - (lane & 15);
+        const int x = (int)bins[b];
+        int in = x;  // over the 16 lanes of a row
+        in += __builtin_amdgcn_update_dpp(0, in, 0x111, 0xf, 0xf, false);
+        in += __builtin_amdgcn_update_dpp(0, in, 0x112, 0xf, 0xf, false);
+        in += __builtin_amdgcn_update_dpp(0, in, 0x114, 0xf, 0xf, false);
+        in += __builtin_amdgcn_update_dpp(0, in, 0x118, 0xf, 0xf, false);
+        const uint64_t hit = __ballot(above + in - x < K && K <= above + in) & 0xffffull;
+        const int at = (int)__builtin_ctzll(hit ? hit : 1ull);
+        bin = __builtin_amdgcn_readlane(b, at);
+        n = __builtin_amdgcn_readlane(x, at);
+        rank = K - 1 - above - __builtin_amdgcn_readlane(in - x, at);
+    }
+    if (n > 64) {
+        __syncthreads();
+        return false;
+    }
+    each_row([&](auto row) __attribute__((always_inline)) {
+        constexpr int r = decltype(row)::value;
+        if (bn[r] == bin) {
+            const uint32_t at = atomicAdd(n_near, 1u);
+            near_k[at] = kq[r];
+            near_p[at] = (uint32_t)(r * NT + tid);
+        }
+    });
+    __syncthreads();
+    // the wanted key: larger keys come before it, and equal ones of lower index
+    uint32_t kth;
+    int pth;
+    {
+        const uint32_t mk = near_k[lane], mp = near_p[lane];  // (lanes from n on: anything)
+        int before = 0;
+        for (int j = 0; j < n; ++j) {
+            const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)mk, j), pj = (uint32_t)__builtin_amdgcn_readlane((int)mp, j);
+            before += (kj > mk || (kj == mk && pj < mp)) ? 1 : 0;
+        }
+        const uint64_t hit = __ballot(lane < n && before == rank);
+        const int src = (int)__builtin_ctzll(hit ? hit : 1ull);
+        kth = (uint32_t)__builtin_amdgcn_readlane((int)mk, src);
+        pth = __builtin_amdgcn_readlane((int)mp, src);
+    }
+    // ascending output: order (row, wave, lane); every wave sums the table of counts (two entries a lane) for itself
+    uint64_t who[R];
+    each_row([&](auto row) __attribute__((always_inline)) {
+        constexpr int r = decltype(row)::value;
+        who[r] = __ballot(bn[r] >= 0 && (kq[r] > kth || (kq[r] == kth && r * NT + tid <= pth)));
+        if (lane == 0) sh.ex_cnt[r * W + wave] = __popcll(who[r]);
+    });
+    __syncthreads();
+    const int2 c = reinterpret_cast<const int2 *>(sh.ex_cnt)[lane];
+    const int c0 = (2 * lane < rows * W) ? c.x : 0, c1 = (2 * lane < rows * W) ? c.y : 0;  // (rows * W is even)
+    const int first = wave_incl_scan_dpp(c0 + c1) - (c0 + c1), second = first + c0;
+    each_row([&](auto row) __attribute__((always_inline)) {
+        constexpr int r = decltype(row)::value;
+        const int at = (r * W + wave) >> 1;  // (uniform, as wave is)
+        const int base = __builtin_amdgcn_readlane((wave & 1) ? second : first, __builtin_amdgcn_readfirstlane(at));
+        if ((who[r] >> lane) & 1ull) emit(base + lanes_below(who[r]), r * NT + tid);
+    });
+    return true;
+}
+
 // emit(pos, p): called once per chosen candidate p with its rank pos in ascending order.
 // keys: Np keys in LDS.  Requires Np <= 64 * NT.
-template <int NT, typename Emit, typename Mark = NoMark>
+// SPREAD: try the one histogram first.
+template <int NT, bool SPREAD = true, typename Emit, typename Mark = NoMark>
 __device__ void select_topk_lds(const uint32_t *keys, int Np, int K, SelectShared<NT> &sh, Emit emit,
                                 Mark mark = Mark())
 {
@@ -78,6 +251,9 @@ __device__ void select_topk_lds(const uint32_t *keys, int Np, int K, SelectShare
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int rows = (Np + NT - 1) / NT;
+    if constexpr (SPREAD) {
+        if (Np <= kSpreadRows * NT && select_topk_spread<NT>(keys, Np, K, sh, emit)) return;
+    }
     for (int i = tid; i < 4 * 256; i += NT) (&sh.hist[0][0])[i] = 0u;
     __syncthreads();
     // every wave tracks the digits found so far and the rank still wanted (same in all waves)

@@ -659,7 +659,8 @@ __global__ __launch_bounds__(kSnapOneWgThreads) void snapkv_pool_select_kernel(c
     __syncthreads();
     if (K_keep <= 0) return;
     int32_t *dst = idx_out + bk * K_keep;
-    select_topk_lds<kSnapOneWgThreads>(s_keys, L, K_keep, sh, [dst](int pos, int p) { dst[pos] = p; });
+    // (votes: a few positions may hold nearly all of the range, and the rest would share a bin of the one histogram)
+    select_topk_lds<kSnapOneWgThreads, false>(s_keys, L, K_keep, sh, [dst](int pos, int p) { dst[pos] = p; });
 }
 
 static size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -652,3 +652,58 @@ def test_splits_of_unit_counts_that_do_not_divide_the_chip(rs, knobs, B, H, T, K
             want = torch.softmax(x, 0) @ vc[b, h, rows].double()
             assert float((out[b, h].double() - want).abs().max()) <= tol * float(want.abs().max()), (b, h)
             assert abs(float(lse[b, h]) - float(torch.logsumexp(x, 0))) <= 1e-5
+
+
+def _score_rows(Np, rng):
+    """Page scores of several kinds, one row each: spread out, tied, crowded beside outliers, not finite, of extreme range."""
+    n = rng.standard_normal(Np)
+    rows = [n, 5 + 0.1 * n, rng.integers(0, 10, Np), np.full(Np, 2.5), np.round(n * 8) / 8, np.exp(6 * n), n * 1e-38, n * 5e37]
+    for big in (1e30, np.inf):
+        x = n.copy()
+        x[rng.integers(0, Np, 3)] = big
+        rows.append(x)
+    rows.append(np.where(rng.random(Np) < 0.3, -np.inf, n))
+    rows.append(np.where(n > 0, 0.0, -0.0))
+    return np.stack(rows).astype(np.float32)
+
+
+@pytest.mark.parametrize("Np,K", [(257, 3), (512, 64), (513, 513), (1024, 1023), (1025, 130), (2049, 256), (4096, 2048), (4097, 2),
+                                  (5120, 640), (5121, 640)])
+def test_selection_over_kinds_of_scores(rs, knobs, Np, K):
+    """Selection from scores that are given exactly (a one-hot query picks one channel of the page bounds): the list is that of a
+    stable sort, whichever way the selection goes about it (one histogram, ranked bin, radix passes), alone and inside the decode."""
+    say("kinds of scores", Np, K)
+    D, P = 64, 16
+    sc = _score_rows(Np, np.random.default_rng(Np))
+    H = sc.shape[0]
+    want = np.empty((H, K), np.int64)
+    for h in range(H):
+        x = sc[h] + 0.0  # -0 to 0
+        x[0] = x[-1] = np.inf
+        if np.isinf(sc[h]).any():  # forced pages come before infinite ones
+            order = np.lexsort((np.arange(Np), -x, ~_forced(Np, 1, 1)))
+        else:
+            order = np.argsort(-x, kind="stable")
+        want[h] = np.sort(order[:K])
+    meta = torch.zeros(1, H, Np, 2, D, device="cuda")
+    meta[0, :, :, 0, 0] = meta[0, :, :, 1, 0] = torch.from_numpy(sc).cuda()
+    q = torch.zeros(1, H, D, device="cuda")
+    q[:, :, 0] = 1
+    s = rs.make_shape(1, H, H, D, Np * P, P, torch.float32)
+    T = Np * P
+    idx = torch.full((1, H, K), -5, dtype=torch.int32, device="cuda")
+    ws = rs.Workspace(max(rs.quest_select_decode_workspace_bytes(s, T), rs.sparse_attn_decode_workspace_bytes(s, T, K)))
+    rs.quest_select_decode(s, q, meta, T, K, 1, 1, idx, None, ws)
+    assert np.array_equal(to_np(idx)[0], want)
+    kc = torch.zeros(1, H, T, D, device="cuda")
+    out, lse = torch.zeros(1, H, D, device="cuda"), torch.zeros(1, H, device="cuda")
+    for two, one in (("1", "0"), ("0", "0"), ("0", "1")):
+        if one == "1" and (Np > 4096 or K > 1024):
+            continue
+        knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", two)
+        knobs.setenv("RATSPARSE_FUSED_ONE_WG", one)
+        idx.fill_(-5)
+        rs.sparse_attn_decode(s, q, kc, kc, T, 1.0, None, K, meta, 1, 1, out, lse, idx, ws)
+        torch.cuda.synchronize()
+        ws.async_status()
+        assert np.array_equal(to_np(idx)[0], want), (two, one)
