@@ -5,6 +5,7 @@
 
 #include <mutex>
 
+#include "append.h"
 #include "common.h"
 #include "decode_fused.h"
 #include "knobs.h"
@@ -38,9 +39,9 @@ void decode_attend_dispatch(int dtype, int D, const void *q, const void *k_cache
                             uint32_t *state, long T_max, const uint32_t *keys, long key_stride, int32_t *idx_out,
                             hipStream_t stream);
 size_t attend_select_lds(long key_stride, int K, int P, int splits);
-void score_keys_dispatch(int dtype, int D, const void *q, const void *meta, uint32_t *keys, int B, int Hq, int Hkv, long Np_cap,
+void score_keys_dispatch(int dtype, int D, const void *q, void *meta, uint32_t *keys, int B, int Hq, int Hkv, long Np_cap,
                          int Np, int K, int n_first, int n_local, int splits, uint32_t *err, const uint32_t *state, long T_max,
-                         int P, long key_stride, hipStream_t stream);
+                         int P, long key_stride, const StepToken *token, hipStream_t stream);
 bool decode_attend_shared_fits(int dtype, int D, int G, int splits);
 void decode_attend_shared_dispatch(int dtype, int D, const void *q, const void *k_cache, const void *v_cache,
                                    const int32_t *idx, void *out, float *lse_out, uint64_t *partial, int B, int Hq, int Hkv,
@@ -659,8 +660,8 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     }
     if (key_splits > 0) {
         uint32_t *keys = (uint32_t *)(w + ((ws_bytes - L.keys_bytes) & ~(size_t)255));
-        score_keys_dispatch(s->dtype, s->D, q, meta, keys, s->B, s->Hq, s->Hkv, s->Tcap / s->P, L.Np, K, n_first, n_local,
-                            L.splits_score, err, nullptr, 0, s->P, key_stride, (hipStream_t)stream);
+        score_keys_dispatch(s->dtype, s->D, q, const_cast<void *>(meta), keys, s->B, s->Hq, s->Hkv, s->Tcap / s->P, L.Np, K, n_first,
+                            n_local, L.splits_score, err, nullptr, 0, s->P, key_stride, nullptr, (hipStream_t)stream);
         if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
         decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, nullptr, out, lse_out, (uint64_t *)(w + L.off_partial), s->B,
                                s->Hq, s->Hkv, s->Tcap, s->P, T_valid, K, scale, key_splits, ctr_att, err, tag,
@@ -830,9 +831,6 @@ int32_t rat_decode_step(const rs_shape *s, const void *k, const void *v, const f
     if (L.Np > 15360) return RS_UNSUPPORTED;  // the selection's keys must fit the LDS: before any launch
     if (!ws || !aligned16(ws) || ws_bytes < L.total) return RS_WORKSPACE_TOO_SMALL;
     char *w = (char *)ws;
-    step_at_state_dispatch(s->dtype, s->D, k, v, g, state_k, state_v, k_cache, v_cache, meta, s->P, s->B * s->Hkv,
-                           s->Tcap, (const uint32_t *)w, T_max, K, (hipStream_t)stream);
-    if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
     // the form of select-then-attend, by the shape at T_max and the rule of sparse_attn_decode: one workgroup per
     // (batch, query head) for short contexts, the persistent launch for long bandwidth-bound steps, the two plain
     // launches in between; all three read the length and the tag from the workspace's state words
@@ -841,7 +839,18 @@ int32_t rat_decode_step(const rs_shape *s, const void *k, const void *v, const f
     const int two_launch = knob_or(knobs().fused_two_launch, (step_bytes >= 450e6 && L.Np >= 512) ? 0 : 1);
     const double unit_bytes = ((double)L.Np * 2 + (double)K * s->P * 2) * s->D * esize(s->dtype);
     const bool unit_rule = two_launch && unit_bytes <= 1.5e6 && (units >= 128 || unit_bytes <= 512e3);
-    if (knob_or(knobs().fused_one_wg, unit_rule ? 1 : 0) && L.Np <= 4096 && K <= 1024) {
+    const bool one_wg = knob_or(knobs().fused_one_wg, unit_rule ? 1 : 0) && L.Np <= 4096 && K <= 1024;
+    const int splits = attend_splits(L, units, (long)K * (s->P / 16));
+    const bool att_selects = !one_wg && two_launch && ws_bytes >= L.total_keys && attend_selects(L.Np, K, s->P, splits);
+    // the scoring launch of the form whose attention selects appends the token as well, where the page that receives it is kept
+    // whatever its score; otherwise the append goes first, by itself
+    const bool appends = att_selects && n_local > 0;
+    if (!appends) {
+        step_at_state_dispatch(s->dtype, s->D, k, v, g, state_k, state_v, k_cache, v_cache, meta, s->P, s->B * s->Hkv,
+                               s->Tcap, (const uint32_t *)w, T_max, K, (hipStream_t)stream);
+        if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
+    }
+    if (one_wg) {
         unit_decode_dispatch(s->dtype, s->D, q, meta, k_cache, v_cache, out, lse_out, idx_out, s->B, s->Hq, s->Hkv,
                              s->Tcap, s->P, T_max, L.Np, K, n_first, n_local, scale, (uint32_t *)w, (hipStream_t)stream);
         return launch_status();
@@ -850,12 +859,13 @@ int32_t rat_decode_step(const rs_shape *s, const void *k, const void *v, const f
         uint32_t *ctr_score = (uint32_t *)w + kCtrlUnit0;
         uint32_t *ctr_att = ctr_score + kMaxUnits;
         uint32_t *err = (uint32_t *)w + kCtrlAsyncErr;
-        const int splits = attend_splits(L, units, (long)K * (s->P / 16));
         uint32_t *state = (uint32_t *)w;
-        if (ws_bytes >= L.total_keys && attend_selects(L.Np, K, s->P, splits)) {
+        if (att_selects) {
             uint32_t *keys = (uint32_t *)(w + ((ws_bytes - L.keys_bytes) & ~(size_t)255));
+            const StepToken token = {k, v, g, state_k, state_v, k_cache, v_cache, s->Tcap};
             score_keys_dispatch(s->dtype, s->D, q, meta, keys, s->B, s->Hq, s->Hkv, s->Tcap / s->P, L.Np, K, n_first, n_local,
-                                L.splits_score, err, state, T_max, s->P, key_row(L.Np), (hipStream_t)stream);
+                                L.splits_score, err, state, T_max, s->P, key_row(L.Np), appends ? &token : nullptr,
+                                (hipStream_t)stream);
             if (launch_status() != RS_OK) return RS_LAUNCH_FAILED;
             decode_attend_dispatch(s->dtype, s->D, q, k_cache, v_cache, nullptr, out, lse_out, (uint64_t *)(w + L.off_partial),
                                    s->B, s->Hq, s->Hkv, s->Tcap, s->P, T_max, K, scale, splits, ctr_att, err, 0u,

@@ -6,6 +6,7 @@
 // 8 channels (one 16-byte bf16 load) each, so a wave touches RPW = 64/LPR rows per load
 // instruction and every global access is a run of full 128/256-byte rows.
 #include <cstdlib>
+#include "append.h"
 #include "attend.h"
 #include "common.h"
 #include "knobs.h"
@@ -263,13 +264,26 @@ int score_select_dispatch(int dtype, int D, int GQ, const void *q, const void *m
 // ------------------------------------------------------------------------------------
 // The same scores as order-preserving keys (pages that are always kept: the top key) for an attention kernel that selects
 // for itself: no hand-over inside the launch, and the chip does not idle while one workgroup of a unit selects.
+// STEP (the replayable decode step, with n_local > 0): the rows of the grid past the query heads append the step's token instead
+// of a launch of their own.  They write the last page's bounds while its scores are formed from them, whatever they hold then: that
+// page is kept anyway and its score goes unused.  32 over 8 heads x 32768, 256 pages 22.2 -> 19.7 us a step.
 // ------------------------------------------------------------------------------------
-template <typename ST, int D>
-__global__ __launch_bounds__(kSelThreads) void quest_score_keys_kernel(const ST *__restrict__ q, const ST *meta, uint32_t *keys,
+template <typename ST, int D, bool STEP>
+__global__ __launch_bounds__(kSelThreads) void quest_score_keys_kernel(const ST *__restrict__ q, ST *meta, uint32_t *keys,
                                                                        int Hq, int Hkv, long Np_cap, int Np, int K, int n_first,
                                                                        int n_local, int splits, uint32_t *err,
-                                                                       const uint32_t *state, long T_max, int P, long key_stride)
+                                                                       const uint32_t *state, long T_max, int P, long key_stride,
+                                                                       StepToken token, int units)
 {
+    if constexpr (STEP) {
+        if ((int)blockIdx.y >= units) {
+            const uint32_t e = ((blockIdx.y - units) * gridDim.x + blockIdx.x) * kSelThreads + threadIdx.x;
+            if (e < (uint32_t)(units / Hq * Hkv * D))
+                append_element(e, (const ST *)token.k, (const ST *)token.v, token.g, token.state_k, token.state_v, (ST *)token.k_cache,
+                               (ST *)token.v_cache, meta, P, D, 1, 0, token.Tcap, state, T_max, K);
+            return;
+        }
+    }
     if (state) {  // the replayable decode step: tokens in the cache + 1 (the step's append has run)
         const long T_valid = *reinterpret_cast<const long *>(state + kCtrlStateT) + 1;
         Np = (int)((T_valid + P - 1) / P);
@@ -314,14 +328,22 @@ __global__ __launch_bounds__(kSelThreads) void quest_score_keys_kernel(const ST 
     }
 }
 
-void score_keys_dispatch(int dtype, int D, const void *q, const void *meta, uint32_t *keys, int B, int Hq, int Hkv, long Np_cap,
+void score_keys_dispatch(int dtype, int D, const void *q, void *meta, uint32_t *keys, int B, int Hq, int Hkv, long Np_cap,
                          int Np, int K, int n_first, int n_local, int splits, uint32_t *err, const uint32_t *state, long T_max,
-                         int P, long key_stride, hipStream_t stream)
+                         int P, long key_stride, const StepToken *token, hipStream_t stream)
 {
-    const dim3 grid((unsigned)splits, (unsigned)(B * Hq));
-#define RS_LAUNCH(ST, DD)                                                                                                       \
-    quest_score_keys_kernel<ST, DD><<<grid, kSelThreads, 0, stream>>>((const ST *)q, (const ST *)meta, keys, Hq, Hkv, Np_cap, Np, \
-                                                                      K, n_first, n_local, splits, err, state, T_max, P, key_stride)
+    const int units = B * Hq;
+    const long n_append = token ? ((long)B * Hkv * D + kSelThreads - 1) / kSelThreads : 0;  // workgroups
+    const dim3 grid((unsigned)splits, (unsigned)(units + (n_append + splits - 1) / splits));
+    const StepToken tk = token ? *token : StepToken{};
+#define RS_LAUNCH_S(ST, DD, SS)                                                                                                 \
+    quest_score_keys_kernel<ST, DD, SS><<<grid, kSelThreads, 0, stream>>>((const ST *)q, (ST *)meta, keys, Hq, Hkv, Np_cap, Np, \
+                                                                          K, n_first, n_local, splits, err, state, T_max, P, key_stride, tk, units)
+#define RS_LAUNCH(ST, DD)                                \
+    do {                                                 \
+        if (token) RS_LAUNCH_S(ST, DD, true);            \
+        else RS_LAUNCH_S(ST, DD, false);                 \
+    } while (0)
     if (dtype == RS_BF16) {
         if (D == 128) RS_LAUNCH(bf16, 128);
         else RS_LAUNCH(bf16, 64);
@@ -329,6 +351,7 @@ void score_keys_dispatch(int dtype, int D, const void *q, const void *meta, uint
         if (D == 128) RS_LAUNCH(float, 128);
         else RS_LAUNCH(float, 64);
     }
+#undef RS_LAUNCH_S
 #undef RS_LAUNCH
 }
 

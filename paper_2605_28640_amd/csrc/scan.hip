@@ -26,6 +26,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "append.h"
 #include "common.h"
 #include "knobs.h"
 
@@ -622,11 +623,7 @@ __global__ __launch_bounds__(NW * 64) void rat_scan_chunk_kernel(
     }
 }
 
-// Few tokens (the decode-time append): one thread per (batch, head, channel).  Nothing but trips to
-// memory: a token's loads, its page's bounds among them, all go out before the first value is needed,
-// and the stored key enters the bounds from its register instead of by way of the cache row just
-// written (one trip instead of three: 3.8 -> 2.8 us for 8 x 32 heads of 128 channels, and a
-// decode step at 4096 tokens 22.1 -> 21.5 us).
+// few tokens (the decode-time append)
 template <typename ST>
 __global__ __launch_bounds__(256) void rat_step_kernel(
     const ST *__restrict__ k, const ST *__restrict__ v, const float *__restrict__ g,
@@ -636,58 +633,7 @@ __global__ __launch_bounds__(256) void rat_step_kernel(
 {
     const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (uint32_t)(BH * D)) return;
-    const uint32_t bh = e / (uint32_t)D, c = e % (uint32_t)D;
-    float sk = state_k[e], sv = state_v[e];
-    const long in0 = (long)bh * T_new * D + c;
-    float gg = g[in0];
-    ST kx = k[in0], vx = v[in0];
-    if (pos_state) {  // replayable step: the write position is the workspace's token count
-        t0 = *reinterpret_cast<const long *>(pos_state + kCtrlStateT);
-        // a step the attention kernel of the same call will refuse (past T_max, or fewer pages than
-        // it must select) appends nothing either: the refused step leaves carries, caches and page
-        // bounds as they were, and the attention kernel reports it
-        if (t0 + T_new > T_max || (t0 + T_new + P - 1) / P < (long)K_min_pages) return;
-    }
-    const uint32_t shift = meta ? (uint32_t)__builtin_ctz((unsigned)P) : 0u;  // P is a power of two
-    ST lo_b, hi_b;  // the bounds so far of the page of the row at hand, as stored
-    if (meta && (t0 & (P - 1)) != 0) {
-        const ST *mn = meta + (((long)bh * (Tcap >> shift) + (t0 >> shift)) * 2) * D + c;
-        lo_b = mn[0];
-        hi_b = mn[D];
-    }
-    for (long t = 0; t < T_new; ++t) {
-        const float om = 1.f - gg;
-        sk = fmaf(gg, sk, om * to_f32(kx));
-        sv = fmaf(gg, sv, om * to_f32(vx));
-        if (t + 1 < T_new) {
-            const long off = in0 + (t + 1) * D;
-            gg = g[off];
-            kx = k[off];
-            vx = v[off];
-        }
-        const long row = t0 + t, o = ((long)bh * Tcap + row) * D + c;
-        ST ks, vs;
-        from_f32(ks, sk);
-        from_f32(vs, sv);
-        k_cache[o] = ks;
-        v_cache[o] = vs;
-        if (meta) {
-            // Quest page min/max of the stored key: a page's first row starts it, later rows fold in
-            const float x = to_f32(ks);
-            float lo = x, hi = x;
-            if ((row & (P - 1)) != 0) {
-                lo = fminf(to_f32(lo_b), x);
-                hi = fmaxf(to_f32(hi_b), x);
-            }
-            from_f32(lo_b, lo);
-            from_f32(hi_b, hi);
-            ST *mn = meta + (((long)bh * (Tcap >> shift) + (row >> shift)) * 2) * D + c;
-            mn[0] = lo_b;
-            mn[D] = hi_b;
-        }
-    }
-    state_k[e] = sk;
-    state_v[e] = sv;
+    append_element(e, k, v, g, state_k, state_v, k_cache, v_cache, meta, P, D, T_new, t0, Tcap, pos_state, T_max, K_min_pages);
 }
 
 template <typename ST, int D, int DS, int PAGE, bool LEAD, ScanTurn TURN>

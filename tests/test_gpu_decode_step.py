@@ -38,6 +38,10 @@ CASES = [
     (synth.C2.scaled(B=2, Hq=8, Hkv=2), 300, 40, 1024, 16, 8, 1, 1),   # GQA bf16, crosses three page edges
     (synth.C1.scaled(B=1, Hq=4, Hkv=4), 2040, 20, 2304, 64, 5, 0, 1),   # f32 D=64, 64-token pages, one edge
     (synth.C3.scaled(B=1, Hq=8, Hkv=8), 9000, 12, 9216, 16, 36, 1, 2),  # several attention slices per unit
+    # 64 pages and more with two launches: the scoring one appends too where the last page is kept anyway, and not without that
+    (synth.C2.scaled(B=3, Hq=16, Hkv=8), 1022, 6, 1040, 16, 12, 1, 1),  # 48 heads in one workgroup row each, a page begun
+    (synth.C2.scaled(B=3, Hq=16, Hkv=8), 1022, 6, 1040, 16, 12, 2, 0),
+    (synth.C1.scaled(B=1, Hq=3, Hkv=3), 4095, 4, 4160, 32, 9, 0, 1),    # f32 D=64: less than a workgroup of elements to append
 ]
 
 
