@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kFusedThreads) __attribute__((amdgpu_waves_per_eu(4
                 uint64_t *dst = a.idx_tagged + (long)unit * a.K;
                 int32_t *plain = a.idx_out ? a.idx_out + (long)unit * a.K : nullptr;
                 const uint32_t tag = tag_;
-                select_topk_lds<kFusedThreads, false>(s_keys, Np_, a.K, sh, [dst, plain, tag](int pos, int p) {
+                select_topk_lds<kFusedThreads, kNoSpread>(s_keys, Np_, a.K, sh, [dst, plain, tag](int pos, int p) {
                     store_u64_agent(&dst[pos], ((uint64_t)tag << 32) | (uint32_t)p);
                     if (plain) plain[pos] = p;
                 }, [&](int ph) { mark(item, ph); });

@@ -88,12 +88,14 @@ __device__ __forceinline__ uint32_t wave_min_dpp(uint32_t x)
 }
 
 // The same selection by one histogram, where the keys' numbers spread over their range: 1023 bins of equal width between the
-// smallest and the largest number (the last bin: keys of 0xffffffff, the pages that are kept anyway), and the K-th largest is
-// ranked among the few keys of its bin.  The keys stay in registers; four barriers, where the radix passes take nine, read the keys
+// smallest and the largest number (the last bin: keys of 0xffffffff, the pages that are kept anyway), or, kByKey, between the
+// smallest and the largest key, whose steps grow with the number (positive numbers of which a few hold nearly all of the range,
+// as SnapKV's votes are), and the K-th largest is ranked among the few keys of its bin.  The keys stay in registers; four barriers, where the radix passes take nine, read the keys
 // anew each time and spend their first pass on a handful of distinct top bytes.  Bound by the vector instructions of two waves
 // a SIMD: 2049 keys by 512 threads 8.2 -> 3.2 us.  False, with nothing emitted, where it does not apply: infinities, NaN or an
-// extreme range among the numbers, or more than 64 keys in the bin.  Requires Np <= kSpreadRows * NT, 512 threads.
-constexpr int kSpreadRows = 10;
+// extreme range among the numbers (not kByKey), or more than 64 keys in the bin (kByKey: in the last of its subdivisions).  Requires Np <= spread_rows(NT) * NT.
+// (16-wave workgroups: 15 rows, as many as the LDS of their callers holds)
+constexpr int spread_rows(int NT) { return NT == 1024 ? 15 : 10; }
 template <int R0, int R, typename Body>
 __device__ __forceinline__ void rows_from(int rows, Body body)
 {
@@ -104,17 +106,20 @@ __device__ __forceinline__ void rows_from(int rows, Body body)
         }
     }
 }
-template <int NT, typename Emit>
+enum SelectSpread { kNoSpread, kByNumber, kByKey };
+template <int NT, SelectSpread HOW, typename Emit>
 __device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np, int K, SelectShared<NT> &sh, Emit emit)
 {
-    constexpr int W = NT / 64, kBins = 4 * 256, R = kSpreadRows;
-    static_assert(W == 8, "the layout of the ranges and counts below");
+    constexpr int W = NT / 64, kBins = 4 * 256, R = spread_rows(NT);
+    static_assert(W == 8 || W == 16, "the layout of the ranges and counts below");
+    constexpr int E = W / 4;  // entries of the table of counts a lane sums (R * W of them at most)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rows = (Np + NT - 1) / NT;
     uint32_t *bins = &sh.hist[0][0];
     uint32_t *range = reinterpret_cast<uint32_t *>(sh.ex_cnt);  // W minima, W complements of maxima; later the table of counts
     uint32_t *near_k = range + 256, *near_p = near_k + 64, *n_near = near_k + 128;  // the keys of the bin, their indices, how many
-    reinterpret_cast<uint2 *>(bins)[tid] = make_uint2(0u, 0u);
+#pragma unroll
+    for (int i = 0; i < kBins / NT; ++i) bins[i * NT + tid] = 0u;
     if (tid == 0) *n_near = 0u;
     // body(integral_constant<r>) for the rows that hold candidates (uniform)
     auto each_row = [&](auto body) __attribute__((always_inline)) { rows_from<0, R>(rows, body); };
@@ -136,38 +141,40 @@ __device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np,
     }
     __syncthreads();
     {
-        uint32_t x = range[lane & 15];  // minima over each half of a row of 16 lanes: lanes 7 and 15
+        uint32_t x = range[lane & (2 * W - 1)];  // lanes W - 1 and 2 W - 1 come to hold the minima over W lanes
         x = min_step_dpp<0x111, 0xf>(x);
         x = min_step_dpp<0x112, 0xf>(x);
-        uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x114, 0xf, 0xf, false);  // lanes 3, 11 into 7, 15
-        x = y < x ? y : x;
-        lo = (uint32_t)__builtin_amdgcn_readlane((int)x, 7);
-        nhi = (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+        x = min_step_dpp<0x114, 0xf>(x);
+        if constexpr (W == 16) x = min_step_dpp<0x118, 0xf>(x);
+        lo = (uint32_t)__builtin_amdgcn_readlane((int)x, W - 1);
+        nhi = (uint32_t)__builtin_amdgcn_readlane((int)x, 2 * W - 1);
     }
     auto number = [](uint32_t k) __attribute__((always_inline)) {
         return __uint_as_float(k ^ (~(uint32_t)((int32_t)k >> 31) | 0x80000000u));
     };
     // finite numbers only: between the keys of the largest negative and positive ones
     const float f_lo = number(lo), width = number(~nhi) - f_lo;
-    if (lo < 0x00800000u || nhi < ~0xff7fffffu || !(width > 1e-30f && width < 1e38f)) {
+    if (HOW == kByNumber && (lo < 0x00800000u || nhi < ~0xff7fffffu || !(width > 1e-30f && width < 1e38f))) {
         __syncthreads();
         return false;
     }
     const float per = (float)(kBins - 1) / width;
+    const uint32_t reach = (~nhi > lo) ? ~nhi - lo : 0u;
+    int shift = reach >= (uint32_t)kBins ? 22 - __builtin_clz(reach) : 0;  // reach >> shift < kBins
     // ascending with the number: difference and product are rounded monotonically
     int bn[R];
     each_row([&](auto row) __attribute__((always_inline)) {
         constexpr int r = decltype(row)::value;
-        const int x = (int)((number(kq[r]) - f_lo) * per);
+        const int x = HOW == kByKey ? (int)((kq[r] - lo) >> shift) : (int)((number(kq[r]) - f_lo) * per);
         bn[r] = kq[r] == 0xffffffffu ? kBins - 1 : x < kBins - 1 ? x : kBins - 2;
         if (r * NT + tid < Np) atomicAdd(&bins[bn[r]], 1u);
         else bn[r] = -1;
     });
     __syncthreads();
-    // lane l owns bins 16 (63 - l) .. + 15: a prefix sum over ascending lanes counts its bins and every higher one; then the same
-    // among the 16 bins of the lane that the K-th largest falls to
-    int bin, rank, n;  // rank: of the wanted key in its bin, from 0; n: keys in the bin
-    {
+    int bin, rank, n, want = K;  // rank: of the wanted key in its bin, from 0; n: keys in the bin
+    for (;;) {
+        // lane l owns bins 16 (63 - l) .. + 15: a prefix sum over ascending lanes counts its bins and every higher one; then the
+        // same among the 16 bins of the lane that the wanted key falls to
         const uint4 *mine = reinterpret_cast<const uint4 *>(bins + 16 * (63 - lane));
         int own = 0;
 #pragma unroll
@@ -176,7 +183,7 @@ __device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np,
             own += (int)(x.x + x.y) + (int)(x.z + x.w);
         }
         const int incl = wave_incl_scan_dpp(own);
-        const uint64_t who = __ballot(incl - own < K && K <= incl);  // exactly one lane
+        const uint64_t who = __ballot(incl - own < want && want <= incl);  // exactly one lane
         const int src = (int)__builtin_ctzll(who ? who : 1ull);
         const int above = __builtin_amdgcn_readlane(incl - own, src);
         const int b = 16 * (63 - src) + 15 - (lane & 15);
@@ -186,15 +193,29 @@ __device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np,
         in += __builtin_amdgcn_update_dpp(0, in, 0x112, 0xf, 0xf, false);
         in += __builtin_amdgcn_update_dpp(0, in, 0x114, 0xf, 0xf, false);
         in += __builtin_amdgcn_update_dpp(0, in, 0x118, 0xf, 0xf, false);
-        const uint64_t hit = __ballot(above + in - x < K && K <= above + in) & 0xffffull;
+        const uint64_t hit = __ballot(above + in - x < want && want <= above + in) & 0xffffull;
         const int at = (int)__builtin_ctzll(hit ? hit : 1ull);
         bin = __builtin_amdgcn_readlane(b, at);
         n = __builtin_amdgcn_readlane(x, at);
-        rank = K - 1 - above - __builtin_amdgcn_readlane(in - x, at);
-    }
-    if (n > 64) {
+        rank = want - 1 - above - __builtin_amdgcn_readlane(in - x, at);
+        if (n <= 64) break;
         __syncthreads();
-        return false;
+        if (HOW != kByKey || shift == 0 || bin == kBins - 1) return false;
+        // a crowded bin: its keys over bins of their own, 1024 to the bin (more land in the last where its width is not that of one)
+        lo += (uint32_t)bin << shift;
+        shift = shift > 10 ? shift - 10 : 0;
+        want = rank + 1;
+#pragma unroll
+        for (int i = 0; i < kBins / NT; ++i) bins[i * NT + tid] = 0u;
+        __syncthreads();
+        each_row([&](auto row) __attribute__((always_inline)) {
+            constexpr int r = decltype(row)::value;
+            const bool in_bin = bn[r] == bin;
+            const uint32_t y = (kq[r] - lo) >> shift;
+            bn[r] = in_bin ? (y < (uint32_t)(kBins - 1) ? (int)y : kBins - 2) : -1;
+            if (in_bin) atomicAdd(&bins[bn[r]], 1u);
+        });
+        __syncthreads();
     }
     each_row([&](auto row) __attribute__((always_inline)) {
         constexpr int r = decltype(row)::value;
@@ -220,21 +241,28 @@ __device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np,
         kth = (uint32_t)__builtin_amdgcn_readlane((int)mk, src);
         pth = __builtin_amdgcn_readlane((int)mp, src);
     }
-    // ascending output: order (row, wave, lane); every wave sums the table of counts (two entries a lane) for itself
+    // ascending output: order (row, wave, lane); every wave sums the table of counts for itself
     uint64_t who[R];
     each_row([&](auto row) __attribute__((always_inline)) {
         constexpr int r = decltype(row)::value;
-        who[r] = __ballot(bn[r] >= 0 && (kq[r] > kth || (kq[r] == kth && r * NT + tid <= pth)));
+        who[r] = __ballot(r * NT + tid < Np && (kq[r] > kth || (kq[r] == kth && r * NT + tid <= pth)));
         if (lane == 0) sh.ex_cnt[r * W + wave] = __popcll(who[r]);
     });
     __syncthreads();
-    const int2 c = reinterpret_cast<const int2 *>(sh.ex_cnt)[lane];
-    const int c0 = (2 * lane < rows * W) ? c.x : 0, c1 = (2 * lane < rows * W) ? c.y : 0;  // (rows * W is even)
-    const int first = wave_incl_scan_dpp(c0 + c1) - (c0 + c1), second = first + c0;
+    int ahead = 0;  // before the entry of this lane's E that has the place of this wave's
+    {
+        int c[E], sum = 0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            c[i] = (E * lane + i < rows * W) ? sh.ex_cnt[E * lane + i] : 0;
+            ahead += i < wave % E ? c[i] : 0;
+            sum += c[i];
+        }
+        ahead += wave_incl_scan_dpp(sum) - sum;
+    }
     each_row([&](auto row) __attribute__((always_inline)) {
         constexpr int r = decltype(row)::value;
-        const int at = (r * W + wave) >> 1;  // (uniform, as wave is)
-        const int base = __builtin_amdgcn_readlane((wave & 1) ? second : first, __builtin_amdgcn_readfirstlane(at));
+        const int base = __builtin_amdgcn_readlane(ahead, __builtin_amdgcn_readfirstlane((r * W + wave) / E));
         if ((who[r] >> lane) & 1ull) emit(base + lanes_below(who[r]), r * NT + tid);
     });
     return true;
@@ -243,7 +271,7 @@ __device__ __forceinline__ bool select_topk_spread(const uint32_t *keys, int Np,
 // emit(pos, p): called once per chosen candidate p with its rank pos in ascending order.
 // keys: Np keys in LDS.  Requires Np <= 64 * NT.
 // SPREAD: try the one histogram first.
-template <int NT, bool SPREAD = true, typename Emit, typename Mark = NoMark>
+template <int NT, SelectSpread SPREAD = kByNumber, typename Emit, typename Mark = NoMark>
 __device__ void select_topk_lds(const uint32_t *keys, int Np, int K, SelectShared<NT> &sh, Emit emit,
                                 Mark mark = Mark())
 {
@@ -251,8 +279,8 @@ __device__ void select_topk_lds(const uint32_t *keys, int Np, int K, SelectShare
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int rows = (Np + NT - 1) / NT;
-    if constexpr (SPREAD) {
-        if (Np <= kSpreadRows * NT && select_topk_spread<NT>(keys, Np, K, sh, emit)) return;
+    if constexpr (SPREAD != kNoSpread) {
+        if (Np <= spread_rows(NT) * NT && select_topk_spread<NT, SPREAD>(keys, Np, K, sh, emit)) return;
     }
     for (int i = tid; i < 4 * 256; i += NT) (&sh.hist[0][0])[i] = 0u;
     __syncthreads();

@@ -632,9 +632,8 @@ __global__ void snapkv_gather_kernel(const ST *__restrict__ k_cache, const ST *_
 // the order-preserving keys of the pooled votes in LDS (the selection the decode kernels use:
 // keys above the K-th, then equal ones by lowest position).  At these sizes the five launches
 // of the spread-out selection above cost more than the work in them.  The whole compression, one workgroup
-// a head / spread out, us: 8 heads x 4096 31 / 44, x 8000 41 / 46, x 12000 54 / 51, x 15360 66 / 54; 8 x 32 heads
-// x 4096 154 / 167, x 15360 533 / 560.  (The line is where the keys still fit beside the selection's own LDS; few heads
-// would gain from one at about 10000.)
+// a head / spread out, us: 8 heads x 4096 26 / 40, x 8000 33 / 42, x 12000 40 / 45, x 15360 48 / 48; 8 x 32 heads
+// x 4096 127 / 141, x 15360 465 / 502.  (The line is where the keys still fit beside the selection's own LDS.)
 constexpr int kSnapOneWgKeys = 15360;  // 60 KiB of keys
 constexpr int kSnapOneWgThreads = 1024;
 
@@ -644,23 +643,43 @@ __global__ __launch_bounds__(kSnapOneWgThreads) void snapkv_pool_select_kernel(c
                                                                                int kernel, int K_keep)
 {
     __shared__ SelectShared<kSnapOneWgThreads> sh;
-    extern __shared__ uint32_t s_keys[];  // L keys
+    extern __shared__ uint32_t s_keys[];  // L keys; the raw votes at first
     const long bk = blockIdx.x;
     const float *row = votes + bk * L;
-    const int half = kernel / 2;
-    for (int p = threadIdx.x; p < L; p += kSnapOneWgThreads) {
-        const int lo = (p - half < 0) ? 0 : p - half;
-        const int hi = (p + half > L - 1) ? L - 1 : p + half;
-        float m = row[lo];
-        for (int j = lo + 1; j <= hi; ++j) m = fmaxf(m, row[j]);
-        if (pooled_out) pooled_out[bk * L + p] = m;
-        s_keys[p] = float_to_key(m);
-    }
+    const int half = kernel / 2, tid = threadIdx.x;
+    // The votes come in by one trip and are pooled from LDS, a place of the window for all of a thread's positions at a time
+    // (a window of dependent trips to the caches per position: 8 x 32 heads x 4096 13.1 us for the launch, now 12.0).
+    constexpr int R = kSnapOneWgKeys / kSnapOneWgThreads;
+    float m[R];
+    auto each_row = [&](auto body) __attribute__((always_inline)) {
+        rows_from<0, R>((L + kSnapOneWgThreads - 1) / kSnapOneWgThreads, body);
+    };
+    auto place = [&](int r) __attribute__((always_inline)) {  // positions past the end repeat the last one
+        const int p = r * kSnapOneWgThreads + tid;
+        return p < L ? p : L - 1;
+    };
+    each_row([&](auto r) __attribute__((always_inline)) { m[r] = row[place(r)]; });
+    each_row([&](auto r) __attribute__((always_inline)) { s_keys[place(r)] = __float_as_uint(m[r]); });
+    __syncthreads();
+    each_row([&](auto r) __attribute__((always_inline)) {
+        const int lo = place(r) - half;
+        m[r] = __uint_as_float(s_keys[lo < 0 ? 0 : lo]);
+    });
+    for (int d = 1 - half; d <= half; ++d)
+        each_row([&](auto r) __attribute__((always_inline)) {
+            const int at = place(r) + d;
+            m[r] = fmaxf(m[r], __uint_as_float(s_keys[at < 0 ? 0 : at < L ? at : L - 1]));
+        });
+    __syncthreads();
+    each_row([&](auto r) __attribute__((always_inline)) {
+        const int p = place(r);
+        if (pooled_out) pooled_out[bk * L + p] = m[r];
+        s_keys[p] = float_to_key(m[r]);
+    });
     __syncthreads();
     if (K_keep <= 0) return;
     int32_t *dst = idx_out + bk * K_keep;
-    // (votes: a few positions may hold nearly all of the range, and the rest would share a bin of the one histogram)
-    select_topk_lds<kSnapOneWgThreads, false>(s_keys, L, K_keep, sh, [dst](int pos, int p) { dst[pos] = p; });
+    select_topk_lds<kSnapOneWgThreads, kByKey>(s_keys, L, K_keep, sh, [dst](int pos, int p) { dst[pos] = p; });
 }
 
 static size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -325,3 +325,32 @@ def test_kept_positions_are_those_of_64_bit_votes(rs):
         assert ((votes[b].double() - want).abs() <= 4e-6 * want).all()
         first = torch.sort(want, dim=1, descending=True, stable=True).indices[:, :keep].sort(1).values
         assert torch.equal(idx[b].long(), first), b
+
+
+@pytest.mark.parametrize("L,K,pool", [(700, 100, 1), (1025, 1, 3), (4032, 512, 7), (9001, 9000, 1), (10241, 700, 5), (15360, 1920, 1)])
+def test_kept_positions_over_kinds_of_votes(rs, L, K, pool):
+    """The kept positions are those of a stable sort of the votes the library itself reports: votes spread evenly, all alike,
+    a few that hold nearly all of the range over a crowd of near-equal ones, two levels, and over forty octaves."""
+    say("kinds of votes", L, K, pool)
+    D, W = 64, 32
+    T = L + W
+    rng = np.random.default_rng(L)
+    n = rng.standard_normal(L)
+    rows = [0.3 * n, np.zeros(L), np.where(rng.random(L) < 3 / L, 12.0, 0.004 * n), np.where(n > 1, 1.0, 0.0), 9 * n]
+    H = len(rows)
+    kc = torch.zeros(1, H, T, D, device="cuda")
+    kc[0, :, :L, 0] = torch.from_numpy(np.stack(rows)).float().cuda()
+    kc = kc.to(torch.bfloat16)
+    q = torch.zeros(1, H, W, D, device="cuda")
+    q[..., 0] = 1 + 0.01 * torch.arange(W, device="cuda")
+    s = rs.make_shape(1, H, H, D, T, 16, torch.bfloat16)
+    ws = rs.Workspace(rs.snapkv_compress_workspace_bytes(s, T, W))
+    ko, vo = (torch.zeros(1, H, K + W, D, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    idx = torch.full((1, H, K), -5, dtype=torch.int32, device="cuda")
+    votes = torch.zeros(1, H, L, device="cuda")
+    rs.snapkv_compress(s, q.to(torch.bfloat16), kc, kc, T, W, K, pool, 1.0, ko, vo, K + W, idx, votes, ws)
+    torch.cuda.synchronize()
+    for h in range(H):
+        want = np.sort(np.argsort(-to_np(votes)[0, h], kind="stable")[:K])
+        assert np.array_equal(to_np(idx)[0, h], want), h
+        assert torch.equal(ko[0, h, :K], kc[0, h, torch.from_numpy(want).cuda()])
