@@ -15,6 +15,7 @@ RS_WS_CTRL_BYTES = 65536
 RS_STATIC_SCRATCH_BYTES = 16 << 20
 
 _lib = None
+_native = None  # the per-token calls, taken apart in C++ (csrc/native.cpp)
 
 
 class RatsparseError(RuntimeError):
@@ -75,7 +76,7 @@ SIGNATURES = {
 
 def load():
     """Load libratsparse.so; raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RatsparseError(
@@ -85,8 +86,20 @@ def load():
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
-        _lib = lib
+        try:
+            from . import _native as native
+        except ImportError as e:
+            raise RatsparseError("_native.so is not built: run `python -m paper_2605_28640_amd.build`") from e
+        native.setup(*(ctypes.cast(getattr(lib, name), _vp).value for name in ("rat_scan", "sparse_attn_decode", "rat_decode_step")),
+                     _ptr, _check, torch._C._cuda_getCurrentRawStream, torch.cuda.current_device, Workspace)
+        _lib, _native = lib, native
     return _lib
+
+
+def _calls():
+    if _native is None:
+        load()
+    return _native
 
 
 def _check(status):
@@ -154,9 +167,7 @@ def rat_scan_workspace_bytes(s, T_new):
 
 
 def rat_scan(s, k, v, g, state_k, state_v, k_cache, v_cache, t0, T_new, ws=None, meta=None):
-    _check(load().rat_scan(ctypes.byref(s), _ptr(k), _ptr(v), _ptr(g), _ptr(state_k), _ptr(state_v),
-                           _ptr(k_cache), _ptr(v_cache), _ptr(meta), t0, T_new, ws.ptr if ws else None,
-                           ws.nbytes if ws else 0, _stream()))
+    _calls().rat_scan(s, k, v, g, state_k, state_v, k_cache, v_cache, t0, T_new, ws, meta)
 
 
 def quest_page_meta(s, k_cache, meta, t_begin, t_end):
@@ -200,9 +211,8 @@ def rat_decode_state_get(ws):
 
 def rat_decode_step(s, k, v, g, state_k, state_v, k_cache, v_cache, meta, q, scale, K, n_first, n_local, T_max,
                     out, lse_out, idx_out, ws):
-    _check(load().rat_decode_step(ctypes.byref(s), _ptr(k), _ptr(v), _ptr(g), _ptr(state_k), _ptr(state_v),
-                                  _ptr(k_cache), _ptr(v_cache), _ptr(meta), _ptr(q), scale, K, n_first, n_local,
-                                  T_max, _ptr(out), _ptr(lse_out), _ptr(idx_out), ws.ptr, ws.nbytes, _stream()))
+    _calls().rat_decode_step(s, k, v, g, state_k, state_v, k_cache, v_cache, meta, q, scale, K, n_first, n_local, T_max,
+                             out, lse_out, idx_out, ws)
 
 
 def selection_hit_update(idx, gold, unit, hit):
@@ -217,9 +227,8 @@ def sparse_attn_decode_workspace_bytes(s, T_valid, K):
 
 def sparse_attn_decode(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out,
                        lse_out, idx_out, ws):
-    _check(load().sparse_attn_decode(ctypes.byref(s), _ptr(q), _ptr(k_cache), _ptr(v_cache), T_valid,
-                                     scale, _ptr(idx), K, _ptr(meta), n_first, n_local, _ptr(out),
-                                     _ptr(lse_out), _ptr(idx_out), ws.ptr, ws.nbytes, _stream()))
+    _calls().sparse_attn_decode(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out, lse_out,
+                                idx_out, ws)
 
 
 def sparse_attn_decode_static(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out,

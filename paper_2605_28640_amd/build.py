@@ -1,13 +1,16 @@
-"""Build libratsparse.so (the C-ABI HIP library) for gfx950 with hipcc, in-tree."""
+"""Build libratsparse.so (the C-ABI HIP library, for gfx950) with hipcc and _native.so (the binding's per-token calls)
+with the host compiler, in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libratsparse.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.hip", "scan.hip", "quest.hip", "decode_fused.hip", "moba.hip", "prefill.hip", "snapkv.hip", "analysis.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # keep the compiler from forming packed-fp32 instructions
@@ -26,11 +29,24 @@ def _compile(src):
     return obj
 
 
+def _native():
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           os.path.join(CSRC, "native.cpp"), "-o", NATIVE, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on native.cpp:\n%s" % r.stderr)
+
+
 def build(jobs: int = 6) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
     with ThreadPoolExecutor(jobs) as ex:
+        native = ex.submit(_native)
         objs = list(ex.map(_compile, srcs))
+        native.result()
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
     return LIB
 
