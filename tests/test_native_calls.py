@@ -23,7 +23,7 @@ def test_signatures(name, names):
 @pytest.mark.parametrize("bad", [torch.zeros(4), torch.zeros(4, 4).t(), torch.nn.Parameter(torch.zeros(2))])
 def test_only_contiguous_device_tensors(bad):
     with pytest.raises(AssertionError):
-        rs.rat_scan(_shape(), bad, *[None] * 7, t0=0, T_new=1)
+        rs.rat_scan(_shape(), bad, *[None] * 6, t0=0, T_new=1)
 
 
 class _Odd(torch.Tensor):
@@ -34,7 +34,7 @@ class _Odd(torch.Tensor):
 
 def test_a_subclass_is_asked_the_way_it_always_was():
     with pytest.raises(ValueError, match="asked"):
-        rs.rat_scan(_shape(), torch.zeros(4).as_subclass(_Odd), *[None] * 7, t0=0, T_new=1)
+        rs.rat_scan(_shape(), torch.zeros(4).as_subclass(_Odd), *[None] * 6, t0=0, T_new=1)
 
 
 @pytest.mark.parametrize("args", [
