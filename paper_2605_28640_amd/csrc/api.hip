@@ -260,6 +260,33 @@ static bool attend_selects(int Np, int K, int P, int splits)
     return Np >= 64 && attend_select_lds(key_row(Np), K, P, splits) <= 48 * 1024;
 }
 
+// A step of less than about 450 MB of page bounds and selected pages (some 90 us), or of short sequences: bound by latency.
+static bool step_is_brief(double step_bytes, long Np) { return step_bytes < 450e6 || Np < 512; }
+
+// Scores and attention as two plain launches, or as one persistent one whose workgroups hand over through tagged words.  The one launch
+// streams everything and keeps every CU at work; the two are faster where the attention's workgroups (units x splits) fill the
+// CUs evenly, for whole turns, and the heads share no rows.  Append + decode, two / one, us, with the share of the CUs' turns that is filled:
+//   64 heads or fewer, even: 4 x 16 over 4 x 65000, 254 pages (64 heads, 166 MB) 37 / 54, 2 x 32 over 8 x 65000, 1015 (565 MB) 88 / 104,
+//     2 x 32 x 65000, 2030 (1197 MB) 201 / 208, float32 2 x 32 x 60000 (739 MB) 143 / 163;
+//   no shared rows, even: 4 x 32 x 65536, 256 (537 MB) 103 / 106, 4 x 32 x 65000, pages of 64 (599 MB) 101 / 113, float32 x 30000 (737 MB)
+//     141 / 160, 4 x 32 x 32768, 512 (671 MB) 127 / 130 -- up to 5120 pages, which the attention ranks from one histogram: past them it
+//     reads its keys several times, 4 x 32 x 81920, 512 pages 167 / 164, x 98304 179 / 172, 2 x 32 x 131072 120 / 110;
+//   less than four fifths filled: 3 x 32 x 65000 (96 heads, 399 MB) 97 / 85, 3 x 32 x 40000 (246 MB) 66 / 61, 11 x 8 x 50000 (281 MB) 78 / 68,
+//     5 x 32 x 40000 (409 MB) 96 / 86, 6 x 32 x 32000 (393 MB) 85 / 82; below that 3 x 32 x 30000 (184 MB) 49 / 48, 6 x 32 x 15000 (183 MB) 44 / 47;
+//   shared rows: 4 x 32 over 8 x 32768 (302 MB) 70 / 66, 8 x 16 over 4 x 30000 (276 MB) 66 / 62, 4 x 32 over 8 x 65000 (549 MB) 100 / 94.
+// splits: of the attention that selects for itself, 0 where that does not apply (the two launches are slower then).
+static bool two_plain_launches(const rs_shape *s, long units, long Np, int splits, double step_bytes)
+{
+    if (splits == 0 || Np < 512) return step_is_brief(step_bytes, Np);
+    const bool at_once = Np <= 5120;  // the selection's one histogram (spread_rows of 512 threads)
+    const long wgs = units * splits, turns = (wgs + 255) / 256;
+    const double filled = (double)wgs / (256.0 * turns);
+    if (filled < 0.8) return step_bytes < 240e6;
+    if (units <= 64) return (at_once && filled >= 0.9) || step_bytes < 450e6;
+    if (s->Hq > s->Hkv) return step_bytes < 270e6;
+    return (at_once && filled >= 0.95 && units > 96 && units < 256) || step_bytes < 450e6;
+}
+
 // work split and buffers of the one-launch decode (score -> select -> attend) for a sequence of
 // T_valid tokens laid out by L; returns the grid
 static long fused_setup(FusedParams &prm, const rs_shape *s, const DecodeLayout &L, char *w, const void *q,
@@ -618,15 +645,15 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     const int32_t *use_idx = idx;
     const uint32_t tag = next_tag();
     if (group && !listed && !fused) return RS_INVALID_ARG;  // the dense path has no selection to share
-    // One persistent launch when the step is long enough to be bound by bandwidth: at least about
-    // 450 MB of page metadata and selected pages (some 90 us) over at least 512 pages per sequence.
-    // Shorter steps are bound by latency, and there the two plain launches are mostly faster.  Append + decode, two launches / persistent,
-    // us: 32 over 8 heads at 32K, batch 1 (75 MB) 25 / 35, 32 heads at 32K, batch 2 (151 MB) 40 / 47, 16K, batch 8 (302 MB) 60 / 68,
-    // float32 at 32K, batch 2 (393 MB) 82 / 92; the other way 64K, batch 4 (537 MB) 109 / 106, 32 over 8 at 64K, batch 4 (604 MB)
-    // 133 / 113, at 16K, batch 8 (570 MB) 110 / 96.  (The two forms cross between 300 and 550 MB, by shape: 64K, batch 3 (403 MB)
-    // 107 / 88 and 32 over 8 at 32K, batch 4 (302 MB) 74 / 67 are on the wrong side of the line; 8K, batch 32 (537 MB) 110 / 110.)
     const double step_bytes = ((double)s->B * s->Hkv * Np * 2 + (double)units * K * s->P * 2) * s->D * esize(s->dtype);
-    const int two_launch = knob_or(knobs().fused_two_launch, (step_bytes >= 450e6 && Np >= 512) ? 0 : 1);
+    int key_splits = 0;  // > 0: the attention of two launches selects for itself, in that many splits
+    const long key_stride = key_row(L.Np);
+    if (fused && !group && ws_bytes >= L.total_keys) {
+        key_splits = attend_splits(L, units, (long)K * (s->P / 16));
+        if (!attend_selects(L.Np, K, s->P, key_splits)) key_splits = 0;
+    }
+    const bool brief = step_is_brief(step_bytes, Np);
+    const int two_launch = knob_or(knobs().fused_two_launch, two_plain_launches(s, units, Np, key_splits, step_bytes) ? 1 : 0);
     // Short contexts (the paper's 4096 tokens): the whole step of a (batch, query head) inside one
     // workgroup, one launch, nothing handed between workgroups.  Taken when a unit's metadata and
     // picked pages are small (at most 1.5 MB, and at most 512 KB unless there are 128 units or
@@ -635,7 +662,7 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
     // 16K 63 / 60 / 68; 16-token pages, 8K, batch 16 54 / 60 / 64; the other way at 32K, batch 2: 60 / 40 / 47.  (At batch 64 and 4096
     // tokens two launches have become the faster form: 106 / 96 / 125.)
     const double unit_bytes = ((double)Np * 2 + (double)K * s->P * 2) * s->D * esize(s->dtype);
-    const bool unit_rule = two_launch && unit_bytes <= 1.5e6 && (units >= 128 || unit_bytes <= 512e3);
+    const bool unit_rule = knob_or(knobs().fused_two_launch, brief ? 1 : 0) && unit_bytes <= 1.5e6 && (units >= 128 || unit_bytes <= 512e3);
     const int one_wg = knob_or(knobs().fused_one_wg, unit_rule ? 1 : 0);
     if (fused && !group && one_wg && Np <= 4096 && K <= 1024) {
         unit_decode_dispatch(s->dtype, s->D, q, meta, k_cache, v_cache, out, lse_out, idx_out, s->B, s->Hq, s->Hkv,
@@ -651,12 +678,6 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
         st = decode_fused_dispatch(s->dtype, s->D, prm, L.Np, (int)grid, (hipStream_t)stream);
         if (st != RS_OK) return st;
         return launch_status();
-    }
-    int key_splits = 0;  // > 0: the attention selects for itself, in that many splits
-    const long key_stride = key_row(L.Np);
-    if (fused && !group && ws_bytes >= L.total_keys) {
-        key_splits = attend_splits(L, units, (long)K * (s->P / 16));
-        if (!attend_selects(L.Np, K, s->P, key_splits)) key_splits = 0;
     }
     if (key_splits > 0) {
         uint32_t *keys = (uint32_t *)(w + ((ws_bytes - L.keys_bytes) & ~(size_t)255));
@@ -836,12 +857,15 @@ int32_t rat_decode_step(const rs_shape *s, const void *k, const void *v, const f
     // launches in between; all three read the length and the tag from the workspace's state words
     const long units = (long)s->B * s->Hq;
     const double step_bytes = ((double)s->B * s->Hkv * L.Np * 2 + (double)units * K * s->P * 2) * s->D * esize(s->dtype);
-    const int two_launch = knob_or(knobs().fused_two_launch, (step_bytes >= 450e6 && L.Np >= 512) ? 0 : 1);
+    int key_splits = attend_splits(L, units, (long)K * (s->P / 16));
+    const int splits = key_splits;
+    if (ws_bytes < L.total_keys || !attend_selects(L.Np, K, s->P, key_splits)) key_splits = 0;
+    const int two_launch = knob_or(knobs().fused_two_launch, two_plain_launches(s, units, L.Np, key_splits, step_bytes) ? 1 : 0);
     const double unit_bytes = ((double)L.Np * 2 + (double)K * s->P * 2) * s->D * esize(s->dtype);
-    const bool unit_rule = two_launch && unit_bytes <= 1.5e6 && (units >= 128 || unit_bytes <= 512e3);
+    const bool unit_rule = knob_or(knobs().fused_two_launch, step_is_brief(step_bytes, L.Np) ? 1 : 0) && unit_bytes <= 1.5e6 &&
+                           (units >= 128 || unit_bytes <= 512e3);
     const bool one_wg = knob_or(knobs().fused_one_wg, unit_rule ? 1 : 0) && L.Np <= 4096 && K <= 1024;
-    const int splits = attend_splits(L, units, (long)K * (s->P / 16));
-    const bool att_selects = !one_wg && two_launch && ws_bytes >= L.total_keys && attend_selects(L.Np, K, s->P, splits);
+    const bool att_selects = !one_wg && two_launch && key_splits > 0;
     // the scoring launch of the form whose attention selects appends the token as well, where the page that receives it is kept
     // whatever its score; otherwise the append goes first, by itself
     const bool appends = att_selects && n_local > 0;

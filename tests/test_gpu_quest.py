@@ -707,3 +707,39 @@ def test_selection_over_kinds_of_scores(rs, knobs, Np, K):
         torch.cuda.synchronize()
         ws.async_status()
         assert np.array_equal(to_np(idx)[0], want), (two, one)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,K,dtype", [
+    (1, 64, 64, 128, 512 * 16 + 1, 32, "bf16"), (2, 33, 33, 128, 1031 * 16 - 5, 16, "bf16"), (1, 130, 1, 64, 777 * 16, 40, "bf16"),
+    (1, 70, 70, 64, 3001 * 16, 60, "f32"), (3, 32, 32, 128, 40000, 160, "bf16"), (4, 32, 8, 128, 32768, 256, "bf16"),
+    (2, 32, 8, 128, 65000, 1015, "bf16"), (4, 32, 32, 128, 32768, 256, "f32")])
+def test_own_choice_of_form_over_fills_of_the_chip(rs, knobs, B, Hq, Hkv, D, T, K, dtype):
+    """The library's own choice between one persistent launch and two plain ones (on each side of its lines: few heads, CUs filled
+    evenly or not, shared rows), and each form by name: the same lists, and outputs that differ by rounding only.  The heads' pages are scored from
+    different first steps of 128 or 256 pages in the two launches: one step or several, whole or with a remainder."""
+    say("own choice of form", B, Hq, Hkv, D, T, K, dtype)
+    P, gen = 16, torch.Generator(device="cuda")
+    gen.manual_seed(T)
+    Np = -(-T // P)
+    s = rs.make_shape(B, Hq, Hkv, D, Np * P, P, tdtype(dtype))
+    kc, vc = (torch.randn(B, Hkv, Np * P, D, generator=gen, device="cuda").to(tdtype(dtype)) for _ in range(2))
+    q = torch.randn(B, Hq, D, generator=gen, device="cuda").to(tdtype(dtype))
+    meta = torch.zeros(B, Hkv, Np, 2, D, dtype=tdtype(dtype), device="cuda")
+    rs.quest_page_meta(s, kc, meta, 0, T)
+    ws = rs.Workspace(rs.sparse_attn_decode_workspace_bytes(s, T, K))
+    got = []
+    for form in (None, "0", "1"):
+        if form is not None:
+            knobs.setenv("RATSPARSE_FUSED_TWO_LAUNCH", form)
+            knobs.setenv("RATSPARSE_FUSED_ONE_WG", "0")
+        out = torch.zeros(B, Hq, D, dtype=tdtype(dtype), device="cuda")
+        lse = torch.zeros(B, Hq, device="cuda")
+        idx = torch.full((B, Hq, K), -5, dtype=torch.int32, device="cuda")
+        rs.sparse_attn_decode(s, q, kc, vc, T, 1.0 / np.sqrt(D), None, K, meta, 1, 1, out, lse, idx, ws)
+        torch.cuda.synchronize()
+        ws.async_status()
+        got.append((to_np(out), to_np(lse), to_np(idx)))
+    for other in got[1:]:
+        np.testing.assert_array_equal(other[2], got[0][2])
+        np.testing.assert_allclose(other[1], got[0][1], rtol=1e-6, atol=2e-6)
+        np.testing.assert_allclose(other[0], got[0][0], rtol=2.0 ** -7 if dtype == "bf16" else 1e-5, atol=2e-6)
