@@ -196,7 +196,7 @@ def main():
 
     for i in range(args.warmup):
         decode_step(i)
-    # wall-timed region: exactly --steps steps, nothing but the two launches of each step on the stream
+    # wall-timed region: exactly --steps steps, nothing but the two calls of each step on the stream
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for j in range(args.steps):
@@ -210,7 +210,7 @@ def main():
     ms_per_step = wall * 1e3 / args.steps
     tok_s = B * args.steps / wall
 
-    # algorithmic bytes of the fused select+attend launch, per step
+    # algorithmic bytes of the fused select+attend call, per step
     def fused_bytes(Tv, Kx=None):
         Kx = K if Kx is None else Kx
         Np = (Tv + P - 1) // P
@@ -223,7 +223,7 @@ def main():
         return {"launches_timed": n, "mean_ms": round(sum(a) / n, 5), "min_ms": round(a[0], 5),
                 "median_ms": round(a[n // 2], 5), "p10_ms": round(a[n // 10], 5), "p90_ms": round(a[(9 * n) // 10], 5)}
 
-    # roofline loop: N_EV further steps of the same run, the fused launch of EVERY one bracketed by HIP events on the
+    # roofline loop: N_EV further steps of the same run, the select+attend call of EVERY one bracketed by HIP events on the
     # launch stream (an event record costs the stream a few us, which is why these steps are not part of the wall-timed
     # region above); the number of launches does not depend on --steps
     base_ev = args.warmup + args.steps
@@ -247,12 +247,12 @@ def main():
         m = re.search(r"^hbm_bytes_per_launch\s*=\s*(\d+)", open(tpath).read(), re.M)
         traffic = int(m.group(1)) if m else None
         traffic_source = "profiles/%s (counters of an earlier rocprofv3 --pmc run of this command, not of this run)" % tname
-    roofline = {"bound": "hbm", "kernel": "decode_fused_kernel (sparse_attn_decode, fused select+attend, one launch per step)",
+    roofline = {"bound": "hbm", "kernel": "quest_score_keys_kernel + decode_attend_kernel (sparse_attn_decode, select+attend in one call per step)",
                 "achieved": round(achieved / 1e9, 1), "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK, 4), "traffic": traffic, "traffic_source": traffic_source,
                 "algorithmic_bytes_per_step": int(mean_bytes),
                 "mean_pages_per_sequence": round(sum((T + base_ev + j + 1 + P - 1) // P for j in range(N_EV)) / N_EV, 1),
-                "timing": "HIP events around each of %d consecutive fused launches after the wall-timed region" % N_EV}
+                "timing": "HIP events around each of %d consecutive select+attend calls after the wall-timed region" % N_EV}
     roofline.update(stats(fused_ms))
     log("decode: %.4f ms/step wall, fused launch %.4f ms mean -> %.0f GB/s (%.1f%% of HBM peak)" %
         (ms_per_step, mean_fused_ms, achieved / 1e9, 100 * achieved / HBM_PEAK))
@@ -775,7 +775,7 @@ def main():
         "config": {"workload": "%s: one decode layer, B=%d, Hq=%d, Hkv=%d, D=%d, context %d (+1 per step), "
                                "%d-token pages, K=%d of %d pages (budget %.4g), first+last page kept"
                                % (w.name, B, Hq, Hkv, D, T, P, K, T // P, args.budget),
-                   "step": "rat_scan append (with page-meta update) + fused select/attend, two launches; tok/s is for ONE layer "
+                   "step": "rat_scan append (with page-meta update) + fused select/attend, two calls; tok/s is for ONE layer "
                            "(a 32-layer model divides it by 32)",
                    "pct_hbm_peak": round(100 * achieved / HBM_PEAK, 2)},
         "roofline": roofline, "cpu_baseline": cpu, "extra": extra,
