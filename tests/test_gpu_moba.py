@@ -373,3 +373,45 @@ def test_launches_around_the_lines_between_the_step_widths(rs, knobs, T, units):
         assert ok, worst
         torch.testing.assert_close(got["1"][1], got["2"][1], rtol=1e-5, atol=1e-5)  # 32-bit sums
     ws.async_status()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,T,block,K", [
+    (1, 3, 1, 128, 1023, 16, 4), (1, 3, 3, 64, 1001, 16, 16), (2, 5, 5, 128, 385, 32, 8), (1, 7, 1, 128, 31, 16, 2),
+    (1, 37, 37, 64, 800, 48, 3), (1, 300, 300, 64, 97, 16, 6), (1, 2, 1, 128, 12289, 512, 20)])
+def test_gate_tiles_of_32_rows(rs, knobs, B, Hq, Hkv, D, T, block, K):
+    """Twelve waves of 32 query rows share a unit's block means: tiles that cross several own blocks, a last tile and a last round of
+    waves that are part empty, unit counts that do not divide the workgroups, more units than workgroups.  The same lists as with the
+    one-wave form, and by the float64 scores no block left out is better than one taken."""
+    say("gate tiles", B, Hq, Hkv, D, T, block, K)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    s = rs.make_shape(B, Hq, Hkv, D, -(-T // 16) * 16, 16, torch.bfloat16)
+    q = torch.randn(B, Hq, T, D, generator=gen, device="cuda").to(torch.bfloat16)
+    kc = torch.randn(B, Hkv, s.Tcap, D, generator=gen, device="cuda").to(torch.bfloat16)
+    Nb = -(-T // block)
+    means = torch.zeros(B, Hkv, Nb, D, device="cuda")
+    ws = rs.Workspace(rs.moba_select_prefill_workspace_bytes(s, T, block))
+    got = []
+    for form in ("0", "1"):
+        knobs.setenv("RATSPARSE_GATE_SHARED", form)
+        idx = torch.full((B, Hq, T, K), -9, dtype=torch.int32, device="cuda")
+        rs.moba_select_prefill(s, q, kc, T, block, K, 0, means, idx, ws)
+        torch.cuda.synchronize()
+        got.append(to_np(idx))
+    np.testing.assert_array_equal(got[1], got[0])
+    m = np.repeat(to_np(means).astype(np.float64), Hq // Hkv, axis=1)
+    sc = np.matmul(to_np(q.float()).astype(np.float64), m.transpose(0, 1, 3, 2))  # [B, Hq, T, Nb]
+    own = np.arange(T) // block
+    take = np.minimum(K, own + 1)
+    listed = got[1]
+    assert np.array_equal((listed >= 0).sum(-1), np.broadcast_to(take, listed.shape[:-1]))
+    picked = np.zeros(sc.shape, bool)
+    b, h, t, j = np.nonzero(listed >= 0)
+    picked[b, h, t, listed[b, h, t, j]] = True
+    assert np.array_equal(picked.sum(-1), np.broadcast_to(take, listed.shape[:-1])) and picked[:, :, np.arange(T), own].all()
+    ahead = np.arange(Nb) > own[:, None]
+    assert not (picked & ahead).any()
+    worst_in = np.where(picked & (np.arange(Nb) != own[:, None]), sc, np.inf).min(-1)
+    best_out = np.where(picked | ahead, -np.inf, sc).max(-1)
+    # (a score is a float32 sum of D products of a bfloat16 and a mean split into bfloat16 terms of 24 bits together)
+    bound = (D + 3) * 2.0 ** -23 * np.matmul(np.abs(to_np(q.float()).astype(np.float64)), np.abs(m).transpose(0, 1, 3, 2)).max(-1)
+    assert (worst_in >= best_out - 2 * bound).all()
