@@ -91,12 +91,14 @@ def load():
         except ImportError as e:
             raise RatsparseError("_native.so is not built: run `python -m paper_2605_28640_amd.build`") from e
         native.setup(*(ctypes.cast(getattr(lib, name), _vp).value for name in ("rat_scan", "sparse_attn_decode", "rat_decode_step")),
-                     _ptr, _check, torch._C._cuda_getCurrentRawStream, torch.cuda.current_device, Workspace)
-        _lib, _native = lib, native
+                     _check, torch._C._cuda_getCurrentRawStream, torch.cuda.current_device, rs_shape, Workspace)
+        _native = native
+        _lib = lib  # last: another thread that finds it set goes on without a look at the rest
     return _lib
 
 
 def _calls():
+    """The per-token calls with plain arguments; each answers False, the call unmade, for any others."""
     if _native is None:
         load()
     return _native
@@ -167,7 +169,11 @@ def rat_scan_workspace_bytes(s, T_new):
 
 
 def rat_scan(s, k, v, g, state_k, state_v, k_cache, v_cache, t0, T_new, ws=None, meta=None):
-    _calls().rat_scan(s, k, v, g, state_k, state_v, k_cache, v_cache, t0, T_new, ws, meta)
+    if _calls().rat_scan(s, k, v, g, state_k, state_v, k_cache, v_cache, t0, T_new, ws, meta):
+        return
+    _check(load().rat_scan(ctypes.byref(s), _ptr(k), _ptr(v), _ptr(g), _ptr(state_k), _ptr(state_v),
+                           _ptr(k_cache), _ptr(v_cache), _ptr(meta), t0, T_new, ws.ptr if ws else None,
+                           ws.nbytes if ws else 0, _stream()))
 
 
 def quest_page_meta(s, k_cache, meta, t_begin, t_end):
@@ -211,8 +217,12 @@ def rat_decode_state_get(ws):
 
 def rat_decode_step(s, k, v, g, state_k, state_v, k_cache, v_cache, meta, q, scale, K, n_first, n_local, T_max,
                     out, lse_out, idx_out, ws):
-    _calls().rat_decode_step(s, k, v, g, state_k, state_v, k_cache, v_cache, meta, q, scale, K, n_first, n_local, T_max,
-                             out, lse_out, idx_out, ws)
+    if _calls().rat_decode_step(s, k, v, g, state_k, state_v, k_cache, v_cache, meta, q, scale, K, n_first, n_local, T_max,
+                                out, lse_out, idx_out, ws):
+        return
+    _check(load().rat_decode_step(ctypes.byref(s), _ptr(k), _ptr(v), _ptr(g), _ptr(state_k), _ptr(state_v),
+                                  _ptr(k_cache), _ptr(v_cache), _ptr(meta), _ptr(q), scale, K, n_first, n_local,
+                                  T_max, _ptr(out), _ptr(lse_out), _ptr(idx_out), ws.ptr, ws.nbytes, _stream()))
 
 
 def selection_hit_update(idx, gold, unit, hit):
@@ -227,8 +237,12 @@ def sparse_attn_decode_workspace_bytes(s, T_valid, K):
 
 def sparse_attn_decode(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out,
                        lse_out, idx_out, ws):
-    _calls().sparse_attn_decode(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out, lse_out,
-                                idx_out, ws)
+    if _calls().sparse_attn_decode(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out, lse_out,
+                                   idx_out, ws):
+        return
+    _check(load().sparse_attn_decode(ctypes.byref(s), _ptr(q), _ptr(k_cache), _ptr(v_cache), T_valid,
+                                     scale, _ptr(idx), K, _ptr(meta), n_first, n_local, _ptr(out),
+                                     _ptr(lse_out), _ptr(idx_out), ws.ptr, ws.nbytes, _stream()))
 
 
 def sparse_attn_decode_static(s, q, k_cache, v_cache, T_valid, scale, idx, K, meta, n_first, n_local, out,
