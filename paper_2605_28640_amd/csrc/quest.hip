@@ -307,17 +307,7 @@ __global__ __launch_bounds__(kSelThreads) void quest_score_keys_kernel(const ST 
     const int per = (Np + splits - 1) / splits;
     const int pb = blockIdx.x * per;
     const int pe = (pb + per < Np) ? pb + per : Np;
-    // Four query heads in turn begin at four different steps of their pages: heads whose bounds lie close to a whole MiB
-    // apart would otherwise walk the same memory channels together.  4 x 32 x 32768, 512 pages 131 -> 127 us a step (x 65536, 256
-    // pages, where nothing collides, 103.1 -> 103.6).
-    constexpr int STEP_P = PPW * (kSelThreads / 64);
-    const int first = pb + wave * PPW;
-    int next = first + (unit & 3) * STEP_P;
-    if (next >= pe) next = first;
-    for (int left = pe - first; left > 0; left -= STEP_P) {
-        const int base = next;
-        next += STEP_P;
-        if (next >= pe) next = first;
+    for (int base = pb + wave * PPW; base < pe; base += PPW * (kSelThreads / 64)) {
         const int n = (pe - base < PPW) ? pe - base : PPW;
         const LdsSource md = lds_source_sized(mbase + (long)base * 2 * D, n * 2 * ROW);
         const uint32_t at = (uint32_t)(rg * 2 * ROW + cl * 8 * (int)sizeof(ST));
