@@ -637,6 +637,15 @@ __global__ void snapkv_gather_kernel(const ST *__restrict__ k_cache, const ST *_
 constexpr int kSnapOneWgKeys = 15360;  // 60 KiB of keys
 constexpr int kSnapOneWgThreads = 1024;
 
+// Up to 256 heads have a CU each, and the selection's chain of barriers is what the launch takes: one histogram (kByKey).  With more
+// heads their workgroups cover each other's waits, and what counts is the work: the radix passes (kNoSpread), and up to 3072
+// positions the window straight from the caches.  This launch with the radix passes and such windows only / with one histogram
+// only / by this rule, us, pooling over 7: 256 heads x 2068 10.6 / 10.5 / 10.4, x 4064 14.5 / 11.7 / 12.0, x 10968 30.6 / 22.0 / 22.1;
+// 288 x 2068 14.0 / 15.9 / 13.6, x 4064 19.5 / 19.6 / 17.2, x 8168 31.5 / 29.9 / 28.1; 512 x 668 12.4 / 12.8 / 11.6, x 2068 14.8 /
+// 17.5 / 14.4, x 4064 19.7 / 22.1 / 19.2, x 8168 32.3 / 33.3 / 29.8; 1024 x 2068 26.4 / 33.1 / 25.5, x 4064 37.0 / 40.2 / 34.1.  From
+// 10240 positions on one histogram is the faster one again, 384 x 14968 50.5 / 46.4.  (That its registers leave room for seven waves
+// a SIMD and so for one workgroup a CU is not the reason: with 84 scalar registers, eight waves, 512 x 4064 is 23.1.)
+template <SelectSpread HOW>
 __global__ __launch_bounds__(kSnapOneWgThreads) void snapkv_pool_select_kernel(const float *__restrict__ votes,
                                                                                float *__restrict__ pooled_out,
                                                                                int32_t *__restrict__ idx_out, int L,
@@ -647,39 +656,50 @@ __global__ __launch_bounds__(kSnapOneWgThreads) void snapkv_pool_select_kernel(c
     const long bk = blockIdx.x;
     const float *row = votes + bk * L;
     const int half = kernel / 2, tid = threadIdx.x;
-    // The votes come in by one trip and are pooled from LDS, a place of the window for all of a thread's positions at a time
-    // (a window of dependent trips to the caches per position: 8 x 32 heads x 4096 13.1 us for the launch, now 12.0).
-    constexpr int R = kSnapOneWgKeys / kSnapOneWgThreads;
-    float m[R];
-    auto each_row = [&](auto body) __attribute__((always_inline)) {
-        rows_from<0, R>((L + kSnapOneWgThreads - 1) / kSnapOneWgThreads, body);
-    };
-    auto place = [&](int r) __attribute__((always_inline)) {  // positions past the end repeat the last one
-        const int p = r * kSnapOneWgThreads + tid;
-        return p < L ? p : L - 1;
-    };
-    each_row([&](auto r) __attribute__((always_inline)) { m[r] = row[place(r)]; });
-    each_row([&](auto r) __attribute__((always_inline)) { s_keys[place(r)] = __float_as_uint(m[r]); });
-    __syncthreads();
-    each_row([&](auto r) __attribute__((always_inline)) {
-        const int lo = place(r) - half;
-        m[r] = __uint_as_float(s_keys[lo < 0 ? 0 : lo]);
-    });
-    for (int d = 1 - half; d <= half; ++d)
+    if (HOW == kNoSpread && L <= 3 * kSnapOneWgThreads) {
+        for (int p = tid; p < L; p += kSnapOneWgThreads) {
+            const int lo = (p - half < 0) ? 0 : p - half;
+            const int hi = (p + half > L - 1) ? L - 1 : p + half;
+            float m = row[lo];
+            for (int j = lo + 1; j <= hi; ++j) m = fmaxf(m, row[j]);
+            if (pooled_out) pooled_out[bk * L + p] = m;
+            s_keys[p] = float_to_key(m);
+        }
+    } else {
+        // The votes come in by one trip and are pooled from LDS, a place of the window for all of a thread's positions at a time
+        // (a window of dependent trips to the caches per position: 8 x 32 heads x 4096 13.1 us for the launch, now 12.0).
+        constexpr int R = kSnapOneWgKeys / kSnapOneWgThreads;
+        float m[R];
+        auto each_row = [&](auto body) __attribute__((always_inline)) {
+            rows_from<0, R>((L + kSnapOneWgThreads - 1) / kSnapOneWgThreads, body);
+        };
+        auto place = [&](int r) __attribute__((always_inline)) {  // positions past the end repeat the last one
+            const int p = r * kSnapOneWgThreads + tid;
+            return p < L ? p : L - 1;
+        };
+        each_row([&](auto r) __attribute__((always_inline)) { m[r] = row[place(r)]; });
+        each_row([&](auto r) __attribute__((always_inline)) { s_keys[place(r)] = __float_as_uint(m[r]); });
+        __syncthreads();
         each_row([&](auto r) __attribute__((always_inline)) {
-            const int at = place(r) + d;
-            m[r] = fmaxf(m[r], __uint_as_float(s_keys[at < 0 ? 0 : at < L ? at : L - 1]));
+            const int lo = place(r) - half;
+            m[r] = __uint_as_float(s_keys[lo < 0 ? 0 : lo]);
         });
-    __syncthreads();
-    each_row([&](auto r) __attribute__((always_inline)) {
-        const int p = place(r);
-        if (pooled_out) pooled_out[bk * L + p] = m[r];
-        s_keys[p] = float_to_key(m[r]);
-    });
+        for (int d = 1 - half; d <= half; ++d)
+            each_row([&](auto r) __attribute__((always_inline)) {
+                const int at = place(r) + d;
+                m[r] = fmaxf(m[r], __uint_as_float(s_keys[at < 0 ? 0 : at < L ? at : L - 1]));
+            });
+        __syncthreads();
+        each_row([&](auto r) __attribute__((always_inline)) {
+            const int p = place(r);
+            if (pooled_out) pooled_out[bk * L + p] = m[r];
+            s_keys[p] = float_to_key(m[r]);
+        });
+    }
     __syncthreads();
     if (K_keep <= 0) return;
     int32_t *dst = idx_out + bk * K_keep;
-    select_topk_lds<kSnapOneWgThreads, kByKey>(s_keys, L, K_keep, sh, [dst](int pos, int p) { dst[pos] = p; });
+    select_topk_lds<kSnapOneWgThreads, HOW>(s_keys, L, K_keep, sh, [dst](int pos, int p) { dst[pos] = p; });
 }
 
 static size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -784,8 +804,9 @@ int snapkv_dispatch(const rs_shape *s, const void *q_win, const void *k_cache, c
 #undef RS_SNAP_ROWS
 #undef RS_SNAP_ROWS1
     if (one_wg) {
-        snapkv_pool_select_kernel<<<(unsigned)BK, kSnapOneWgThreads, (size_t)L * 4, stream>>>(
-            votes, votes_out, idx_out, (int)L, pool_kernel, K_keep);
+        const bool spread = BK <= 256 || L > 10 * kSnapOneWgThreads;
+        auto kern = spread ? snapkv_pool_select_kernel<kByKey> : snapkv_pool_select_kernel<kNoSpread>;
+        kern<<<(unsigned)BK, kSnapOneWgThreads, (size_t)L * 4, stream>>>(votes, votes_out, idx_out, (int)L, pool_kernel, K_keep);
     } else {
         const dim3 gs((unsigned)Ly.n_slices, (unsigned)BK);
         // the raw votes are not needed past the pooling: the slices' bins take their place (kSelBins words a slice

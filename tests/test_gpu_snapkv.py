@@ -354,3 +354,37 @@ def test_kept_positions_over_kinds_of_votes(rs, L, K, pool):
         want = np.sort(np.argsort(-to_np(votes)[0, h], kind="stable")[:K])
         assert np.array_equal(to_np(idx)[0, h], want), h
         assert torch.equal(ko[0, h, :K], kc[0, h, torch.from_numpy(want).cuda()])
+
+
+@pytest.mark.parametrize("H,L,K,pool", [(257, 700, 90, 7), (260, 3071, 400, 5), (257, 3072, 3072, 63), (257, 3073, 1, 3), (300, 4064, 500, 7),
+                                        (257, 10240, 700, 1), (257, 10241, 1000, 7), (256, 3000, 400, 7)])
+def test_more_heads_than_compute_units(rs, knobs, H, L, K, pool):
+    """Up to 256 heads and above, on both sides of the lengths where the pooling and the selection change their form: the votes and
+    the positions of the launches that spread a head over the chip, and the positions of a stable sort."""
+    say("more heads", H, L, K, pool)
+    D, W = 64, 32
+    T = L + W
+    gen = torch.Generator(device="cuda").manual_seed(L + H)
+    kc = torch.zeros(1, H, T, D, device="cuda", dtype=torch.bfloat16)
+    x = torch.randn(H, L, generator=gen, device="cuda")
+    x[1::5] = 0  # all alike
+    x[2::5] = torch.where(x[2::5] > 2.5, 12.0, 0.004 * x[2::5])  # a few hold nearly all of the range
+    x[3::5] = (x[3::5] > 1).float()
+    x[4::5] *= 9
+    kc[0, :, :L, 0] = x
+    q = torch.zeros(1, H, W, D, device="cuda")
+    q[..., 0] = 1 + 0.01 * torch.arange(W, device="cuda")
+    s = rs.make_shape(1, H, H, D, T, 16, torch.bfloat16)
+    ws = rs.Workspace(rs.snapkv_compress_workspace_bytes(s, T, W))
+    got = []
+    for form in ("1", "0"):
+        knobs.setenv("RATSPARSE_SNAP_ONE_WG", form)
+        ko, vo = (torch.zeros(1, H, K + W, D, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        idx = torch.full((1, H, K), -5, dtype=torch.int32, device="cuda")
+        votes = torch.zeros(1, H, L, device="cuda")
+        rs.snapkv_compress(s, q.to(torch.bfloat16), kc, kc, T, W, K, pool, 1.0, ko, vo, K + W, idx, votes, ws)
+        torch.cuda.synchronize()
+        got.append((idx, votes))
+    assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][0], got[1][0])
+    want = torch.sort(got[0][1][0], dim=1, descending=True, stable=True).indices[:, :K].sort(1).values
+    assert torch.equal(got[0][0][0].long(), want)
