@@ -887,22 +887,24 @@ static unsigned prefill_spare_lds(int D, long n, long tiles)
 }
 
 // Units of an XCD whose causal tiles go out together.  The tiles of a group keep the XCD's 96 workgroups busy for about as
-// long as its heaviest tile takes (group * n_diag^2 / 2 steps over 96, against n_diag), and never fewer than four units or than
-// the query heads of a KV head; more units than that only widen what its 4 MB of L2 see at a time: 8 x 32 heads x 4096
-// tokens by bit sets, 32 units at a time 1530 us, 6 at a time 1213, one after the other 1270; 9 and 12 at a time no better.
-// A remainder is a group that does not fill the XCD, so the units are divided evenly (the heads of a KV head together) where that
-// is possible with more than half as many at a time.  As above with the remainder / divided evenly, us: 2 x 32 heads x 4001 (8 units: 2 + 6 / 4 + 4) 262 / 249,
-// by bit sets with routing 315 / 306, 8 x 32 x 4096 (32: 2 + 5 of 6 / 8 of 4) 1040 / 1008 and 1232 / 1213, 3 x 32 x 2500
-// (12: 2 + 10 / 6 + 6) 170 / 166; four at least instead of two: 32 over 8 heads x 16001 1752 / 1735, 32 x 16000 1760 / 1740.
-static int prefill_group(long units, int heads_per_kv, int n_diag)
+// long as its heaviest tile takes (group * n_diag^2 / 2 steps over 96, against n_diag), and there are never fewer than four: with
+// two, 32 heads x 16000 1771 us, with four 1758, 32 over 8 heads 1743 / 1719, of 64 channels 1007 / 1000 (each side's runs within 7).
+// More units than that only widen what the XCD's 4 MB of L2 see at a time: 8 x 32 heads x 4096 tokens by bit sets, 32 units at a time
+// 1530 us, 6 at a time 1213, one after the other 1270.
+// A remainder goes out first and does not fill the XCD.  Where every head has keys of its own, of 128 channels, the units are
+// divided evenly instead if that is possible with more than half as many at a time.  With the remainder / divided evenly, us:
+// 4 x 32 heads x 1983 (16 units an XCD: 4 + 12 / 8 + 8) 148 / 139, x 2300 192 / 179, x 2500 211 / 216, 6 x 32 x 1300 (6 + 18 / 12 + 12)
+// 116 / 110, 8 x 32 x 1000 96 / 92, 2 x 32 x 4001 (2 + 6 / 4 + 4) 255 / 251, 3 x 32 x 6000 818 / 783, by bit sets with routing 2 x 32 x
+// 4001 307 / 302, 8 x 32 x 4001 1208 / 1194.  The other way where heads share keys or have half the bytes, and L2 is not what counts:
+// 6 x 32 over 8 heads x 1535 (8 + 16 / 12 + 12) 120 / 125, by bit sets 160 / 165, 4 x 32 over 8 x 2300 166 / 170, 64 channels 3 x 32 x
+// 2300 77 / 83, 6 x 16 over 8 x 2500 90 / 95, 8 x 32 over 8 x 1000 48.7 / 51.5.
+static int prefill_group(long units, int heads_per_kv, int D, int n_diag)
 {
     int want = (192 + n_diag - 1) / n_diag;
     if (want < 4) want = 4;
-    want = (want + heads_per_kv - 1) / heads_per_kv * heads_per_kv;
-    if (units % 8) return want;
-    const long u = units / 8;
-    for (int g = want; 2 * g > want; g -= heads_per_kv)
-        if (u % g == 0) return g;
+    if (units % 8 || heads_per_kv > 1 || D == 64) return want;
+    for (int g = want; 2 * g > want; --g)
+        if ((units / 8) % g == 0) return g;
     return want;
 }
 
@@ -971,7 +973,7 @@ int prefill_dispatch(const rs_shape *s, const void *q, const void *k_cache, cons
     p.K = K;
     p.block = block;
     p.n_diag = (int)((T + kMT - 1) / kMT);
-    p.group = prefill_group(units, s->Hq / s->Hkv, p.n_diag);
+    p.group = prefill_group(units, s->Hq / s->Hkv, s->D, p.n_diag);
     p.T = T;
     p.Tcap = s->Tcap;
     p.scale = scale;
