@@ -264,27 +264,34 @@ static bool attend_selects(int Np, int K, int P, int splits)
 static bool step_is_brief(double step_bytes, long Np) { return step_bytes < 450e6 || Np < 512; }
 
 // Scores and attention as two plain launches, or as one persistent one whose workgroups hand over through tagged words.  The one launch
-// streams everything and keeps every CU at work; the two are faster where the attention's workgroups (units x splits) fill the
-// CUs evenly, for whole turns, and the heads share no rows.  Append + decode, two / one, us, with the share of the CUs' turns that is filled:
-//   64 heads or fewer, even: 4 x 16 over 4 x 65000, 254 pages (64 heads, 166 MB) 37 / 54, 2 x 32 over 8 x 65000, 1015 (565 MB) 88 / 104,
-//     2 x 32 x 65000, 2030 (1197 MB) 201 / 208, float32 2 x 32 x 60000 (739 MB) 143 / 163;
-//   no shared rows, even: 4 x 32 x 65536, 256 (537 MB) 103 / 106, 4 x 32 x 65000, pages of 64 (599 MB) 101 / 113, float32 x 30000 (737 MB)
-//     141 / 160, 4 x 32 x 32768, 512 (671 MB) 127 / 130 -- up to 5120 pages, which the attention ranks from one histogram: past them it
-//     reads its keys several times, 4 x 32 x 81920, 512 pages 167 / 164, x 98304 179 / 172, 2 x 32 x 131072 120 / 110;
-//   less than four fifths filled: 3 x 32 x 65000 (96 heads, 399 MB) 97 / 85, 3 x 32 x 40000 (246 MB) 66 / 61, 11 x 8 x 50000 (281 MB) 78 / 68,
-//     5 x 32 x 40000 (409 MB) 96 / 86, 6 x 32 x 32000 (393 MB) 85 / 82; below that 3 x 32 x 30000 (184 MB) 49 / 48, 6 x 32 x 15000 (183 MB) 44 / 47;
-//   shared rows: 4 x 32 over 8 x 32768 (302 MB) 70 / 66, 8 x 16 over 4 x 30000 (276 MB) 66 / 62, 4 x 32 over 8 x 65000 (549 MB) 100 / 94.
+// streams everything and keeps every CU at work; the two have less to do, and are faster where the attention's workgroups (units x
+// splits) fill whole turns of the CUs.  Append + decode, time with two / with one, the median and the range over 1161 shapes of 2 to
+// 960 heads, 512 to 11000 pages, pages of 16 to 64 tokens, 1/16 to 1/4 of them and a few with more (the lines cost 0.5 % against the
+// faster form of each, 450 MB alone 1.9 %):
+//   less than four fifths of the turns filled: 100-240 MB 0.96 (0.81-1.14), 240-400 MB 1.04 (0.92-1.25), above 1.13 (0.91-1.34);
+//     rows of 128 bytes, which the one launch moves at a lower rate: 240-480 MB 0.97 (0.87-1.10), above 1.01 (0.98-1.10);
+//   filled, 64 heads or fewer: below 400 MB 0.81 (0.60-1.21), 400-700 MB 0.93 (0.83-1.27), above 1.02 (0.93-1.12);
+//   filled, heads that share rows, which the one launch finds in L2 more often: 100-200 MB 0.91 (0.79-1.08), 200-400 MB 1.01 (0.86-1.22),
+//     above 1.08 (0.94-1.18); rows of 128 bytes: below 500 MB 0.86 (0.72-1.01), above 0.96 (0.84-1.07);
+//   filled, no shared rows: below 450 MB 0.86 (0.63-0.97), above by the bytes of the page bounds alone, whose launch every split of the
+//     attention follows with a selection: below 200 MB 0.94 (0.83-1.02), 200-330 MB 0.98 (0.88-1.05), 330-600 MB 1.03 (0.97-1.15).
+//     us at 96 heads x 50000 (460 MB, 0.56 filled) 98 / 86, 112 x 50000 93 / 97, 128 x 65536 94 / 106, 192 x 32768 (0.75) 110 / 108,
+//     208 x 32768 109 / 115, 255 x 32768 137 / 139, 256 x 32768 134 / 137, x 50000 (410 MB of bounds) 211 / 207, 512 x 16000 of
+//     float32 468 / 484, x 32768 (537 MB of bounds) 283 / 270;
+//   past 5120 pages the attention reads its keys several times: 8 such shapes above 450 MB 1.05 (0.98-1.08).
 // splits: of the attention that selects for itself, 0 where that does not apply (the two launches are slower then).
 static bool two_plain_launches(const rs_shape *s, long units, long Np, int splits, double step_bytes)
 {
     if (splits == 0 || Np < 512) return step_is_brief(step_bytes, Np);
     const bool at_once = Np <= 5120;  // the selection's one histogram (spread_rows of 512 threads)
-    const long wgs = units * splits, turns = (wgs + 255) / 256;
+    const long wgs = units * splits, turns = (wgs + 255) / 256, row = (long)s->D * esize(s->dtype);
     const double filled = (double)wgs / (256.0 * turns);
-    if (filled < 0.8) return step_bytes < 240e6;
+    const bool narrow = row < 256, shared = s->Hq > s->Hkv;
+    if (filled < 0.8) return step_bytes < (narrow ? 480e6 : 240e6);
     if (units <= 64) return (at_once && filled >= 0.9) || step_bytes < 450e6;
-    if (s->Hq > s->Hkv) return step_bytes < 270e6;
-    return (at_once && filled >= 0.95 && units > 96 && units < 256) || step_bytes < 450e6;
+    if (shared && !narrow) return step_bytes < 270e6;
+    const double bounds = (double)s->B * s->Hkv * Np * 2 * row;
+    return (at_once && (shared || bounds < 330e6)) || step_bytes < 450e6;
 }
 
 // work split and buffers of the one-launch decode (score -> select -> attend) for a sequence of

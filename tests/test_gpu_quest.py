@@ -712,11 +712,14 @@ def test_selection_over_kinds_of_scores(rs, knobs, Np, K):
 @pytest.mark.parametrize("B,Hq,Hkv,D,T,K,dtype", [
     (1, 64, 64, 128, 512 * 16 + 1, 32, "bf16"), (2, 33, 33, 128, 1031 * 16 - 5, 16, "bf16"), (1, 130, 1, 64, 777 * 16, 40, "bf16"),
     (1, 70, 70, 64, 3001 * 16, 60, "f32"), (3, 32, 32, 128, 40000, 160, "bf16"), (4, 32, 8, 128, 32768, 256, "bf16"),
-    (2, 32, 8, 128, 65000, 1015, "bf16"), (4, 32, 32, 128, 32768, 256, "f32")])
+    (2, 32, 8, 128, 65000, 1015, "bf16"), (4, 32, 32, 128, 32768, 256, "f32"),
+    # rows of 128 bytes, shared and the CUs filled or not; more than 450 MB with few and with many page bounds
+    (8, 32, 8, 64, 30000, 469, "bf16"), (5, 32, 8, 64, 34918, 545, "bf16"), (7, 16, 16, 128, 50000, 390, "bf16"),
+    (16, 32, 32, 64, 38400, 150, "bf16")])
 def test_own_choice_of_form_over_fills_of_the_chip(rs, knobs, B, Hq, Hkv, D, T, K, dtype):
     """The library's own choice between one persistent launch and two plain ones (on each side of its lines: few heads, CUs filled
-    evenly or not, shared rows), and each form by name: the same lists, and outputs that differ by rounding only.  The heads' pages are scored from
-    different first steps of 128 or 256 pages in the two launches: one step or several, whole or with a remainder."""
+    evenly or not, shared rows), and each form by name: the same lists, and outputs that differ by rounding only.  The pages are scored in steps of
+    128 or 256: one step or several, whole or with a remainder."""
     say("own choice of form", B, Hq, Hkv, D, T, K, dtype)
     P, gen = 16, torch.Generator(device="cuda")
     gen.manual_seed(T)
