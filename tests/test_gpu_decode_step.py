@@ -261,10 +261,13 @@ def test_step_replays_from_a_captured_graph(rs, knobs, case, form):
     ws_a.async_status()
 
 
-def test_step_at_the_measured_size_equals_the_two_calls(rs, knobs):
+@pytest.mark.parametrize("form", ["persistent", "own"])
+def test_step_at_the_measured_size_equals_the_two_calls(rs, knobs, form):
     """The measured configuration (batch 4, 32 heads, 64K context, 256 of 4096+ pages): several
-    score and attention slices per unit, page count growing under the fixed work split."""
-    _force_form(knobs, "persistent")
+    score and attention slices per unit, page count growing under the fixed work split.  In the persistent form, and in the one the
+    library takes by itself (two launches: the scores' also appends, the attention selects)."""
+    if form != "own":
+        _force_form(knobs, form)
     B, H, D, P, K = 4, 32, 128, 16, 256
     T0, steps = 65536 - 6, 14  # crosses the edge of page 4096
     Tcap = 65536 + 64

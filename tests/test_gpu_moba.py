@@ -377,7 +377,11 @@ def test_launches_around_the_lines_between_the_step_widths(rs, knobs, T, units):
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,T,block,K", [
     (1, 3, 1, 128, 1023, 16, 4), (1, 3, 3, 64, 1001, 16, 16), (2, 5, 5, 128, 385, 32, 8), (1, 7, 1, 128, 31, 16, 2),
-    (1, 37, 37, 64, 800, 48, 3), (1, 300, 300, 64, 97, 16, 6), (1, 2, 1, 128, 12289, 512, 20)])
+    (1, 37, 37, 64, 800, 48, 3), (1, 300, 300, 64, 97, 16, 6),
+    # more tiles than waves: two to five a wave, the next one's rows sent for under the picks, a last tile of 1, 17 or 12 rows
+    (1, 64, 16, 128, 4001, 64, 8), (1, 128, 128, 64, 3217, 64, 16), (1, 257, 257, 64, 1100, 32, 4),
+    # (not shared by waves: a list of more than 16 blocks is picked from LDS)
+    (1, 2, 1, 128, 12289, 512, 20)])
 def test_gate_tiles_of_32_rows(rs, knobs, B, Hq, Hkv, D, T, block, K):
     """Twelve waves of 32 query rows share a unit's block means: tiles that cross several own blocks, a last tile and a last round of
     waves that are part empty, unit counts that do not divide the workgroups, more units than workgroups.  The same lists as with the
