@@ -265,7 +265,7 @@ static bool step_is_brief(double step_bytes, long Np) { return step_bytes < 450e
 
 // Scores and attention as two plain launches, or as one persistent one whose workgroups hand over through tagged words.  The one launch
 // streams everything and keeps every CU at work; the two have less to do, and are faster where the attention's workgroups (units x
-// splits) fill whole turns of the CUs.  Append + decode, time with two / with one, the median and the range over 1161 shapes of 2 to
+// splits) fill whole turns of the CUs.  Append + decode, time with two / with one, the median and the range over 1182 shapes of 2 to
 // 960 heads, 512 to 11000 pages, pages of 16 to 64 tokens, 1/16 to 1/4 of them and a few with more (the lines cost 0.5 % against the
 // faster form of each, 450 MB alone 1.9 %):
 //   less than four fifths of the turns filled: 100-240 MB 0.96 (0.81-1.14), 240-400 MB 1.04 (0.92-1.25), above 1.13 (0.91-1.34);
@@ -273,24 +273,25 @@ static bool step_is_brief(double step_bytes, long Np) { return step_bytes < 450e
 //   filled, 64 heads or fewer: below 400 MB 0.81 (0.60-1.21), 400-700 MB 0.93 (0.83-1.27), above 1.02 (0.93-1.12);
 //   filled, heads that share rows, which the one launch finds in L2 more often: 100-200 MB 0.91 (0.79-1.08), 200-400 MB 1.01 (0.86-1.22),
 //     above 1.08 (0.94-1.18); rows of 128 bytes: below 500 MB 0.86 (0.72-1.01), above 0.96 (0.84-1.07);
-//   filled, no shared rows: below 450 MB 0.86 (0.63-0.97), above by the bytes of the page bounds alone, whose launch every split of the
-//     attention follows with a selection: below 200 MB 0.94 (0.83-1.02), 200-330 MB 0.98 (0.88-1.05), 330-600 MB 1.03 (0.97-1.15).
-//     us at 96 heads x 50000 (460 MB, 0.56 filled) 98 / 86, 112 x 50000 93 / 97, 128 x 65536 94 / 106, 192 x 32768 (0.75) 110 / 108,
-//     208 x 32768 109 / 115, 255 x 32768 137 / 139, 256 x 32768 134 / 137, x 50000 (410 MB of bounds) 211 / 207, 512 x 16000 of
-//     float32 468 / 484, x 32768 (537 MB of bounds) 283 / 270;
+//   filled, no shared rows: below 450 MB 0.86 (0.63-0.97), above by the page bounds alone, the part that the one launch does better: their
+//     bytes over the share of the turns that their own launch fills, below 200 MB 0.93 (0.83-1.02), 200-330 MB 0.98 (0.88-1.02),
+//     330-450 MB 1.02 (0.99-1.08), above 1.05 (0.97-1.15).  us at 96 heads x 50000 (460 MB, 0.56 filled) 98 / 86, float32 x 51903
+//     (319 MB of bounds, 0.56) 299 / 282, 112 x 50000 93 / 97, 128 x 50000 105 / 108, float32 x 40000 (1638 MB) 274 / 292, 192 x 32768
+//     (0.75) 110 / 108, 208 x 32768 109 / 115, 256 x 32768 134 / 137, x 50000 (410 MB of bounds) 211 / 207, 512 x 32768 283 / 270;
 //   past 5120 pages the attention reads its keys several times: 8 such shapes above 450 MB 1.05 (0.98-1.08).
 // splits: of the attention that selects for itself, 0 where that does not apply (the two launches are slower then).
-static bool two_plain_launches(const rs_shape *s, long units, long Np, int splits, double step_bytes)
+static bool two_plain_launches(const rs_shape *s, long units, long Np, int splits, int splits_score, double step_bytes)
 {
     if (splits == 0 || Np < 512) return step_is_brief(step_bytes, Np);
     const bool at_once = Np <= 5120;  // the selection's one histogram (spread_rows of 512 threads)
-    const long wgs = units * splits, turns = (wgs + 255) / 256, row = (long)s->D * esize(s->dtype);
-    const double filled = (double)wgs / (256.0 * turns);
+    auto share = [units](int n) { return (double)(units * n) / (double)((units * n + 255) / 256 * 256); };  // of the turns of 256 CUs
+    const double filled = share(splits);
+    const long row = (long)s->D * esize(s->dtype);
     const bool narrow = row < 256, shared = s->Hq > s->Hkv;
     if (filled < 0.8) return step_bytes < (narrow ? 480e6 : 240e6);
     if (units <= 64) return (at_once && filled >= 0.9) || step_bytes < 450e6;
     if (shared && !narrow) return step_bytes < 270e6;
-    const double bounds = (double)s->B * s->Hkv * Np * 2 * row;
+    const double bounds = (double)s->B * s->Hkv * Np * 2 * row / share(splits_score);
     return (at_once && (shared || bounds < 330e6)) || step_bytes < 450e6;
 }
 
@@ -660,7 +661,7 @@ static int32_t attn_decode_impl(bool group, const rs_shape *s, const void *q, co
         if (!attend_selects(L.Np, K, s->P, key_splits)) key_splits = 0;
     }
     const bool brief = step_is_brief(step_bytes, Np);
-    const int two_launch = knob_or(knobs().fused_two_launch, two_plain_launches(s, units, Np, key_splits, step_bytes) ? 1 : 0);
+    const int two_launch = knob_or(knobs().fused_two_launch, two_plain_launches(s, units, Np, key_splits, L.splits_score, step_bytes) ? 1 : 0);
     // Short contexts (the paper's 4096 tokens): the whole step of a (batch, query head) inside one
     // workgroup, one launch, nothing handed between workgroups.  Taken when a unit's metadata and
     // picked pages are small (at most 1.5 MB, and at most 512 KB unless there are 128 units or
@@ -867,7 +868,7 @@ int32_t rat_decode_step(const rs_shape *s, const void *k, const void *v, const f
     int key_splits = attend_splits(L, units, (long)K * (s->P / 16));
     const int splits = key_splits;
     if (ws_bytes < L.total_keys || !attend_selects(L.Np, K, s->P, key_splits)) key_splits = 0;
-    const int two_launch = knob_or(knobs().fused_two_launch, two_plain_launches(s, units, L.Np, key_splits, step_bytes) ? 1 : 0);
+    const int two_launch = knob_or(knobs().fused_two_launch, two_plain_launches(s, units, L.Np, key_splits, L.splits_score, step_bytes) ? 1 : 0);
     const double unit_bytes = ((double)L.Np * 2 + (double)K * s->P * 2) * s->D * esize(s->dtype);
     const bool unit_rule = knob_or(knobs().fused_two_launch, step_is_brief(step_bytes, L.Np) ? 1 : 0) && unit_bytes <= 1.5e6 &&
                            (units >= 128 || unit_bytes <= 512e3);

@@ -887,8 +887,9 @@ static unsigned prefill_spare_lds(int D, long n, long tiles)
 }
 
 // Units of an XCD whose causal tiles go out together.  The tiles of a group keep the XCD's 96 workgroups busy for about as
-// long as its heaviest tile takes (group * n_diag^2 / 2 steps over 96, against n_diag), and there are never fewer than four: with
-// two, 32 heads x 16000 1771 us, with four 1758, 32 over 8 heads 1743 / 1719, of 64 channels 1007 / 1000 (each side's runs within 7).
+// long as its heaviest tile takes (group * n_diag^2 / 2 steps over 96, against n_diag).  Four instead of two or three where units
+// fill XCDs: 32 heads x 16000 1771 -> 1758 us, 32 over 8 1743 -> 1719, of 64 channels 1007 -> 1000 (each side's runs within 7), 7 x 8 heads x
+// 9549 1108 -> 1091; but not where that leaves one by itself: 5 x 8 heads x 9549 779 / 853, 9 x 8 1395 / 1502, 5 x 8 x 13000 1413 / 1590.
 // More units than that only widen what the XCD's 4 MB of L2 see at a time: 8 x 32 heads x 4096 tokens by bit sets, 32 units at a time
 // 1530 us, 6 at a time 1213, one after the other 1270.
 // A remainder goes out first and does not fill the XCD.  Where every head has keys of its own, of 128 channels, the units are
@@ -901,10 +902,12 @@ static unsigned prefill_spare_lds(int D, long n, long tiles)
 static int prefill_group(long units, int heads_per_kv, int D, int n_diag)
 {
     int want = (192 + n_diag - 1) / n_diag;
-    if (want < 4) want = 4;
-    if (units % 8 || heads_per_kv > 1 || D == 64) return want;
+    if (units % 8) return want;
+    const long u = units / 8;
+    if (want < 4) return u % 4 == 1 ? 3 : 4;
+    if (heads_per_kv > 1 || D == 64) return want;
     for (int g = want; 2 * g > want; --g)
-        if ((units / 8) % g == 0) return g;
+        if (u % g == 0) return g;
     return want;
 }
 
