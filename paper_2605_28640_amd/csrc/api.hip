@@ -271,13 +271,18 @@ static bool step_is_brief(double step_bytes, long Np) { return step_bytes < 450e
 //   less than four fifths of the turns filled: 100-240 MB 0.96 (0.81-1.14), 240-400 MB 1.04 (0.92-1.25), above 1.13 (0.91-1.34);
 //     rows of 128 bytes, which the one launch moves at a lower rate: 240-480 MB 0.97 (0.87-1.10), above 1.01 (0.98-1.10);
 //   filled, 64 heads or fewer: below 400 MB 0.81 (0.60-1.21), 400-700 MB 0.93 (0.83-1.27), above 1.02 (0.93-1.12);
+//     heads that share rows, and the scores' workgroups leave part of a turn empty (449 shapes of 40 to 60 heads): rows of 256 bytes below
+//     400 MB 0.92 (0.76-1.06), 400-500 MB 1.00, above 1.06, past 5120 pages from 160 MB on 1.12 (0.96-1.25); of 512 bytes below 270 MB 0.96
+//     (0.82-1.05), above 1.04 (0.95-1.16), past 5120 pages 1.17 (1.07-1.23); of 128 bytes below 500 MB 0.86 (0.67-1.03);
 //   filled, heads that share rows, which the one launch finds in L2 more often: 100-200 MB 0.91 (0.79-1.08), 200-400 MB 1.01 (0.86-1.22),
 //     above 1.08 (0.94-1.18); rows of 128 bytes: below 500 MB 0.86 (0.72-1.01), above 0.96 (0.84-1.07);
 //   filled, no shared rows: below 450 MB 0.86 (0.63-0.97), above by the page bounds alone, the part that the one launch does better: their
 //     bytes over the share of the turns that their own launch fills, below 200 MB 0.93 (0.83-1.02), 200-330 MB 0.98 (0.88-1.02),
-//     330-450 MB 1.02 (0.99-1.08), above 1.05 (0.97-1.15).  us at 96 heads x 50000 (460 MB, 0.56 filled) 98 / 86, float32 x 51903
-//     (319 MB of bounds, 0.56) 299 / 282, 112 x 50000 93 / 97, 128 x 50000 105 / 108, float32 x 40000 (1638 MB) 274 / 292, 192 x 32768
-//     (0.75) 110 / 108, 208 x 32768 109 / 115, 256 x 32768 134 / 137, x 50000 (410 MB of bounds) 211 / 207, 512 x 32768 283 / 270;
+//     330-450 MB 1.02 (0.99-1.08), above 1.05 (0.97-1.15); float32, whose bounds the one launch scores more slowly, with 250-520 MB
+//     of bounds (81 more shapes) 0.95 (0.86-1.00) where their own launch fills the CUs and 1.07 (0.90-1.16) where it doesn't.
+//     us at 96 heads x 50000 (460 MB, 0.56 filled) 98 / 86, float32 x 51903 (319 MB of bounds, 0.56) 299 / 282, 112 x 50000
+//     93 / 97, 128 x 50000 105 / 108, float32 x 48816 (400 MB of bounds) 219 / 224, 192 x 32768 (0.75) 110 / 108, 208 x 32768 109 / 115,
+//     256 x 32768 134 / 137, x 50000 (410 MB of bounds) 211 / 207, 512 x 32768 283 / 270;
 //   past 5120 pages the attention reads its keys several times: 8 such shapes above 450 MB 1.05 (0.98-1.08).
 // splits: of the attention that selects for itself, 0 where that does not apply (the two launches are slower then).
 static bool two_plain_launches(const rs_shape *s, long units, long Np, int splits, int splits_score, double step_bytes)
@@ -289,10 +294,13 @@ static bool two_plain_launches(const rs_shape *s, long units, long Np, int split
     const long row = (long)s->D * esize(s->dtype);
     const bool narrow = row < 256, shared = s->Hq > s->Hkv;
     if (filled < 0.8) return step_bytes < (narrow ? 480e6 : 240e6);
-    if (units <= 64) return (at_once && filled >= 0.9) || step_bytes < 450e6;
+    const double scored = share(splits_score), bounds = (double)s->B * s->Hkv * Np * 2 * row / scored;
+    if (units <= 64) {
+        if (shared && !narrow && scored < 0.95) return step_bytes < (row > 256 ? 270e6 : at_once ? 450e6 : 200e6);
+        return (at_once && filled >= 0.9) || step_bytes < 450e6;
+    }
     if (shared && !narrow) return step_bytes < 270e6;
-    const double bounds = (double)s->B * s->Hkv * Np * 2 * row / share(splits_score);
-    return (at_once && (shared || bounds < 330e6)) || step_bytes < 450e6;
+    return (at_once && (shared || bounds < 330e6 || (s->dtype == RS_F32 && scored >= 0.95))) || step_bytes < 450e6;
 }
 
 // work split and buffers of the one-launch decode (score -> select -> attend) for a sequence of
