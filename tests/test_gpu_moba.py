@@ -316,12 +316,15 @@ def test_prefill_scores_that_outgrow_the_reference(rs, knobs, D, order, sub):
     ws.async_status()
 
 
-@pytest.mark.parametrize("heads", [56, 50])  # seven units per XCD in groups of six; in launch order in groups of 48
-def test_tile_order_over_many_heads(rs, knobs, heads):
+@pytest.mark.parametrize("heads,T,D", [
+    (56, 4001, 64), (50, 4001, 64),  # seven units per XCD in groups of six; in launch order in groups of 48
+    (64, 4001, 128),                 # eight of 128 channels in two groups of four
+    (40, 8300, 64), (48, 8300, 64)])  # long heads: five in groups of three, six in groups of four
+def test_tile_order_over_many_heads(rs, knobs, heads, T, D):
     """Causal tiles go out over groups of heads with a remainder first: every tile once, whatever the
     grouping, so each head gets the bits it gets in a call with few heads (steps of one length in all calls)."""
     knobs.setenv("RATSPARSE_PREFILL_SUB", "1")
-    T, D, block, K = 4001, 64, 64, 8
+    block, K = 64, 8
     gen = torch.Generator(device="cuda")
     gen.manual_seed(heads)
     q, k, v = (torch.randn(1, heads, T, D, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
@@ -339,7 +342,7 @@ def test_tile_order_over_many_heads(rs, knobs, heads):
         return out, lse
 
     for lists in (None, idx):
-        say("tile order", heads, lists is not None)
+        say("tile order", heads, T, D, lists is not None)
         out, lse = run(0, heads, lists)
         for lo in range(0, heads, 5):
             few, few_lse = run(lo, min(lo + 5, heads), lists)
