@@ -859,7 +859,8 @@ __global__ __launch_bounds__(kUnitThreads) void quest_unit_decode_kernel(
     // One histogram instead of the radix passes, us a step: 256 heads of 64 channels x 520 pages 20.0 -> 17.8, x 978 27.3 -> 24.6, of 128
     // channels x 520 28.4 -> 25.9, x 978 44.8 -> 42.3.  With more heads than CUs the gain is less and for some shapes a loss, on no
     // side of any line: 480 heads of 64 channels x 520 24.7 -> 22.4, x 978 37.8 -> 38.4, 512 over 128 KV heads x 800 33.3 -> 35.2, 768 x 800
-    // 51.7 -> 49.8, of 128 channels 288 x 597 34.7 -> 36.0, 320 x 260 21.4 -> 18.6, x 520 31.4 -> 32.5, x 800 51.0 -> 49.6.
+    // 51.7 -> 49.8, of 128 channels 288 x 597 34.7 -> 36.0, 320 x 260 21.4 -> 18.6, x 520 31.4 -> 32.5, x 800 51.0 -> 49.6; over 40 drawn
+    // shapes of 272 to 1024 heads 0.973 to 1.094 times the speed, 1.022 in the mean.
     if (Np <= kUnitThreads / 2) select_topk_few<kUnitThreads>(s_keys, Np, K, sh.wave_tot, emit);
     else select_topk_lds<kUnitThreads>(s_keys, Np, K, sh, emit);
     __syncthreads();
